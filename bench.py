@@ -27,11 +27,11 @@ PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_F32_TFLOPS = 157.3
 
 STAGE_NAMES = {2: "roots + sample + distinct-node rows + prologue (pack weights, clear), one launch",
-               3: "state gather + time-encode (GRU input) + slot-to-row map",
-               4: "GRU input + hidden projections (MFMA, one launch)",
-               6: "GRU gates + slot-sort scan",
-               9: "per-node projections K, V, q, merge (MFMA)",
-               8: "per-node score vectors U = q W_k^c (MFMA)",
+               3: "state gather + time-encode + GRU (MFMA, one launch) + slot-sort scan",
+               4: "GRU input + hidden projections (only when the node path does not fit)",
+               6: "GRU gates (only when the node path does not fit)",
+               9: "per-node projections K, V, q, merge (only when the node path does not fit)",
+               8: "per-node projections K, V, q, merge and score vectors U = q W_k^c (MFMA, one launch)",
                10: "attention forward: edge-feature gather, time encoding, scores, softmax, weighted sums (+ slot-sort fill)",
                7: "attention output = node part + Zp W_v^c^T (MFMA)",
                11: "merge layer (MFMA; only when the root chain does not fit)",
@@ -600,8 +600,8 @@ def main():
                    "avg_launch_us": res["attention_fwd"]["avg_launch_us"],
                    "traffic": recorded_traffic(head, "fattn_fwd")},
         "state_gather": dict(res["state_gather"], bound="hbm", peak=PEAK_HBM_GBS,
-                             kernel="gather_kernel: memory, mail and the mail's edge-feature row of every distinct node "
-                                    "into the GRU input"),
+                             kernel="node_update_kernel: memory, mail and the mail's edge-feature row of every distinct node "
+                                    "into the GRU input, and the GRU in the same launch (bytes of the gather only)"),
         "writeback": res.get("writeback_standalone"),
         "weight_gradients": wg,
         "step_model": res["step_model"],

@@ -332,9 +332,10 @@ int32_t tgnn_zero_params(tgnn_ctx* ctx, tgnn_params* g, void* stream);
 
 /* Stage timing with HIP events on the call's own stream.  Stages of tgnn_train_step (launches, in step order):
  *  2 first launch: roots + sample + distinct-node rows, and the prologue (pack weights, clear loss/grads, batch
- *    descriptors)   3 state gather + time-encode (GRU input; with the slot -> row map)   4 GRU input and hidden
- *    projections (MFMA, one launch)   6 GRU gates (with the scan of the slot sort)
- *  9 per-node projections K, V, q, merge (MFMA)   8 per-node score vectors U = q W_k^c (MFMA)
+ *    descriptors)
+ *  3 state gather, time-encode and GRU per distinct node (MFMA; with the scan of the slot sort)   8 per-node projections
+ *    K, V, q, merge and score vectors U = q W_k^c (MFMA).  Where that does not fit (d_mem > 128, d_mem + d_static > 256 or
+ *    a very wide GRU input): 3 state gather + time-encode   4 GRU products   6 GRU gates   9 projections   8 U
  *  10 attention forward: gathers the slots' edge features, time encoding, scores, softmax, weighted sums (with the fill
  *    pass of the slot sort)   7 attention output = node part + Zp (W_v^c)^T (MFMA)
  *  12 root chain: merge layer, decoder + loss and their backward pass down to the gradient of the attention output,

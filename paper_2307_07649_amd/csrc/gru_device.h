@@ -2,7 +2,6 @@
 #pragma once
 #include "tgnn_internal.h"
 #include "device_math.h"
-#include "unique_device.h"
 
 namespace tgnn {
 
@@ -15,13 +14,6 @@ __device__ __forceinline__ float tanhf_(float x) {
 
 // gates layout per row: [r | z | n | W_hn h + b_hn], each block ldh floats wide.  block: 0 .. gru_total_blocks(a) - 1
 __device__ __forceinline__ void gru_fwd_block(const GruFwdArgs& a, int block) {
-  if (a.scan.ucnt != nullptr) {   // block 0 is a passenger: the scan of the slot sort
-    if (block == 0) {
-      uniq_scan_block(a.scan);
-      return;
-    }
-    --block;
-  }
   const int dm = a.dm, ldh = a.ldh, ld3 = a.ld3;
   const int n = a.n_dev ? min(a.n_max, *a.n_dev) : a.n_max;
   const long long stride = (long long)a.gru_blocks * blockDim.x;

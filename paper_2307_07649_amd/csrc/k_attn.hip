@@ -45,7 +45,7 @@ __device__ __forceinline__ void slot_ids(const FusedAttn& a, int r, int j, int c
   const int s = r * a.k + j;
   if (j < c) {
     e = a.neid != nullptr ? a.neid[s] : s;
-    row = a.slot_row != nullptr ? a.slot_row[a.R + s] : a.R + s;
+    row = !forward || a.slot_gid == nullptr ? (a.slot_row != nullptr ? a.slot_row[a.R + s] : a.R + s) : a.uidx[a.slot_gid[a.R + s]];
     if (!forward) dt = a.dtk[s];
     else if (a.dt_in != nullptr) dt = a.dt_in[s];
     else if (a.dt_source != 0) dt = a.root_t[r] - a.nts[s];
@@ -218,7 +218,7 @@ __device__ __forceinline__ void softmax_heads(float* sa, int HK, int k, int c, i
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_FWD_WAVES, TGNN_FATTN_FWD_WAVES))) void fattn_fwd_fast_kernel(FusedAttn a) {
   extern __shared__ float lds[];
   int block = blockIdx.x;
-  if (a.fill.ucnt != nullptr) {   // the first blocks are passengers: the fill pass of the slot sort
+  if (a.fill.gcnt != nullptr) {   // the first blocks are passengers: the fill pass of the slot sort
     const int fill_blocks = uniq_blocks(a.fill.S);
     if (block < fill_blocks) {
       uniq_fill_block(a.fill, block);
@@ -239,14 +239,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_
   // node row and query time.  Padding slots carry -1 in both index arrays.
   const int sl = r * a.k + min(lane, a.k - 1);
   int my_e = a.neid != nullptr ? a.neid[sl] : sl;
-  int my_row = a.slot_row != nullptr ? a.slot_row[a.R + sl] : a.R + sl;
-  const int my_qrow = a.slot_row != nullptr ? a.slot_row[r] : r;
+  int my_row = a.R + sl, my_qrow = r;
+  if (a.slot_gid != nullptr) {
+    const int my_gid = a.slot_gid[a.R + sl], q_gid = a.slot_gid[r];
+    my_row = a.uidx[max(my_gid, 0)];
+    my_qrow = a.uidx[q_gid];
+  } else if (a.slot_row != nullptr) {
+    my_row = a.slot_row[a.R + sl];
+    my_qrow = a.slot_row[r];
+  }
   double my_dt = 0.0;
   const bool from_tau = a.dt_in == nullptr && a.dt_source == 0;
   if (a.dt_in != nullptr) my_dt = a.dt_in[sl];
   else if (a.dt_source != 0) my_dt = a.root_t[r] - a.nts[sl];
   else my_dt = a.root_t[r];
   const bool own = lane < a.k && lane < c;
+  if (a.slot_gid != nullptr) {   // the rows, for the launches after this one
+    if (lane < a.k) a.slot_row[a.R + sl] = own ? my_row : -1;
+    if (lane == 0) a.slot_row[r] = my_qrow;
+  }
   if (!own) { my_e = -1; my_row = 0; }
   if (c == 0) {
     if (lane < a.k) a.dtk[(size_t)r * a.k + lane] = 0.0;
@@ -558,7 +569,7 @@ __device__ __forceinline__ GenLds gen_lds(char* base, int wave, int k, int H) {
 __global__ __launch_bounds__(256) void fattn_fwd_gen_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   int block = blockIdx.x;
-  if (a.fill.ucnt != nullptr) {
+  if (a.fill.gcnt != nullptr) {
     const int fill_blocks = uniq_blocks(a.fill.S);
     if (block < fill_blocks) {
       uniq_fill_block(a.fill, block);
@@ -581,7 +592,10 @@ __global__ __launch_bounds__(256) void fattn_fwd_gen_kernel(FusedAttn a) {
     slot_ids(a, r, j, c, e, row, dt, true);
     L.e[j] = e; L.row[j] = row; L.dt[j] = dt;
     a.dtk[(size_t)r * a.k + j] = dt;
+    if (a.slot_gid != nullptr) a.slot_row[a.R + r * a.k + j] = j < c ? row : -1;
   }
+  const size_t qrow = a.slot_gid != nullptr ? (size_t)a.uidx[a.slot_gid[r]] : a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
+  if (a.slot_gid != nullptr && lane == 0) a.slot_row[r] = (int)qrow;
   if (c == 0) {
     for (int p = lane; p < HK; p += 64) pr[p] = 0.f;
     for (int e = lane; e < a.dO; e += 64) out[e] = 0.f;
@@ -589,7 +603,6 @@ __global__ __launch_bounds__(256) void fattn_fwd_gen_kernel(FusedAttn a) {
     return;
   }
   wave_lds_sync();
-  const size_t qrow = a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
   const float* qv = a.P + qrow * a.ldp + a.off_q;
   const float* urow = a.U + qrow * a.ldz;
   const float scale = 1.0f / sqrtf((float)c);
@@ -747,7 +760,7 @@ static bool fast_path(const FusedAttn& a) {
 
 void fattn_fwd(const FusedAttn& a, hipStream_t s) {
   if (a.R <= 0) return;
-  const int fill_blocks = a.fill.ucnt != nullptr ? uniq_blocks(a.fill.S) : 0;
+  const int fill_blocks = a.fill.gcnt != nullptr ? uniq_blocks(a.fill.S) : 0;
   const dim3 grid((a.R + 3) / 4 + fill_blocks);
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_fwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);

@@ -14,13 +14,12 @@ template <int VEC>
 __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
   if (a.epoch_bump != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.epoch_bump += 1ull;   // nothing here reads it
   int block = blockIdx.x, n_blocks = gridDim.x;
-  if (a.map.ucnt != nullptr) {   // the first blocks are passengers: the slot -> row map
-    const int map_blocks = uniq_blocks(a.map.S);
-    if (block < map_blocks) {
-      uniq_map_block(a.map, block);
+  if (a.scan.gcnt != nullptr) {   // the first block is a passenger: the scan of the slot sort
+    if (block == 0) {
+      uniq_scan_block(a.scan);
       return;
     }
-    block -= map_blocks; n_blocks -= map_blocks;
+    --block; --n_blocks;
   }
   const int lane = threadIdx.x & 63;
   const int wpb = blockDim.x >> 6;
@@ -144,7 +143,7 @@ void gather_rows(const GatherArgs& a, hipStream_t s) {
   const int rows_launched = a.n_dev == nullptr ? a.n_slots
                             : a.launch_rows > 0 ? std::min(a.n_slots, a.launch_rows)
                                                 : std::min(a.n_slots, std::max(512, (a.n_slots + 3) / 4));
-  const int blocks = (rows_launched + 3) / 4 + (a.map.ucnt != nullptr ? uniq_blocks(a.map.S) : 0);
+  const int blocks = (rows_launched + 3) / 4 + (a.scan.gcnt != nullptr ? 1 : 0);
   if (vec == 4) hipLaunchKernelGGL(gather_kernel<4>, dim3(blocks), dim3(256), 0, s, a);
   else if (vec == 2) hipLaunchKernelGGL(gather_kernel<2>, dim3(blocks), dim3(256), 0, s, a);
   else hipLaunchKernelGGL(gather_kernel<1>, dim3(blocks), dim3(256), 0, s, a);

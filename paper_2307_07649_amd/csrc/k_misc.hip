@@ -13,60 +13,90 @@ __global__ void prologue_kernel(PrologueArgs a) { prologue_block(a, blockIdx.x, 
 // the blocks that multiply the node rows, the per-slot rows and the attention output, and the transposed
 // copies that the data-gradient GEMMs read.
 void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, const SgdSet* sgd, const SgdSet* zero,
-                   float* loss, PrologueArgs& pa) {
+                   float* loss, int what, PrologueArgs& pa) {
   const Dims& d = ctx->d;
   Ws& w = ctx->w;
   static_assert(sizeof(PrologueArgs) <= 4096, "kernel argument block too large");
   memset(&pa, 0, sizeof(pa));
   int n = 0;
   auto add = [&](const float* src, float* dst, int rows, int cols, int zero_to, int ldd, int srs, int scs) {
-    pa.d[n++] = PackDesc{src, dst, rows, cols, zero_to, ldd, srs, scs, 0, 0, 0, 0, 0};
+    PackDesc& q = pa.d[n++];
+    q.src = src; q.dst = dst; q.rows = rows; q.cols = cols; q.zero_to = zero_to; q.ldd = ldd; q.srs = srs; q.scs = scs;
   };
   // block-diagonal over the heads: block h of `rows` x `cols` lands at rows h * brd, columns h * bcd of dst
   auto add_bd = [&](const float* src, float* dst, int rows, int cols, int ldd, int srs, int scs, int brd, int bcd, int bsrc) {
-    pa.d[n++] = PackDesc{src, dst, rows, cols, 0, ldd, srs, scs, 0, d.H, brd, bcd, bsrc};
+    PackDesc& q = pa.d[n++];
+    q.src = src; q.dst = dst; q.rows = rows; q.cols = cols; q.ldd = ldd; q.srs = srs; q.scs = scs;
+    q.nblk = d.H; q.brd = brd; q.bcd = bcd; q.bsrc = bsrc;
   };
+  const bool backward = what != PACK_FORWARD, chain = what == PACK_CHAIN;
   if (p != nullptr) {
     const int dO = d.dO, dm = d.dm, dx = d.dx, dkv = d.dkv, dmrg = d.dO + d.dx, half = d.ldkv;
-    add(p->gru_wih, w.Wih_p, 3 * dm, d.d_in, d.ldx, d.ldx, d.d_in, 1);
-    add(p->gru_whh, w.Whh_p, 3 * dm, dm, d.ldh, d.ldh, dm, 1);
-    // node part of every projection of x = {s' | static}: rows {W_k ; W_v} then, from row `half`, {W_q ; W_o}
-    // (rows 2 d_o .. half stay zero); row pitch = the pitch of the node rows
-    add(p->wk, w.Wx, dO, dx, d.ldxr, d.ldxr, dkv, 1);
-    add(p->wv, w.Wx + (size_t)dO * d.ldxr, dO, dx, d.ldxr, d.ldxr, dkv, 1);
-    add(p->wq, w.Wx + (size_t)half * d.ldxr, dO, dx, d.ldxr, d.ldxr, d.dq, 1);
-    add(p->wo + dO, w.Wx + (size_t)(half + dO) * d.ldxr, dO, dx, d.ldxr, d.ldxr, dmrg, 1);
+    // node part of every projection of x = {s' | static}: output columns {W_k ; W_v} then, from column `half`,
+    // {W_q ; W_o} (columns 2 d_o .. half stay zero)
+    if (d.nd_rb > 0) {   // split operands of the node path (pads stay zero)
+      auto add_split = [&](const float* src, unsigned short* dst, int rows, int cols, int srs, int scs, int ks, int groups, int group,
+                           int row0, int col0) {
+        PackDesc& q = pa.d[n++];
+        q.src = src; q.dst = reinterpret_cast<float*>(dst); q.rows = rows; q.cols = cols; q.srs = srs; q.scs = scs;
+        q.split_ks = ks; q.split_groups = groups; q.split_group = group; q.row0 = row0; q.col0 = col0;
+      };
+      for (int g = 0; g < 3; ++g) {   // GRU gates r, z, n: input columns, then memory columns
+        add_split(p->gru_wih + (size_t)g * dm * d.d_in, w.Wg_s, dm, d.d_in, d.d_in, 1, d.nd_kx + d.nd_kh, 3, g, 0, 0);
+        add_split(p->gru_whh + (size_t)g * dm * dm, w.Wg_s, dm, dm, dm, 1, d.nd_kx + d.nd_kh, 3, g, 0, 32 * d.nd_kx);
+      }
+      add_split(p->wk, w.Wp_s, dO, dx, dkv, 1, d.nd_kp, 1, 0, 0, 0);
+      add_split(p->wv, w.Wp_s, dO, dx, dkv, 1, d.nd_kp, 1, 0, dO, 0);
+      add_split(p->wq, w.Wp_s, dO, dx, d.dq, 1, d.nd_kp, 1, 0, half, 0);
+      add_split(p->wo + dO, w.Wp_s, dO, dx, dmrg, 1, d.nd_kp, 1, 0, half + dO, 0);
+      pa.Wu_s = w.Wp_s + (size_t)(d.ldp / 16) * d.nd_kp * 1536;
+      pa.wk = p->wk; pa.dkv = dkv; pa.dc = d.de + d.dt; pa.dcp = d.dcp; pa.H = d.H; pa.kp = d.nd_kp;
+    } else {
+      add(p->gru_wih, w.Wih_p, 3 * dm, d.d_in, d.ldx, d.ldx, d.d_in, 1);
+      add(p->gru_whh, w.Whh_p, 3 * dm, dm, d.ldh, d.ldh, dm, 1);
+      add(p->wk, w.Wx, dO, dx, d.ldxr, d.ldxr, dkv, 1);
+      add(p->wv, w.Wx + (size_t)dO * d.ldxr, dO, dx, d.ldxr, d.ldxr, dkv, 1);
+      add(p->wq, w.Wx + (size_t)half * d.ldxr, dO, dx, d.ldxr, d.ldxr, d.dq, 1);
+      add(p->wo + dO, w.Wx + (size_t)(half + dO) * d.ldxr, dO, dx, d.ldxr, d.ldxr, dmrg, 1);
+    }
     // its transpose, dynamic columns only: WxT[c, j] = Wx[j, c], c < d_m
     // (rows c >= d_m, the static columns, are read only when the static memory is co-trained)
-    add(p->wk, w.WxT, dx, dO, dO, d.ldp, 1, dkv);
-    add(p->wv, w.WxT + dO, dx, dO, dO, d.ldp, 1, dkv);
-    add(p->wq, w.WxT + half, dx, dO, dO, d.ldp, 1, d.dq);
-    add(p->wo + dO, w.WxT + half + dO, dx, dO, dO, d.ldp, 1, dmrg);
+    if (backward) {
+      add(p->wk, w.WxT, dx, dO, dO, d.ldp, 1, dkv);
+      add(p->wv, w.WxT + dO, dx, dO, dO, d.ldp, 1, dkv);
+      add(p->wq, w.WxT + half, dx, dO, dO, d.ldp, 1, d.dq);
+      add(p->wo + dO, w.WxT + half + dO, dx, dO, dO, d.ldp, 1, dmrg);
+    }
     // {e | Phi} columns of W_k, W_v (the slots' own inputs), per head: head h owns output rows [h dh, (h + 1) dh)
     if (d.de + d.dt > 0) {
       const int dh = dO / d.H, dc = d.de + d.dt;
       // row h dcp + c, column h dh + dd  <-  W[h dh + dd, d_x + c]
-      add_bd(p->wk + dx, w.WkcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
-      add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
+      if (d.nd_rb == 0) add_bd(p->wk + dx, w.WkcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
+      if (backward) add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
       // row h dh + dd, column h dcp + c  <-  W[h dh + dd, d_x + c]
-      add_bd(p->wk + dx, w.Wkc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
+      if (backward) add_bd(p->wk + dx, w.Wkc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
       add_bd(p->wv + dx, w.Wvc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
     }
     // merge layer, attention-output columns, and their transpose
-    add(p->wo, w.Wo_o, dO, dO, d.ldh, d.ldh, dmrg, 1);
-    add(p->wo, w.WoT_o, dO, dO, d.ldh, d.ldh, 1, dmrg);
+    if (!chain) add(p->wo, w.Wo_o, dO, dO, d.ldh, d.ldh, dmrg, 1);
+    if (!chain && backward) add(p->wo, w.WoT_o, dO, dO, d.ldh, d.ldh, 1, dmrg);
     // decoder hidden layer per root: rows {W_s ; W_d}; and for the way back, side by side and transposed:
     // WdecT[c, j] = W_s[j, c], WdecT[c, d_o + j] = W_d[j, c]
-    add(p->dec_ws, w.Wdec_p, dO, dO, d.ldh, d.ldh, dO, 1);
-    add(p->dec_wd, w.Wdec_p + (size_t)dO * d.ldh, dO, dO, d.ldh, d.ldh, dO, 1);
-    add(p->dec_ws, w.WdecT, dO, dO, dO, d.ldkv, 1, dO);
-    add(p->dec_wd, w.WdecT + dO, dO, dO, d.ldkv - dO, d.ldkv, 1, dO);
-    add(p->gru_wih + 2 * dm, w.WihT_phi, d.dt, 3 * dm, d.ld3, d.ld3, 1, d.d_in);
-    if (w.rc_pk != nullptr) {   // the root chain's copies, in MFMA B-operand order: [out column][k]
+    if (!chain) {
+      add(p->dec_ws, w.Wdec_p, dO, dO, d.ldh, d.ldh, dO, 1);
+      add(p->dec_wd, w.Wdec_p + (size_t)dO * d.ldh, dO, dO, d.ldh, d.ldh, dO, 1);
+    }
+    if (!chain && backward) {
+      add(p->dec_ws, w.WdecT, dO, dO, dO, d.ldkv, 1, dO);
+      add(p->dec_wd, w.WdecT + dO, dO, dO, d.ldkv - dO, d.ldkv, 1, dO);
+    }
+    if (backward) add(p->gru_wih + 2 * dm, w.WihT_phi, d.dt, 3 * dm, d.ld3, d.ld3, 1, d.d_in);
+    if (chain) {   // the root chain's copies, in MFMA B-operand order: [out column][k]
       const int ks = (dO + 15) / 16;
       const size_t blk = (size_t)ks * ks * 256;
       auto add_mfma = [&](const float* src, int which, int srs, int scs) {
-        pa.d[n++] = PackDesc{src, w.rc_pk + which * blk, dO, dO, 0, 0, srs, scs, ks, 0, 0, 0, 0};
+        PackDesc& q = pa.d[n++];
+        q.src = src; q.dst = w.rc_pk + which * blk; q.rows = dO; q.cols = dO; q.srs = srs; q.scs = scs; q.mfma_ks = ks;
       };
       add_mfma(p->wo, 0, dmrg, 1);       // z column n      <- h columns k:      W_o[n, k]
       add_mfma(p->dec_ws, 1, dO, 1);     // hidden column j <- z columns k:      W_s[j, k]
@@ -93,13 +123,13 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
   pa.adam_t = (sgd != nullptr && ctx->adam) ? w.adam_t : nullptr;   // a step that updates the weights is one Adam step
 }
 
-dim3 prologue_grid(const PrologueArgs& pa) { return dim3(96, pa.n_pack + pa.zero.cnt + 1); }
+dim3 prologue_grid(const PrologueArgs& pa) { return dim3(96, prologue_rows(pa)); }
 void* prologue_func() { return reinterpret_cast<void*>(prologue_kernel); }
 
 void prologue(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, const SgdSet* sgd, const SgdSet* zero,
               float* loss, hipStream_t s) {
   PrologueArgs pa;
-  prologue_fill(ctx, p, bs, sgd, zero, loss, pa);
+  prologue_fill(ctx, p, bs, sgd, zero, loss, PACK_ALL, pa);
   hipLaunchKernelGGL(prologue_kernel, prologue_grid(pa), dim3(256), 0, s, pa);
 }
 

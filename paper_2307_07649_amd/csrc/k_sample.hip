@@ -6,6 +6,7 @@
 
 #include "tgnn_internal.h"
 #include "prologue_device.h"
+#include "unique_device.h"
 
 namespace tgnn {
 
@@ -23,6 +24,7 @@ namespace tgnn {
 template <bool FUSED, int G>
 __device__ __forceinline__ void sample_block(const SampleArgs& a, const BatchSet& bs, unsigned long long ep, int block) {
   __shared__ int blk_count, blk_base;
+  __shared__ UniqTable<FUSED ? CLAIM_TABLE : 1> tab;   // the nodes this block's slots refer to, with their slot counts
   constexpr int QW = 64 / G;   // queries per wavefront
   const UniqPtrs& uq = a.uq;
   const int N = a.N, n_roots = a.n_roots, k = a.k;
@@ -34,6 +36,7 @@ __device__ __forceinline__ void sample_block(const SampleArgs& a, const BatchSet
   if (!FUSED && G == 64 && !active) return;
   if (FUSED) {
     if (threadIdx.x == 0) blk_count = 0;
+    uniq_table_clear(tab);
     __syncthreads();
   }
   int claim = -1;   // (replica, node) this lane wants a row for
@@ -122,23 +125,61 @@ __device__ __forceinline__ void sample_block(const SampleArgs& a, const BatchSet
     if (FUSED && active) claim = gl < k ? (nb >= 0 ? rep_base + nb : -1) : (gl == k ? root_gid : -1);
   }
   if (FUSED) {
-    // Row numbers for the nodes claimed first by this block: winners are counted per wave (ballot), per block
-    // (LDS) and only then on the device-wide row counter, whose atomics serialise in the L2.
-    bool won = false;
-    if (claim >= 0 && __atomic_load_n(uq.utag + claim, __ATOMIC_RELAXED) < ep)   // popular nodes: look first
-      won = atomicMax(uq.utag + claim, ep) < ep;
-    const unsigned long long winners = __ballot(won);
+    // The block's slots are gathered by node in an LDS table first, so that a node costs one look at its claim word and
+    // one count per block however many slots refer to it.  Row numbers for the nodes claimed first by this block:
+    // winners are counted per wave (ballot), per block (LDS) and only then on the device-wide row counter, whose
+    // atomics serialise in the L2.
+    if (claim >= 0) atomicAdd(&tab.val[uniq_table_slot(tab, claim)], 1);
+    __syncthreads();
+    constexpr int PER = CLAIM_TABLE / (64 * SAMPLE_WAVES);
+    static_assert(CLAIM_TABLE % (64 * SAMPLE_WAVES) == 0 && CLAIM_TABLE >= 64 * SAMPLE_WAVES * 2, "table entries per thread; load at most a half");
+    int key[PER], eid[PER];
+    double mem_ts[PER], mail_ts[PER];
+    bool won[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      key[u] = tab.key[threadIdx.x + u * 64 * SAMPLE_WAVES];
+      won[u] = false;
+      eid[u] = -1;
+      mem_ts[u] = mail_ts[u] = 0.0;
+      if (key[u] >= 0) {   // (the node's mail event and times are asked for beside the claim word: one round trip)
+        eid[u] = uq.mail_eid[key[u]];
+        mem_ts[u] = uq.mem_ts[key[u]];
+        mail_ts[u] = uq.mail_ts[key[u]];
+        won[u] = __atomic_load_n(uq.utag + key[u], __ATOMIC_RELAXED) < ep;   // popular nodes: look first
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (key[u] >= 0 && uq.gcnt != nullptr) atomicAdd(uq.gcnt + key[u], tab.val[threadIdx.x + u * 64 * SAMPLE_WAVES]);
+      if (won[u]) won[u] = atomicMax(uq.utag + key[u], ep) < ep;
+    }
+    int mine = 0, total = 0;   // winners of the wavefront in the rounds so far; in all
+    unsigned long long winners[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      winners[u] = __ballot(won[u]);
+      total += __popcll(winners[u]);
+    }
     int wave_base = 0;
-    if (winners != 0ull && lane == 0) wave_base = atomicAdd(&blk_count, __popcll(winners));
+    if (total > 0 && lane == 0) wave_base = atomicAdd(&blk_count, total);
     __syncthreads();
     if (threadIdx.x == 0) blk_base = blk_count > 0 ? atomicAdd(uq.ucount, blk_count) : 0;
     __syncthreads();
     wave_base = __shfl(wave_base, 0);   // all lanes take part: lane 0 need not be a winner itself
-    if (won) {
-      const int row = blk_base + wave_base + __popcll(winners & ((1ull << lane) - 1ull));
-      uq.uidx[claim] = row;
-      uq.ulist[row] = claim;
-      uq.ucnt[row] = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      if (won[u]) {
+        const int row = blk_base + wave_base + mine + __popcll(winners[u] & ((1ull << lane) - 1ull));
+        uq.uidx[key[u]] = row;
+        uq.ulist[row] = key[u];
+        const bool has = eid[u] >= 0;
+        uq.row_eid[row] = eid[u];
+        uq.has[row] = has ? 1 : 0;
+        uq.delta[row] = has ? mail_ts[u] - mem_ts[u] : 0.0;
+        uq.tau[row] = has ? mail_ts[u] : mem_ts[u];
+      }
+      mine += __popcll(winners[u]);
     }
   }
 }
@@ -167,24 +208,24 @@ static SampleArgs sample_args(const Dims& d, const tgnn_graph* g, int n_roots) {
   return a;
 }
 
-void head_fill(tgnn_ctx* ctx, const tgnn_graph* g, int n_roots, const tgnn_params* p, const BatchSet* bs,
-               const SgdSet* sgd, const SgdSet* zero, float* loss, HeadArgs& h) {
+void head_fill(tgnn_ctx* ctx, const tgnn_graph* g, const tgnn_state* st, int n_roots, const tgnn_params* p, const BatchSet* bs,
+               const SgdSet* sgd, const SgdSet* zero, float* loss, int what, bool count, HeadArgs& h) {
   const Dims& d = ctx->d;
   Ws& w = ctx->w;
   h.sa = sample_args(d, g, n_roots);
   h.sa.out_nbr = w.nbr; h.sa.out_eid = w.neid; h.sa.out_ts = w.nts; h.sa.out_cnt = w.cnt;
   h.sa.root_node = w.root_node; h.sa.root_t = w.root_t; h.sa.slot_gid = w.slot_gid; h.sa.slot_node = w.slot_node;
   h.sa.winkey = w.winkey; h.sa.bad_ids = w.bad_ids;
-  h.sa.uq = UniqPtrs{w.utag, w.epoch, w.uidx, w.ucount, w.ulist, w.ucnt};
+  h.sa.uq = UniqPtrs{w.utag, w.epoch, w.uidx, w.ucount, w.ulist, w.row_eid, w.has, w.delta, w.tau, st->mail_eid, st->mem_ts, st->mail_ts, count ? w.gcnt : nullptr};
   const int per_block = SAMPLE_WAVES * (d.k < 16 ? 4 : 1);   // four roots per wavefront when a lane group of 16 holds k + 1 claims
   h.sample_blocks = (n_roots + per_block - 1) / per_block;
   h.pro_bx = 12 * 16 / SAMPLE_WAVES;   // blocks of 1024 threads per grid row of the prologue (C1: 12 measured best of 2 .. 48; 24: +1.6 us per step)
-  prologue_fill(ctx, p, bs, sgd, zero, loss, h.pa);
+  prologue_fill(ctx, p, bs, sgd, zero, loss, what, h.pa);
   h.pa.head_of_step = 1;
   h.pa.ucount_next = w.ucount_pair + (w.ucount == w.ucount_pair ? 1 : 0);
 }
 
-dim3 head_grid(const HeadArgs& h) { return dim3(h.sample_blocks + h.pro_bx * (h.pa.n_pack + h.pa.zero.cnt + 1)); }
+dim3 head_grid(const HeadArgs& h) { return dim3(h.sample_blocks + h.pro_bx * prologue_rows(h.pa)); }
 void* head_func() { return reinterpret_cast<void*>(step_head_kernel); }
 
 void step_head(const HeadArgs& h, hipStream_t s) {

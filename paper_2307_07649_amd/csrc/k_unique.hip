@@ -14,8 +14,8 @@ namespace tgnn {
 SortArgs sort_args(tgnn_ctx* ctx, int S) {
   Ws& w = ctx->w;
   SortArgs a;
-  a.ucount = w.ucount; a.ucnt = w.ucnt; a.rowptr = w.rowptr; a.cursor = w.cursor;
-  a.S = S; a.slot_gid = w.slot_gid; a.uidx = w.uidx; a.slot_row = w.slot_row; a.sorted = w.sorted;
+  a.ucount = w.ucount; a.gcnt = w.gcnt; a.ulist = w.ulist; a.rowptr = w.rowptr; a.cursor = w.cursor;
+  a.S = S; a.slot_gid = w.slot_gid; a.uidx = w.uidx; a.sorted = w.sorted;
   a.sorted_row = w.sorted_row; a.total = w.sort_total;
   return a;
 }

@@ -1,13 +1,77 @@
 // Device side of the prologue (weight packing, clears, descriptor copies; see PrologueArgs), callable from any
-// kernel: the work is laid out on a grid of nbx x (n_pack + zero.cnt + 1) blocks of any size; (bx, y) is the
+// kernel: the work is laid out on a grid of nbx x prologue_rows() blocks of any size; (bx, y) is the
 // calling block's place in it.
 #pragma once
 #include "tgnn_internal.h"
 #include "device_math.h"
+#include "split3.h"
 
 namespace tgnn {
 
+// where element (row n, column k) of a split operand with ks slabs and `groups` interleaved operands lives (part 0)
+__device__ __forceinline__ size_t split_place(int n, int k, int ks, int groups, int group) {
+  return ((size_t)((n >> 4) * ks + (k >> 5)) * groups + group) * 1536 + (((k & 31) >> 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
+
+// The composite weights of the score vectors (see PrologueArgs::Wu_s), on nbx * PRO_COMP blocks.  A wavefront takes 64
+// consecutive columns c of one head (its loads of W_k are coalesced) and four columns j of x.
+constexpr int PRO_COMP = 4;   // grid rows
+__device__ __forceinline__ void prologue_composite(const PrologueArgs& a, int block, int blocks) {
+  const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6;
+  const int dh = a.dO / a.H, c_chunks = (a.dc + 63) >> 6;
+  constexpr int JW = 4;
+  const int j_chunks = (a.dx + JW - 1) / JW, hc_all = a.H * c_chunks, total = hc_all * j_chunks;
+  for (int i = __builtin_amdgcn_readfirstlane(block + blocks * (int)(threadIdx.x >> 6)); i < total; i += blocks * wpb) {
+    const int jc = i / hc_all, hc = i % hc_all, cc = hc % c_chunks, h = hc / c_chunks;
+    const int c = min(cc * 64 + lane, a.dc - 1), n = h * a.dcp + c;
+    const float* __restrict__ pk = a.wk + (size_t)h * dh * a.dkv + a.dx + c;
+    const float* __restrict__ pq = a.wq + (size_t)h * dh * a.dq;
+    const bool live = cc * 64 + lane < a.dc;
+    float acc[JW] = {0.f, 0.f, 0.f, 0.f};
+    for (int d0 = 0; d0 < dh; d0 += 64) {   // a lane brings W_q's elements of one d, broadcast below
+      float q[JW];
+#pragma unroll
+      for (int u = 0; u < JW; ++u) q[u] = pq[(size_t)min(d0 + lane, dh - 1) * a.dq + min(jc * JW + u, a.dq - 1)];   // (past column d_x: not stored)
+#pragma unroll 1
+      for (int d1 = 0; d1 < min(64, dh - d0); d1 += 25) {
+        float v[25];
+#pragma unroll
+        for (int d = 0; d < 25; ++d) v[d] = pk[(size_t)min(d0 + d1 + d, dh - 1) * a.dkv];
+#pragma unroll
+        for (int d = 0; d < 25; ++d)
+          if (d1 + d < min(64, dh - d0)) {
+#pragma unroll
+            for (int u = 0; u < JW; ++u) acc[u] += v[d] * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(q[u]), d1 + d));
+          }
+      }
+    }
+    if (live) {
+#pragma unroll
+      for (int u = 0; u < JW; ++u) {
+        const int j = jc * JW + u;
+        if (j < a.dx) {
+          unsigned q[3];
+          split_pair(acc[u], 0.f, q[0], q[1], q[2]);
+          unsigned short* o = a.Wu_s + split_place(n, j, a.kp, 1, 0);
+#pragma unroll
+          for (int p = 0; p < 3; ++p) o[p * 512] = (unsigned short)q[p];
+        }
+      }
+    }
+  }
+}
+
+// rows of the block grid
+__host__ __device__ inline int prologue_rows(const PrologueArgs& a) { return a.n_pack + a.zero.cnt + 1 + (a.Wu_s != nullptr ? PRO_COMP : 0); }
+
 __device__ __forceinline__ void prologue_block(const PrologueArgs& a, int bx, int nbx, int y) {
+  if (a.Wu_s != nullptr) {   // first: the longest chain of loads
+    if (y < PRO_COMP) {
+      prologue_composite(a, y * nbx + bx, PRO_COMP * nbx);
+      return;
+    }
+    y -= PRO_COMP;
+  }
   if (y < a.n_pack) {
     const PackDesc d = a.d[y];
     if (d.mfma_ks > 0) {   // MFMA B-operand order
@@ -17,6 +81,27 @@ __device__ __forceinline__ void prologue_block(const PrologueArgs& a, int bx, in
         const int cb = slab / d.mfma_ks, s = slab - cb * d.mfma_ks;
         const int row = cb * 16 + (lane & 15), k = s * 16 + (lane >> 4) * 4 + c;
         d.dst[i] = (row < d.rows && k < d.cols) ? d.src[(size_t)row * d.srs + (size_t)k * d.scs] : 0.f;
+      }
+      return;
+    }
+    if (d.split_ks > 0) {   // the three bf16 parts in MFMA operand order
+      unsigned short* dst = reinterpret_cast<unsigned short*>(d.dst);
+      {   // eight columns per thread (col0 is a multiple of eight)
+        const int c8 = (d.cols + 7) >> 3, total = d.rows * c8;
+        for (int i = bx * blockDim.x + threadIdx.x; i < total; i += nbx * blockDim.x) {
+          const int r = i / c8, c = (i - r * c8) * 8;
+          const float* __restrict__ src = d.src + (size_t)r * d.srs + (size_t)c * d.scs;
+          floatx4 lo, hi;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            lo[e] = c + e < d.cols ? src[e * d.scs] : 0.f;
+            hi[e] = c + 4 + e < d.cols ? src[(4 + e) * d.scs] : 0.f;
+          }
+          const Split8 s = split8(lo, hi);
+          bf16x8* o = reinterpret_cast<bf16x8*>(dst + split_place(d.row0 + r, d.col0 + c, d.split_ks, d.split_groups, d.split_group));
+#pragma unroll
+          for (int p = 0; p < 3; ++p) o[p * 64] = s.p[p];
+        }
       }
       return;
     }

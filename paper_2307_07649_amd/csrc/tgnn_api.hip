@@ -94,7 +94,7 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   w.bad_ids = b.take<int32_t>(1);
   const size_t NG = (size_t)d.nrep * d.N, U = d.maxU;
   w.utag = b.take<unsigned long long>(NG); w.uidx = b.take<int32_t>(NG); w.ucount_pair = b.take<int32_t>(2); w.ucount = w.ucount_pair;
-  w.ulist = b.take<int32_t>(U); w.slot_row = b.take<int32_t>(S); w.ucnt = b.take<int32_t>(U);
+  w.ulist = b.take<int32_t>(U + 4); w.slot_row = b.take<int32_t>(S); w.gcnt = b.take<int32_t>(NG); w.row_eid = b.take<int32_t>(U);
   w.rowptr = b.take<int32_t>(U + 1); w.cursor = b.take<int32_t>(U); w.sorted = b.take<int32_t>(S);
   w.sorted_row = b.take<int32_t>(S); w.sort_total = b.take<int32_t>(1);
   w.ds_row = b.take<float>(S * d.ldh);
@@ -104,7 +104,7 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   w.sgd_dev = b.take<SgdSet>(1);
   w.q_part = b.take<float>((size_t)QPHI_BLOCKS * d.dO);
   w.X = b.take<float>(S * d.ldx); w.Hm = b.take<float>(S * d.ldh);
-  w.gi = b.take<float>(S * d.ld3); w.gh = b.take<float>(S * d.ld3);
+  w.gi = d.nd_rb > 0 ? nullptr : b.take<float>(S * d.ld3); w.gh = d.nd_rb > 0 ? nullptr : b.take<float>(S * d.ld3);
   w.gates = b.take<float>(S * 4 * d.ldh); w.Xrow = b.take<float>(S * d.ldxr);
   w.dgi = b.take<float>(S * d.ld3); w.dgh = b.take<float>(S * d.ld3);
   // node rows of a standalone attention call are its slots, so P / dP hold S rows (a step uses far fewer)
@@ -122,10 +122,15 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   w.logits = b.take<float>(std::max(B2, (size_t)d.maxEv * (size_t)d.nC));
   w.dlog = b.take<float>(d.nC > 0 ? (size_t)d.maxEv * d.ldc : 4);
   w.loss_acc = b.take<float>(TGNN_MAX_BATCHES);
-  w.Wih_p = b.take<float>((size_t)3 * d.dm * d.ldx); w.Whh_p = b.take<float>((size_t)3 * d.dm * d.ldh);
+  // either the split operands of the one-launch node path or the copies that the separate products read
+  const bool nd = d.nd_rb > 0;
+  w.Wg_s = nd ? b.take<unsigned short>((size_t)d.nd_cb * (d.nd_kx + d.nd_kh) * 3 * 1536) : nullptr;
+  w.Wp_s = nd ? b.take<unsigned short>((size_t)((d.ldp + d.ldz) / 16) * d.nd_kp * 1536) : nullptr;
+  w.Wih_p = nd ? nullptr : b.take<float>((size_t)3 * d.dm * d.ldx);
+  w.Whh_p = nd ? nullptr : b.take<float>((size_t)3 * d.dm * d.ldh);
   w.Wdec_p = b.take<float>((size_t)2 * d.dO * d.ldh);
-  w.Wx = b.take<float>((size_t)d.ldp * d.ldxr); w.bias_x = b.take<float>((size_t)d.ldp);
-  w.WkcT = b.take<float>((size_t)d.H * d.dcp * d.ldh + 32); w.WvcT = b.take<float>((size_t)d.H * d.dcp * d.ldh + 32);
+  w.Wx = nd ? nullptr : b.take<float>((size_t)d.ldp * d.ldxr); w.bias_x = b.take<float>((size_t)d.ldp + (nd ? d.ldz : 0));
+  w.WkcT = nd ? nullptr : b.take<float>((size_t)d.H * d.dcp * d.ldh + 32); w.WvcT = b.take<float>((size_t)d.H * d.dcp * d.ldh + 32);
   w.Wkc = b.take<float>((size_t)d.dO * d.ldz); w.Wvc = b.take<float>((size_t)d.dO * d.ldz);
   w.Wo_o = b.take<float>((size_t)d.dO * d.ldh);
   {
@@ -206,7 +211,8 @@ static void gru_forward(tgnn_ctx* ctx, const tgnn_params* p, int n, hipStream_t 
 // What the attention kernels need to know about a call.  slot_row maps root slot r and neighbour slot R + r k + j
 // to node rows (NULL: slot = row).  efeat / neid / dt_in: see FusedAttn.
 struct AttnIn {
-  const int32_t* slot_row;
+  int32_t* slot_row;
+  const int32_t *slot_gid, *uidx;   // forward pass of a step: the rows are looked up and left in slot_row
   const int32_t* cnt;
   const float* efeat;
   const int32_t* neid;
@@ -221,7 +227,7 @@ static FusedAttn fused_args(tgnn_ctx* ctx, int R, const AttnIn& in) {
   a.R = R; a.k = d.k; a.H = d.H; a.dO = d.dO; a.dh = d.dO / d.H; a.de = d.de; a.dt = d.dt; a.dcp = d.dcp;
   a.ldz = d.ldz; a.ldh = d.ldh; a.ldp = d.ldp; a.ldy = d.ldy; a.off_q = d.ldkv; a.dt_source = d.dt_source;
   a.force_generic = (ctx->cfg.flags & TGNN_FLAG_GENERIC_ATTN) != 0;
-  a.P = w.P; a.U = w.Umat; a.slot_row = in.slot_row; a.cnt = in.cnt; a.efeat = in.efeat; a.neid = in.neid;
+  a.P = w.P; a.U = w.Umat; a.slot_gid = in.slot_gid; a.uidx = in.uidx; a.slot_row = in.slot_row; a.cnt = in.cnt; a.efeat = in.efeat; a.neid = in.neid;
   a.root_t = w.root_t; a.nts = w.nts; a.tau = w.tau; a.dt_in = in.dt_in;
   a.time_w = in.p->time_w; a.time_b = in.p->time_b; a.dtk = w.dtk; a.prob = w.prob;
   a.Onode = w.Onode; a.Zp = w.Zp; a.dOmat = w.dOmat; a.G = w.Gmat;
@@ -229,27 +235,30 @@ static FusedAttn fused_args(tgnn_ctx* ctx, int R, const AttnIn& in) {
   return a;
 }
 
-// Attention (Eq. 4-7) and the merge layer, from the node rows ws.Xrow [n_rows].  Every projection is linear in
+// Attention (Eq. 4-7) and the merge layer.  With `products` from the node rows ws.Xrow [n_rows], otherwise from what
+// node_project left in ws.P and ws.Umat.  Every projection is linear in
 // {x | e | Phi}, and x depends on the node only, so the x part of K, V, q and of the merge layer is one GEMM over the
 // distinct node rows (ws.P).  The {e | Phi} part never becomes a key or value row (k_attn.hip): the scores need
 // U = q (W_k^c) per head (a second GEMM over the node rows), the output is the kernel's node part plus Zp (W_v^c)^T
 // (a GEMM over the roots).  n_rows_dev (may be NULL): device-side row count.
 static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows, const int* n_rows_dev, const AttnIn& in,
-                         StageTimer* tm, hipStream_t s, const SortArgs& fill = SortArgs(), bool with_merge = true) {
+                         StageTimer* tm, hipStream_t s, bool products, const SortArgs& fill = SortArgs(), bool with_merge = true) {
   const Dims& d = ctx->d; Ws& w = ctx->w;
-  const bool slot_part = d.de + d.dt > 0;   // (always: d_t > 0)
-  if (tm) tm->begin(9);
-  const NtProblem node_part = nt_live(nt_problem(w.Xrow, d.ldxr, w.Wx, d.ldxr, w.bias_x, w.P, d.ldp, n_rows,
-                                                 d.ldkv + 2 * d.dO, d.ldxr, d.ldp, false, n_rows_dev), d.dx);
-  gemm_nt_group(&node_part, 1, s);
-  if (tm) { tm->end(9); tm->begin(8); }
-  if (slot_part) {   // U = q (W_k^c)_h per head: A is the q section of P (its pad columns meet zero columns of the weights)
-    const NtProblem u = nt_blocks(nt_live(nt_problem(w.P + d.ldkv, d.ldp, w.WkcT, d.ldh, nullptr, w.Umat, d.ldz, n_rows,
-                                                     d.H * d.dcp, d.ldh, d.ldz, false, n_rows_dev), d.dO),
-                                  d.dcp, d.dO / d.H);
-    gemm_nt_group(&u, 1, s);
+  if (products) {
+    if (tm) tm->begin(9);
+    const NtProblem node_part = nt_live(nt_problem(w.Xrow, d.ldxr, w.Wx, d.ldxr, w.bias_x, w.P, d.ldp, n_rows,
+                                                   d.ldkv + 2 * d.dO, d.ldxr, d.ldp, false, n_rows_dev), d.dx);
+    gemm_nt_group(&node_part, 1, s);
+    if (tm) { tm->end(9); tm->begin(8); }
+    {   // U = q (W_k^c)_h per head: A is the q section of P (its pad columns meet zero columns of the weights)
+      const NtProblem u = nt_blocks(nt_live(nt_problem(w.P + d.ldkv, d.ldp, w.WkcT, d.ldh, nullptr, w.Umat, d.ldz, n_rows,
+                                                       d.H * d.dcp, d.ldh, d.ldz, false, n_rows_dev), d.dO),
+                                    d.dcp, d.dO / d.H);
+      gemm_nt_group(&u, 1, s);
+    }
+    if (tm) tm->end(8);
   }
-  if (tm) { tm->end(8); tm->begin(10); }
+  if (tm) tm->begin(10);
   FusedAttn fa = fused_args(ctx, R, in);
   fa.fill = fill;
   fattn_fwd(fa, s);
@@ -395,6 +404,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
 static int replay_steps(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, const tgnn_params* p, tgnn_params* grads,
                         const BatchSet* sets, int n_steps, int parity, float lr, float* out_loss, float* out_logits,
                         int32_t* out_winner, hipStream_t s);
+static int step_packs(const tgnn_ctx* ctx, const BatchSet& bs);
 
 extern "C" {
 
@@ -443,6 +453,7 @@ int32_t tgnn_create(const tgnn_config* cfg, tgnn_ctx** out) {
     return set_error(TGNN_E_OUT_OF_RANGE, "max_batch * n_replicas * (2 + max_neg_sets) * (1 + k) exceeds the slot index range");
   }
   d.maxEv = (int)maxEv; d.maxR = (2 + d.maxNeg) * d.maxEv; d.maxRK = d.maxR * d.k; d.maxS = d.maxR + d.maxRK;
+  node_dims(d);
   {  // distinct (replica, node) rows a step can touch
     const long long ng = (long long)d.nrep * d.N;
     d.maxU = (int)(ng < d.maxS ? ng : d.maxS);
@@ -590,6 +601,14 @@ int32_t tgnn_gru_update(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_slots, co
   if (d.de > 0) REQ_PTR(mail_efeat);
   hipStream_t s = as_stream(stream);
   prologue(ctx, p, nullptr, nullptr, nullptr, nullptr, s);
+  if (d.nd_rb > 0) {
+    NodeArgs na = node_args(ctx, p, n_slots, nullptr);
+    na.mem = mem; na.mail = mail; na.efeat = mail_efeat; na.mem_ts = mem_ts; na.mail_ts = mail_ts; na.has_in = has_mail;
+    na.tau = out_tau; na.Xrow = out_s_new; na.ldxr = d.dm; na.ds = 0; na.bias_u = nullptr;
+    node_update(na, s);
+    TGNN_LAUNCH_CHECK();
+    return TGNN_OK;
+  }
   GatherArgs a;
   memset(&a, 0, sizeof(a));
   a.mem = mem; a.mail = mail; a.efeat = mail_efeat; a.mem_ts = mem_ts; a.mail_ts = mail_ts;
@@ -623,11 +642,19 @@ int32_t tgnn_temporal_attn_fwd(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_ro
   hipStream_t s = as_stream(stream);
   prologue(ctx, p, nullptr, nullptr, nullptr, nullptr, s);
   TGNN_HIP_CHECK(hipMemcpyAsync(w.cnt, cnt, sizeof(int32_t) * n_roots, hipMemcpyDeviceToDevice, s));
-  stage_x_rows(n_roots, d.k, d.dx, x_root, x_nbr, cnt, w.Xrow, d.ldxr, s);
+  const bool nd = d.nd_rb > 0;
+  if (nd) {
+    node_bias(node_args(ctx, p, 0, nullptr), s);
+    NodeArgs na = node_args(ctx, p, n_roots * (1 + d.k), nullptr);
+    na.x_root = x_root; na.x_nbr = x_nbr; na.cnt = cnt; na.R = n_roots; na.k = d.k;
+    node_project(na, s);
+  } else {
+    stage_x_rows(n_roots, d.k, d.dx, x_root, x_nbr, cnt, w.Xrow, d.ldxr, s);
+  }
   // the caller's rows have to stay as they are until the backward call (the slots' inputs are read again there)
   ctx->last_attn = AttnCall{e_nbr, dt_nbr};
-  const AttnIn in{nullptr, w.cnt, e_nbr, nullptr, dt_nbr, p};
-  attn_forward(ctx, p, n_roots, n_roots * (1 + d.k), nullptr, in, nullptr, s);
+  const AttnIn in{nullptr, nullptr, nullptr, w.cnt, e_nbr, nullptr, dt_nbr, p};
+  attn_forward(ctx, p, n_roots, n_roots * (1 + d.k), nullptr, in, nullptr, s, !nd);
   TGNN_HIP_CHECK(hipMemcpy2DAsync(out_z, (size_t)d.dO * 4, w.z, (size_t)d.ldh * 4, (size_t)d.dO * 4, n_roots,
                                   hipMemcpyDeviceToDevice, s));
   TGNN_LAUNCH_CHECK();
@@ -652,7 +679,7 @@ int32_t tgnn_temporal_attn_bwd(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_ro
   TnBatch tn;
   Side side{ctx, s, false};
   const int RK = n_roots * d.k;
-  const AttnIn in{nullptr, w.cnt, ctx->last_attn.e_nbr, nullptr, ctx->last_attn.dt_nbr, p};
+  const AttnIn in{nullptr, nullptr, nullptr, w.cnt, ctx->last_attn.e_nbr, nullptr, ctx->last_attn.dt_nbr, p};
   attn_backward(ctx, grads, p, n_roots, in, tn, side, s, nullptr);
   slots_to_dp(ctx, n_roots, RK, qphi_args(ctx, p, grads), s);
   node_proj_backward(ctx, grads, n_roots + RK, nullptr, tn, false, s);
@@ -995,8 +1022,9 @@ static int replay_steps(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     for (int i = 0; i < n_steps; ++i) {
       ctx->w.ucount = ctx->w.ucount_pair + ((parity + i) & 1);
       HeadArgs h;
-      head_fill(ctx, g, (2 + sets[i].nneg) * sets[i].total, p, &sets[i], lr != 0.0f ? &sgd_set : nullptr,
-                overwrite && !ctx->eval ? &zero_set_ : nullptr, out_loss != nullptr ? out_loss + i : nullptr, h);
+      head_fill(ctx, g, st, (2 + sets[i].nneg) * sets[i].total, p, &sets[i], lr != 0.0f ? &sgd_set : nullptr,
+                overwrite && !ctx->eval ? &zero_set_ : nullptr, out_loss != nullptr ? out_loss + i : nullptr,
+                step_packs(ctx, sets[i]), !ctx->eval, h);
       void* kargs[1] = {&h};
       hipKernelNodeParams np;
       memset(&np, 0, sizeof(np));
@@ -1010,6 +1038,16 @@ static int replay_steps(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
   hit->last_use = ++ctx->graph_clock;
   TGNN_HIP_CHECK(hipGraphLaunch(hit->exec, s));
   return TGNN_OK;
+}
+
+// Merge layer, decoder + loss and their backward down to the attention output are one launch (the root chain) when the
+// layer width allows it; the chain is laid out for three roots per event, the link decoder, and always runs its backward
+// half.
+static bool step_chain(const tgnn_ctx* ctx, const BatchSet& bs) {
+  return root_chain_fits(ctx->d) && bs.nneg == 1 && bs.ncls == 0 && !ctx->eval;
+}
+static int step_packs(const tgnn_ctx* ctx, const BatchSet& bs) {
+  return ctx->eval ? PACK_FORWARD : step_chain(ctx, bs) ? PACK_CHAIN : PACK_ALL;
 }
 
 // Enqueues every launch of one training step on `s` (and the context's side stream).
@@ -1030,7 +1068,8 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
   tm.begin(2);
   {  // first launch: the sampler's blocks, then the prologue's
     HeadArgs h;
-    head_fill(ctx, g, R, p, &bs, lr != 0.0f ? &sgd_set : nullptr, overwrite ? &zero_set_ : nullptr, out_loss, h);
+    head_fill(ctx, g, st, R, p, &bs, lr != 0.0f ? &sgd_set : nullptr, overwrite ? &zero_set_ : nullptr, out_loss, step_packs(ctx, bs),
+              !eval, h);
     step_head(h, s);
   }
   tm.end(2);
@@ -1039,45 +1078,60 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
   // distinct node rows to expect: an eighth of the slots (a step's slots repeat nodes many times over on the
   // power-law graphs), but never more than there are nodes.  Kernels that stride over the rows are launched for it.
   const int U_est = std::min(U, std::max(S / 8, 64));
-  GatherArgs a;
-  memset(&a, 0, sizeof(a));
-  a.mem = st->mem; a.mail = st->mail; a.efeat = g->efeat; a.mem_ts = st->mem_ts; a.mail_ts = st->mail_ts;
-  a.mail_eid = st->mail_eid; a.slot_gid = w.ulist; a.gid_add = 0; a.n_dev = w.ucount;
-  a.o_mem = w.Hm; a.p_mem = d.ldh; a.z_mem = d.ldh - d.dm;
-  a.o_mail = w.X; a.p_mail = d.ldx;
-  a.o_phi = w.X + 2 * d.dm; a.p_phi = d.ldx;
-  a.o_ef = w.X + 2 * d.dm + d.dt; a.p_ef = d.ldx; a.z_ef = d.ldx - d.d_in;
-  a.o_tau = w.tau; a.o_delta = w.delta; a.o_has = w.has;
-  a.time_w = p->time_w; a.time_b = p->time_b;
-  a.n_slots = U; a.dm = d.dm; a.dt = d.dt; a.de = d.de;
-  a.launch_rows = U_est;
-  a.map = sort_args(ctx, S);   // the slot -> row map rides along
-  a.epoch_bump = w.epoch;      // the first launch worked with epoch + 1; from here on that is the epoch
-  tm.begin(3);
-  gather_rows(a, s);
-  tm.end(3);
-  tm.begin(4);
-  {  // W_ih x and W_hh h are independent: one launch
-    const NtProblem pr[2] = {
-        nt_live(nt_problem(w.X, d.ldx, w.Wih_p, d.ldx, p->gru_bih, w.gi, d.ld3, U, 3 * d.dm, d.ldx, d.ld3, false, w.ucount),
-                d.d_in),
-        nt_live(nt_problem(w.Hm, d.ldh, w.Whh_p, d.ldh, p->gru_bhh, w.gh, d.ld3, U, 3 * d.dm, d.ldh, d.ld3, false, w.ucount),
-                d.dm)};
-    gemm_nt_group(pr, 2, s);
+  const bool nd = d.nd_rb > 0;
+  const SortArgs sort = eval ? SortArgs() : sort_args(ctx, S);   // (only the backward pass needs the sorted slot list)
+  if (nd) {   // state rows and GRU; the node part of every projection and U
+    NodeArgs na = node_args(ctx, p, U, w.ucount);
+    na.gid = w.ulist; na.row_eid = w.row_eid; na.delta = w.delta; na.mem = st->mem; na.mail = st->mail; na.efeat = g->efeat;
+    na.stat = st->stat;
+    if (!eval) {
+      na.X = w.X; na.Hm = w.Hm; na.gates = w.gates; na.dP = w.dP;
+    }
+    na.scan = sort;
+    na.epoch_bump = w.epoch;   // the first launch worked with epoch + 1; from here on that is the epoch
+    tm.begin(3);
+    node_update(na, s);
+    tm.end(3);
+    tm.begin(8);
+    node_project(na, s);
+    tm.end(8);
+  } else {
+    GatherArgs a;
+    memset(&a, 0, sizeof(a));
+    a.mem = st->mem; a.mail = st->mail; a.efeat = g->efeat; a.mem_ts = st->mem_ts; a.mail_ts = st->mail_ts;
+    a.mail_eid = st->mail_eid; a.slot_gid = w.ulist; a.gid_add = 0; a.n_dev = w.ucount;
+    a.o_mem = w.Hm; a.p_mem = d.ldh; a.z_mem = d.ldh - d.dm;
+    a.o_mail = w.X; a.p_mail = d.ldx;
+    a.o_phi = w.X + 2 * d.dm; a.p_phi = d.ldx;
+    a.o_ef = w.X + 2 * d.dm + d.dt; a.p_ef = d.ldx; a.z_ef = d.ldx - d.d_in;
+    a.o_tau = w.tau; a.o_delta = w.delta; a.o_has = w.has;
+    a.time_w = p->time_w; a.time_b = p->time_b;
+    a.n_slots = U; a.dm = d.dm; a.dt = d.dt; a.de = d.de;
+    a.launch_rows = U_est;
+    a.scan = sort;
+    a.epoch_bump = w.epoch;
+    tm.begin(3);
+    gather_rows(a, s);
+    tm.end(3);
+    tm.begin(4);
+    {  // W_ih x and W_hh h are independent: one launch
+      const NtProblem pr[2] = {
+          nt_live(nt_problem(w.X, d.ldx, w.Wih_p, d.ldx, p->gru_bih, w.gi, d.ld3, U, 3 * d.dm, d.ldx, d.ld3, false, w.ucount),
+                  d.d_in),
+          nt_live(nt_problem(w.Hm, d.ldh, w.Whh_p, d.ldh, p->gru_bhh, w.gh, d.ld3, U, 3 * d.dm, d.ldh, d.ld3, false, w.ucount),
+                  d.dm)};
+      gemm_nt_group(pr, 2, s);
+    }
+    tm.end(4);
+    tm.begin(6);   // the GRU gates -> node rows x = {s' | static}
+    gru_gates_fwd(gru_gates_args(d, U, w.ucount, w.gi, w.gh, w.Hm, w.has, w.gates, w.Xrow, d.ldxr, d.ds ? st->stat : nullptr,
+                                 w.ulist, w.dP, d.ldp, U_est), s);
+    tm.end(6);
   }
-  tm.end(4);
-  // The GRU gates (with the scan of the slot sort) -> node rows x = {s' | static}
-  tm.begin(6);
-  gru_gates_fwd(gru_gates_args(d, U, w.ucount, w.gi, w.gh, w.Hm, w.has, w.gates, w.Xrow, d.ldxr, d.ds ? st->stat : nullptr,
-                               w.ulist, w.dP, d.ldp, sort_args(ctx, S), U_est), s);
-  tm.end(6);
   // (the fill pass of the slot sort, needed by the backward pass only, rides in the attention launch)
-  // Merge layer, decoder + loss and their backward pass down to the attention output are local to an event's
-  // three roots: one launch when the layer width allows it.
-  // (the one-launch chain is laid out for three roots per event, the link decoder, and always runs its backward half)
-  const bool chain = root_chain_fits(d) && bs.nneg == 1 && !eval && !classes;
-  const AttnIn ain{w.slot_row, w.cnt, g->efeat, w.neid, nullptr, p};
-  attn_forward(ctx, p, R, U, w.ucount, ain, &tm, s, sort_args(ctx, S), !chain);
+  const bool chain = step_chain(ctx, bs);
+  const AttnIn ain{w.slot_row, w.slot_gid, w.uidx, w.cnt, g->efeat, w.neid, nullptr, p};
+  attn_forward(ctx, p, R, U, w.ucount, ain, &tm, s, !nd, sort, !chain);
 
   tm.begin(12);
   if (chain) {

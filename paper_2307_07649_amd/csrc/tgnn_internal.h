@@ -31,6 +31,9 @@ struct Dims {
   int maxNeg;   // negative sets a step may carry
   int nC, ldc;  // classes of the edge-classification head (0: link prediction) and the pitch of its [events, nC] rows
   int maxEv, maxR, maxRK, maxS, maxU;
+  // node path (k_node.hip): row blocks of 16 per tile that fit in LDS (0: the path does not fit), column blocks of the
+  // memory width, 32-wide k slabs of the GRU input, the memory row and the node row
+  int nd_rb, nd_cb, nd_kx, nd_kh, nd_kp;
 };
 
 struct BatchDesc {
@@ -67,7 +70,9 @@ struct Ws {
   int32_t *uidx, *ucount, *ulist;              // [nrep*N] row of a claimed node; [1] number of rows; [maxU] row -> gid
   int32_t* ucount_pair;                        // [2] ucount points at one of them: training steps alternate, and
                                                // each clears the counter of the next one
-  int32_t *slot_row, *ucnt, *rowptr, *cursor, *sorted;  // [S] slot -> row; [maxU] slots per row; CSR of slots by row
+  int32_t *slot_row, *gcnt, *rowptr, *cursor, *sorted;  // [S] slot -> row; [nrep*N] slots per (replica, node) of the step
+                                               // in flight, zero between steps; CSR of slots by row
+  int32_t* row_eid;                            // [maxU] event of a row's mail, -1: none
   int32_t *sorted_row, *sort_total;            // [S] row of every sorted slot; [1] number of sorted slots
   float* ds_row;                               // [maxS, ldh] gradient reaching s' per row
   float* dstat;                                // [maxS, ldst] gradient reaching the static columns per row (co-training)
@@ -95,6 +100,7 @@ struct Ws {
   float* dlog;                                 // [B, ldc] d loss / d logit of the edge-classification head
   float* loss_acc;                                   // [TGNN_MAX_BATCHES] per-batch loss sums
   // packed weights
+  unsigned short *Wg_s, *Wp_s;   // split operands of the node path: GRU; node projections followed by x -> U
   float *Wih_p, *Whh_p, *Wdec_p;
   float *Wx, *bias_x;       // [ldkv + 2 d_o, ldxr] rows {W_k ; W_v ; 0 ; W_q ; W_o} restricted to the x columns; [ldp]
   // {e | Phi} columns of W_k, W_v, block-diagonal over the heads (off-diagonal blocks stay zero):
@@ -384,12 +390,21 @@ struct PackDesc {
   // (16 columns), lane (li, lg) and c < 4:  dst[((cb * mfma_ks + s) * 64 + lg * 16 + li) * 4 + c] =
   // src[(16 cb + li) * srs + (16 s + 4 lg + c) * scs], zero beyond rows / cols: a wavefront then reads the operand
   // of one MFMA slab as 1 KB of contiguous memory.
-  int mfma_ks;
+  int16_t mfma_ks;
+  // split_ks > 0: the three bf16 parts (split3.h) in MFMA operand order instead, for blocks of split_ks k slabs of 32
+  // columns: element (r, c) is row n = row0 + r, column k = col0 + c of the operand, part p of it goes to
+  // dst[(((n / 16 * split_ks + k / 32) * split_groups + split_group) * 3 + p) * 512 + ((k % 32) / 8 * 16 + n % 16) * 8 + k % 8]
+  // (16-bit units): a wavefront reads one part of one operand slab as 1 KB of contiguous memory.  Nothing else is written.
+  int16_t split_ks, split_groups, split_group, row0, col0;
   // nblk > 0: block-diagonal instead (zero_to, mfma_ks unused).  For block h < nblk, r < rows, c < cols:
   // dst[(h * brd + r) * ldd + h * bcd + c] = src[h * bsrc + r * srs + c * scs]; nothing else is written.
-  int nblk, brd, bcd, bsrc;
+  int16_t nblk, brd, bcd;
+  int bsrc;
 };
-constexpr int MAX_PACK = 32;
+constexpr int MAX_PACK = 30;
+// What a call needs packed: every copy but the root chain's (PACK_ALL), the root chain's instead of the separate merge and
+// decoder products' (PACK_CHAIN), or only what a forward pass reads (PACK_FORWARD).
+enum { PACK_ALL = 0, PACK_CHAIN = 1, PACK_FORWARD = 2 };
 struct PrologueArgs {
   PackDesc d[MAX_PACK];
   int n_pack;
@@ -401,6 +416,11 @@ struct PrologueArgs {
   float* loss;
   unsigned long long* epoch;
   int32_t* ucount;
+  // composite weights of the score vectors (node path; Wu_s == NULL: not wanted): row h dcp + c, column j of the split
+  // operand is sum_d W_k[h dh + d, d_x + c] W_q[h dh + d, j]
+  unsigned short* Wu_s;
+  const float* wk;
+  int dkv, dc, dcp, H, kp;
   // bq_out[n] = bq[n] + sum_c wq[n, dx + c] * cos(time_b[c]): the query's time encoding Phi(0) is a constant
   const float *bq, *wq, *time_b;
   float* bq_out;
@@ -415,7 +435,7 @@ struct PrologueArgs {
   int32_t* adam_t;      // non-NULL: *adam_t += 1 (one Adam step is about to be applied)
 };
 void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, const SgdSet* sgd, const SgdSet* zero,
-                   float* loss, PrologueArgs& pa);
+                   float* loss, int what, PrologueArgs& pa);
 dim3 prologue_grid(const PrologueArgs& pa);
 void* prologue_func();
 // One launch at the start of a call: packs the weights, optionally zeroes the gradient tensors in `zero`,
@@ -432,7 +452,14 @@ void copy_f4(const void* src, void* dst, size_t n_float4, hipStream_t s);
 struct UniqPtrs {
   unsigned long long* utag;
   const unsigned long long* epoch;
-  int32_t *uidx, *ucount, *ulist, *ucnt;
+  int32_t *uidx, *ucount, *ulist;
+  // what the node's launch needs to know about a row before it can ask for its pieces: the mail's event (-1: none), its
+  // time difference and the update time of the memory as used
+  int32_t *row_eid, *has;
+  double *delta, *tau;
+  const int32_t* mail_eid;
+  const double *mem_ts, *mail_ts;
+  int32_t* gcnt;   // slots per (replica, node); NULL in a forward-only pass
 };
 // The first launch of a training step: roots of every batch (node, time, slot ids), write-back arbitration marks,
 // neighbour sampling and row claims (blocks 0 .. sample_blocks - 1, a lane group of 16 or 64 per root, 64 * SAMPLE_WAVES threads per
@@ -465,8 +492,8 @@ struct HeadArgs {
 #define TGNN_SAMPLE_WAVES 8
 #endif
 constexpr int SAMPLE_WAVES = TGNN_SAMPLE_WAVES;   // wavefronts per block in the first launch of a step (four roots each when k < 16)
-void head_fill(tgnn_ctx* ctx, const tgnn_graph* g, int n_roots, const tgnn_params* p, const BatchSet* bs,
-               const struct SgdSet* sgd, const struct SgdSet* zero, float* loss, HeadArgs& h);
+void head_fill(tgnn_ctx* ctx, const tgnn_graph* g, const tgnn_state* st, int n_roots, const tgnn_params* p, const BatchSet* bs,
+               const struct SgdSet* sgd, const struct SgdSet* zero, float* loss, int what, bool count, HeadArgs& h);
 dim3 head_grid(const HeadArgs& h);
 void* head_func();
 void step_head(const HeadArgs& h, hipStream_t s);
@@ -487,18 +514,17 @@ struct QPhi {
   int dO = 0, dq_w = 0, dx = 0, dt = 0;
 };
 __host__ __device__ inline int qphi_blocks(const QPhi& q) { return q.part != nullptr ? (q.dO * q.dt + 255) / 256 : 0; }
-// Slot -> row map and the row-sorted slot list (the latter needed by seg_reduce only).  Three small passes:
-// map (slot_row[s] = uidx[slot_gid[s]], slots counted per row), an exclusive scan of the counts, and the fill
-// (every slot takes the next free position of its row).  None gets a launch of its own in the training
-// step: they ride as extra blocks in the state-gather, GRU-gates and softmax-attention launches
-// (unique_device.h).  ucnt == NULL: nothing to do.
+// The row-sorted slot list, needed by seg_reduce only.  The first launch of a step counts the slots of every
+// (replica, node); two small passes follow: an exclusive scan of the counts in row order, and the fill (every slot takes
+// the next free position of its row).  Neither gets a launch of its own: the scan is one extra block of the
+// node launch, the fill rides as extra blocks in the attention launch (unique_device.h).  gcnt == NULL: nothing to do.
 struct SortArgs {
   const int32_t* ucount = nullptr;   // device row count
-  int32_t* ucnt = nullptr;           // slots per row
+  int32_t* gcnt = nullptr;           // slots per (replica, node); the scan leaves zeros behind
+  const int32_t* ulist = nullptr;    // row -> (replica, node)
   int32_t *rowptr = nullptr, *cursor = nullptr;
   int S = 0;
   const int32_t *slot_gid = nullptr, *uidx = nullptr;
-  int32_t* slot_row = nullptr;
   int32_t *sorted = nullptr, *sorted_row = nullptr;   // the sorted slots and, beside them, their rows
   int32_t* total = nullptr;                           // number of sorted slots (= rowptr[*ucount])
 };
@@ -522,8 +548,7 @@ void expand_rows(tgnn_ctx* ctx, int S, const float* src, int ld, const double* s
 // GRU gates (Eq. 3) from the two projections gi = W_ih x + b_ih, gh = W_hh h + b_hh, as a record: blocks of 256
 // threads, gru_total_blocks() of them.  n_dev (device, may be NULL) caps the row count.  s' goes to
 // x_out [n, ld_x]; with stat != NULL the node's static row stat[gid[row] % N] is appended (columns d_m ..
-// d_m + d_s).  zero_buf (may be NULL) [n, zero_w] is cleared for the backward pass.  scan.ucnt != NULL: block 0
-// runs the scan of the slot sort instead.
+// d_m + d_s).  zero_buf (may be NULL) [n, zero_w] is cleared for the backward pass.
 struct GruFwdArgs {
   int n_max = 0;
   const int* n_dev = nullptr;
@@ -538,14 +563,13 @@ struct GruFwdArgs {
   int N = 0;
   float* zero_buf = nullptr;
   int zero_w = 0, gru_blocks = 0;
-  SortArgs scan;
 };
 __host__ __device__ inline int gru_total_blocks(const GruFwdArgs& a) {
-  return a.gi != nullptr ? a.gru_blocks + (a.scan.ucnt != nullptr ? 1 : 0) : 0;
+  return a.gi != nullptr ? a.gru_blocks : 0;
 }
 GruFwdArgs gru_gates_args(const Dims& d, int n, const int* n_dev, const float* gi, const float* gh, const float* Hm,
                           const int32_t* has, float* gates, float* x_out, int ld_x, const float* stat, const int32_t* gid,
-                          float* zero_buf, int zero_w, const SortArgs& scan = SortArgs(), int launch_rows = 0);
+                          float* zero_buf, int zero_w, int launch_rows = 0);
 void gru_gates_fwd(const GruFwdArgs& a, hipStream_t s);
 
 // ---- k_gather.hip -------------------------------------------------------------------
@@ -567,10 +591,53 @@ struct GatherArgs {
   int32_t* o_has;
   const float *time_w, *time_b;
   int n_slots, dm, dt, de;
-  SortArgs map;             // map.ucnt != NULL: the first blocks of the launch run the slot -> row map instead
+  SortArgs scan;            // scan.gcnt != NULL: block 0 of the launch runs the scan of the slot sort instead
   unsigned long long* epoch_bump;   // may be NULL: *epoch_bump += 1 (the step's epoch becomes official here)
 };
 void gather_rows(const GatherArgs& a, hipStream_t s);
+
+// ---- k_node.hip ---------------------------------------------------------------------
+// Everything that depends on a distinct node only: its state rows and UPDT (Eq. 1-3; node_update), and the projections of
+// its row x = {s' | static} (Eq. 4-6 and the merge layer) with the score vectors U = q W_k^c (node_project).
+struct NodeArgs {
+  const int32_t* n_dev;      // device row count (NULL: n_max rows)
+  int n_max;
+  // sources: row r is node gid[r] and its mail's event row_eid[r], time difference delta[r]; gid == NULL: the staged layout
+  // of tgnn_gru_update (state of row r in row r, has_in and the times given, tau wanted); x_root != NULL: the node rows are given (tgnn_temporal_attn_fwd)
+  const int32_t* gid;
+  const float *mem, *mail, *efeat;
+  const double *mem_ts, *mail_ts;
+  const int32_t *row_eid, *has_in;
+  const double* delta;
+  const float* stat;         // static node memory [N, ds]
+  int N;
+  const float *x_root, *x_nbr;
+  const int32_t* cnt;
+  int R, k;
+  const float *time_w, *time_b;
+  // results.  X, Hm, gates, dP: kept for (cleared for) the backward pass, NULL in a forward-only pass
+  float *X, *Hm, *gates, *dP;
+  double* tau;
+  float *Xrow, *P, *U;
+  int ldx, ldh, ldxr, ldp, ldz;
+  // split weights (see PackDesc) and biases
+  const unsigned short *Wg, *Wp;
+  const float *bih, *bhh, *bias_x;   // bias_x [ldp + ldz]: biases of P, then of U, which the update launch forms:
+  float* bias_u;                     // bias_u[h dcp + c] = sum_d W_k[h dh + d, d_x + c] bias_q[h dh + d]
+  const float *wk, *bias_q;
+  int dkv, dO, dc, dcp, H;
+  int dm, dt, de, ds, dx, d_in;
+  int cb, kx, kh, kp;        // column blocks of the memory width; k slabs
+  int rb_max;                // row blocks per tile at most
+  int unit_blocks;           // blocks of the update launch before its passengers (set by node_update)
+  SortArgs scan;             // scan.gcnt != NULL: block 0 runs the scan of the slot sort instead
+  unsigned long long* epoch_bump;   // may be NULL: *epoch_bump += 1
+};
+void node_dims(Dims& d);     // fills nd_*
+NodeArgs node_args(tgnn_ctx* ctx, const tgnn_params* p, int n_max, const int32_t* n_dev);
+void node_bias(const NodeArgs& a, hipStream_t s);   // the biases of U alone
+void node_update(const NodeArgs& a, hipStream_t s);
+void node_project(const NodeArgs& a, hipStream_t s);
 
 // Standalone attention call: node rows from the caller's x_root / x_nbr (rows of absent neighbours zeroed).
 void stage_x_rows(int R, int k, int dx, const float* x_root, const float* x_nbr, const int32_t* cnt, float* Xrow,
@@ -578,12 +645,15 @@ void stage_x_rows(int R, int k, int dx, const float* x_root, const float* x_nbr,
 
 // ---- k_attn.hip ---------------------------------------------------------------------
 // Arguments of the attention kernels (Eq. 4-7 forward and backward; see k_attn.hip).  Root r's node row is
-// slot_row[r], neighbour slot (r, j)'s is slot_row[R + r k + j] (slot_row == NULL: row = slot).
+// slot_row[r], neighbour slot (r, j)'s is slot_row[R + r k + j] (slot_row == NULL: row = slot).  With slot_gid the
+// forward pass looks the rows up, uidx[slot_gid[slot]], and leaves them in slot_row for every later launch (-1: no slot).
 struct FusedAttn {
   int R, k, H, dO, dh, de, dt, dcp, ldz, ldh, ldp, ldy, off_q, dt_source, force_generic;
   const float* P;            // node rows {K | V || q | merge}, pitch ldp; q at column off_q
   const float* U;            // [rows, ldz]
-  const int32_t *slot_row, *cnt;
+  const int32_t *slot_gid, *uidx;   // forward only, may be NULL
+  int32_t* slot_row;
+  const int32_t* cnt;
   const float* efeat;        // [E, d_e]; or [R k, d_e] when neid == NULL
   const int32_t* neid;       // [R, k] edge-feature row of every slot
   const double *root_t, *nts, *tau;   // query times [R], edge times [R, k], update times per node row
@@ -594,7 +664,7 @@ struct FusedAttn {
   float *Onode, *Zp;         // forward out: node part of the attention output [R, ldh], per-head sums [R, ldz]
   const float *dOmat, *G;    // backward in: gradient of the attention output [R, ldh], G [R, ldz]
   float *dscore, *dqn, *Zs, *Y, *Qroot;   // backward out
-  SortArgs fill;             // forward only, fill.ucnt != NULL: the first blocks run the fill pass of the slot sort
+  SortArgs fill;             // forward only, fill.gcnt != NULL: the first blocks run the fill pass of the slot sort
 };
 void fattn_fwd(const FusedAttn& a, hipStream_t s);
 void fattn_bwd(const FusedAttn& a, hipStream_t s);

@@ -1,0 +1,94 @@
+"""The node path (UPDT and the per-node projections on split bf16 operands) at the row counts where its tiling changes, at
+widths with remainders in every block size, and the separate launches that take over where it does not fit."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from gpu_common import GpuSide, OracleSide, batch_np, compare_state, compare_step, custom_problem, rel_err
+from oracle import tgnn_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+# A pre-activation is a sum of K <= 850 products whose factors are at most 1/sqrt(K) and a few units: fp32 sums are off by
+# less than K 2^-24 times the largest product, 7e-6 here in the worst case and under 1e-6 in practice; the gates and the
+# projections that follow do not enlarge that.
+NODE_TOL = 1e-5
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def dims(d_mem, d_time, d_edge, d_static=0, H=1, k=10, batch=400):
+    return synth.ModelDims(n_nodes=50, d_mem=d_mem, d_time=d_time, d_edge=d_edge, d_static=d_static, n_heads=H, k=k, batch=batch)
+
+
+def make(d):
+    from paper_2307_07649_amd import tgnn
+    p32 = synth.gen_params(d, seed=3, random_phase=True)
+    ctx = tgnn.Context(d.n_nodes, d.d_mem, d.d_time, d.d_edge, d.d_static, d.n_heads, d.k, d.batch)
+    return tgnn, ctx, p32, tgnn.Params.from_numpy(p32)
+
+
+# rows: one tile, a remainder of one row, both sides of every change of row blocks and column groups (252 workgroups)
+ROWS = [1, 15, 16, 17, 1008, 1009, 1344, 1345, 2017, 4033, 6049, 8065, 12097, 13200]
+
+
+@pytest.mark.parametrize("widths,n", [((100, 100, 172), n) for n in ROWS]
+                         + [(w, n) for w in ((128, 1, 255), (16, 5, 0), (7, 30, 3)) for n in (1, 17, 1345, 4033, 12097)])
+def test_gru_update_row_counts(widths, n):
+    d = dims(*widths)
+    tgnn, ctx, p32, params = make(d)
+    rng = np.random.default_rng(n)
+    mem = rng.uniform(-1, 1, (n, d.d_mem)).astype(np.float32); mail = rng.uniform(-1, 1, (n, 2 * d.d_mem)).astype(np.float32)
+    ef = rng.standard_normal((n, d.d_edge)).astype(np.float32)
+    has = (rng.random(n) < 0.8).astype(np.int32)
+    mem_ts = rng.uniform(0, 1e6, n); mail_ts = mem_ts + rng.uniform(0, 1e6, n)
+    s, tau = ctx.tgnn_gru_update(params, dict(mem=dev(mem), mail=dev(mail), mail_efeat=dev(ef) if d.d_edge else torch.empty(n, 0, device="cuda"),
+                                              mem_ts=dev(mem_ts), mail_ts=dev(mail_ts), has_mail=dev(has)))
+    p = O.to_f64(p32)
+    x = np.concatenate([mail, O.time_encode(mail_ts - mem_ts, p["time_w"], p["time_b"]), ef], axis=1).astype(np.float64)
+    ref = O.gru_cell(x, mem.astype(np.float64), p["gru_wih"], p["gru_whh"], p["gru_bih"], p["gru_bhh"])
+    ref = np.where(has[:, None] > 0, ref, mem)
+    assert rel_err(s.cpu().numpy(), ref) <= NODE_TOL
+    assert np.array_equal(tau.cpu().numpy(), np.where(has > 0, mail_ts, mem_ts))
+
+
+# node rows R (1 + k) of the stand-alone attention call: row blocks of 16, 32, 64, remainders; one and two heads, a head
+# boundary inside a column block, static columns (more k slabs)
+@pytest.mark.parametrize("widths,R", [((100, 100, 172, 0, 2), R) for R in (1, 3, 93, 186, 373, 745, 1200)]
+                         + [(w, R) for w in ((100, 100, 131, 100, 2), (30, 9, 5, 3, 3)) for R in (3, 745)])
+def test_projections_row_counts(widths, R):
+    d = dims(*widths)
+    tgnn, ctx, p32, params = make(d)
+    rng = np.random.default_rng(R)
+    k = d.k
+    x_root = rng.uniform(-1, 1, (R, d.d_x)).astype(np.float32); x_nbr = rng.uniform(-1, 1, (R, k, d.d_x)).astype(np.float32)
+    e = rng.standard_normal((R, k, d.d_edge)).astype(np.float32); dt = rng.uniform(0, 3e5, (R, k))
+    cnt = rng.integers(0, k + 1, R).astype(np.int32); cnt[0] = k
+    z = ctx.tgnn_temporal_attn_fwd(params, dev(x_root), dev(x_nbr.reshape(R * k, -1)), dev(e.reshape(R * k, -1)),
+                                   dev(dt.reshape(-1)), dev(cnt))
+    mask = np.arange(k)[None] < cnt[:, None]
+    ref, _ = O.attention_fwd(O.to_f64(p32), x_root.astype(np.float64), x_nbr * mask[..., None], e * mask[..., None], dt * mask,
+                             cnt.astype(np.int64), d.n_heads)
+    assert rel_err(z.cpu().numpy(), ref) <= NODE_TOL
+
+
+# where the node path does not fit: a memory wider than eight column blocks, a GRU input wider than the LDS tile, node rows
+# of more than eight k slabs; and one just inside (a single row block per tile)
+@pytest.mark.parametrize("shape", [
+    dict(d_mem=130, d_time=10, d_edge=4, d_static=0, n_heads=2, k=4),
+    dict(d_mem=16, d_time=10, d_edge=2500, d_static=0, n_heads=1, k=3),
+    dict(d_mem=20, d_time=10, d_edge=6, d_static=300, n_heads=2, k=4),
+    dict(d_mem=16, d_time=10, d_edge=1200, d_static=0, n_heads=1, k=3),
+])
+def test_step_at_the_limits_of_the_node_path(shape):
+    P = custom_problem(n_nodes=60, E=240, batch=40, seed=5, **shape)
+    G = GpuSide(P); Or = OracleSide(P)
+    for s in range(4):
+        b = batch_np(P, s * 40, (s + 1) * 40)
+        g = G.step([b], lr=0.01)
+        o = Or.step([b], lr=0.01, gpu=g)
+        compare_step(g, o, label=f"{shape} step {s}")
+    compare_state(G.state_np(), Or.states[0])
