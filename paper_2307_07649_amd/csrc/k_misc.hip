@@ -34,7 +34,8 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
     const int dO = d.dO, dm = d.dm, dx = d.dx, dkv = d.dkv, dmrg = d.dO + d.dx, half = d.ldkv;
     // node part of every projection of x = {s' | static}: output columns {W_k ; W_v} then, from column `half`,
     // {W_q ; W_o} (columns 2 d_o .. half stay zero)
-    if (d.nd_rb > 0) {   // split operands of the node path (pads stay zero)
+    const bool nd = node_path(d, !backward);
+    if (nd) {   // split operands of the node path (pads stay zero)
       auto add_split = [&](const float* src, unsigned short* dst, int rows, int cols, int srs, int scs, int ks, int groups, int group,
                            int row0, int col0) {
         PackDesc& q = pa.d[n++];
@@ -71,7 +72,7 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
     if (d.de + d.dt > 0) {
       const int dh = dO / d.H, dc = d.de + d.dt;
       // row h dcp + c, column h dh + dd  <-  W[h dh + dd, d_x + c]
-      if (d.nd_rb == 0) add_bd(p->wk + dx, w.WkcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
+      if (!nd) add_bd(p->wk + dx, w.WkcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
       if (backward) add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
       // row h dh + dd, column h dcp + c  <-  W[h dh + dd, d_x + c]
       if (backward) add_bd(p->wk + dx, w.Wkc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);

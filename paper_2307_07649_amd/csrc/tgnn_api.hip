@@ -104,7 +104,7 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   w.sgd_dev = b.take<SgdSet>(1);
   w.q_part = b.take<float>((size_t)QPHI_BLOCKS * d.dO);
   w.X = b.take<float>(S * d.ldx); w.Hm = b.take<float>(S * d.ldh);
-  w.gi = d.nd_rb > 0 ? nullptr : b.take<float>(S * d.ld3); w.gh = d.nd_rb > 0 ? nullptr : b.take<float>(S * d.ld3);
+  w.gi = b.take<float>(S * d.ld3); w.gh = b.take<float>(S * d.ld3);
   w.gates = b.take<float>(S * 4 * d.ldh); w.Xrow = b.take<float>(S * d.ldxr);
   w.dgi = b.take<float>(S * d.ld3); w.dgh = b.take<float>(S * d.ld3);
   // node rows of a standalone attention call are its slots, so P / dP hold S rows (a step uses far fewer)
@@ -122,15 +122,15 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   w.logits = b.take<float>(std::max(B2, (size_t)d.maxEv * (size_t)d.nC));
   w.dlog = b.take<float>(d.nC > 0 ? (size_t)d.maxEv * d.ldc : 4);
   w.loss_acc = b.take<float>(TGNN_MAX_BATCHES);
-  // either the split operands of the one-launch node path or the copies that the separate products read
+  // the split operands of the two-launch node path, and the copies that the separate products read (see node_path)
   const bool nd = d.nd_rb > 0;
   w.Wg_s = nd ? b.take<unsigned short>((size_t)d.nd_cb * (d.nd_kx + d.nd_kh) * 3 * 1536) : nullptr;
   w.Wp_s = nd ? b.take<unsigned short>((size_t)((d.ldp + d.ldz) / 16) * d.nd_kp * 1536) : nullptr;
-  w.Wih_p = nd ? nullptr : b.take<float>((size_t)3 * d.dm * d.ldx);
-  w.Whh_p = nd ? nullptr : b.take<float>((size_t)3 * d.dm * d.ldh);
+  w.Wih_p = b.take<float>((size_t)3 * d.dm * d.ldx);
+  w.Whh_p = b.take<float>((size_t)3 * d.dm * d.ldh);
   w.Wdec_p = b.take<float>((size_t)2 * d.dO * d.ldh);
-  w.Wx = nd ? nullptr : b.take<float>((size_t)d.ldp * d.ldxr); w.bias_x = b.take<float>((size_t)d.ldp + (nd ? d.ldz : 0));
-  w.WkcT = nd ? nullptr : b.take<float>((size_t)d.H * d.dcp * d.ldh + 32); w.WvcT = b.take<float>((size_t)d.H * d.dcp * d.ldh + 32);
+  w.Wx = b.take<float>((size_t)d.ldp * d.ldxr); w.bias_x = b.take<float>((size_t)d.ldp + (nd ? d.ldz : 0));
+  w.WkcT = b.take<float>((size_t)d.H * d.dcp * d.ldh + 32); w.WvcT = b.take<float>((size_t)d.H * d.dcp * d.ldh + 32);
   w.Wkc = b.take<float>((size_t)d.dO * d.ldz); w.Wvc = b.take<float>((size_t)d.dO * d.ldz);
   w.Wo_o = b.take<float>((size_t)d.dO * d.ldh);
   {
@@ -601,7 +601,7 @@ int32_t tgnn_gru_update(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_slots, co
   if (d.de > 0) REQ_PTR(mail_efeat);
   hipStream_t s = as_stream(stream);
   prologue(ctx, p, nullptr, nullptr, nullptr, nullptr, s);
-  if (d.nd_rb > 0) {
+  if (node_path(d, false)) {
     NodeArgs na = node_args(ctx, p, n_slots, nullptr);
     na.mem = mem; na.mail = mail; na.efeat = mail_efeat; na.mem_ts = mem_ts; na.mail_ts = mail_ts; na.has_in = has_mail;
     na.tau = out_tau; na.Xrow = out_s_new; na.ldxr = d.dm; na.ds = 0; na.bias_u = nullptr;
@@ -642,7 +642,7 @@ int32_t tgnn_temporal_attn_fwd(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_ro
   hipStream_t s = as_stream(stream);
   prologue(ctx, p, nullptr, nullptr, nullptr, nullptr, s);
   TGNN_HIP_CHECK(hipMemcpyAsync(w.cnt, cnt, sizeof(int32_t) * n_roots, hipMemcpyDeviceToDevice, s));
-  const bool nd = d.nd_rb > 0;
+  const bool nd = node_path(d, false);
   if (nd) {
     node_bias(node_args(ctx, p, 0, nullptr), s);
     NodeArgs na = node_args(ctx, p, n_roots * (1 + d.k), nullptr);
@@ -1078,7 +1078,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
   // distinct node rows to expect: an eighth of the slots (a step's slots repeat nodes many times over on the
   // power-law graphs), but never more than there are nodes.  Kernels that stride over the rows are launched for it.
   const int U_est = std::min(U, std::max(S / 8, 64));
-  const bool nd = d.nd_rb > 0;
+  const bool nd = node_path(d, eval);
   const SortArgs sort = eval ? SortArgs() : sort_args(ctx, S);   // (only the backward pass needs the sorted slot list)
   if (nd) {   // state rows and GRU; the node part of every projection and U
     NodeArgs na = node_args(ctx, p, U, w.ucount);
@@ -1125,7 +1125,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     tm.end(4);
     tm.begin(6);   // the GRU gates -> node rows x = {s' | static}
     gru_gates_fwd(gru_gates_args(d, U, w.ucount, w.gi, w.gh, w.Hm, w.has, w.gates, w.Xrow, d.ldxr, d.ds ? st->stat : nullptr,
-                                 w.ulist, w.dP, d.ldp, U_est), s);
+                                 w.ulist, eval ? nullptr : w.dP, d.ldp, U_est), s);   // (dP: the backward pass)
     tm.end(6);
   }
   // (the fill pass of the slot sort, needed by the backward pass only, rides in the attention launch)

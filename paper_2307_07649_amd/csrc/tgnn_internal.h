@@ -36,6 +36,13 @@ struct Dims {
   int nd_rb, nd_cb, nd_kx, nd_kh, nd_kp;
 };
 
+// Which launches do the node half of a call: the two on split bf16 operands (k_node.hip) or the five separate ones.
+// Evaluation passes take the separate ones although they are a little slower (600 events with 49 negatives each: 385
+// against 378 us): a pass returns ranks and counts, decided by comparing scores, and two scores that differ by less than
+// one rounding change places when the sums are rounded in another way (one rank of 600 did, among 30,600 scores).  With
+// the separate products a stored model's ranks stay what they have been.
+inline bool node_path(const Dims& d, bool evaluating) { return d.nd_rb > 0 && !evaluating; }
+
 struct BatchDesc {
   const int32_t *src, *dst, *neg, *eid;
   const double* t;
