@@ -15,11 +15,10 @@
 
 #include "tgnn_internal.h"
 #include "device_math.h"
+#include "split3.h"
 #include "writeback_device.h"
 
 namespace tgnn {
-
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // A row count that an earlier kernel left in memory, read through the scalar cache (a third of the latency of a
 // vector load; nothing in these kernels writes it).
@@ -455,25 +454,29 @@ void gemm_nt(const float* A, int lda, const float* B, int ldb, const float* bias
 
 // ------------------------------------------------------------------------------------------------
 // TN with accumulation: G[n, k] += sum_m D[m, n] * A[m, k], bias[n] += sum_m D[m, n].
-// Both operands are m-major.  The MFMA sums over four m values per instruction (one per lane group), and
-// which n (k) a lane feeds is free as long as the result is read back the same way: lane (li, lg) takes TD
-// consecutive floats D[m][n0 + TD*li ..] and TA consecutive floats A[m][k0 + TA*li ..] of row m = 4 step + lg
-// and issues TD*TA MFMAs from them, instruction (t, u) covering the strided columns n = n0 + TD*i + t,
-// k = k0 + TA*j + u.  Those two runs are one vector load each straight from global memory (a lane group reads
-// one contiguous piece of a row), and no element is used by more than one wavefront, so nothing is staged in
-// LDS and the main loop has no barrier: every wavefront streams its own rows, several steps of loads ahead.
+// Both operands are m-major, and the sum runs over m: an operand run of the MFMA is eight rows of one column.  Lane
+// (li, lg) takes TD consecutive floats D[m][n0 + TD*li ..] and TA consecutive floats A[m][k0 + TA*li ..] of the eight
+// rows m = 32 step + 8 lg + j (sixteen vector loads, a lane group reads one contiguous piece of a row), which is the
+// operand run of TD (TA) strided columns n = n0 + TD*i + t (k = k0 + TA*j + u): the transposition happens in the
+// lane's own registers while the fp32 values are split into their three bf16 parts (split3.h), nothing is staged in
+// LDS and the main loop has no barrier.
 // A workgroup of TN_W wavefronts owns a (16 TD) x (16 TA) tile of G (64 x 64 in the bulk, narrower pieces
 // at the right and bottom edges so that little of the tile is padding) over a chunk of the rows; its
-// wavefronts take the 4-row steps of the chunk in turn, and their partial tiles are added in LDS before one
+// wavefronts take the 32-row steps of the chunk in turn, and their partial tiles are added in LDS before one
 // float atomic per element goes to memory.  The reduction over m is split over workgroups.
+// What bounds it: the operands (190 MB a step of 4,000 events) come from beyond the L2s, once per chunk, and a tile
+// re-reads them from its XCD's L2; the six MFMAs per pair of operands are 17 us of the launch.  Weight gradients of a
+// 4,000-event step 113 -> 80 us, of a 600-event one 24.0 -> 18.6 us, of the stand-alone backward call 58 -> 49 us
+// against fp32 MFMAs on 4-row steps.  Relative error against double over 600 to 2,400 roots: 1.3e-7 to 2.0e-7 for W_v
+// and W_o (fp32 MFMA: 1.6e-7 to 2.5e-7).
 // The bias gradient rides along as column K of A, which the loader replaces by ones.
 // ------------------------------------------------------------------------------------------------
 constexpr int TT = 64;        // bulk tile edge
 #ifndef TGNN_TN_WAVES
-#define TGNN_TN_WAVES 8
+#define TGNN_TN_WAVES 4
 #endif
 constexpr int TN_W = TGNN_TN_WAVES;   // wavefronts per workgroup
-constexpr int TN_AHEAD = 4;   // 4-row steps whose loads a wavefront keeps in flight
+constexpr int TN_STEP = 32;   // rows per step of a wavefront: the depth of one MFMA
 constexpr int TN_ROWS = 32;   // row chunks are multiples of this
 
 // A length is cut into 64-wide pieces plus one narrower one (16, 32 or again 64 wide) for the remainder.  (With
@@ -514,20 +517,10 @@ template <int T> __device__ __forceinline__ typename FragT<T>::type frag_zero() 
   return f;
 }
 
-// One global load of T floats per lane, issued without a wait; tn_wait_loads<N> then waits until at most N of
-// the loads issued so far are pending and ties the registers to that wait, so that no use can move above it.
-template <int T> __device__ __forceinline__ void tn_issue_load(typename FragT<T>::type& r, const float* p);
-template <> __device__ __forceinline__ void tn_issue_load<4>(FragT<4>::type& r, const float* p) {
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=&v"(r) : "v"(p) : "memory");
-}
-template <> __device__ __forceinline__ void tn_issue_load<2>(FragT<2>::type& r, const float* p) {
-  asm volatile("global_load_dwordx2 %0, %1, off" : "=&v"(r) : "v"(p) : "memory");
-}
-template <> __device__ __forceinline__ void tn_issue_load<1>(float& r, const float* p) {
-  asm volatile("global_load_dword %0, %1, off" : "=&v"(r) : "v"(p) : "memory");
-}
-template <int N, class FD, class FA> __device__ __forceinline__ void tn_wait_loads(FD& d, FA& a) {
-  asm volatile("s_waitcnt vmcnt(%2)" : "+v"(d), "+v"(a) : "n"(N));
+// The MFMA operand run of column t: eight rows of one column, as three bf16 parts.
+template <int T> __device__ __forceinline__ Split8 tn_split(const typename FragT<T>::type (&f)[8], int t) {
+  return split8(floatx4{frag_get<T>(f[0], t), frag_get<T>(f[1], t), frag_get<T>(f[2], t), frag_get<T>(f[3], t)},
+                floatx4{frag_get<T>(f[4], t), frag_get<T>(f[5], t), frag_get<T>(f[6], t), frag_get<T>(f[7], t)});
 }
 
 // Where partial-tile element (t, u, v) of lane (li, lg) lives in a reduction buffer: element-major, lane-minor
@@ -557,73 +550,76 @@ __device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float
     for (int u = 0; u < TA; ++u) acc[t][u] = floatx4{0.f, 0.f, 0.f, 0.f};
 
   // Column offsets are clamped into the row (results of columns >= N or > K are dropped at the end); rows
-  // >= m_hi are clamped and D is zeroed there by a select when the step is used.
+  // >= m_hi are clamped and D is zeroed there.
   const int c_nom = k0 + TA * li;
   const float* pd = D + min(n0 + TD * li, dw - TD);   // dw, aw: columns that may be read from D, A (<= the pitch)
   const float* pa = A + min(c_nom, aw - TA);
-  const int one_comp = (with_bias && K >= c_nom && K < c_nom + TA) ? K - c_nom : -1;
-  const int n_steps = (m_hi - m_lo + 3) >> 2;
+  const bool ones = with_bias && K >= k0 && K < k0 + 16 * TA;
+  const int n_steps = (m_hi - m_lo + TN_STEP - 1) / TN_STEP;
 
-  // The loads are issued as inline assembly and waited for by count: left to itself the compiler sinks them
-  // next to their uses and the wavefront then waits out the full memory latency at every step.  Loads return in
-  // order, so when slot p is needed only the loads of the other TN_AHEAD - 1 slots (two each) may be pending.
-  // 4-row steps whose loads a wavefront keeps in flight: a step of a narrow tile has few MFMAs to hide the
-  // memory latency behind, so more of them are kept in flight.
-  constexpr int AH = TD * TA >= 16 ? TN_AHEAD : TD * TA >= 8 ? TN_AHEAD + 2 : 2 * TN_AHEAD;
-  FD fd[AH];
-  FA fa[AH];
-  auto issue = [&](int step, FD& d, FA& a) __attribute__((always_inline)) {
-    const size_t m = (size_t)min(m_lo + 4 * step + lg, M - 1);
-    tn_issue_load<TD>(d, pd + m * ldd);
-    tn_issue_load<TA>(a, pa + m * lda);
-  };
-  auto use = [&](int step, FD d, FA a) __attribute__((always_inline)) {
-    if (m_lo + 4 * step + lg >= m_hi) d = frag_zero<TD>();   // rows out of range: zeros times whatever A holds
-    if (one_comp >= 0) {
+  FD fd[8];
+  FA fa[8];
+  auto load = [&](int step) __attribute__((always_inline)) {   // (past the end: clamped rows, unused)
+    const int m = m_lo + TN_STEP * step + 8 * lg;
 #pragma unroll
-      for (int u = 0; u < TA; ++u)
-        if (one_comp == u) frag_set<TA>(a, u, 1.f);
-    }
+    for (int j = 0; j < 8; ++j) fd[j] = *reinterpret_cast<const FD*>(pd + (size_t)min(m + j, M - 1) * ldd);
 #pragma unroll
-    for (int t = 0; t < TD; ++t)
-#pragma unroll
-      for (int u = 0; u < TA; ++u)
-        acc[t][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(frag_get<TD>(d, t), frag_get<TA>(a, u), acc[t][u], 0, 0, 0);
+    for (int j = 0; j < 8; ++j) fa[j] = *reinterpret_cast<const FA*>(pa + (size_t)min(m + j, M - 1) * lda);
   };
 
-  // Steps are not dealt out in advance beyond the first TN_AHEAD per wavefront: a wavefront that is done with a
-  // step claims the next free one from a counter in LDS.  The wavefronts of a workgroup share their SIMDs
-  // unevenly (the oldest wins the MFMA pipe), and with a fixed split the youngest would still be at work, alone
-  // and unable to hide its load latency, long after the others had reached the barrier below.
+  // Steps are not dealt out in advance beyond the first per wavefront: a wavefront that is done with a step claims the
+  // next free one from a counter in LDS (the wavefronts of a workgroup share their SIMDs unevenly).
   int* next_step = reinterpret_cast<int*>(lds + (TN_W / 2) * TT * TT);
   auto claim = [&]() __attribute__((always_inline)) {
     int v = 0;
     if (lane == 0) v = atomicAdd(next_step, 1);
     return __builtin_amdgcn_readfirstlane(v);
   };
-  int sidx[AH];   // the step each slot holds; claims only grow, so a slot past the end means all later are
-#pragma unroll
-  for (int p = 0; p < AH; ++p) {
-    sidx[p] = wave + p * TN_W;
-    issue(sidx[p], fd[p], fa[p]);   // past the end: clamped rows, unused
-  }
-  if (tid == 0) *next_step = TN_W * AH;   // (after the first loads are on their way)
+  int step = wave;
+  load(step);
+  if (tid == 0) *next_step = TN_W;   // (after the first loads are on their way)
   __syncthreads();
-  int nxt = claim();
-  // slot 0 holds the oldest claim: once that is past the end, so are the others
-  while (sidx[0] < n_steps) {
+  while (step < n_steps) {
+    const int nxt = claim();
+    if (m_lo + TN_STEP * (step + 1) > m_hi) {   // rows out of range: zeros times whatever A holds
+      const int m = m_lo + TN_STEP * step + 8 * lg;
 #pragma unroll
-    for (int p = 0; p < AH; ++p) {   // (unrolled: the slots are registers)
-      tn_wait_loads<2 * (AH - 1)>(fd[p], fa[p]);
-      if (sidx[p] < n_steps) use(sidx[p], fd[p], fa[p]);
-      sidx[p] = nxt;
-      issue(nxt, fd[p], fa[p]);
-      nxt = claim();
+      for (int j = 0; j < 8; ++j)
+        if (m + j >= m_hi) fd[j] = frag_zero<TD>();
+    }
+    if (ones) {
+#pragma unroll
+      for (int u = 0; u < TA; ++u)
+        if (c_nom + u == K) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) frag_set<TA>(fa[j], u, 1.f);
+        }
+    }
+    Split8 d[TD], a[TA];
+#pragma unroll
+    for (int t = 0; t < TD; ++t) d[t] = tn_split<TD>(fd, t);
+#pragma unroll
+    for (int u = 0; u < TA; ++u) a[u] = tn_split<TA>(fa, u);
+    // the next step's rows are asked for as soon as the registers are free, and come in beside this step's products
+    __builtin_amdgcn_sched_barrier(0);
+    step = nxt;
+    load(step);
+    __builtin_amdgcn_sched_barrier(0);
+    // A step's sum is formed from zero, smallest terms first, and added to the running sum once: one rounding of the
+    // large sum per 32 rows instead of six.
+#pragma unroll
+    for (int t = 0; t < TD; ++t) {
+      floatx4 part[TA];
+#pragma unroll
+      for (int q = 0; q < SPLIT_TERMS; ++q)
+#pragma unroll
+        for (int u = 0; u < TA; ++u)
+          part[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(d[t].p[split_ta(q)], a[u].p[split_tb(q)],
+                                                            q == 0 ? floatx4{0.f, 0.f, 0.f, 0.f} : part[u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < TA; ++u) acc[t][u] += part[u];
     }
   }
-  // every issued load has to land before its registers are given to anything else
-#pragma unroll
-  for (int p = 0; p < AH; ++p) tn_wait_loads<0>(fd[p], fa[p]);
 
   // Add the wavefronts' partial tiles in LDS: the lower half of the wavefronts store theirs into a buffer
   // each, the upper half add theirs on top, then every thread sums the buffers for its elements and issues
@@ -676,7 +672,7 @@ __device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float
 }
 
 static_assert(sizeof(TnGroup) <= 4096, "the group travels as a kernel argument");
-__global__ __launch_bounds__(64 * TN_W) void gemm_tn_kernel(TnGroup grp) {
+__global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tn_kernel(TnGroup grp) {
   // Several independent problems share one launch (all weight gradients of a step): find this workgroup's.
   // The argument block is indexed through the kernel-argument segment itself (scalar loads at a computed
   // offset); indexing the by-value parameter would make the compiler spill the whole block to scratch.
@@ -784,12 +780,12 @@ void TnBatch::add(const float* D, int ldd, const float* A, int lda, int M, int N
 // finish early, and queues of 72 to 88 measured best on MI355X for the weight gradients of a 600-event step
 // (64 and 96: a fifth slower).  All problems of a launch use the same chunk length.
 // What in-kernel timestamps say about such a launch: a workgroup sees its first rows 3 to 5 us after it starts
-// (argument block, device-side row count, then the rows: three dependent round trips), a wavefront then takes
-// 0.5 to 0.8 us per 4-row step whatever the tile width, because the loads of narrow tiles are 64- to 256-byte
-// pieces of four rows and the texture addresser, not the MFMA pipe, is what the 16 wavefronts of a compute unit
-// queue for; the reduction and the atomics take 2 to 3 us.
+// (argument block, device-side row count, then the rows: three dependent round trips); the reduction and the atomics
+// take 2 to 3 us.  Four wavefronts per workgroup, two workgroups per compute unit: one's reduction runs beside the
+// other's products (eight: 108 against 90 us on a 4,000-event step, 21.7 against 18.3 us on a 600-event one, both with
+// chunks of at most 1,024 rows; 2,048 rows: 77 us on the former, the atomics halve).
 #ifndef TGNN_TN_MAX_ROWS
-#define TGNN_TN_MAX_ROWS 1024
+#define TGNN_TN_MAX_ROWS 2048
 #endif
 #ifndef TGNN_TN_WGS_PER_XCD
 #define TGNN_TN_WGS_PER_XCD 80
