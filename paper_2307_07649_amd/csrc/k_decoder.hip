@@ -117,10 +117,9 @@ __global__ __launch_bounds__(256) void dec_pair_kernel(const BatchSet* __restric
   if (lane == 0) { red[wave][256] = gb; red[wave][257] = lsum; }
   __syncthreads();
   if (wave == 0) {
-    if (g_w2 != nullptr)    // (NULL in a forward-only pass)
-      for (int c = lane; c < dO; c += 64) atomicAdd(g_w2 + c, red[0][c] + red[1][c] + red[2][c] + red[3][c]);
+    for (int c = lane; c < dO; c += 64) atomicAdd(g_w2 + c, red[0][c] + red[1][c] + red[2][c] + red[3][c]);
     if (lane == 0) {
-      if (g_b2 != nullptr) atomicAdd(g_b2, red[0][256] + red[1][256] + red[2][256] + red[3][256]);
+      atomicAdd(g_b2, red[0][256] + red[1][256] + red[2][256] + red[3][256]);
       if (out_loss != nullptr) atomicAdd(out_loss, red[0][257] + red[1][257] + red[2][257] + red[3][257]);
     }
   }
@@ -134,119 +133,247 @@ void decoder_pairs(const Dims& d, const BatchSet* bs, int total, const float* Pd
                      w2, b2, logits, out_loss, h1, d.ldh, dPdec, g_w2, g_b2);
 }
 
-// Edge-classification head (Sec. 4 "Datasets": C classes, several true per event).  One wavefront per event: hidden
-// layer h = ReLU(W_s z_src + W_d z_dst + b1) from the two roots' rows of Pdec, then class by class the logit
-// W2[c] . h + b2[c] (a row of W2 per lane round, summed over the wavefront), its cross-entropy term
+// Edge-classification head (Sec. 4 "Datasets": C classes, several true per event): hidden layer
+// h = ReLU(W_s z_src + W_d z_dst + b1) from the two roots' rows of Pdec, logits W2 h + b2, cross-entropy terms
 // softplus(logit) - y logit, d loss / d logit = (sigmoid(logit) - y) / (n C), and the hidden layer's gradient
-// sum_c dlogit_c W2[c] gated by the ReLU.  Roots of batch b: [src | dst] from root 2 * ev_off on.  The weight
+// W2^T dlogit gated by the ReLU.  Roots of batch b: [src | dst] from root 2 * ev_off on.  The weight
 // gradients of W2 / b2 are left to the weight-gradient GEMM (dlog^T h1).
+// A workgroup takes DC_E events; both products are fp32 MFMAs (16 events x 16 columns per wavefront and round) whose
+// left operands stay in LDS, and the cross-entropy is evaluated once per (event, class).  4,000 events with 56 classes:
+// 77 us with a wavefront per event that went through the classes one by one (all 64 lanes evaluating the same
+// exponentials), 18 us this way; the launch is then bound by its phases' latencies.
+constexpr int DC_E = 16;
+constexpr int DC_HP = 256 + 4, DC_LP = 256 + 4;   // LDS pitches: widest hidden layer, most classes (4 mod 64 banks)
 __global__ __launch_bounds__(256) void dec_class_kernel(const BatchSet* __restrict__ bsp, int dO, int C,
                                                         const float* __restrict__ Pdec, int ldp,
                                                         const float* __restrict__ b1, const float* __restrict__ w2,
                                                         const float* __restrict__ b2, float* __restrict__ logits,
                                                         float* __restrict__ out_loss, float* __restrict__ h1, int ldh,
                                                         float* __restrict__ dPdec, float* __restrict__ dlog, int ldc) {
-  __shared__ float red[4];
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) float H[DC_E * DC_HP], L[DC_E * DC_LP];
+  __shared__ const float* y_s[DC_E];
+  __shared__ float inv_s[DC_E], red[4];
+  __shared__ int src_s[DC_E], dst_s[DC_E];
+  const BatchSet& bs = *bsp;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const int ev0 = blockIdx.x * DC_E, n_here = min(DC_E, bs.total - ev0);
+  if (tid < DC_E) {
+    const int ev = ev0 + min(tid, n_here - 1), b = batch_of_row(bs, ev, 1), off = bs.b[b].ev_off, n = bs.b[b].n, i = ev - off;
+    src_s[tid] = 2 * off + i;
+    dst_s[tid] = 2 * off + i + n;
+    y_s[tid] = bs.b[b].labels + (size_t)i * C;
+    inv_s[tid] = tid < n_here ? 1.0f / ((float)n * (float)C) : 0.f;
+  }
+  __syncthreads();
+  const int dOp = (dO + 63) & ~63, Cp = (C + 63) & ~63;   // four k slabs of either product at a time
+#pragma unroll 4
+  for (int idx = tid; idx < DC_E * dOp; idx += 256) {
+    const int e = idx / dOp, c = idx - e * dOp;
+    float h = 0.f;
+    if (c < dO) {
+      h = fmaxf(Pdec[(size_t)src_s[e] * ldp + c] + b1[c] + Pdec[(size_t)dst_s[e] * ldp + dO + c], 0.f);
+      if (e < n_here) h1[(size_t)(ev0 + e) * ldh + c] = h;
+    }
+    H[e * DC_HP + c] = h;
+  }
+  __syncthreads();
+  float lsum = 0.f;
+  for (int cb = wave; cb < Cp / 16; cb += 4) {
+    const int cls = cb * 16 + li;
+    const float* __restrict__ wr = w2 + (size_t)min(cls, C - 1) * dO;
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s0 = 0; s0 < dOp / 16; s0 += 4)
+#pragma unroll
+    for (int s = s0; s < s0 + 4; ++s) {
+      const floatx4 a4 = *reinterpret_cast<const floatx4*>(&H[li * DC_HP + 16 * s + 4 * lg]);
+      float w[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w[c] = wr[min(16 * s + 4 * lg + c, dO - 1)];   // (columns past d_o meet zeros of H)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[c], w[c], acc, 0, 0, 0);
+    }
+    const float bias = b2[min(cls, C - 1)];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int e = 4 * lg + v;
+      const float lgt = acc[v] + bias, yv = y_s[e][min(cls, C - 1)];
+      const float sgm = 1.0f / (1.0f + expf(-lgt));
+      const bool live = cls < C && e < n_here;
+      const float dl = live ? (sgm - yv) * inv_s[e] : 0.f;
+      if (live) {
+        lsum += (fmaxf(lgt, 0.f) + log1pf(expf(-fabsf(lgt))) - yv * lgt) * inv_s[e];
+        logits[(size_t)(ev0 + e) * C + cls] = lgt;
+        dlog[(size_t)(ev0 + e) * ldc + cls] = dl;
+      }
+      L[e * DC_LP + cls] = dl;
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
+  if (lane == 0) red[wave] = lsum;
+  __syncthreads();
+  if (tid == 0 && out_loss != nullptr) atomicAdd(out_loss, (red[0] + red[1] + red[2] + red[3]) / (float)bs.nb);
+  for (int cb = wave; cb * 16 < dO; cb += 4) {
+    const int col = cb * 16 + li, colc = min(col, dO - 1);
+    floatx4 acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s0 = 0; s0 < Cp / 16; s0 += 4)
+#pragma unroll
+    for (int s = s0; s < s0 + 4; ++s) {
+      const floatx4 a4 = *reinterpret_cast<const floatx4*>(&L[li * DC_LP + 16 * s + 4 * lg]);
+      float w[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) w[c] = w2[(size_t)min(16 * s + 4 * lg + c, C - 1) * dO + colc];   // (classes past C meet zeros)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[c], w[c], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int e = 4 * lg + v;
+      if (col < dO && e < n_here) {
+        const float gq = H[e * DC_HP + col] > 0.f ? acc[v] : 0.f;
+        const size_t ra = (size_t)src_s[e] * ldp, rb = (size_t)dst_s[e] * ldp;
+        dPdec[ra + col] = gq; dPdec[ra + dO + col] = 0.f;
+        dPdec[rb + col] = 0.f; dPdec[rb + dO + col] = gq;
+      }
+    }
+  }
+}
+
+// Logits of the classification head in an evaluation pass: a wavefront per event, the classes one after the other.  A
+// pass returns counts decided by the sign of a logit, so its sums keep the order they have always been taken in
+// (a lane's columns, then the exchange over the wavefront), not the one of the MFMAs above.
+__global__ __launch_bounds__(256) void class_scores_kernel(const BatchSet* __restrict__ bsp, int dO, int C,
+                                                           const float* __restrict__ Pdec, int ldp,
+                                                           const float* __restrict__ b1, const float* __restrict__ w2,
+                                                           const float* __restrict__ b2, float* __restrict__ logits) {
   const BatchSet& bs = *bsp;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   float bb[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) bb[q] = lane + 64 * q < dO ? b1[lane + 64 * q] : 0.f;
-  float lsum = 0.f;
   for (int ev = blockIdx.x * 4 + wave; ev < bs.total; ev += gridDim.x * 4) {
     const int b = batch_of_row(bs, ev, 1);
     const int off = bs.b[b].ev_off, n = bs.b[b].n;
-    const int i = ev - off;
-    const size_t ra = (size_t)(2 * off + i) * ldp, rb = ra + (size_t)n * ldp;   // the source's and the destination's row
-    const float* __restrict__ y = bs.b[b].labels + (size_t)i * C;
-    const float inv = 1.0f / ((float)n * (float)C);
-    float h[4], dh[4] = {0.f, 0.f, 0.f, 0.f};
+    const size_t ra = (size_t)(2 * off + ev - off) * ldp, rb = ra + (size_t)n * ldp;   // the source's and the destination's row
+    float h[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int c = lane + 64 * q;
       h[q] = c < dO ? fmaxf(Pdec[ra + c] + bb[q] + Pdec[rb + dO + c], 0.f) : 0.f;
-      if (c < dO) h1[(size_t)ev * ldh + c] = h[q];
     }
-    float lterm = 0.f;
     for (int cls = 0; cls < C; ++cls) {
       const float* __restrict__ wr = w2 + (size_t)cls * dO;
-      float wv[4], acc = 0.f;
+      float acc = 0.f;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int c = lane + 64 * q;
-        wv[q] = c < dO ? wr[c] : 0.f;
-        acc += h[q] * wv[q];
+        acc += h[q] * (c < dO ? wr[c] : 0.f);
       }
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
-      const float lg = acc + b2[cls], yv = y[cls];
-      const float sgm = 1.0f / (1.0f + expf(-lg));
-      lterm += fmaxf(lg, 0.f) + log1pf(expf(-fabsf(lg))) - yv * lg;
-      const float dl = (sgm - yv) * inv;
-      if (lane == 0) {
-        logits[(size_t)ev * C + cls] = lg;
-        dlog[(size_t)ev * ldc + cls] = dl;
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) dh[q] += dl * wv[q];
-    }
-    if (lane == 0) lsum += lterm * inv / (float)bs.nb;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int c = lane + 64 * q;
-      if (c < dO) {
-        const float gq = h[q] > 0.f ? dh[q] : 0.f;
-        dPdec[ra + c] = gq; dPdec[ra + dO + c] = 0.f;
-        dPdec[rb + c] = 0.f; dPdec[rb + dO + c] = gq;
-      }
+      if (lane == 0) logits[(size_t)ev * C + cls] = acc + b2[cls];
     }
   }
-  if (lane == 0) red[wave] = lsum;
-  __syncthreads();
-  if (threadIdx.x == 0 && out_loss != nullptr) atomicAdd(out_loss, red[0] + red[1] + red[2] + red[3]);
 }
 
 void decoder_classes(const Dims& d, const BatchSet* bs, int total, const float* Pdec, int ldp, const float* b1,
                      const float* w2, const float* b2, float* logits, float* out_loss, float* h1, float* dPdec,
                      float* dlog, hipStream_t s) {
   if (total <= 0) return;
-  hipLaunchKernelGGL(dec_class_kernel, dim3(std::min((total + 3) / 4, 4 * DP_BLOCKS)), dim3(256), 0, s, bs, d.dO, d.nC, Pdec,
-                     ldp, b1, w2, b2, logits, out_loss, h1, d.ldh, dPdec, dlog, d.ldc);
+  hipLaunchKernelGGL(dec_class_kernel, dim3((total + DC_E - 1) / DC_E), dim3(256), 0, s, bs, d.dO, d.nC, Pdec, ldp, b1, w2, b2,
+                     logits, out_loss, h1, d.ldh, dPdec, dlog, d.ldc);
 }
 
-// Rank of every event's true pair among its pairs with the sampled negative destinations (pair layout of the
-// epoch-parallel step); one thread per event, the sum of the reciprocal ranks once per block.
-__global__ __launch_bounds__(256) void rank_kernel(const BatchSet* __restrict__ bsp, const float* __restrict__ logits,
-                                                   float* __restrict__ rank, float* __restrict__ rr_sum) {
-  __shared__ float red[4];
+void class_scores(const Dims& d, const BatchSet* bs, int total, const float* Pdec, int ldp, const float* b1, const float* w2,
+                  const float* b2, float* logits, hipStream_t s) {
+  if (total <= 0) return;
+  hipLaunchKernelGGL(class_scores_kernel, dim3(std::min((total + 3) / 4, 4 * DP_BLOCKS)), dim3(256), 0, s, bs, d.dO, d.nC, Pdec,
+                     ldp, b1, w2, b2, logits);
+}
+
+// An evaluation pass: the scores of an event's 1 + J pairs (pair layout of the epoch-parallel step), and the rank of its
+// true pair among them.  `per` wavefronts (1 or 4) share an event, each takes every per-th pair, RK_U pairs' rows in
+// flight at a time; the scores meet in LDS and one wavefront counts, a lane per negative destination.  The sum of a score
+// is taken as in dec_pair_kernel (a lane's columns, then the exchange over the wavefront).  600 events with 49 negatives:
+// 67 us in dec_pair_kernel (which also wrote the backward pass's rows) and 14 us for the ranks (a thread per event), now
+// 15 us together.
+constexpr int RK_U = 7;   // 13 pairs of a wavefront (49 negatives) in two rounds
+__global__ __launch_bounds__(256) void pair_rank_kernel(const BatchSet* __restrict__ bsp, int dO, const float* __restrict__ Pdec,
+                                                        int ldp, const float* __restrict__ b1, const float* __restrict__ w2,
+                                                        const float* __restrict__ b2, float* __restrict__ logits,
+                                                        float* __restrict__ rank, float* __restrict__ rr_sum, int per) {
+  __shared__ float sc[4][TGNN_MAX_NEG_SETS + 1];
   const BatchSet& bs = *bsp;
-  const int ev = blockIdx.x * 256 + threadIdx.x;
-  float rr = 0.f;
-  if (ev < bs.total) {
-    const int b = batch_of_row(bs, ev, 1);
-    const int off = bs.b[b].ev_off, n = bs.b[b].n, J = bs.nneg;
-    const size_t r0 = (size_t)(1 + J) * off + (ev - off);
-    const float st = logits[r0];
-    int above = 0, same = 0;
-    for (int g = 0; g < J; ++g) {
-      const float sn = logits[r0 + (size_t)(1 + g) * n];
-      above += sn > st ? 1 : 0;
-      same += sn == st ? 1 : 0;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int sub = per == 1 ? wave : 0, part = per == 1 ? 0 : wave;
+  const int ev = per == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
+  const bool mine = ev < bs.total;
+  const int b = mine ? batch_of_row(bs, ev, 1) : 0;
+  const int off = bs.b[b].ev_off, n = bs.b[b].n, J = bs.nneg;
+  const size_t r0 = (size_t)(1 + J) * off + (ev - off);
+  if (mine) {
+    float bb[4], ww[4], ps[4];
+    const size_t ra = (size_t)((2 + J) * off + ev - off) * ldp;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int c = lane + 64 * q;
+      bb[q] = c < dO ? b1[c] : 0.f;
+      ww[q] = c < dO ? w2[c] : 0.f;
+      ps[q] = c < dO ? Pdec[ra + c] + bb[q] : 0.f;
     }
+    const float b2v = b2[0];
+    for (int p0 = part; p0 <= J; p0 += per * RK_U) {
+      float x[RK_U][4], acc[RK_U];
+#pragma unroll
+      for (int i = 0; i < RK_U; ++i) {
+        const size_t rb = ra + (size_t)(1 + min(p0 + i * per, J)) * n * ldp + dO;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (64 * q < dO) x[i][q] = Pdec[rb + min(lane + 64 * q, dO - 1)];
+      }
+#pragma unroll
+      for (int i = 0; i < RK_U; ++i) {
+        acc[i] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (64 * q < dO) {
+            const float h = lane + 64 * q < dO ? fmaxf(ps[q] + x[i][q], 0.f) : 0.f;
+            acc[i] += h * ww[q];
+          }
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int i = 0; i < RK_U; ++i) acc[i] += __shfl_xor(acc[i], o);
+#pragma unroll
+      for (int i = 0; i < RK_U; ++i)
+        if (lane == 0 && p0 + i * per <= J) sc[sub][p0 + i * per] = acc[i] + b2v;
+    }
+  }
+  __syncthreads();
+  if (!mine || part != 0) return;
+  const float st = sc[sub][0], sn = sc[sub][1 + min(lane, J - 1)];
+  const int above = __popcll(__ballot(lane < J && sn > st)), same = __popcll(__ballot(lane < J && sn == st));
+  if (lane < J) logits[r0 + (size_t)(1 + lane) * n] = sn;
+  if (lane == 0) {
+    logits[r0] = st;
     const float r = 1.0f + (float)above + 0.5f * (float)same;
     rank[ev] = r;
-    rr = 1.0f / r;
+    atomicAdd(rr_sum, 1.0f / r);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) rr += __shfl_xor(rr, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = rr;
-  __syncthreads();
-  if (threadIdx.x == 0) atomicAdd(rr_sum, red[0] + red[1] + red[2] + red[3]);
 }
 
-void reciprocal_ranks(const BatchSet* bs, int total, const float* logits, float* rank, float* rr_sum, hipStream_t s) {
+void pair_ranks(const Dims& d, const BatchSet* bs, int total, int nneg, const float* Pdec, int ldp, const float* b1,
+                const float* w2, const float* b2, float* logits, float* rank, float* rr_sum, hipStream_t s) {
+  static_assert(TGNN_MAX_NEG_SETS <= 64, "a lane per negative destination");
   if (total <= 0) return;
-  hipLaunchKernelGGL(rank_kernel, dim3((total + 255) / 256), dim3(256), 0, s, bs, logits, rank, rr_sum);
+  const int per = nneg >= 8 ? 4 : 1;   // (fewer pairs than that do not feed four wavefronts)
+  hipLaunchKernelGGL(pair_rank_kernel, dim3(per == 4 ? total : (total + 3) / 4), dim3(256), 0, s, bs, d.dO, Pdec, ldp, b1, w2, b2,
+                     logits, rank, rr_sum, per);
 }
 
 // Predictions of the classification head against the targets: one thread per (event, class), counts summed per

@@ -1148,8 +1148,23 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     ca.loss = out_loss; ca.g_w2 = grads->dec_w2; ca.g_b2 = grads->dec_b2;
     root_chain(ca, bs, (ctx->cfg.flags & TGNN_FLAG_WIDE_ROOT_TILES) != 0, s);
   } else {   // decoder + loss (also produces d loss / d hidden)
-    gemm_nt(w.z, d.ldh, w.Wdec_p, d.ldh, nullptr, w.Pdec, d.ldkv, R, 2 * d.dO, d.ldh, 2 * d.dO, false, s);
-    if (classes)
+    // A source meets only W_s, a destination only W_d.  In one batch the sources' rows come first: two products side by
+    // side, each over its own rows and half of the columns; with several batches both halves for every root.
+    if (bs.nb == 1) {
+      const int n = bs.total;
+      const NtProblem pr[2] = {nt_problem(w.z + (size_t)n * d.ldh, d.ldh, w.Wdec_p + (size_t)d.dO * d.ldh, d.ldh, nullptr,
+                                          w.Pdec + (size_t)n * d.ldkv + d.dO, d.ldkv, R - n, d.dO, d.ldh, d.dO, false),
+                               nt_problem(w.z, d.ldh, w.Wdec_p, d.ldh, nullptr, w.Pdec, d.ldkv, n, d.dO, d.ldh, d.dO, false)};
+      gemm_nt_group(pr, 2, s);
+    } else {
+      gemm_nt(w.z, d.ldh, w.Wdec_p, d.ldh, nullptr, w.Pdec, d.ldkv, R, 2 * d.dO, d.ldh, 2 * d.dO, false, s);
+    }
+    if (eval && classes)
+      class_scores(d, w.bs_dev, bs.total, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, s);
+    else if (eval)
+      pair_ranks(d, w.bs_dev, bs.total, bs.nneg, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, ctx->out_rank,
+                 ctx->out_rr, s);
+    else if (classes)
       decoder_classes(d, w.bs_dev, bs.total, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, out_loss, w.h1,
                       w.dPdec, w.dlog, s);
     else
@@ -1161,7 +1176,6 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     // Evaluation (Sec. 4: rank of the true destination among the sampled ones): no backward half; the write-back
     // scatter leaves in a launch of its own.
     if (classes) class_counts(w.bs_dev, bs.total, d.nC, w.logits, ctx->out_counts, s);
-    else reciprocal_ranks(w.bs_dev, bs.total, w.logits, ctx->out_rank, ctx->out_rr, s);
     WbArgs wb = writeback_args(d, w.bs_dev, bs.total, st, w.winkey, w.epoch, w.Xrow, d.ldxr, w.tau, w.slot_row, nullptr,
                                nullptr, nullptr, nullptr, out_winner, nullptr, 0, 0.0f);
     gemm_nt_group(nullptr, 0, s, &wb);

@@ -685,8 +685,13 @@ void decoder_pairs(const Dims& d, const BatchSet* bs, int total, const float* Pd
 void decoder_classes(const Dims& d, const BatchSet* bs, int total, const float* Pdec, int ldp, const float* b1,
                      const float* w2, const float* b2, float* logits, float* out_loss, float* h1, float* dPdec,
                      float* dlog, hipStream_t s);
+// the logits alone (evaluation passes)
+void class_scores(const Dims& d, const BatchSet* bs, int total, const float* Pdec, int ldp, const float* b1, const float* w2,
+                  const float* b2, float* logits, hipStream_t s);
+// Evaluation pass of link prediction: logits of every event's 1 + nneg pairs,
 // rank[ev] = 1 + #(negative pairs of the event scoring above its true pair) + 0.5 #(scoring the same); rr_sum += sum 1/rank
-void reciprocal_ranks(const BatchSet* bs, int total, const float* logits, float* rank, float* rr_sum, hipStream_t s);
+void pair_ranks(const Dims& d, const BatchSet* bs, int total, int nneg, const float* Pdec, int ldp, const float* b1,
+                const float* w2, const float* b2, float* logits, float* rank, float* rr_sum, hipStream_t s);
 // counts[0..2] += tp, fp, fn of the predictions logit > 0 against the batches' class targets (logits [total, C])
 void class_counts(const BatchSet* bs, int total, int C, const float* logits, int32_t* counts, hipStream_t s);
 void mask_dz(int R, int dO, const float* dz_in, int p_in, const float* z, int ldz, float* dz_out, hipStream_t s);

@@ -254,3 +254,33 @@ def test_evaluation_pass_two_replicas_ragged_batches():
         assert abs(g["rr_sum"] - float((1.0 / g["rank"].astype(np.float64)).sum())) <= 1e-4
     for r in range(2):
         compare_state(G.state_np(r), Or.states[r], label=f"evaluation replica {r}")
+
+
+# the classification head's tiles: events around a tile of 16, classes and widths around 16 and 64, the widest of both
+@pytest.mark.parametrize("d_mem,heads,classes,batch", [(8, 1, 1, 1), (16, 2, 16, 15), (20, 1, 17, 16), (64, 2, 63, 17),
+                                                       (66, 2, 65, 33), (256, 2, 256, 18)])
+def test_classification_head_tile_edges(d_mem, heads, classes, batch):
+    P = synth.custom_problem(n_nodes=40, E=6 * batch, d_mem=d_mem, d_time=8, d_edge=4, d_static=0, n_heads=heads, k=3, batch=batch,
+                       n_classes=classes, n_true=1, seed=classes)
+    G = GpuSide(P); Or = OracleSide(P)
+    for s in range(4):
+        b = batch_np(P, s * batch, (s + 1) * batch)
+        g = G.step([b], lr=0.01)
+        o = Or.step([b], lr=0.01, gpu=g)
+        compare_step(g, o, label=f"{classes} classes, {d_mem} wide, {batch} events, step {s}")
+
+
+# one wavefront per event (J < 8) and four, pairs around a round of each, the most negatives, widths on both sides of 64
+@pytest.mark.parametrize("J,d_mem,batch", [(1, 8, 1), (7, 64, 5), (8, 65, 6), (27, 100, 3), (28, 128, 3), (63, 130, 2), (64, 256, 2)])
+def test_rank_kernel_pair_counts(J, d_mem, batch):
+    P = synth.custom_problem(n_nodes=40, E=6 * batch, d_mem=d_mem, d_time=8, d_edge=4, d_static=0, n_heads=1, k=3, batch=batch, seed=J)
+    G = GpuSide(P, max_neg_sets=J); Or = OracleSide(P)
+    rng = np.random.default_rng(J)
+    for s in range(4):
+        b = batch_np(P, s * batch, (s + 1) * batch)
+        b["neg"] = rng.integers(0, 40, (J, batch)).astype(np.int32)
+        g = G.eval_step([b], J)
+        ref = Or.step([b], lr=0.0)["outs"][0]["logits"]
+        assert rel_err(g["logits"], ref) <= TOL
+        rank, mrr = O.reciprocal_rank(g["logits"][:batch].astype(np.float64), g["logits"][batch:].reshape(J, batch).astype(np.float64))
+        assert np.array_equal(g["rank"], rank.astype(np.float32)) and abs(g["rr_sum"] / batch - mrr) <= 1e-6
