@@ -191,20 +191,81 @@ __device__ __forceinline__ void zero_head_rows(const FusedAttn& a, float* row, i
   for (int i = lane; i < a.H * a.dcp; i += 64) row[i] = 0.f;
 }
 
-// per-head softmax over the c valid scores in sa[0 .. HK): weights to sa[HK ..) and to prob
-__device__ __forceinline__ void softmax_heads(float* sa, int HK, int k, int c, int lane, float* pr) {
-  for (int p = lane; p < HK; p += 64) {
-    const int h = p / k, j = p - h * k;
-    float v = 0.f;
-    if (j < c) {
-      float mx = -INFINITY;
-      for (int jj = 0; jj < c; ++jj) mx = fmaxf(mx, sa[h * k + jj]);
-      float den = 0.f;
-      for (int jj = 0; jj < c; ++jj) den += expf(sa[h * k + jj] - mx);
-      v = expf(sa[p] - mx) / den;
-    }
-    sa[HK + p] = v;
-    pr[p] = v;
+// Sums over the wavefront of the 20 per-slot, per-head shares, each exchange serving two of them: after the half-wave
+// swap a register holds one sum in its lower and another in its upper half, after the row swap four, and the remaining
+// four exchanges stay inside rows of 16 lanes (DPP rotations, which add in the same instruction).  50 vector instructions
+// in place of 120 exchanges through the LDS pipe and as many additions; every addition has the same two operands as in
+// an exclusive-or exchange over 32, 16, .. 1 lanes, so the sums are the same bit for bit.  Score (slot j, head hh) is
+// n = KR hh + j: register n % 5 of the result, lanes 16 (n / 5) ..
+static_assert(FA_KR == 10 && FA_HM == 2, "laid out for twenty sums");
+constexpr int FA_SR = 5;
+template <int CTRL> __device__ __forceinline__ float dpp_add(float x) {
+  return x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ void sum_scores(const float (&part)[FA_KR][FA_HM], float (&sum)[FA_SR]) {
+  float half[2 * FA_SR];
+#pragma unroll
+  for (int n = 0; n < 2 * FA_SR; ++n) {   // {n | n + 10}
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(part[n][0]), __float_as_uint(part[n][1]), false, false);
+    half[n] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  }
+#pragma unroll
+  for (int m = 0; m < FA_SR; ++m) {       // {m | m + 5 | m + 10 | m + 15}
+    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[m]), __float_as_uint(half[m + FA_SR]), false, false);
+    float v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+    v = dpp_add<0x128>(v);   // row_ror:8, 4, 2, 1
+    v = dpp_add<0x124>(v);
+    v = dpp_add<0x122>(v);
+    sum[m] = dpp_add<0x121>(v);
+  }
+}
+// which sum a lane (of the first FA_SR of a row) takes: its slot and head
+struct ScoreOf {
+  int j, hh;
+  bool mine;   // a slot and head that the call has
+};
+__device__ __forceinline__ ScoreOf score_of(const FusedAttn& a, int lane) {
+  ScoreOf o;
+  o.hh = lane >> 5;
+  o.j = (lane & 15) + FA_SR * ((lane >> 4) & 1);
+  o.mine = (lane & 15) < FA_SR && o.j < a.k && o.hh < a.H;
+  return o;
+}
+__device__ __forceinline__ float score_pick(const float (&sum)[FA_SR], int lane) {
+  float v = sum[0];
+#pragma unroll
+  for (int m = 1; m < FA_SR; ++m) {
+    const float x = sum[m];   // (a value: a choice between array elements would put the array into memory)
+    v = (lane & 15) == m ? x : v;
+  }
+  return v;
+}
+
+// per-head softmax over the c valid scores in sa[0 .. HK) (the others -infinity; HK <= 64): weights to sa[HK ..) and to
+// prob.  A lane evaluates its own exponential, the head's ten meet in LDS again for their sum.
+__device__ __forceinline__ void softmax_fast(float* sa, int HK, int k, int c, int lane, float* pr) {
+  const int p = min(lane, HK - 1), h0 = p >= k ? k : 0;   // (at most two heads)
+  float x[FA_KR];
+#pragma unroll
+  for (int jj = 0; jj < FA_KR; ++jj) x[jj] = sa[h0 + min(jj, k - 1)];   // (past the last slot: one of the head's, twice)
+  const float own = sa[p];
+  float mx = x[0];
+#pragma unroll
+  for (int jj = 1; jj < FA_KR; ++jj) mx = fmaxf(mx, x[jj]);
+  const float e = p - h0 < c ? expf(own - mx) : 0.f;
+  if (lane < HK) sa[HK + lane] = e;
+  wave_lds_sync();
+  float den = 0.f;
+#pragma unroll
+  for (int jj = 0; jj < FA_KR; ++jj) {
+    const float ej = sa[HK + h0 + min(jj, k - 1)];
+    den += jj < c ? ej : 0.f;
+  }
+  wave_lds_sync();
+  if (lane < HK) {
+    const float v = p - h0 < c ? e / den : 0.f;
+    sa[HK + lane] = v;
+    pr[lane] = v;
   }
 }
 
@@ -323,21 +384,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_
       part[j][hh] = acc;
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int j = 0; j < FA_KR; ++j)
-#pragma unroll
-      for (int hh = 0; hh < FA_HM; ++hh) part[j][hh] += __shfl_xor(part[j][hh], o);
-  float mine = -INFINITY;
-#pragma unroll
-  for (int j = 0; j < FA_KR; ++j)
-#pragma unroll
-    for (int hh = 0; hh < FA_HM; ++hh)
-      if (lane == hh * a.k + j && j < c && hh < a.H) mine = part[j][hh] * scale;
-  if (lane < HK) sa[lane] = mine;
+  float sum[FA_SR];
+  sum_scores(part, sum);
+  const ScoreOf so = score_of(a, lane);
+  const float score = score_pick(sum, lane) * scale;
+  if (so.mine) sa[so.hh * a.k + so.j] = so.j < c ? score : -INFINITY;
   wave_lds_sync();
-  softmax_heads(sa, HK, a.k, c, lane, pr);
+  softmax_fast(sa, HK, a.k, c, lane, pr);
   wave_lds_sync();
   // weighted sums: node part of the output, and the per-head sums of the slots' own inputs
   float o[FA_E] = {0.f, 0.f};
@@ -444,28 +497,22 @@ __global__ __launch_bounds__(256) void fattn_bwd_fast_kernel(FusedAttn a) {
       part[j][hh] = acc;
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-    for (int j = 0; j < FA_KR; ++j)
-#pragma unroll
-      for (int hh = 0; hh < FA_HM; ++hh) part[j][hh] += __shfl_xor(part[j][hh], o);
-  float dp = 0.f;
-#pragma unroll
-  for (int j = 0; j < FA_KR; ++j)
-#pragma unroll
-    for (int hh = 0; hh < FA_HM; ++hh)
-      if (lane == hh * a.k + j && j < c && hh < a.H) dp = part[j][hh];
-  if (lane < HK) sa[HK + lane] = dp;
+  float sum[FA_SR];
+  sum_scores(part, sum);
+  const ScoreOf so = score_of(a, lane);
+  const float dp = score_pick(sum, lane);
+  if (so.mine) sa[HK + so.hh * a.k + so.j] = so.j < c ? dp : 0.f;
   wave_lds_sync();
   float da = 0.f;
-  if (lane < HK) {   // softmax backward, scaled by 1 / sqrt(|N_v|)
-    const int h = lane / a.k, j = lane - h * a.k;
-    if (j < c) {
-      float sdot = 0.f;
-      for (int jj = 0; jj < c; ++jj) sdot += sa[h * a.k + jj] * sa[HK + h * a.k + jj];
-      da = sa[lane] * (sa[HK + lane] - sdot) * scale;
-    }
+  {   // softmax backward, scaled by 1 / sqrt(|N_v|)
+    const int p = min(lane, HK - 1), h0 = p >= a.k ? a.k : 0;
+    float w[FA_KR], x[FA_KR];
+#pragma unroll
+    for (int jj = 0; jj < FA_KR; ++jj) { w[jj] = sa[h0 + min(jj, a.k - 1)]; x[jj] = sa[HK + h0 + min(jj, a.k - 1)]; }
+    float sdot = 0.f;
+#pragma unroll
+    for (int jj = 0; jj < FA_KR; ++jj) sdot += (jj < c ? w[jj] : 0.f) * x[jj];
+    if (p - h0 < c) da = sa[p] * (sa[HK + p] - sdot) * scale;
   }
   wave_lds_sync();
   if (lane < HK) {
@@ -537,6 +584,23 @@ __global__ __launch_bounds__(256) void fattn_bwd_fast_kernel(FusedAttn a) {
 // Generic path: any k <= TGNN_MAX_K, any widths, any number of heads.  Same arithmetic with plain loops: a
 // slot's columns are recomputed wherever they are needed instead of being kept in registers.
 // ---------------------------------------------------------------------------------------------------------
+// per-head softmax over the c valid scores in sa[0 .. HK): weights to sa[HK ..) and to prob
+__device__ __forceinline__ void softmax_heads(float* sa, int HK, int k, int c, int lane, float* pr) {
+  for (int p = lane; p < HK; p += 64) {
+    const int h = p / k, j = p - h * k;
+    float v = 0.f;
+    if (j < c) {
+      float mx = -INFINITY;
+      for (int jj = 0; jj < c; ++jj) mx = fmaxf(mx, sa[h * k + jj]);
+      float den = 0.f;
+      for (int jj = 0; jj < c; ++jj) den += expf(sa[h * k + jj] - mx);
+      v = expf(sa[p] - mx) / den;
+    }
+    sa[HK + p] = v;
+    pr[p] = v;
+  }
+}
+
 // column `col` < d_e + d_t of slot input c_j; sn receives the sine of a time column (0 for an edge-feature column)
 __device__ __forceinline__ float slot_col(const FusedAttn& a, int e, double dt, int col, float& sn) {
   sn = 0.f;
