@@ -73,7 +73,11 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
       const int dh = dO / d.H, dc = d.de + d.dt;
       // row h dcp + c, column h dh + dd  <-  W[h dh + dd, d_x + c]
       if (!nd) add_bd(p->wk + dx, w.WkcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
-      if (backward) add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
+      if (backward && !chain) add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
+      if (chain) {
+        add_bd(p->wv + dx, w.rc_wg, dc, dh, 0, 1, dkv, d.dcp, dh, dh * dkv);
+        pa.d[n - 1].mfma_ks = (dO + 15) / 16;
+      }
       // row h dh + dd, column h dcp + c  <-  W[h dh + dd, d_x + c]
       if (backward) add_bd(p->wk + dx, w.Wkc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
       add_bd(p->wv + dx, w.Wvc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);

@@ -11,6 +11,7 @@
 //   pairs  : hidden = ReLU(Pdec_src + Pdec_dst + b1), logit, loss, d/d(logit), d/d(hidden) -> dPdec per root
 //   dz     = gate_z(dPdec W_s) for sources, gate_z(dPdec W_d) for destinations
 //   dOmat  = dz W_oh
+//   G_h    = dO_h (W_v^c)_h per head, what the attention's backward pass dots with the slots' own inputs
 // The weights are read from global memory (L2) as MFMA B operands, from copies laid out in operand order (the
 // prologue writes them): 1 KB of contiguous memory per wavefront, column block and 16-wide k slab.
 // z, h1, dPdec ({W_s part | W_d part}, the unused half zero), dz and dOmat go to memory for the weight-gradient
@@ -105,6 +106,53 @@ __device__ __forceinline__ void rc_mma(const RcSet<KS>& set, int cb, const float
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[j][c], set.w[G::template unit_ws<SPLIT>(j)][s][c], acc[j], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);   // nothing moves across k slabs
   }
+}
+
+// G = dO W_v^c, per head: rows [h bn, (h + 1) bn) of the weights (columns of G) meet columns [h bk, (h + 1) bk) of dO
+// only, so a column block of 16 runs the k slabs that its heads reach into (the others hold zeros and are not even read).
+// In a launch of its own G took 21 us on 12,000 roots and 7.1 on 1,800 (dO out to memory and in again, and a launch);
+// here it adds 10.5 and 6 to the chain's 29.5 and 14.3, bound by the weights' way from L2 and the rows' way out.
+struct RcHeads {
+  int n, bn, bk;
+};
+__device__ __forceinline__ void rc_g_range(const RcHeads& h, int cb, int& lo, int& hi) {
+  lo = (min(cb * 16, h.n - 1) / h.bn * h.bk) >> 4;
+  hi = ((min(cb * 16 + 15, h.n - 1) / h.bn + 1) * h.bk + 15) >> 4;
+}
+template <int KS>
+__device__ __forceinline__ void rc_g_load(floatx4 (&w)[KS], const RcHeads& h, int cb, int blocks, const float* __restrict__ W, int lane) {
+  if (cb >= blocks) return;
+  int lo, hi;
+  rc_g_range(h, cb, lo, hi);
+  const float* p = W + ((size_t)cb * KS * 64 + lane) * 4;
+#pragma unroll
+  for (int s = 0; s < KS; ++s)
+    if (s >= lo && s < hi) w[s] = *reinterpret_cast<const floatx4*>(p + s * 256);
+}
+// The weights are the MFMA's first operand here: a lane ends up with four consecutive columns of one row and stores 16 bytes.
+template <int KS, int E>
+__device__ __forceinline__ void rc_g_block(const floatx4 (&w)[KS], const RcHeads& h, int cb, const float* T, int li, int lg,
+                                           float* const (&row)[RcGeom<E>::NB], const bool (&live)[RcGeom<E>::NB]) {
+  constexpr int NB = RcGeom<E>::NB;
+  int lo, hi;
+  rc_g_range(h, cb, lo, hi);
+  floatx4 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    if (s >= lo && s < hi) {   // (uniform; around a slab's MFMAs, not around single ones)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const floatx4 x = *reinterpret_cast<const floatx4*>(T + (j * 16 + li) * RC_PL + s * 16 + lg * 4);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s][c], x[c], acc[j], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    if (live[j]) *reinterpret_cast<floatx4*>(row[j] + cb * 16) = acc[j];
 }
 
 template <int KS, int E>
@@ -326,15 +374,38 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
   __syncthreads();
 
   // ---- dOmat = dz W_oh ----
+  // the weights of this wavefront's first two column blocks of G come in beside it
+  RcHeads gh;
+  gh.n = a.H * a.dcp; gh.bn = a.dcp; gh.bk = dO / a.H;
+  const int g_blocks = a.ldz / 16;   // (a multiple of two; blocks past the last head's columns meet zero weights)
+  rc_g_load<KS>(wa.w[0], gh, wave, g_blocks, a.Wg_pk, lane);
+  rc_g_load<KS>(wa.w[1], gh, wave + RC_WAVES, g_blocks, a.Wg_pk, lane);
   if (has_cb) {
-    rc_mma<KS, E, false, 0>(wb, cb, T1, li, lg, acc, wa, nullptr, nullptr);
+    rc_mma<KS, E, false, 0>(wb, cb, T1, li, lg, acc, wb, nullptr, nullptr);
 #pragma unroll
     for (int j = 0; j < G::NU_SHARED; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int lr = j * 16 + lg * 4 + v;
+        T0[lr * RC_PL + col] = acc[j][v];   // (columns past d_o: zero weights)
         if (col < dO && live(lr)) a.dOmat[(size_t)groot(lr) * ldh + col] = acc[j][v];
       }
+  }
+  __syncthreads();
+
+  // ---- G_h = dO_h (W_v^c)_h ----
+  float* grow[G::NB];   // where this lane's row of each row block goes
+  bool glive[G::NB];
+#pragma unroll
+  for (int j = 0; j < G::NB; ++j) {
+    grow[j] = a.Gmat + (size_t)groot(j * 16 + li) * a.ldz + 4 * lg;
+    glive[j] = live(j * 16 + li);
+  }
+  for (int b0 = wave; b0 < g_blocks; b0 += 2 * RC_WAVES) {
+    rc_g_block<KS, E>(wa.w[0], gh, b0, T0, li, lg, grow, glive);
+    rc_g_load<KS>(wa.w[0], gh, b0 + 2 * RC_WAVES, g_blocks, a.Wg_pk, lane);
+    if (b0 + RC_WAVES < g_blocks) rc_g_block<KS, E>(wa.w[1], gh, b0 + RC_WAVES, T0, li, lg, grow, glive);
+    rc_g_load<KS>(wa.w[1], gh, b0 + 3 * RC_WAVES, g_blocks, a.Wg_pk, lane);
   }
 }
 

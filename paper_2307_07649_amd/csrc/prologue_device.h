@@ -74,6 +74,19 @@ __device__ __forceinline__ void prologue_block(const PrologueArgs& a, int bx, in
   }
   if (y < a.n_pack) {
     const PackDesc d = a.d[y];
+    if (d.mfma_ks > 0 && d.nblk > 0) {   // MFMA B-operand order, block-diagonal
+      const int per = d.rows * d.cols, total = d.nblk * per;
+      for (int i = bx * blockDim.x + threadIdx.x; i < total; i += nbx * blockDim.x) {
+        const int h = i / per, rc = i - h * per;
+        int r, c;   // (consecutive threads walk whichever index is contiguous in the source)
+        if (d.srs == 1) { c = rc / d.rows; r = rc - c * d.rows; }
+        else { r = rc / d.cols; c = rc - r * d.cols; }
+        const int row = h * d.brd + r, k = h * d.bcd + c;
+        d.dst[((size_t)((row >> 4) * d.mfma_ks + (k >> 4)) * 64 + ((k & 15) >> 2) * 16 + (row & 15)) * 4 + (k & 3)] =
+            d.src[(size_t)h * d.bsrc + (size_t)r * d.srs + (size_t)c * d.scs];
+      }
+      return;
+    }
     if (d.mfma_ks > 0) {   // MFMA B-operand order
       const int total = ((d.rows + 15) >> 4) * d.mfma_ks * 256;
       for (int i = bx * blockDim.x + threadIdx.x; i < total; i += nbx * blockDim.x) {

@@ -136,6 +136,7 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   {
     const size_t ks = (size_t)(d.dO + 15) / 16;
     w.rc_pk = root_chain_fits(d) ? b.take<float>(6 * ks * ks * 256) : nullptr;
+    w.rc_wg = root_chain_fits(d) ? b.take<float>((size_t)d.ldz / 16 * ks * 256) : nullptr;
   }
   w.WdecT = b.take<float>((size_t)d.dO * d.ldkv); w.WihT_phi = b.take<float>((size_t)d.dt * d.ld3);
   w.WxT = b.take<float>((size_t)d.dx * d.ldp);
@@ -294,18 +295,20 @@ static QPhi qphi_args(tgnn_ctx* ctx, const tgnn_params* p, tgnn_params* g) {
 // sums that give the gradients of the time-encoding parameters through the keys; adds the column sums of dq to
 // ws.q_part, which the caller cleared (consumed by qphi_block in a later launch).
 static void attn_backward(tgnn_ctx* ctx, tgnn_params* g, const tgnn_params* p, int R, const AttnIn& in, TnBatch& tn,
-                          Side& side, hipStream_t s, StageTimer* tm, bool have_dOmat = false) {
+                          Side& side, hipStream_t s, StageTimer* tm, bool have_G = false) {
   const Dims& d = ctx->d; Ws& w = ctx->w;
   tn.add(w.dz, d.ldh, w.Omat, d.ldh, R, d.dO, d.dO, single_out(g->wo, d.dO + d.dx, nullptr));
-  if (!have_dOmat) gemm_nt(w.dz, d.ldh, w.WoT_o, d.ldh, nullptr, w.dOmat, d.ldh, R, d.dO, d.ldh, d.ldh, false, s);
-  if (tm) tm->begin(19);
-  {   // G = dO (W_v^c)_h per head
+  if (!have_G) {   // (otherwise the root chain has left both)
+    gemm_nt(w.dz, d.ldh, w.WoT_o, d.ldh, nullptr, w.dOmat, d.ldh, R, d.dO, d.ldh, d.ldh, false, s);
+    if (tm) tm->begin(19);
+    // G = dO (W_v^c)_h per head
     const NtProblem gm = nt_blocks(nt_live(nt_problem(w.dOmat, d.ldh, w.WvcT, d.ldh, nullptr, w.Gmat, d.ldz, R, d.H * d.dcp,
                                                       d.ldh, d.ldz, false), d.dO),
                                    d.dcp, d.dO / d.H);
     gemm_nt_group(&gm, 1, s);
+    if (tm) tm->end(19);
   }
-  if (tm) { tm->end(19); tm->begin(14); }
+  if (tm) tm->begin(14);
   fattn_bwd(fused_args(ctx, R, in), s);
   if (tm) { tm->end(14); tm->begin(5); }
   {   // dq = node part + Zs (W_k^c)^T, with its column sums over the roots (for the query's Phi(0))
@@ -1143,6 +1146,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
       ca.Wo_pk = w.rc_pk; ca.Ws_pk = w.rc_pk + blk; ca.Wd_pk = w.rc_pk + 2 * blk; ca.WsT_pk = w.rc_pk + 3 * blk;
       ca.WdT_pk = w.rc_pk + 4 * blk; ca.WoT_pk = w.rc_pk + 5 * blk;
     }
+    ca.Wg_pk = w.rc_wg; ca.Gmat = w.Gmat; ca.H = d.H; ca.dcp = d.dcp; ca.ldz = d.ldz;
     ca.b1 = p->dec_b1; ca.w2 = p->dec_w2; ca.b2 = p->dec_b2;
     ca.z = w.z; ca.h1 = w.h1; ca.logits = w.logits; ca.dPdec = w.dPdec; ca.dz = w.dz; ca.dOmat = w.dOmat;
     ca.loss = out_loss; ca.g_w2 = grads->dec_w2; ca.g_b2 = grads->dec_b2;

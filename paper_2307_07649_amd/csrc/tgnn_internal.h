@@ -114,7 +114,8 @@ struct Ws {
   float *WkcT, *WvcT;       // [H dcp, ldh]  row h dcp + c, column d of head h: W[d, d_x + c]   (U = q WkcT^T, G = dO WvcT^T)
   float *Wkc, *Wvc;         // [d_o, ldz]    row d of head h, column h dcp + c: W[d, d_x + c]   (dq += Zs Wkc^T, O += Zp Wvc^T)
   float *Wo_o;              // [d_o, ldh] W_o restricted to the attention-output columns
-  float *rc_pk;             // six [d_o, d_o] blocks in MFMA B-operand order for the root chain (NULL: it does not fit)
+  // for the root chain (NULL: it does not fit), in MFMA B-operand order: six [d_o, d_o] blocks; (W_v^c)^T per head [ldz, d_o]
+  float *rc_pk, *rc_wg;
   float *WdecT, *WihT_phi;
   float *WxT;               // [d_x, ldp]   transposed Wx (rows >= d_m: the static columns)
   float *WoT_o;             // [d_o, ldh]   transposed Wo_o
@@ -396,7 +397,8 @@ struct PackDesc {
   // mfma_ks > 0: MFMA B-operand order instead (zero_to, ldd unused).  For column block cb (16 rows), k slab s < mfma_ks
   // (16 columns), lane (li, lg) and c < 4:  dst[((cb * mfma_ks + s) * 64 + lg * 16 + li) * 4 + c] =
   // src[(16 cb + li) * srs + (16 s + 4 lg + c) * scs], zero beyond rows / cols: a wavefront then reads the operand
-  // of one MFMA slab as 1 KB of contiguous memory.
+  // of one MFMA slab as 1 KB of contiguous memory.  (nblk > 0 as well: block h of rows x cols lies at row h * brd, column
+  // h * bcd of the operand; nothing else is written.)
   int16_t mfma_ks;
   // split_ks > 0: the three bf16 parts (split3.h) in MFMA operand order instead, for blocks of split_ks k slabs of 32
   // columns: element (r, c) is row n = row0 + r, column k = col0 + c of the operand, part p of it goes to
@@ -711,6 +713,9 @@ struct ChainArgs {
   // weight blocks in MFMA B-operand order (see PackDesc): merge layer (attention-output columns), W_s, W_d, and
   // their transposes
   const float *Wo_pk, *Ws_pk, *Wd_pk, *WsT_pk, *WdT_pk, *WoT_pk;
+  const float* Wg_pk;         // (W_v^c)^T, block-diagonal over the heads: H dcp columns of G (ldz with pads), k = d_o
+  float* Gmat;                // [R, ldz]
+  int H, dcp, ldz;
   const float *b1, *w2, *b2;
   float *z, *h1, *logits, *dPdec, *dz, *dOmat;
   float *loss, *g_w2, *g_b2;
