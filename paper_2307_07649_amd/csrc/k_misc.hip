@@ -80,7 +80,11 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
       }
       // row h dh + dd, column h dcp + c  <-  W[h dh + dd, d_x + c]
       if (backward) add_bd(p->wk + dx, w.Wkc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
-      add_bd(p->wv + dx, w.Wvc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
+      if (!chain) add_bd(p->wv + dx, w.Wvc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
+      else {
+        add_bd(p->wv + dx, w.rc_wv, dh, dc, 0, dkv, 1, dh, d.dcp, dh * dkv);
+        pa.d[n - 1].mfma_ks = d.ldz / 16;
+      }
     }
     // merge layer, attention-output columns, and their transpose
     if (!chain) add(p->wo, w.Wo_o, dO, dO, d.ldh, d.ldh, dmrg, 1);

@@ -6,6 +6,7 @@
 // blocks, one per role (each contiguous in the root order [src | dst | neg] of a batch), when a step has many
 // events; E = 5, one 16-row block {5 src | 5 dst | 5 neg | pad}, when it has few and more workgroups (compute
 // units) are worth more than full blocks:
+//   h      = O_node + Zp (W_v^c)^T per head                       (the attention output)
 //   z      = ReLU(h W_oh^T + P_o[row(root)])                      (P_o: node part of the merge layer, bias included)
 //   Pdec   = z W_s^T for sources, z W_d^T for destinations         (only the half a root needs)
 //   pairs  : hidden = ReLU(Pdec_src + Pdec_dst + b1), logit, loss, d/d(logit), d/d(hidden) -> dPdec per root
@@ -14,7 +15,7 @@
 //   G_h    = dO_h (W_v^c)_h per head, what the attention's backward pass dots with the slots' own inputs
 // The weights are read from global memory (L2) as MFMA B operands, from copies laid out in operand order (the
 // prologue writes them): 1 KB of contiguous memory per wavefront, column block and 16-wide k slab.
-// z, h1, dPdec ({W_s part | W_d part}, the unused half zero), dz and dOmat go to memory for the weight-gradient
+// h, z, h1, dPdec ({W_s part | W_d part}, the unused half zero), dz and dOmat go to memory for the weight-gradient
 // products and the attention backward pass.
 #include "tgnn_internal.h"
 #include "device_math.h"
@@ -25,6 +26,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int RC_WAVES = 8;
 constexpr int RC_MAXD = 128;             // widest d_o (8 column blocks of 16, one per wavefront)
+constexpr int RC_ZC = 256, RC_ZP = RC_ZC + 4;   // columns of Zp staged at a time, and their pitch
 constexpr int RC_PL = RC_MAXD + 4;       // LDS row pitch: 33 float4 chunks, so 16 rows x one chunk cover all banks
 
 // Geometry of a tile of E events.  Local rows: E = 16: role * 16 + e; E = 5: role * 5 + e, row 15 is padding.
@@ -158,8 +160,10 @@ __device__ __forceinline__ void rc_g_block(const floatx4 (&w)[KS], const RcHeads
 template <int KS, int E>
 __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) {
   typedef RcGeom<E> G;
-  __shared__ __attribute__((aligned(16))) float T0[G::ROWS * RC_PL];   // h -> Pdec -> dPdec
-  __shared__ __attribute__((aligned(16))) float T1[G::ROWS * RC_PL];   // z -> dz
+  __shared__ __attribute__((aligned(16))) float T[2 * G::ROWS * RC_PL];
+  float* const T0 = T;                       // h -> Pdec -> dPdec -> dO
+  float* const T1 = T + G::ROWS * RC_PL;     // z -> dz
+  static_assert(RC_ZP <= 2 * RC_PL, "a chunk of Zp rows lies over both");
   __shared__ float red[E][2 * 64 + 2];
 
   // which E events: tiles are dealt batch by batch (sizes from the argument block: no memory round trip)
@@ -186,22 +190,39 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
   auto live = [&](int lr) { return G::ev(lr) < n_here; };   // not padding, not past a ragged batch end
 
   RcSet<KS> wa, wb;
-  // Order of the first loads (they return in order): the attention output, which the first product waits
-  // for; its weights; the node rows of the roots this lane finishes.  Once those rows are known, the node part
-  // of the merge layer, needed only after the first product's MFMAs.
-  // (all of a thread's pieces of the attention output are loaded before the first goes to LDS: a load -> store loop
+  // Order of the first loads (they return in order): the first chunk of the rows' weighted sums Zp, which the first product
+  // waits for; its weights; the node rows of the roots this lane finishes.  Once those rows are known, the node part
+  // of the merge layer, needed only after the second product's MFMAs.
+  // (all of a thread's pieces of a chunk are loaded before the first goes to LDS: a load -> store loop
   // would pay one memory latency per pass)
-  constexpr int OM_CHUNKS = G::ROWS * (RC_PL / 4), OM_PER = (OM_CHUNKS + 64 * RC_WAVES - 1) / (64 * RC_WAVES);
-  floatx4 om[OM_PER];
+  constexpr int ZC_PER = G::ROWS * (RC_ZC / 4) / (64 * RC_WAVES);
+  static_assert(G::ROWS * (RC_ZC / 4) % (64 * RC_WAVES) == 0, "whole rounds");
+  const int z_slabs = a.ldz / 16, z_chunks = (a.ldz + RC_ZC - 1) / RC_ZC;
+  floatx4 zc[ZC_PER];
+  auto z_load = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
-  for (int u = 0; u < OM_PER; ++u) {
-    const int idx = min(tid + u * 64 * RC_WAVES, OM_CHUNKS - 1);
-    const int lr = idx / (RC_PL / 4), c = (idx - lr * (RC_PL / 4)) * 4;
-    om[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if (c < dO) om[u] = *reinterpret_cast<const floatx4*>(a.Omat + (size_t)groot(lr) * ldh + c);
-  }
+    for (int u = 0; u < ZC_PER; ++u) {
+      const int idx = tid + u * 64 * RC_WAVES, lr = idx / (RC_ZC / 4), c = idx % (RC_ZC / 4);
+      zc[u] = *reinterpret_cast<const floatx4*>(a.Zp + (size_t)groot(lr) * a.ldz + min(chunk * RC_ZC + 4 * c, a.ldz - 4));   // (columns past the row: no slab reads them)
+    }
+  };
+  RcHeads oh;   // column blocks of the output meet the k slabs of their heads' blocks of Zp
+  oh.n = dO; oh.bn = dO / a.H; oh.bk = a.dcp;
+  int o_lo, o_hi;
+  rc_g_range(oh, cb, o_lo, o_hi);
+  constexpr int OG = RC_ZC / 32;   // slabs per group: half a chunk
+  floatx4 w0[OG], w1[OG];
+  auto o_load = [&](floatx4 (&w)[OG], int g) __attribute__((always_inline)) {
+    const float* p = a.Wv_pk + ((size_t)cb * z_slabs * 64 + lane) * 4;
+#pragma unroll
+    for (int i = 0; i < OG; ++i) {
+      const int s = g * OG + i;
+      if (s >= o_lo && s < o_hi) w[i] = *reinterpret_cast<const floatx4*>(p + (size_t)s * 256);
+    }
+  };
+  z_load(0);
   __builtin_amdgcn_sched_barrier(0);   // keep this issue order
-  rc_load<KS, false>(wa, cb, a.Wo_pk, nullptr, lane);
+  o_load(w0, 0);
   int prow[G::NB][4];
 #pragma unroll
   for (int j = 0; j < G::NB; ++j)
@@ -220,16 +241,11 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
     ww[q] = c < dO ? a.w2[c] : 0.f;
   }
   __builtin_amdgcn_sched_barrier(0);
-  // attention output rows -> T0 (columns >= d_o zero)
+  float on[G::NB][4];   // node part of the attention output
 #pragma unroll
-  for (int u = 0; u < OM_PER; ++u) {
-    const int idx = tid + u * 64 * RC_WAVES;
-    if (idx < OM_CHUNKS) {
-      const int lr = idx / (RC_PL / 4), c = (idx - lr * (RC_PL / 4)) * 4;
-      *reinterpret_cast<floatx4*>(&T0[lr * RC_PL + c]) = om[u];
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);
+  for (int j = 0; j < G::NB; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) on[j][v] = a.Onode[(size_t)groot(j * 16 + lg * 4 + v) * ldh + min(cb * 16 + li, dO - 1)];
   float addv[G::NB][4];
 #pragma unroll
   for (int j = 0; j < G::NB; ++j) {
@@ -237,10 +253,62 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
 #pragma unroll
     for (int v = 0; v < 4; ++v) addv[j][v] = a.P_o[(size_t)prow[j][v] * a.ldp + col];
   }
-  __syncthreads();
-
   const int col = cb * 16 + li;   // this lane's column in every product
   floatx4 acc[3];
+
+  // ---- h = O_node + Zp (W_v^c)^T, per head, in chunks of RC_ZC columns of Zp ----
+  // (the next chunk's rows and the next half chunk's weights are on their way beside the products; same products in the
+  // same order as gemm_nt_group's, so h is the same bit for bit.  A launch of its own took 21 us on 12,000 roots and 9 on
+  // 1,800; here it adds 14 and 6 to the chain, bound by the column block that two heads share: it runs all k slabs.)
+  {
+    floatx4 oacc[G::NB];
+#pragma unroll
+    for (int j = 0; j < G::NB; ++j) oacc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto o_mma = [&](const floatx4 (&w)[OG], int g, int half) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < OG; ++i) {
+        const int s = g * OG + i;
+        if (s >= o_lo && s < o_hi) {
+#pragma unroll
+          for (int j = 0; j < G::NB; ++j) {
+            const floatx4 x = *reinterpret_cast<const floatx4*>(T + (j * 16 + li) * RC_ZP + (half * OG + i) * 16 + lg * 4);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) oacc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[c], w[i][c], oacc[j], 0, 0, 0);
+          }
+        }
+      }
+    };
+    for (int ch = 0; ch < z_chunks; ++ch) {
+      if (ch > 0) __syncthreads();   // the chunk before has been read
+#pragma unroll
+      for (int u = 0; u < ZC_PER; ++u) {
+        const int idx = tid + u * 64 * RC_WAVES, lr = idx / (RC_ZC / 4), c = idx % (RC_ZC / 4);
+        *reinterpret_cast<floatx4*>(T + lr * RC_ZP + 4 * c) = zc[u];
+      }
+      __syncthreads();
+      if (ch + 1 < z_chunks) z_load(ch + 1);
+      if (has_cb) {
+        o_load(w1, 2 * ch + 1);
+        o_mma(w0, 2 * ch, 0);
+        if (ch + 1 < z_chunks) o_load(w0, 2 * ch + 2);
+        o_mma(w1, 2 * ch + 1, 1);
+      }
+    }
+    rc_load<KS, false>(wa, cb, a.Wo_pk, nullptr, lane);
+    __syncthreads();
+    if (has_cb) {
+#pragma unroll
+      for (int j = 0; j < G::NB; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int lr = j * 16 + lg * 4 + v;
+          const float x = col < dO ? oacc[j][v] + on[j][v] : 0.f;
+          T0[lr * RC_PL + col] = x;
+          if (col < dO && live(lr)) a.Omat[(size_t)groot(lr) * ldh + col] = x;
+        }
+    }
+  }
+  __syncthreads();
 
   // ---- z = ReLU(h W_oh^T + P_o[row]) ----
   // next: Pdec, sources through W_s, destinations through W_d

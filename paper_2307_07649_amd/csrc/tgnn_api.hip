@@ -136,6 +136,7 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   {
     const size_t ks = (size_t)(d.dO + 15) / 16;
     w.rc_pk = root_chain_fits(d) ? b.take<float>(6 * ks * ks * 256) : nullptr;
+    w.rc_wv = root_chain_fits(d) ? b.take<float>((size_t)d.ldz / 16 * ks * 256) : nullptr;
     w.rc_wg = root_chain_fits(d) ? b.take<float>((size_t)d.ldz / 16 * ks * 256) : nullptr;
   }
   w.WdecT = b.take<float>((size_t)d.dO * d.ldkv); w.WihT_phi = b.take<float>((size_t)d.dt * d.ld3);
@@ -243,7 +244,7 @@ static FusedAttn fused_args(tgnn_ctx* ctx, int R, const AttnIn& in) {
 // U = q (W_k^c) per head (a second GEMM over the node rows), the output is the kernel's node part plus Zp (W_v^c)^T
 // (a GEMM over the roots).  n_rows_dev (may be NULL): device-side row count.
 static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows, const int* n_rows_dev, const AttnIn& in,
-                         StageTimer* tm, hipStream_t s, bool products, const SortArgs& fill = SortArgs(), bool with_merge = true) {
+                         StageTimer* tm, hipStream_t s, bool products, const SortArgs& fill = SortArgs(), bool with_output = true) {
   const Dims& d = ctx->d; Ws& w = ctx->w;
   if (products) {
     if (tm) tm->begin(9);
@@ -263,7 +264,9 @@ static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows,
   FusedAttn fa = fused_args(ctx, R, in);
   fa.fill = fill;
   fattn_fwd(fa, s);
-  if (tm) { tm->end(10); tm->begin(7); }
+  if (tm) tm->end(10);
+  if (!with_output) return;   // the caller's next launch (the root chain) holds the attention output and the merge layer
+  if (tm) tm->begin(7);
   {   // attention output = node part + Zp (W_v^c)^T
     RowAdd add;
     add.src = w.Onode; add.ld = d.ldh; add.index = nullptr; add.row0 = 0;
@@ -273,7 +276,6 @@ static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows,
     gemm_nt_group(&o, 1, s);
   }
   if (tm) tm->end(7);
-  if (!with_merge) return;   // the caller's next launch holds the merge layer
   if (tm) tm->begin(11);
   RowAdd m_add;
   m_add.src = w.P + d.ldkv + d.dO; m_add.ld = d.ldp; m_add.index = in.slot_row; m_add.row0 = 0;
@@ -1140,7 +1142,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
   if (chain) {
     ChainArgs ca;
     ca.dO = d.dO; ca.ldh = d.ldh; ca.ldkv = d.ldkv; ca.ldp = d.ldp;
-    ca.Omat = w.Omat; ca.P_o = w.P + d.ldkv + d.dO; ca.slot_row = w.slot_row;
+    ca.Onode = w.Onode; ca.Zp = w.Zp; ca.Wv_pk = w.rc_wv; ca.Omat = w.Omat; ca.P_o = w.P + d.ldkv + d.dO; ca.slot_row = w.slot_row;
     {
       const size_t ks = (size_t)(d.dO + 15) / 16, blk = ks * ks * 256;
       ca.Wo_pk = w.rc_pk; ca.Ws_pk = w.rc_pk + blk; ca.Wd_pk = w.rc_pk + 2 * blk; ca.WsT_pk = w.rc_pk + 3 * blk;

@@ -114,8 +114,9 @@ struct Ws {
   float *WkcT, *WvcT;       // [H dcp, ldh]  row h dcp + c, column d of head h: W[d, d_x + c]   (U = q WkcT^T, G = dO WvcT^T)
   float *Wkc, *Wvc;         // [d_o, ldz]    row d of head h, column h dcp + c: W[d, d_x + c]   (dq += Zs Wkc^T, O += Zp Wvc^T)
   float *Wo_o;              // [d_o, ldh] W_o restricted to the attention-output columns
-  // for the root chain (NULL: it does not fit), in MFMA B-operand order: six [d_o, d_o] blocks; (W_v^c)^T per head [ldz, d_o]
-  float *rc_pk, *rc_wg;
+  // for the root chain (NULL: it does not fit), in MFMA B-operand order: six [d_o, d_o] blocks; (W_v^c)^T per head [ldz, d_o],
+  // and W_v^c [d_o, ldz]
+  float *rc_pk, *rc_wg, *rc_wv;
   float *WdecT, *WihT_phi;
   float *WxT;               // [d_x, ldp]   transposed Wx (rows >= d_m: the static columns)
   float *WoT_o;             // [d_o, ldh]   transposed Wo_o
@@ -707,7 +708,9 @@ void zero_f32(float* p, int n, hipStream_t s);
 struct ChainArgs {
   int nb, n[TGNN_MAX_BATCHES];   // batch sizes (events of batch b follow those of the batches before it); set by root_chain
   int dO, ldh, ldkv, ldp;
-  const float* Omat;          // [R, ldh] attention output
+  const float *Onode, *Zp;    // [R, ldh], [R, ldz]: node part of the attention output, weighted sums of the slots' own inputs
+  float* Omat;                // [R, ldh] attention output
+  const float* Wv_pk;         // W_v^c, block-diagonal over the heads: d_o columns of the output, k = ldz
   const float* P_o;           // node part of the merge layer (bias included), row pitch ldp
   const int32_t* slot_row;    // root slot -> node row (NULL: identity)
   // weight blocks in MFMA B-operand order (see PackDesc): merge layer (attention-output columns), W_s, W_d, and
