@@ -38,12 +38,15 @@ __device__ __forceinline__ float slot_grad(const SlotGrads& g, int sl, int c) {
 #define TGNN_SEG_CHUNK 16
 #endif
 constexpr int SEG_CHUNK = TGNN_SEG_CHUNK;
-// SPAN: consecutive chunks per wavefront (1, 2 or 4).  The accumulators of a run of equal rows carry over from chunk
-// to chunk, so a node with thousands of slots (a tenth of a step's slots sit on one node of a power-law graph) costs
-// one atomic row update per SPAN chunks.  Measured on MI355X it does not pay: the launch is bound by the chain of
-// dependent loads of a wavefront, not by the atomics on the popular rows (SPAN 4 against 1: 57 against 49 us for a
-// 4,000-event step, SPAN 2: 19 against 14 us for a 600-event step), so the launcher uses 1.
-template <int SPAN>
+// What bounds it: a wavefront's two dependent round trips (slot ids, then rows), so what counts is how many wavefronts a
+// SIMD holds.  With up to two heads (TWO) the score gradients and softmax weights of a whole chunk are one gather, a lane
+// per (slot, head, which of the two), handed out by readlane and chosen per column, instead of four loads and registers
+// per slot and column.  A run of equal rows that lies inside the chunk belongs to this wavefront alone and is stored; only
+// runs that go on in a neighbouring chunk need atomics (dP is cleared by the node launches).
+// Against four loads per slot and column and atomics throughout: 51.7 -> 49.1 us on 132,000 slots of 11,000 rows (102 instead
+// of 150 registers); with the atomics gone from most rows, 8 replicas 698 -> 682 us a step, 4,000 events 505 -> 490.
+// (Two or four chunks per wavefront, so that a popular row costs fewer atomic updates: slower on 600 and on 4,000 events.)
+template <bool TWO>
 __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, const int32_t* __restrict__ sort_total,
                                                          const int32_t* __restrict__ sorted,
                                                          const int32_t* __restrict__ sorted_row,
@@ -59,17 +62,20 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
     block -= nq;
   }
   const int lane = threadIdx.x & 63;
-  const int p0 = (block * 4 + (threadIdx.x >> 6)) * SEG_CHUNK * SPAN;
-  // lanes fetch the span's slot ids and rows in parallel, without waiting for the length of the list (entries
-  // past it are dropped below); they are broadcast afterwards
+  const int p0 = (block * 4 + (threadIdx.x >> 6)) * SEG_CHUNK;
+  // lanes fetch the chunk's slot ids and rows in parallel, and the rows of the entries after and before it (lanes
+  // SEG_CHUNK, SEG_CHUNK + 1), without waiting for the length of the list (entries past it are dropped below); they are
+  // broadcast afterwards
   int my_slot = -1, my_row = -1;
-  if (lane < SEG_CHUNK * SPAN && p0 + lane < S) {
-    my_slot = sorted[p0 + lane];
-    my_row = sorted_row[p0 + lane];
+  const int at = lane <= SEG_CHUNK ? p0 + lane : p0 - 1;
+  if (lane < SEG_CHUNK + 2 && at >= 0 && at < S) {
+    my_slot = sorted[at];
+    my_row = sorted_row[at];
   }
   const int total = *sort_total;
   if (p0 >= total) return;
-  if (p0 + lane >= total) my_slot = my_row = -1;
+  if (at >= total) my_slot = my_row = -1;
+  const int next_row = __builtin_amdgcn_readlane(my_row, SEG_CHUNK), prev_row = __builtin_amdgcn_readlane(my_row, SEG_CHUNK + 1);
   // a neighbour slot's root and position among the root's neighbours: one division per slot, done by the lane that
   // fetched it, not one per element
   int my_r = 0, my_j = 0;
@@ -79,90 +85,109 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
     my_j = sl - my_r * sg.k;
   }
   const int HK = sg.H * sg.k;
+  static_assert(SEG_CHUNK * 4 <= 64, "a lane per slot, head and weight");
+  float my_w = 1.f;
+  if (TWO) {   // (one head: the second one's lanes repeat the first's)
+    const int i = lane >> 2, h = min((lane >> 1) & 1, sg.H - 1);
+    const int wr = __shfl(my_r, i), wj = __shfl(my_j, i), ws = __shfl(my_slot, i);
+    const float* src = (lane & 1) ? sg.prob : sg.dscore;
+    if (i < SEG_CHUNK && ws >= R) my_w = src[(size_t)wr * HK + h * sg.k + wj];
+  }
   for (int cb = 0; cb < dO; cb += 128) {   // 128 columns of each of the two sections per pass, 2 + 2 per lane
-    // this lane's columns (the same in the key / query section and in the value / merge section) and their head's
-    // offset into a root's score gradients and softmax weights
-    int ck[2], hoff[2];
+    // this lane's columns (the same in the key / query section and in the value / merge section) and their head
+    int ck[2], head[2];
     bool live[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int c = cb + lane + 64 * u;
       live[u] = c < dO;
       ck[u] = live[u] ? c : 0;
-      hoff[u] = (ck[u] / sg.dh) * sg.k;
+      head[u] = ck[u] / sg.dh;
     }
     float aK[2] = {0.f, 0.f}, aV[2] = {0.f, 0.f}, aQ[2] = {0.f, 0.f}, aM[2] = {0.f, 0.f};
     bool any_kv = false, any_qm = false;
     int cur = -1;
-    auto flush = [&]() __attribute__((always_inline)) {
+    auto flush = [&](bool whole) __attribute__((always_inline)) {
       if (cur < 0) return;
       float* row = dP + (size_t)cur * ldp;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         if (live[u]) {
-          if (any_kv) { atomicAdd(row + ck[u], aK[u]); atomicAdd(row + dO + ck[u], aV[u]); }
-          if (any_qm) { atomicAdd(row + ldkv + ck[u], aQ[u]); atomicAdd(row + ldkv + dO + ck[u], aM[u]); }
+          if (any_kv) {
+            if (whole) { row[ck[u]] = aK[u]; row[dO + ck[u]] = aV[u]; }
+            else { atomicAdd(row + ck[u], aK[u]); atomicAdd(row + dO + ck[u], aV[u]); }
+          }
+          if (any_qm) {
+            if (whole) { row[ldkv + ck[u]] = aQ[u]; row[ldkv + dO + ck[u]] = aM[u]; }
+            else { atomicAdd(row + ldkv + ck[u], aQ[u]); atomicAdd(row + ldkv + dO + ck[u], aM[u]); }
+          }
         }
       }
     };
+    int slots[SEG_CHUNK], rows[SEG_CHUNK];
 #pragma unroll
-    for (int ci = 0; ci < SPAN; ++ci) {
-      if (p0 + ci * SEG_CHUNK >= total) break;   // uniform over the wavefront
-      __builtin_amdgcn_sched_barrier(0);         // one chunk's loads in flight at a time (registers)
-      int slots[SEG_CHUNK], rows[SEG_CHUNK], rr[SEG_CHUNK], jj[SEG_CHUNK];
+    for (int i = 0; i < SEG_CHUNK; ++i) {
+      // (readlane: the values are the same for every lane, so they live in scalar registers)
+      slots[i] = __builtin_amdgcn_readlane(my_slot, i);
+      rows[i] = __builtin_amdgcn_readlane(my_row, i);
+    }
+    // all row loads of the chunk are issued before any is consumed.  Which arrays a slot reads is uniform over the
+    // wavefront (a root slot: its dq and dz rows; a neighbour slot: its root's q and dO rows with the slot's score
+    // gradient and softmax weight per head: dK = ds q, dV = p dO)
+    float xa[SEG_CHUNK][2], xb[SEG_CHUNK][2], wa[TWO ? 1 : SEG_CHUNK][2], wb[TWO ? 1 : SEG_CHUNK][2];
 #pragma unroll
-      for (int i = 0; i < SEG_CHUNK; ++i) {
-        // (readlane: the values are the same for every lane, so they live in scalar registers)
-        slots[i] = __builtin_amdgcn_readlane(my_slot, ci * SEG_CHUNK + i);
-        rows[i] = __builtin_amdgcn_readlane(my_row, ci * SEG_CHUNK + i);
-        rr[i] = __builtin_amdgcn_readlane(my_r, ci * SEG_CHUNK + i);
-        jj[i] = __builtin_amdgcn_readlane(my_j, ci * SEG_CHUNK + i);
-      }
-      // all row loads of the chunk are issued before any is consumed.  Which arrays a slot reads is uniform over the
-      // wavefront (a root slot: its dq and dz rows; a neighbour slot: its root's q and dO rows with the slot's score
-      // gradient and softmax weight per head: dK = ds q, dV = p dO)
-      float xa[SEG_CHUNK][2], xb[SEG_CHUNK][2], wa[SEG_CHUNK][2], wb[SEG_CHUNK][2];
+    for (int i = 0; i < SEG_CHUNK; ++i) {
+      const bool on = rows[i] >= 0;
+      const bool root = slots[i] < R;
+      const int rr = __builtin_amdgcn_readlane(my_r, i);
+      const size_t ro = (size_t)(root ? max(slots[i], 0) : rr);
+      const float* pa = (root ? sg.dq : sg.Qroot) + ro * sg.ldh;
+      const float* pb = (root ? sg.dz : sg.dOmat) + ro * sg.ldh;
 #pragma unroll
-      for (int i = 0; i < SEG_CHUNK; ++i) {
-        const bool on = rows[i] >= 0;
-        const bool root = slots[i] < R;
-        const size_t ro = (size_t)(root ? max(slots[i], 0) : rr[i]);
-        const float* pa = (root ? sg.dq : sg.Qroot) + ro * sg.ldh;
-        const float* pb = (root ? sg.dz : sg.dOmat) + ro * sg.ldh;
-        const float* qa = sg.dscore + ro * HK + jj[i];
-        const float* qb = sg.prob + ro * HK + jj[i];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const bool ld = on && live[u];
-          xa[i][u] = ld ? pa[ck[u]] : 0.f;
-          xb[i][u] = ld ? pb[ck[u]] : 0.f;
-          wa[i][u] = (ld && !root) ? qa[hoff[u]] : 1.f;
-          wb[i][u] = (ld && !root) ? qb[hoff[u]] : 1.f;
+      for (int u = 0; u < 2; ++u) {
+        const bool ld = on && live[u];
+        xa[i][u] = ld ? pa[ck[u]] : 0.f;
+        xb[i][u] = ld ? pb[ck[u]] : 0.f;
+        if (!TWO) {
+          const size_t wo = ro * HK + __builtin_amdgcn_readlane(my_j, i) + head[u] * sg.k;
+          wa[i][u] = (ld && !root) ? sg.dscore[wo] : 1.f;
+          wb[i][u] = (ld && !root) ? sg.prob[wo] : 1.f;
         }
       }
+    }
+    bool from_start = true;   // the run began with the chunk's first entry
 #pragma unroll
-      for (int i = 0; i < SEG_CHUNK; ++i) {
-        if (rows[i] != cur) {
-          flush();
+    for (int i = 0; i < SEG_CHUNK; ++i) {
+      if (rows[i] != cur) {
+        flush(!(from_start && prev_row == cur));
+        if (i > 0) from_start = false;
 #pragma unroll
-          for (int u = 0; u < 2; ++u) aK[u] = aV[u] = aQ[u] = aM[u] = 0.f;
-          any_kv = any_qm = false;
-          cur = rows[i];
-        }
-        if (rows[i] >= 0) {
-          if (slots[i] < R) {
-            any_qm = true;
+        for (int u = 0; u < 2; ++u) aK[u] = aV[u] = aQ[u] = aM[u] = 0.f;
+        any_kv = any_qm = false;
+        cur = rows[i];
+      }
+      if (rows[i] >= 0) {
+        if (slots[i] < R) {
+          any_qm = true;
 #pragma unroll
-            for (int u = 0; u < 2; ++u) { aQ[u] += xa[i][u]; aM[u] += xb[i][u]; }
-          } else {
-            any_kv = true;
+          for (int u = 0; u < 2; ++u) { aQ[u] += xa[i][u]; aM[u] += xb[i][u]; }
+        } else {
+          any_kv = true;
+          float w[4];
+          if (TWO) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) { aK[u] += xa[i][u] * wa[i][u]; aV[u] += xb[i][u] * wb[i][u]; }
+            for (int q = 0; q < 4; ++q)
+              w[q] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_w), 4 * i + q));
+          }
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            aK[u] += xa[i][u] * (TWO ? (head[u] > 0 ? w[2] : w[0]) : wa[TWO ? 0 : i][u]);
+            aV[u] += xb[i][u] * (TWO ? (head[u] > 0 ? w[3] : w[1]) : wb[TWO ? 0 : i][u]);
           }
         }
       }
     }
-    flush();
+    flush(!(from_start && prev_row == cur) && next_row != cur);
   }
 }
 
@@ -178,15 +203,13 @@ static SlotGrads slot_grads(tgnn_ctx* ctx, int R) {
 void seg_reduce(tgnn_ctx* ctx, int R, int S, const QPhi& qphi, hipStream_t s) {
   const Dims& d = ctx->d;
   Ws& w = ctx->w;
-  const int span = 1;   // chunks per wavefront (see the kernel)
-  const int waves = (S + SEG_CHUNK * span - 1) / (SEG_CHUNK * span);
+  const int waves = (S + SEG_CHUNK - 1) / SEG_CHUNK;
   const dim3 grid((waves + 3) / 4 + qphi_blocks(qphi));
-#define TGNN_SEG_CASE(SP)                                                                                             \
-  hipLaunchKernelGGL(seg_reduce_kernel<SP>, grid, dim3(256), 0, s, R, S, d.dO, w.sort_total, w.sorted, w.sorted_row,  \
+#define TGNN_SEG_CASE(TWO)                                                                                             \
+  hipLaunchKernelGGL(seg_reduce_kernel<TWO>, grid, dim3(256), 0, s, R, S, d.dO, w.sort_total, w.sorted, w.sorted_row,  \
                      slot_grads(ctx, R), d.ldkv, w.dP, d.ldp, qphi)
-  if (span == 4) TGNN_SEG_CASE(4);
-  else if (span == 2) TGNN_SEG_CASE(2);
-  else TGNN_SEG_CASE(1);
+  if (d.H <= 2) TGNN_SEG_CASE(true);
+  else TGNN_SEG_CASE(false);
 #undef TGNN_SEG_CASE
 }
 
