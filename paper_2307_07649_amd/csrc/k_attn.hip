@@ -584,20 +584,39 @@ __global__ __launch_bounds__(256) void fattn_bwd_fast_kernel(FusedAttn a) {
 // Generic path: any k <= TGNN_MAX_K, any widths, any number of heads.  Same arithmetic with plain loops: a
 // slot's columns are recomputed wherever they are needed instead of being kept in registers.
 // ---------------------------------------------------------------------------------------------------------
-// per-head softmax over the c valid scores in sa[0 .. HK): weights to sa[HK ..) and to prob
+// per-head softmax over the c valid scores in sa[0 .. HK): weights to sa[HK ..) and to prob.  Every exponential is
+// evaluated once and left in LDS for its head's sum (in the order of the slots).
 __device__ __forceinline__ void softmax_heads(float* sa, int HK, int k, int c, int lane, float* pr) {
-  for (int p = lane; p < HK; p += 64) {
-    const int h = p / k, j = p - h * k;
-    float v = 0.f;
-    if (j < c) {
+  constexpr int PER = (TGNN_MAX_HEADS * TGNN_MAX_K + 63) / 64;
+  float v[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int p = lane + 64 * u, h = p / k, j = p - h * k;
+    v[u] = 0.f;
+    if (p < HK && j < c) {
       float mx = -INFINITY;
+#pragma unroll 4
       for (int jj = 0; jj < c; ++jj) mx = fmaxf(mx, sa[h * k + jj]);
-      float den = 0.f;
-      for (int jj = 0; jj < c; ++jj) den += expf(sa[h * k + jj] - mx);
-      v = expf(sa[p] - mx) / den;
+      v[u] = expf(sa[p] - mx);
     }
-    sa[HK + p] = v;
-    pr[p] = v;
+    if (p < HK) sa[HK + p] = v[u];
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int p = lane + 64 * u, h = p / k, j = p - h * k;
+    if (p < HK && j < c) {
+      float den = 0.f;
+#pragma unroll 4
+      for (int jj = 0; jj < c; ++jj) den += sa[HK + h * k + jj];
+      v[u] /= den;
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int p = lane + 64 * u;
+    if (p < HK) { sa[HK + p] = v[u]; pr[p] = v[u]; }
   }
 }
 
@@ -630,6 +649,61 @@ __device__ __forceinline__ GenLds gen_lds(char* base, int wave, int k, int H) {
   return g;
 }
 
+// the slots' ids, node rows and time differences to LDS (and, in a step's forward pass, the rows for the launches after)
+__device__ __forceinline__ void gen_load_slots(const FusedAttn& a, int r, int c, int lane, const GenLds& L, size_t& qrow) {
+  for (int j = lane; j < a.k; j += 64) {
+    int e, row;
+    double dt;
+    slot_ids(a, r, j, c, e, row, dt, true);
+    L.e[j] = e; L.row[j] = row; L.dt[j] = dt;
+    a.dtk[(size_t)r * a.k + j] = dt;
+    if (a.slot_gid != nullptr) a.slot_row[a.R + r * a.k + j] = j < c ? row : -1;
+  }
+  qrow = a.slot_gid != nullptr ? (size_t)a.uidx[a.slot_gid[r]] : a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
+  if (a.slot_gid != nullptr && lane == 0) a.slot_row[r] = (int)qrow;
+}
+__device__ __forceinline__ void gen_bwd_empty(const FusedAttn& a, int r, int lane, int HK, float* yrow) {   // no neighbours
+  for (int p = lane; p < HK; p += 64) a.dscore[(size_t)r * HK + p] = 0.f;
+  for (int e = lane; e < a.dO; e += 64) a.dqn[(size_t)r * a.ldh + e] = a.Qroot[(size_t)r * a.ldh + e] = 0.f;
+  zero_head_rows(a, a.Zs + (size_t)r * a.ldz, lane);
+  for (int i = lane; i < 2 * a.dt; i += 64) yrow[i] = 0.f;
+}
+__device__ __forceinline__ void gen_bwd_load(const FusedAttn& a, int r, int c, int lane, int HK, const GenLds& L) {
+  for (int j = lane; j < a.k; j += 64) {
+    int e, row;
+    double dt;
+    slot_ids(a, r, j, c, e, row, dt, false);
+    L.e[j] = e; L.row[j] = row; L.dt[j] = dt;
+  }
+  for (int p = lane; p < HK; p += 64) L.sa[p] = a.prob[(size_t)r * HK + p];
+}
+// softmax backward, scaled by 1 / sqrt(|N_v|): dp in sa[HK ..) becomes ds there and in memory
+__device__ __forceinline__ void gen_softmax_bwd(const FusedAttn& a, int r, int c, int lane, int HK, const GenLds& L) {
+  const float scale = 1.0f / sqrtf((float)c);
+  constexpr int PER = (TGNN_MAX_HEADS * TGNN_MAX_K + 63) / 64;
+  float da[PER];
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int p = lane + 64 * u, h = p / a.k, j = p - h * a.k;
+    da[u] = 0.f;
+    if (p < HK && j < c) {
+      float sdot = 0.f;
+#pragma unroll 4
+      for (int jj = 0; jj < c; ++jj) sdot += L.sa[h * a.k + jj] * L.sa[HK + h * a.k + jj];
+      da[u] = L.sa[p] * (L.sa[HK + p] - sdot) * scale;
+    }
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const int p = lane + 64 * u;
+    if (p < HK) {
+      L.sa[HK + p] = da[u];
+      a.dscore[(size_t)r * HK + p] = da[u];
+    }
+  }
+}
+
 __global__ __launch_bounds__(256) void fattn_fwd_gen_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   int block = blockIdx.x;
@@ -650,16 +724,8 @@ __global__ __launch_bounds__(256) void fattn_fwd_gen_kernel(FusedAttn a) {
   const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
   float* pr = a.prob + (size_t)r * HK;
   float* out = a.Onode + (size_t)r * a.ldh;
-  for (int j = lane; j < a.k; j += 64) {
-    int e, row;
-    double dt;
-    slot_ids(a, r, j, c, e, row, dt, true);
-    L.e[j] = e; L.row[j] = row; L.dt[j] = dt;
-    a.dtk[(size_t)r * a.k + j] = dt;
-    if (a.slot_gid != nullptr) a.slot_row[a.R + r * a.k + j] = j < c ? row : -1;
-  }
-  const size_t qrow = a.slot_gid != nullptr ? (size_t)a.uidx[a.slot_gid[r]] : a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
-  if (a.slot_gid != nullptr && lane == 0) a.slot_row[r] = (int)qrow;
+  size_t qrow;
+  gen_load_slots(a, r, c, lane, L, qrow);
   if (c == 0) {
     for (int p = lane; p < HK; p += 64) pr[p] = 0.f;
     for (int e = lane; e < a.dO; e += 64) out[e] = 0.f;
@@ -723,26 +789,16 @@ __global__ __launch_bounds__(256) void fattn_bwd_gen_kernel(FusedAttn a) {
   const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
   float* yrow = a.Y + (size_t)r * a.ldy;
   if (c == 0) {
-    for (int p = lane; p < HK; p += 64) a.dscore[(size_t)r * HK + p] = 0.f;
-    for (int e = lane; e < a.dO; e += 64) a.dqn[(size_t)r * a.ldh + e] = a.Qroot[(size_t)r * a.ldh + e] = 0.f;
-    zero_head_rows(a, a.Zs + (size_t)r * a.ldz, lane);
-    for (int i = lane; i < 2 * a.dt; i += 64) yrow[i] = 0.f;
+    gen_bwd_empty(a, r, lane, HK, yrow);
     return;
   }
-  for (int j = lane; j < a.k; j += 64) {
-    int e, row;
-    double dt;
-    slot_ids(a, r, j, c, e, row, dt, false);
-    L.e[j] = e; L.row[j] = row; L.dt[j] = dt;
-  }
-  for (int p = lane; p < HK; p += 64) L.sa[p] = a.prob[(size_t)r * HK + p];
+  gen_bwd_load(a, r, c, lane, HK, L);
   wave_lds_sync();
   const size_t qrow = a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
   const float* qv = a.P + qrow * a.ldp + a.off_q;
   const float* urow = a.U + qrow * a.ldz;
   const float* grow = a.G + (size_t)r * a.ldz;
   const float* dov = a.dOmat + (size_t)r * a.ldh;
-  const float scale = 1.0f / sqrtf((float)c);
   for (int j = 0; j < c; ++j) {
     const float* prow = a.P + (size_t)L.row[j] * a.ldp + a.dO;
     for (int h = 0; h < a.H; ++h) {
@@ -757,24 +813,7 @@ __global__ __launch_bounds__(256) void fattn_bwd_gen_kernel(FusedAttn a) {
     }
   }
   wave_lds_sync();
-  float da_keep[(TGNN_MAX_HEADS * TGNN_MAX_K + 63) / 64];
-  int it = 0;
-  for (int p = lane; p < HK; p += 64, ++it) {
-    const int h = p / a.k, j = p - h * a.k;
-    float da = 0.f;
-    if (j < c) {
-      float sdot = 0.f;
-      for (int jj = 0; jj < c; ++jj) sdot += L.sa[h * a.k + jj] * L.sa[HK + h * a.k + jj];
-      da = L.sa[p] * (L.sa[HK + p] - sdot) * scale;
-    }
-    da_keep[it] = da;
-  }
-  wave_lds_sync();
-  it = 0;
-  for (int p = lane; p < HK; p += 64, ++it) {
-    L.sa[HK + p] = da_keep[it];
-    a.dscore[(size_t)r * HK + p] = da_keep[it];
-  }
+  gen_softmax_bwd(a, r, c, lane, HK, L);
   wave_lds_sync();
   for (int e = lane; e < a.dO; e += 64) {
     const int h = e / a.dh;
@@ -817,6 +856,345 @@ __global__ __launch_bounds__(256) void fattn_bwd_gen_kernel(FusedAttn a) {
   }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Middle path: up to four heads, d_e + d_t <= 320 and d_o <= 128, any number of neighbours.  The slots go through in groups
+// of four: their columns are formed once for all heads (the generic path forms them per slot and head, one load and one
+// exchange over the wavefront at a time) and once more for the weighted sums, loads and sums of a group are in flight
+// together, four sums share their exchanges.  Every sum has the same terms in the same order as in the generic path.
+// 17 neighbours, 3 heads, 83 columns, 999 roots: forward and backward 28 and 32 us, the whole step 268 -> 171 us.  Bound by
+// the vector ALUs (sines and cosines twice per slot) and, with few roots, by the chain of a wavefront.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int MA_B = 4, MA_M = 5, MA_H = 4, MA_E = 2;
+
+// sums over the wavefront of four values; lane 16 r holds that of value mid_of(r)
+__device__ __forceinline__ float mid_sum4(const float (&v)[MA_B]) {
+  float half[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * i]), __float_as_uint(v[2 * i + 1]), false, false);
+    half[i] = __uint_as_float(x[0]) + __uint_as_float(x[1]);   // {2 i | 2 i + 1}
+  }
+  const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(half[0]), __float_as_uint(half[1]), false, false);
+  float t = __uint_as_float(x[0]) + __uint_as_float(x[1]);     // {0 | 2 | 1 | 3}
+  t = dpp_add<0x128>(t);
+  t = dpp_add<0x124>(t);
+  t = dpp_add<0x122>(t);
+  return dpp_add<0x121>(t);
+}
+__device__ __forceinline__ int mid_of(int row) { return row == 1 ? 2 : row == 2 ? 1 : row; }
+
+struct MidSlots {
+  int e[MA_B], row[MA_B];   // (slots past the last one: the last one's, their results are dropped or weigh nothing)
+  double dt[MA_B];
+};
+__device__ __forceinline__ MidSlots mid_slots(const GenLds& L, int j0, int c) {
+  MidSlots q;
+#pragma unroll
+  for (int i = 0; i < MA_B; ++i) {
+    const int j = min(j0 + i, c - 1);
+    q.e[i] = __builtin_amdgcn_readfirstlane(L.e[j]);
+    q.row[i] = __builtin_amdgcn_readfirstlane(L.row[j]);
+    const double dt = L.dt[j];
+    q.dt[i] = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(dt)), __builtin_amdgcn_readfirstlane(__double2loint(dt)));
+  }
+  return q;
+}
+// this lane's frequencies and phases: column lane + 64 m of {e | Phi}
+struct MidTime {
+  float w[MA_M], b[MA_M];
+};
+__device__ __forceinline__ MidTime mid_time(const FusedAttn& a, int lane) {
+  MidTime t;
+#pragma unroll
+  for (int m = 0; m < MA_M; ++m) {
+    const int tc = lane + 64 * m - a.de;
+    const bool live = tc >= 0 && tc < a.dt;
+    const int i = live ? tc : 0;
+    const float w = a.time_w[i], b = a.time_b[i];
+    t.w[m] = live ? w : 0.f;
+    t.b[m] = live ? b : 0.f;
+  }
+  return t;
+}
+// the group's columns (zero past d_e + d_t), and the sines of the time columns (zero on edge-feature columns)
+template <bool BWD>
+__device__ __forceinline__ void mid_cols(const FusedAttn& a, int lane, const MidSlots& q, const MidTime& t, float (&cv)[MA_M][MA_B],
+                                         float (&sv)[MA_M][MA_B]) {
+#pragma unroll
+  for (int m = 0; m < MA_M; ++m)
+#pragma unroll
+    for (int i = 0; i < MA_B; ++i) {
+      cv[m][i] = 0.f;
+      if (64 * m < a.de) cv[m][i] = a.efeat[(size_t)q.e[i] * a.de + min(lane + 64 * m, a.de - 1)];
+    }
+#pragma unroll
+  for (int m = 0; m < MA_M; ++m) {
+    const int col = lane + 64 * m;
+    const bool is_t = col >= a.de && col < a.de + a.dt;
+    if (64 * m < a.de + a.dt && 64 * m + 64 > a.de) {   // (uniform) some lane has a time column
+#pragma unroll
+      for (int i = 0; i < MA_B; ++i) {
+        float sn, cs;
+        sincos_reduced(fma((double)t.w[m], q.dt[i], (double)t.b[m]), sn, cs);
+        const float ev = cv[m][i];
+        cv[m][i] = is_t ? cs : col < a.de ? ev : 0.f;
+        if (BWD) sv[m][i] = is_t ? sn : 0.f;
+      }
+    } else if (BWD) {
+#pragma unroll
+      for (int i = 0; i < MA_B; ++i) sv[m][i] = 0.f;
+    }
+  }
+}
+// a root's per-head row (U or G), and its query (output gradient): columns lane + 64 m of every head's block, element
+// h d_h + lane + 64 t; zero past the widths
+__device__ __forceinline__ void mid_head_row(const FusedAttn& a, const float* row, int lane, float (&x)[MA_H][MA_M]) {
+  const int dc = a.de + a.dt;
+#pragma unroll
+  for (int h = 0; h < MA_H; ++h)
+#pragma unroll
+    for (int m = 0; m < MA_M; ++m) {
+      const int col = lane + 64 * m;
+      float v = 0.f;
+      if (h < a.H && 64 * m < dc) v = row[h * a.dcp + min(col, dc - 1)];
+      x[h][m] = col < dc ? v : 0.f;
+    }
+}
+__device__ __forceinline__ void mid_head_vec(const FusedAttn& a, const float* v, int lane, float (&x)[MA_H][MA_E]) {
+#pragma unroll
+  for (int h = 0; h < MA_H; ++h)
+#pragma unroll
+    for (int t = 0; t < MA_E; ++t) {
+      float y = 0.f;
+      if (h < a.H && 64 * t < a.dh) y = v[h * a.dh + min(lane + 64 * t, a.dh - 1)];
+      x[h][t] = lane + 64 * t < a.dh ? y : 0.f;
+    }
+}
+// per slot of the group and head: x . c_j + v . P[row_j][off ..], times scale, to out[h k + j]
+__device__ __forceinline__ void mid_scores(const FusedAttn& a, int lane, int j0, int c, const MidSlots& q, const float (&cv)[MA_M][MA_B],
+                                           const float (&x)[MA_H][MA_M], const float (&v)[MA_H][MA_E], int off, float scale, float* out) {
+  float pn[MA_H][MA_E][MA_B];
+#pragma unroll
+  for (int h = 0; h < MA_H; ++h)
+#pragma unroll
+    for (int t = 0; t < MA_E; ++t)
+#pragma unroll
+      for (int i = 0; i < MA_B; ++i) {
+        pn[h][t][i] = 0.f;
+        if (h < a.H && 64 * t < a.dh) pn[h][t][i] = a.P[(size_t)q.row[i] * a.ldp + off + h * a.dh + min(lane + 64 * t, a.dh - 1)];
+      }
+  const int j = j0 + mid_of(lane >> 4);
+#pragma unroll
+  for (int h = 0; h < MA_H; ++h) {
+    if (h >= a.H) break;
+    float acc[MA_B];
+#pragma unroll
+    for (int i = 0; i < MA_B; ++i) {
+      acc[i] = 0.f;
+#pragma unroll
+      for (int m = 0; m < MA_M; ++m) acc[i] += x[h][m] * cv[m][i];
+#pragma unroll
+      for (int t = 0; t < MA_E; ++t) acc[i] += v[h][t] * pn[h][t][i];
+    }
+    const float sum = mid_sum4(acc) * scale;
+    if ((lane & 15) == 0 && j < c) out[h * a.k + j] = sum;
+  }
+}
+
+__global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  int block = blockIdx.x;
+  if (a.fill.gcnt != nullptr) {
+    const int fill_blocks = uniq_blocks(a.fill.S);
+    if (block < fill_blocks) {
+      uniq_fill_block(a.fill, block);
+      return;
+    }
+    block -= fill_blocks;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int r = block * 4 + wave;
+  if (r >= a.R) return;
+  const int HK = a.H * a.k;
+  GenLds L = gen_lds(lds_raw, wave, a.k, a.H);
+  const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
+  float* pr = a.prob + (size_t)r * HK;
+  float* out = a.Onode + (size_t)r * a.ldh;
+  size_t qrow;
+  gen_load_slots(a, r, c, lane, L, qrow);
+  if (c == 0) {
+    for (int p = lane; p < HK; p += 64) pr[p] = 0.f;
+    for (int e = lane; e < a.dO; e += 64) out[e] = 0.f;
+    zero_head_rows(a, a.Zp + (size_t)r * a.ldz, lane);
+    return;
+  }
+  wave_lds_sync();
+  float u[MA_H][MA_M], qv[MA_H][MA_E], cv[MA_M][MA_B], unused[MA_M][MA_B];
+  mid_head_row(a, a.U + qrow * a.ldz, lane, u);
+  mid_head_vec(a, a.P + qrow * a.ldp + a.off_q, lane, qv);
+  const MidTime tm = mid_time(a, lane);
+  const float scale = 1.0f / sqrtf((float)c);
+  for (int j0 = 0; j0 < c; j0 += MA_B) {
+    const MidSlots q = mid_slots(L, j0, c);
+    mid_cols<false>(a, lane, q, tm, cv, unused);
+    mid_scores(a, lane, j0, c, q, cv, u, qv, 0, scale, L.sa);
+  }
+  wave_lds_sync();
+  softmax_heads(L.sa, HK, a.k, c, lane, pr);
+  wave_lds_sync();
+  int he[MA_E];
+#pragma unroll
+  for (int t = 0; t < MA_E; ++t) he[t] = min(lane + 64 * t, a.dO - 1) / a.dh;
+  float o[MA_E] = {0.f, 0.f}, z[MA_H][MA_M];
+#pragma unroll
+  for (int h = 0; h < MA_H; ++h)
+#pragma unroll
+    for (int m = 0; m < MA_M; ++m) z[h][m] = 0.f;
+  for (int j0 = 0; j0 < c; j0 += MA_B) {
+    const MidSlots q = mid_slots(L, j0, c);
+    float pv[MA_E][MA_B];
+#pragma unroll
+    for (int t = 0; t < MA_E; ++t)
+#pragma unroll
+      for (int i = 0; i < MA_B; ++i)
+        pv[t][i] = 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + a.dO + min(lane + 64 * t, a.dO - 1)] : 0.f;
+    mid_cols<false>(a, lane, q, tm, cv, unused);
+#pragma unroll
+    for (int i = 0; i < MA_B; ++i) {
+      const int j = min(j0 + i, c - 1);
+      const bool on = j0 + i < c;
+#pragma unroll
+      for (int t = 0; t < MA_E; ++t) {
+        const float w = L.sa[HK + he[t] * a.k + j];
+        o[t] += (on ? w : 0.f) * pv[t][i];
+      }
+#pragma unroll
+      for (int h = 0; h < MA_H; ++h) {
+        if (h >= a.H) break;
+        const float w = L.sa[HK + h * a.k + j], p = on ? w : 0.f;
+#pragma unroll
+        for (int m = 0; m < MA_M; ++m) z[h][m] += p * cv[m][i];
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < MA_E; ++t)
+    if (lane + 64 * t < a.dO) out[lane + 64 * t] = o[t];
+  float* zrow = a.Zp + (size_t)r * a.ldz;
+#pragma unroll
+  for (int h = 0; h < MA_H; ++h)
+#pragma unroll
+    for (int m = 0; m < MA_M; ++m)
+      if (h < a.H && lane + 64 * m < a.dcp) zrow[h * a.dcp + lane + 64 * m] = z[h][m];
+}
+
+__global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
+  extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int r = blockIdx.x * 4 + wave;
+  if (r >= a.R) return;
+  const int HK = a.H * a.k, dc = a.de + a.dt;
+  GenLds L = gen_lds(lds_raw, wave, a.k, a.H);
+  const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
+  float* yrow = a.Y + (size_t)r * a.ldy;
+  if (c == 0) {
+    gen_bwd_empty(a, r, lane, HK, yrow);
+    return;
+  }
+  gen_bwd_load(a, r, c, lane, HK, L);
+  wave_lds_sync();
+  const size_t qrow = a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
+  const float* qv = a.P + qrow * a.ldp + a.off_q;
+  float u[MA_H][MA_M], g[MA_H][MA_M], dv[MA_H][MA_E], cv[MA_M][MA_B], sv[MA_M][MA_B];
+  mid_head_row(a, a.U + qrow * a.ldz, lane, u);
+  mid_head_row(a, a.G + (size_t)r * a.ldz, lane, g);
+  mid_head_vec(a, a.dOmat + (size_t)r * a.ldh, lane, dv);
+  const MidTime tm = mid_time(a, lane);
+  for (int j0 = 0; j0 < c; j0 += MA_B) {
+    const MidSlots q = mid_slots(L, j0, c);
+    mid_cols<false>(a, lane, q, tm, cv, sv);
+    mid_scores(a, lane, j0, c, q, cv, g, dv, a.dO, 1.0f, L.sa + HK);
+  }
+  wave_lds_sync();
+  gen_softmax_bwd(a, r, c, lane, HK, L);
+  wave_lds_sync();
+  int he[MA_E];
+#pragma unroll
+  for (int t = 0; t < MA_E; ++t) he[t] = min(lane + 64 * t, a.dO - 1) / a.dh;
+  float dq[MA_E] = {0.f, 0.f}, z[MA_H][MA_M], yw[MA_M], yb[MA_M];
+#pragma unroll
+  for (int m = 0; m < MA_M; ++m) {
+    yw[m] = yb[m] = 0.f;
+#pragma unroll
+    for (int h = 0; h < MA_H; ++h) z[h][m] = 0.f;
+  }
+  for (int j0 = 0; j0 < c; j0 += MA_B) {
+    const MidSlots q = mid_slots(L, j0, c);
+    float pk[MA_E][MA_B];
+#pragma unroll
+    for (int t = 0; t < MA_E; ++t)
+#pragma unroll
+      for (int i = 0; i < MA_B; ++i)
+        pk[t][i] = 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + min(lane + 64 * t, a.dO - 1)] : 0.f;
+    mid_cols<true>(a, lane, q, tm, cv, sv);
+#pragma unroll
+    for (int i = 0; i < MA_B; ++i) {
+      const int j = min(j0 + i, c - 1);
+      const bool on = j0 + i < c;
+#pragma unroll
+      for (int t = 0; t < MA_E; ++t) {
+        const float w = L.sa[HK + he[t] * a.k + j];
+        dq[t] += (on ? w : 0.f) * pk[t][i];
+      }
+      float dphi[MA_M];
+#pragma unroll
+      for (int m = 0; m < MA_M; ++m) dphi[m] = 0.f;
+#pragma unroll
+      for (int h = 0; h < MA_H; ++h) {
+        if (h >= a.H) break;
+        const float w = L.sa[HK + h * a.k + j], x = L.sa[h * a.k + j], ds = on ? w : 0.f, p = on ? x : 0.f;
+#pragma unroll
+        for (int m = 0; m < MA_M; ++m) {
+          z[h][m] += ds * cv[m][i];
+          dphi[m] += ds * u[h][m] + p * g[h][m];
+        }
+      }
+      const float dtf = (float)q.dt[i];
+#pragma unroll
+      for (int m = 0; m < MA_M; ++m) {
+        const float t = -dphi[m] * sv[m][i];
+        yb[m] += t;
+        yw[m] += t * dtf;
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < MA_E; ++t) {
+    const int e = lane + 64 * t;
+    if (e < a.dO) {
+      a.dqn[(size_t)r * a.ldh + e] = dq[t];
+      a.Qroot[(size_t)r * a.ldh + e] = qv[e];
+    }
+  }
+  float* zrow = a.Zs + (size_t)r * a.ldz;
+#pragma unroll
+  for (int m = 0; m < MA_M; ++m) {
+    const int col = lane + 64 * m;
+#pragma unroll
+    for (int h = 0; h < MA_H; ++h)
+      if (h < a.H && col < a.dcp) zrow[h * a.dcp + col] = z[h][m];
+    if (col >= a.de && col < dc) {
+      yrow[col - a.de] = yw[m];
+      yrow[a.dt + col - a.de] = yb[m];
+    }
+  }
+}
+
+// the widths the middle path holds in registers
+static bool mid_path(const FusedAttn& a) {
+  return !a.force_generic && a.H <= MA_H && a.dcp <= 64 * MA_M && a.dO <= 64 * MA_E;
+}
+
 static bool fast_path(const FusedAttn& a) {
   return !a.force_generic && a.k <= FA_KR && a.de <= 64 * FA_NE && a.dt <= 64 * FA_NT && a.dO <= 64 * FA_E &&
          a.H <= FA_HM && a.H * a.k <= 64;
@@ -828,6 +1206,8 @@ void fattn_fwd(const FusedAttn& a, hipStream_t s) {
   const dim3 grid((a.R + 3) / 4 + fill_blocks);
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_fwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);
+  else if (mid_path(a))
+    hipLaunchKernelGGL(fattn_fwd_mid_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
   else
     hipLaunchKernelGGL(fattn_fwd_gen_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
 }
@@ -837,6 +1217,8 @@ void fattn_bwd(const FusedAttn& a, hipStream_t s) {
   const dim3 grid((a.R + 3) / 4);
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_bwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);
+  else if (mid_path(a))
+    hipLaunchKernelGGL(fattn_bwd_mid_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
   else
     hipLaunchKernelGGL(fattn_bwd_gen_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
 }
