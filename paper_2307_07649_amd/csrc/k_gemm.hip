@@ -11,6 +11,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <functional>
 #include <cstring>
 
 #include "tgnn_internal.h"
@@ -478,16 +479,14 @@ constexpr int TT = 64;        // bulk tile edge
 constexpr int TN_W = TGNN_TN_WAVES;   // wavefronts per workgroup
 constexpr int TN_STEP = 32;   // rows per step of a wavefront: the depth of one MFMA
 constexpr int TN_ROWS = 32;   // row chunks are multiples of this
+constexpr int TN_MAX_ROWS = 4096, TN_MIN_UNITS = 4;   // longest chunk that the plan looks at, and the shortest (a step per wavefront)
 
-// A length is cut into 64-wide pieces plus one narrower one (16, 32 or again 64 wide) for the remainder.  (With
-// TGNN_TN_SPLIT48 a remainder of 33 .. 48 becomes a 32- and a 16-wide piece instead of a padded 64-wide one: fewer
-// MFMAs, one more tile; measured on MI355X the extra tile costs slightly more than the padding.)
-#ifndef TGNN_TN_SPLIT48
-#define TGNN_TN_SPLIT48 0
-#endif
+// A length is cut into 64-wide pieces plus one narrower one (16, 32 or again 64 wide) for the remainder.  (A remainder of
+// 33 .. 48 as a 32- and a 16-wide piece instead of a padded 64-wide one: fewer MFMAs, one more tile; measured on MI355X the
+// extra tile costs more than the padding, 83 against 77 us on 4,000 events.)
 __host__ __device__ inline int tn_pieces(int len) {
   const int r = len % TT;
-  return len / TT + (r == 0 ? 0 : (TGNN_TN_SPLIT48 && r > 32 && r <= 48) ? 2 : 1);
+  return len / TT + (r == 0 ? 0 : 1);
 }
 __device__ __forceinline__ void tn_piece(int len, int idx, int& off, int& width) {
   const int full = len / TT;
@@ -496,7 +495,6 @@ __device__ __forceinline__ void tn_piece(int len, int idx, int& off, int& width)
   off = full * TT;
   if (r <= 16) width = 16;
   else if (r <= 32) width = 32;
-  else if (TGNN_TN_SPLIT48 && r <= 48) { if (idx == full) width = 32; else { off += 32; width = 16; } }
   else width = TT;
 }
 // Column window of D that one head of head_n columns is tiled over (its start is rounded down to 16 bytes).
@@ -771,27 +769,27 @@ void TnBatch::add(const float* D, int ldd, const float* A, int lda, int M, int N
   g.n++;
 }
 
-// Chunking and placement.  A workgroup's life is a first wait for data, its share of the rows at the pace of
-// the MFMA pipes it shares, and a reduction with one float atomic per tile element; a launch takes as long
-// as the number of rounds the chip needs to hold all workgroups times the life of one.  So a small launch
-// (all weight gradients of a step on a few thousand rows) gets the largest number of row chunks with which
-// no XCD queue exceeds TN_WGS_PER_XCD workgroups, and a large one gets chunks of TN_MAX_ROWS rows and runs
-// in rounds.  An XCD holds 64 workgroups at once (two per compute unit); workgroups with narrow edge tiles
-// finish early, and queues of 72 to 88 measured best on MI355X for the weight gradients of a 600-event step
-// (64 and 96: a fifth slower).  All problems of a launch use the same chunk length.
+// Chunking and placement.  A workgroup's life is a first wait for data, its share of the rows at the pace at which its
+// compute unit's loads come in, and a reduction with one float atomic per tile element.  An XCD holds 64 workgroups at
+// once (two per compute unit) and takes the rest of its queue as these end, so what a chunk length costs is decided by
+// rounds: on a 600-event step queues of 66 workgroups take 18 us, of 84 29 us; on the classification head's 4,000 events
+// queues of 77 long ones 74 us, of 96 shorter ones 59 us.  The rule is the shortest chunks with which no queue exceeds
+// TN_QUEUE workgroups (chunks of TN_BASE_ROWS if that cannot be), unless a walk of the most loaded XCD's queue
+// (tn_makespan) finds another length more than 15 % faster: the walk's constants are fitted to 18 launches of five shapes
+// and its error is up to 20 %, so smaller differences mean nothing (taken for them, 80 -> 86 us on 4,000 events, 18.6 ->
+// 21.9 on 600).  All problems of a launch use the same chunk length.  With the walk: classification 77 -> 60 us, stand-alone
+// backward call 49 -> 36 us, a 333-event step of odd widths 21 -> 15 us.
 // What in-kernel timestamps say about such a launch: a workgroup sees its first rows 3 to 5 us after it starts
 // (argument block, device-side row count, then the rows: three dependent round trips); the reduction and the atomics
 // take 2 to 3 us.  Four wavefronts per workgroup, two workgroups per compute unit: one's reduction runs beside the
 // other's products (eight: 108 against 90 us on a 4,000-event step, 21.7 against 18.3 us on a 600-event one, both with
-// chunks of at most 1,024 rows; 2,048 rows: 77 us on the former, the atomics halve).
-#ifndef TGNN_TN_MAX_ROWS
-#define TGNN_TN_MAX_ROWS 2048
-#endif
-#ifndef TGNN_TN_WGS_PER_XCD
-#define TGNN_TN_WGS_PER_XCD 80
-#endif
-constexpr int TN_MAX_ROWS = TGNN_TN_MAX_ROWS;
-constexpr int TN_WGS_PER_XCD = TGNN_TN_WGS_PER_XCD;
+// chunks of 1,024 rows at most).
+constexpr int TN_SLOTS = 64;            // workgroups an XCD holds at once
+constexpr int TN_QUEUE = 80, TN_BASE_ROWS = 2048;
+constexpr float TN_PLAN_GAIN = 0.85f;
+constexpr float TN_COST_WG = 8.0f;      // us: start, reduction, atomics
+constexpr float TN_COST_ROW = 0.020f;   // us per row of a 64 x 64 tile
+constexpr float TN_COST_LOADS = 0.3f;   // share of that which follows the columns loaded, the rest follows the products
 
 // Chunks of `rows_per_chunk` rows for every problem, then the placement on the eight XCDs: problems in order
 // of decreasing size, each rotated so that the XCDs which receive one chunk more than the others are the least
@@ -832,26 +830,105 @@ static int tn_place(TnGroup& g, const int* rows, int rows_per_chunk) {
   return *std::max_element(load, load + 8);
 }
 
+// What the launch would take, after tn_place: the most loaded XCD's queue on TN_SLOTS slots, each taking the next workgroup
+// as it gets free.
+static float tn_makespan(const TnGroup& g, const int* rows) {
+  float cost[TN_MAX_GROUP][4][4], load[8];   // of a workgroup, by the widths of its tile in units of 16
+  int chunks_of[8][TN_MAX_GROUP];
+  for (int i = 0; i < g.n; ++i) {
+    const int r = (rows[i] + g.p[i].chunks - 1) / g.p[i].chunks;
+    for (int a = 0; a < 4; ++a)
+      for (int b = 0; b < 4; ++b)
+        cost[i][a][b] = TN_COST_WG + TN_COST_ROW * r * (TN_COST_LOADS * (a + b + 2) / 8.0f + (1.0f - TN_COST_LOADS) * (a + 1) * (b + 1) / 16.0f);
+  }
+  auto widths = [](int len, int idx) { const int r = len - idx * TT; return r > 32 ? 3 : r > 16 ? 1 : 0; };   // of piece idx, in 16s less one
+  auto each_tile = [&](int i, auto&& f) {
+    const TnProblem& p = g.p[i];
+    const bool heads = p.out.head_k > 0;
+    const int n = heads ? tn_head_width(p.out.head_n) : p.N;
+    const int k = (heads ? p.out.head_cols : p.K) + (p.out.bias[0] != nullptr || p.out.bias[1] != nullptr ? 1 : 0);
+    for (int h = 0; h < p.heads; ++h)
+      for (int a = 0; a < tn_pieces(n); ++a)
+        for (int b = 0; b < tn_pieces(k); ++b) f(cost[i][widths(n, a)][widths(k, b)]);
+  };
+  int worst = 0;
+  for (int x = 0; x < 8; ++x) {
+    load[x] = 0.f;
+    for (int o = 0; o < g.n; ++o) {
+      const int i = g.qprob[o];
+      chunks_of[x][o] = (g.qbegin[x][o + 1] - g.qbegin[x][o]) / g.p[i].tiles;
+      float sum = 0.f;
+      each_tile(i, [&](float c) { sum += c; });
+      load[x] += sum * chunks_of[x][o];
+    }
+    if (load[x] > load[worst]) worst = x;
+  }
+  float heap[TN_SLOTS] = {}, end = 0.f;   // when each slot gets free, smallest at the front
+  for (int o = 0; o < g.n; ++o)
+    for (int c = 0; c < chunks_of[worst][o]; ++c)
+      each_tile(g.qprob[o], [&](float t) {
+        std::pop_heap(heap, heap + TN_SLOTS, std::greater<float>());
+        heap[TN_SLOTS - 1] += t;
+        end = std::max(end, heap[TN_SLOTS - 1]);
+        std::push_heap(heap, heap + TN_SLOTS, std::greater<float>());
+      });
+  return end;
+}
+
+// The chunk length (in units of TN_ROWS) for a launch.  Depends on the problems' shapes only; the last few are remembered, per
+// thread, so that a program that calls an operator again does not walk the queues again.
+static int tn_plan(TnGroup& g, const int* rows) {
+  struct Plan {
+    int key[1 + 4 * TN_MAX_GROUP], units;
+  };
+  constexpr int KEEP = 8;
+  static thread_local Plan kept[KEEP] = {};
+  static thread_local int next = 0;
+  Plan q = {};
+  q.key[0] = g.n;
+  for (int i = 0; i < g.n; ++i) {
+    const TnProblem& p = g.p[i];
+    const bool bias = p.out.bias[0] != nullptr || p.out.bias[1] != nullptr;
+    q.key[1 + 4 * i] = rows[i]; q.key[2 + 4 * i] = p.N; q.key[3 + 4 * i] = 2 * p.K + (bias ? 1 : 0);
+    q.key[4 + 4 * i] = p.heads * 65536 + p.tiles;
+  }
+  for (const Plan& k : kept)
+    if (memcmp(k.key, q.key, sizeof(q.key)) == 0) return k.units;
+  // the shortest chunks with which no queue exceeds TN_QUEUE (a round, and the narrow tiles' early ends)
+  int lo = TN_MIN_UNITS, hi = TN_BASE_ROWS / TN_ROWS;   // hi: taken if nothing smaller fits
+  if (tn_place(g, rows, hi * TN_ROWS) <= TN_QUEUE)
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (tn_place(g, rows, mid * TN_ROWS) <= TN_QUEUE) hi = mid; else lo = mid + 1;
+    }
+  q.units = hi;
+  tn_place(g, rows, hi * TN_ROWS);
+  float best = TN_PLAN_GAIN * tn_makespan(g, rows);
+  // lengths whose chunk counts differ for the longest problem
+  const int most = *std::max_element(rows, rows + g.n);
+  int last = 0;
+  for (int chunks = std::max(1, (most + TN_MAX_ROWS - 1) / TN_MAX_ROWS); chunks <= 64; chunks += 1 + chunks / 6) {
+    const int units = std::max(TN_MIN_UNITS, ((most + chunks - 1) / chunks + TN_ROWS - 1) / TN_ROWS);
+    if (units == last) { if (units == TN_MIN_UNITS) break; continue; }
+    last = units;
+    tn_place(g, rows, units * TN_ROWS);
+    const float t = tn_makespan(g, rows);
+    if (t < best) { best = t; q.units = units; }
+  }
+  kept[next] = q;
+  next = (next + 1) % KEEP;
+  return q.units;
+}
+
 void TnBatch::launch(hipStream_t s) {
   if (g.n == 0) return;
-  const int per_xcd = TN_WGS_PER_XCD;
-  const int max_rows = TN_MAX_ROWS;
   int rows[TN_MAX_GROUP];
   // a row count that lives on the device (distinct nodes of a step) is usually a small part of its bound
   for (int i = 0; i < g.n; ++i)
     rows[i] = g.p[i].m_dev == nullptr ? g.p[i].M
               : dev_rows_est > 0      ? std::min(g.p[i].M, dev_rows_est)
                                       : (g.p[i].M + 7) / 8;
-  // smallest chunk length (in units of TN_ROWS) whose placement fits the chip at once, by bisection
-  int lo = 4, hi = max_rows / TN_ROWS;   // lo: at least four steps per wavefront; hi: taken if nothing smaller fits
-  int longest = tn_place(g, rows, hi * TN_ROWS);
-  if (longest <= per_xcd) {
-    while (lo < hi) {
-      const int mid = (lo + hi) / 2;
-      if (tn_place(g, rows, mid * TN_ROWS) <= per_xcd) hi = mid; else lo = mid + 1;
-    }
-    longest = tn_place(g, rows, hi * TN_ROWS);
-  }
+  const int longest = tn_place(g, rows, tn_plan(g, rows) * TN_ROWS);
   const int total_wgs = 8 * longest;
   hipLaunchKernelGGL(gemm_tn_kernel, dim3(total_wgs), dim3(64 * TN_W), 0, s, g);
   g.n = 0;
