@@ -33,11 +33,11 @@ STAGE_NAMES = {2: "roots + sample + distinct-node rows + prologue (pack weights,
                9: "per-node projections K, V, q, merge (only when the node path does not fit)",
                8: "per-node projections K, V, q, merge and score vectors U = q W_k^c (MFMA, one launch)",
                10: "attention forward: edge-feature gather, time encoding, scores, softmax, weighted sums (+ slot-sort fill)",
-               7: "attention output = node part + Zp W_v^c^T (MFMA)",
+               7: "attention output = node part + Zp W_v^c^T (MFMA; only when the root chain does not fit)",
                11: "merge layer (MFMA; only when the root chain does not fit)",
                12: "root chain: merge layer, decoder + loss, their backward down to the attention output (MFMA, one launch)",
                13: "decoder backward (only when the root chain does not fit)",
-               19: "G = dO W_v^c per root (MFMA)",
+               19: "G = dO W_v^c per root (MFMA; only when the root chain does not fit)",
                14: "attention backward: edge-feature gather, time encoding, softmax backward, per-root sums",
                5: "dq = node part + Zs W_k^c^T (MFMA)",
                15: "per-node gradient sums; node projections + GRU gates backward",
@@ -578,7 +578,7 @@ def main():
 
     d = P["d"]
     wg = res["weight_gradients"]
-    dom = dict(kernel="gemm_tn_kernel: all weight gradients of the step in one grouped launch (fp32 MFMA 16x16x4), the "
+    dom = dict(kernel="gemm_tn_kernel: all weight gradients of the step in one grouped launch (fp32 operands as three bf16 parts, six bf16 MFMAs each; peak: fp32 MFMA), the "
                       "longest launch of the step; useful flops of its nine products", tag="gemm_tn")
     dk = wg
     out = {

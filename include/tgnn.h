@@ -337,11 +337,12 @@ int32_t tgnn_zero_params(tgnn_ctx* ctx, tgnn_params* g, void* stream);
  *    K, V, q, merge and score vectors U = q W_k^c (MFMA).  Where that does not fit (d_mem > 128, d_mem + d_static > 256 or
  *    a very wide GRU input): 3 state gather + time-encode   4 GRU products   6 GRU gates   9 projections   8 U
  *  10 attention forward: gathers the slots' edge features, time encoding, scores, softmax, weighted sums (with the fill
- *    pass of the slot sort)   7 attention output = node part + Zp (W_v^c)^T (MFMA)
- *  12 root chain: merge layer, decoder + loss and their backward pass down to the gradient of the attention output,
- *    one launch (d_mem a multiple of 4 and <= 128; otherwise 11 merge layer, 12 decoder forward + loss, 13 decoder
- *    backward, and the attention-output gradient GEMM)
- *  19 G = dO W_v^c per root (MFMA)   14 attention backward   5 dq = node part + Zs (W_k^c)^T (MFMA)
+ *    pass of the slot sort)
+ *  12 root chain: attention output = node part + Zp (W_v^c)^T, merge layer, decoder + loss, their backward pass down to
+ *    the gradient dO of the attention output, and G = dO W_v^c per root, one launch (d_mem a multiple of 4 and <= 128;
+ *    otherwise 7 attention output, 11 merge layer, 12 decoder forward + loss, 13 decoder backward, the attention-output
+ *    gradient GEMM, 19 G)
+ *  14 attention backward   5 dq = node part + Zs (W_k^c)^T (MFMA)
  *  15 per-node gradient sums (with the gradients through the query's Phi(0)) + node projections backward with GRU
  *    gates backward
  *  16 all weight gradients and the time-encoding gradients of the keys (one grouped MFMA GEMM)   17 time-encoding

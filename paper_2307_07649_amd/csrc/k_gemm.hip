@@ -1,4 +1,5 @@
-// fp32 MFMA GEMMs for the dense contractions of the step: the GRU and attention projections
+// GEMMs for the dense contractions of the step: NT on fp32 MFMAs, the weight gradients (TN) on split bf16 operands.
+// NT: the GRU and attention projections
 // (Eq. 3-6), the merge layer, the decoder, and their data / weight gradients.
 //
 // v_mfma_f32_16x16x4_f32: lane l supplies A[i = l%16][kk = l/16] and B[kk = l/16][j = l%16]; its four
@@ -6,7 +7,7 @@
 // feed any four k indices per instruction as long as both operands use the same ones: lane group g reads
 // one float4 (k = 4g .. 4g+3 of a 16-wide slab) and issues four MFMAs from it.
 //
-// Both kernels keep two register tile sets in flight (global loads issued two stages ahead) and two LDS
+// The NT kernel keeps two register tile sets in flight (global loads issued two stages ahead) and two LDS
 // buffers, so a workgroup waits for memory only when the chip has nothing else resident to run.
 #include <stdlib.h>
 
