@@ -6,7 +6,10 @@ namespace tgnn {
 
 // sin and cos of `arg`.  The argument of the time encoding, w * dt + b, reaches ~1e6 rad, where one float
 // ulp is a quarter of a radian; so the argument is formed and reduced to [-pi/4, pi/4] in double, and only
-// the polynomial is evaluated in float (absolute error ~1e-7).
+// the polynomial is evaluated in float.  The two polynomials' coefficients are those of sinf / cosf in the Cephes
+// mathematical library (S. L. Moshier, single/sinf.c).  On [-pi/4, pi/4] the polynomials are within 2.7e-9 (sine) and
+// 1.1e-10 (cosine) of the functions, with their roundings to float within 4.6e-8 and 7.4e-8
+// (tests/test_device_math.py).
 __device__ __forceinline__ void sincos_reduced(double arg, float& s, float& c) {
   // j = arg * 2/pi rounded to the nearest integer, by adding and taking off 1.5 * 2^52 (round-to-nearest mode): the
   // sum's low mantissa bits then are j's low bits in two's complement, which gives the quadrant j mod 4 without a
