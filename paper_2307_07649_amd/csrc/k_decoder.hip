@@ -305,7 +305,7 @@ constexpr int RK_U = 7;   // 13 pairs of a wavefront (49 negatives) in two round
 __global__ __launch_bounds__(256) void pair_rank_kernel(const BatchSet* __restrict__ bsp, int dO, const float* __restrict__ Pdec,
                                                         int ldp, const float* __restrict__ b1, const float* __restrict__ w2,
                                                         const float* __restrict__ b2, float* __restrict__ logits,
-                                                        float* __restrict__ rank, float* __restrict__ rr_sum, int per) {
+                                                        float* __restrict__ rank, int per) {
   __shared__ float sc[4][TGNN_MAX_NEG_SETS + 1];
   const BatchSet& bs = *bsp;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -361,19 +361,17 @@ __global__ __launch_bounds__(256) void pair_rank_kernel(const BatchSet* __restri
   if (lane < J) logits[r0 + (size_t)(1 + lane) * n] = sn;
   if (lane == 0) {
     logits[r0] = st;
-    const float r = 1.0f + (float)above + 0.5f * (float)same;
-    rank[ev] = r;
-    atomicAdd(rr_sum, 1.0f / r);
+    rank[ev] = 1.0f + (float)above + 0.5f * (float)same;   // (the reciprocals are added up in the write-back launch)
   }
 }
 
 void pair_ranks(const Dims& d, const BatchSet* bs, int total, int nneg, const float* Pdec, int ldp, const float* b1,
-                const float* w2, const float* b2, float* logits, float* rank, float* rr_sum, hipStream_t s) {
+                const float* w2, const float* b2, float* logits, float* rank, hipStream_t s) {
   static_assert(TGNN_MAX_NEG_SETS <= 64, "a lane per negative destination");
   if (total <= 0) return;
   const int per = nneg >= 8 ? 4 : 1;   // (fewer pairs than that do not feed four wavefronts)
   hipLaunchKernelGGL(pair_rank_kernel, dim3(per == 4 ? total : (total + 3) / 4), dim3(256), 0, s, bs, d.dO, Pdec, ldp, b1, w2, b2,
-                     logits, rank, rr_sum, per);
+                     logits, rank, per);
 }
 
 // Predictions of the classification head against the targets: one thread per (event, class), counts summed per

@@ -1168,8 +1168,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     if (eval && classes)
       class_scores(d, w.bs_dev, bs.total, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, s);
     else if (eval)
-      pair_ranks(d, w.bs_dev, bs.total, bs.nneg, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, ctx->out_rank,
-                 ctx->out_rr, s);
+      pair_ranks(d, w.bs_dev, bs.total, bs.nneg, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, ctx->out_rank, s);
     else if (classes)
       decoder_classes(d, w.bs_dev, bs.total, w.Pdec, d.ldkv, p->dec_b1, p->dec_w2, p->dec_b2, w.logits, out_loss, w.h1,
                       w.dPdec, w.dlog, s);
@@ -1184,6 +1183,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     if (classes) class_counts(w.bs_dev, bs.total, d.nC, w.logits, ctx->out_counts, s);
     WbArgs wb = writeback_args(d, w.bs_dev, bs.total, st, w.winkey, w.epoch, w.Xrow, d.ldxr, w.tau, w.slot_row, nullptr,
                                nullptr, nullptr, nullptr, out_winner, nullptr, 0, 0.0f);
+    if (!classes) wb.rr = RankSum{ctx->out_rank, ctx->out_rr, bs.total, (bs.total + 255) / 256};
     gemm_nt_group(nullptr, 0, s, &wb);
     if (out_logits)
       TGNN_HIP_CHECK(hipMemcpyAsync(out_logits, w.logits, sizeof(float) * n_logits, hipMemcpyDeviceToDevice, s));

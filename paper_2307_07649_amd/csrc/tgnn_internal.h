@@ -229,6 +229,14 @@ struct StatUpd {
   int blocks = 0;
 };
 
+// Sum of the reciprocal ranks of an evaluation pass: 256 events per block are added up before anything goes to rr_sum,
+// which a caller may have carried on over a whole split (added one by one, terms of 0.02 to 0.5 lose their low digits in it).
+struct RankSum {
+  const float* rank = nullptr;    // [n]; NULL: off
+  float* rr_sum = nullptr;
+  int n = 0, blocks = 0;
+};
+
 // Last-event-wins write-back (k_writeback.hip) as a record, so that it can ride in another launch.
 struct WbPtrs {
   float *mem, *mail;
@@ -252,9 +260,10 @@ struct WbArgs {
   float lr = 0.f;
   const AdamSet* adam = nullptr;  // non-NULL: the update is Adam's
   StatUpd stat;                   // ... followed by stat.blocks for the static-memory rows
+  RankSum rr;                     // ... and by rr.blocks for the reciprocal ranks
 };
 inline int wb_total_blocks(const WbArgs& a) {
-  return a.bs != nullptr ? a.wb_blocks + (a.sgd != nullptr ? 64 * a.sgd_cnt : 0) + a.stat.blocks : 0;
+  return a.bs != nullptr ? a.wb_blocks + (a.sgd != nullptr ? 64 * a.sgd_cnt : 0) + a.stat.blocks + a.rr.blocks : 0;
 }
 
 // ---- k_gemm.hip ---------------------------------------------------------------------
@@ -692,9 +701,9 @@ void decoder_classes(const Dims& d, const BatchSet* bs, int total, const float* 
 void class_scores(const Dims& d, const BatchSet* bs, int total, const float* Pdec, int ldp, const float* b1, const float* w2,
                   const float* b2, float* logits, hipStream_t s);
 // Evaluation pass of link prediction: logits of every event's 1 + nneg pairs,
-// rank[ev] = 1 + #(negative pairs of the event scoring above its true pair) + 0.5 #(scoring the same); rr_sum += sum 1/rank
+// rank[ev] = 1 + #(negative pairs of the event scoring above its true pair) + 0.5 #(scoring the same)
 void pair_ranks(const Dims& d, const BatchSet* bs, int total, int nneg, const float* Pdec, int ldp, const float* b1,
-                const float* w2, const float* b2, float* logits, float* rank, float* rr_sum, hipStream_t s);
+                const float* w2, const float* b2, float* logits, float* rank, hipStream_t s);
 // counts[0..2] += tp, fp, fn of the predictions logit > 0 against the batches' class targets (logits [total, C])
 void class_counts(const BatchSet* bs, int total, int C, const float* logits, int32_t* counts, hipStream_t s);
 void mask_dz(int R, int dO, const float* dz_in, int p_in, const float* z, int ldz, float* dz_out, hipStream_t s);

@@ -1,6 +1,6 @@
 // Device side of the last-event-wins write-back (see k_writeback.hip) and of the SGD update, callable from any
 // kernel with blocks of 256 threads: block b < wb_blocks scatters four occurrences, the blocks after that update
-// the parameters (64 blocks per tensor).
+// the parameters (64 blocks per tensor), the co-trained static rows, and sum up an evaluation pass's ranks.
 #pragma once
 #include "tgnn_internal.h"
 #include "device_math.h"
@@ -70,13 +70,29 @@ __device__ __forceinline__ void stat_update_block(const StatUpd& u, int block) {
   }
 }
 
+// 256 events of an evaluation pass: one wavefront adds up their reciprocal ranks, 64 at a time, and adds the sum to rr_sum.
+__device__ __forceinline__ void rank_sum_block(const RankSum& a, int block) {
+  if (threadIdx.x >= 64) return;
+  float sum[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int ev = block * 256 + 64 * q + (int)threadIdx.x;
+    float v = ev < a.n ? 1.0f / a.rank[ev] : 0.f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    sum[q] = v;
+  }
+  if (threadIdx.x == 0) atomicAdd(a.rr_sum, sum[0] + sum[1] + sum[2] + sum[3]);
+}
+
 // block: 0 .. wb_total_blocks(a) - 1
 __device__ __forceinline__ void wb_sgd_block(const WbArgs& a, int block) {
   if (block >= a.wb_blocks) {
     const int extra = block - a.wb_blocks;
     const int n_sgd = a.sgd != nullptr ? 64 * a.sgd_cnt : 0;
     if (extra >= n_sgd) {
-      if (a.stat.drow != nullptr && extra - n_sgd < a.stat.blocks) stat_update_block(a.stat, extra - n_sgd);
+      if (extra - n_sgd < a.stat.blocks) stat_update_block(a.stat, extra - n_sgd);
+      else if (a.rr.rank != nullptr) rank_sum_block(a.rr, extra - n_sgd - a.stat.blocks);
       return;
     }
     const int t = extra >> 6, x = extra & 63;

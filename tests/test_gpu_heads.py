@@ -2,6 +2,7 @@
 reciprocal rank among sampled negative destinations) against the oracle."""
 import numpy as np
 import pytest
+import torch
 
 from gpu_common import GpuSide, OracleSide, batch_np, compare_state, compare_step, make_problem, rel_err, TOL
 from oracle import tgnn_oracle as O
@@ -284,3 +285,23 @@ def test_rank_kernel_pair_counts(J, d_mem, batch):
         assert rel_err(g["logits"], ref) <= TOL
         rank, mrr = O.reciprocal_rank(g["logits"][:batch].astype(np.float64), g["logits"][batch:].reshape(J, batch).astype(np.float64))
         assert np.array_equal(g["rank"], rank.astype(np.float32)) and abs(g["rr_sum"] / batch - mrr) <= 1e-6
+
+
+# the sum of the reciprocal ranks is carried on by the caller: below, at and above one block of 256 events, one wavefront
+# per event and four
+@pytest.mark.parametrize("J,batch", [(49, 255), (49, 256), (3, 700), (49, 600)])
+def test_reciprocal_rank_sum_added_to_a_large_one(J, batch):
+    from paper_2307_07649_amd import tgnn
+    P = synth.custom_problem(n_nodes=300, E=3 * batch, d_mem=16, d_time=8, d_edge=4, d_static=0, n_heads=1, k=3, batch=batch, seed=J)
+    G = GpuSide(P, max_neg_sets=J)
+    rng = np.random.default_rng(J)
+    start = float(2 ** 17)
+    rank = torch.empty(batch, device="cuda"); rr = torch.full((1,), start, device="cuda")
+    want = start
+    for s in range(3):
+        b = batch_np(P, s * batch, (s + 1) * batch)
+        neg = rng.integers(0, 300, J * batch).astype(np.int32)
+        G.ctx.tgnn_eval_step(G.graph, G.state, G.params, [tgnn.Batch(b["src"], b["dst"], neg, b["eid"], b["t"])], J, rank, rr)
+        want += float((1.0 / rank.cpu().numpy().astype(np.float64)).sum())
+    # 256 events are one addition to the large sum, of half an ulp (2^-7) each; what they add up to is exact to 1e-5
+    assert abs(float(rr.item()) - want) <= 3 * ((batch + 255) // 256) * (2.0 ** -7 + 1e-5)
