@@ -171,7 +171,8 @@ int32_t tgnn_gather_memory(tgnn_ctx* ctx, const tgnn_graph* g, const tgnn_state*
 
 /* Eq. 3 with the mail of Eq. 1-2: for each staged row s (the outputs of tgnn_gather_memory):
  * has_mail ? s' = GRU({mail || Phi(mail_ts - mem_ts) || mail_efeat}, mem), tau = mail_ts
- *          : s' = mem, tau = mem_ts.    out_s_new [n_slots, d_m], out_tau [n_slots]. */
+ *          : s' = mem, tau = mem_ts.    out_s_new [n_slots, d_m], out_tau [n_slots].
+ * The results may lie over the inputs (out_s_new over mem, out_tau over mem_ts or mail_ts: an update in place). */
 int32_t tgnn_gru_update(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_slots, const float* mem,
                         const float* mail, const float* mail_efeat, const double* mem_ts,
                         const double* mail_ts, const int32_t* has_mail, float* out_s_new, double* out_tau,

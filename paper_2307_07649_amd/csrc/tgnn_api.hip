@@ -387,6 +387,11 @@ static void node_proj_backward(tgnn_ctx* ctx, tgnn_params* g, int n_rows, const 
 
 static hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
+static bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a != nullptr && b != nullptr && x < y + b_bytes && y < x + a_bytes;
+}
+
 static void fill_param_set(const Dims& d, const tgnn_params* p, const tgnn_params* g, int first, SgdSet& set) {
   memset(&set, 0, sizeof(set));
   float* const* pp = reinterpret_cast<float* const*>(p);
@@ -610,7 +615,21 @@ int32_t tgnn_gru_update(tgnn_ctx* ctx, const tgnn_params* p, int32_t n_slots, co
     NodeArgs na = node_args(ctx, p, n_slots, nullptr);
     na.mem = mem; na.mail = mail; na.efeat = mail_efeat; na.mem_ts = mem_ts; na.mail_ts = mail_ts; na.has_in = has_mail;
     na.tau = out_tau; na.Xrow = out_s_new; na.ldxr = d.dm; na.ds = 0; na.bias_u = nullptr;
+    // A row's columns are shared out among workgroups, each of which reads the whole row: results that go over an input
+    // (a program that updates its staged rows in place) wait in the workspace until all of them are done.
+    const size_t n = (size_t)n_slots;
+    const struct { const void* p; size_t bytes; } in[] = {{mem, 4 * n * d.dm}, {mail, 8 * n * d.dm}, {mail_efeat, 4 * n * d.de},
+                                                          {mem_ts, 8 * n}, {mail_ts, 8 * n}, {has_mail, 4 * n}};
+    bool in_place = false;
+    for (const auto& x : in)
+      in_place = in_place || overlap(x.p, x.bytes, out_s_new, 4 * n * d.dm) || overlap(x.p, x.bytes, out_tau, 8 * n);
+    if (in_place) { na.Xrow = w.Hm; na.ldxr = d.ldh; na.tau = w.delta; }
     node_update(na, s);
+    if (in_place) {
+      TGNN_HIP_CHECK(hipMemcpy2DAsync(out_s_new, (size_t)d.dm * 4, w.Hm, (size_t)d.ldh * 4, (size_t)d.dm * 4, n,
+                                      hipMemcpyDeviceToDevice, s));
+      TGNN_HIP_CHECK(hipMemcpyAsync(out_tau, w.delta, 8 * n, hipMemcpyDeviceToDevice, s));
+    }
     TGNN_LAUNCH_CHECK();
     return TGNN_OK;
   }

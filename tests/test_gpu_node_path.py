@@ -55,6 +55,25 @@ def test_gru_update_row_counts(widths, n):
     assert np.array_equal(tau.cpu().numpy(), np.where(has > 0, mail_ts, mem_ts))
 
 
+# results over the inputs: a program that updates its staged rows in place, with one and with several column groups per tile
+@pytest.mark.parametrize("n,tau_over", [(17, "mem_ts"), (1009, "mail_ts"), (4033, "mem_ts")])
+def test_gru_update_in_place(n, tau_over):
+    import ctypes
+    d = dims(100, 100, 172)
+    tgnn, ctx, _, params = make(d)
+    rng = np.random.default_rng(n)
+    mem_ts = rng.uniform(0, 1e6, n)
+    rows = dict(mem=dev(rng.uniform(-1, 1, (n, d.d_mem)).astype(np.float32)), mail=dev(rng.uniform(-1, 1, (n, 2 * d.d_mem)).astype(np.float32)),
+                mail_efeat=dev(rng.standard_normal((n, d.d_edge)).astype(np.float32)), mem_ts=dev(mem_ts),
+                mail_ts=dev(mem_ts + rng.uniform(0, 1e6, n)), has_mail=dev((rng.random(n) < 0.8).astype(np.int32)))
+    s, tau = ctx.tgnn_gru_update(params, rows)
+    ptr = [rows[x].data_ptr() for x in ("mem", "mail", "mail_efeat", "mem_ts", "mail_ts", "has_mail")]
+    rc = tgnn._lib.tgnn_gru_update(ctx.h, ctypes.byref(params.c), n, *ptr, rows["mem"].data_ptr(), rows[tau_over].data_ptr(),
+                                   torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    assert torch.equal(rows["mem"], s) and torch.equal(rows[tau_over], tau)
+
+
 # node rows R (1 + k) of the stand-alone attention call: row blocks of 16, 32, 64, remainders; one and two heads, a head
 # boundary inside a column block, static columns (more k slabs)
 @pytest.mark.parametrize("widths,R", [((100, 100, 172, 0, 2), R) for R in (1, 3, 93, 186, 373, 745, 1200)]
