@@ -531,7 +531,7 @@ __device__ __forceinline__ int tn_slot(int t, int u, int v, int li, int lg) {
 }
 
 template <int TD, int TA>
-__device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float* __restrict__ A, int ldd, int lda, int dw,
+__device__ __forceinline__ bool tn_tile(const float* __restrict__ D, const float* __restrict__ A, int ldd, int lda, int dw,
                                         int aw, int n_lo, int N, int K, float* p00, float* p01, float* p10, float* p11,
                                         int ld00, int ld01, int ld10, int ld11, int n_split, int k_split, float* bias0,
                                         float* bias1, int M, int m_lo, int m_hi, int n0, int k0, float* lds) {
@@ -576,7 +576,7 @@ __device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float
   };
   int step = wave;
   load(step);
-  if (tid == 0) *next_step = TN_W;   // (after the first loads are on their way)
+  if (tid == 0) { next_step[0] = TN_W; next_step[1] = 0; }   // (after the first loads are on their way)
   __syncthreads();
   while (step < n_steps) {
     const int nxt = claim();
@@ -620,6 +620,15 @@ __device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float
     }
   }
 
+  // Has an operand come by that the split cannot take (split3.h)?  Every sum it enters is NaN: one in D a whole row of the tile,
+  // one in A a whole column, so a lane looks at one of its columns and one of its rows.
+  float any = 0.f;
+#pragma unroll
+  for (int t = 0; t < TD; ++t) any += (acc[t][0][0] + acc[t][0][1]) + (acc[t][0][2] + acc[t][0][3]);
+#pragma unroll
+  for (int u = 1; u < TA; ++u) any += acc[0][u][0];
+  if (__builtin_expect(any != any, 0)) next_step[1] = 1;
+
   // Add the wavefronts' partial tiles in LDS: the lower half of the wavefronts store theirs into a buffer
   // each, the upper half add theirs on top, then every thread sums the buffers for its elements and issues
   // one atomic per element.  acc[t][u][v] of lane (li, lg) is n = TD (4 lg + v) + t, k = TA li + u of the tile.
@@ -643,6 +652,7 @@ __device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float
         for (int v = 0; v < 4; ++v) red[tn_slot<TA>(t, u, v, li, lg)] += acc[t][u][v];
   }
   __syncthreads();
+  if (__builtin_expect(next_step[1] != 0, 0)) return true;   // the tile is left to tn_again
   constexpr int NT = 64 * TN_W;
 #pragma unroll
   for (int i = 0; i < (TILE + NT - 1) / NT; ++i) {
@@ -668,6 +678,47 @@ __device__ __forceinline__ void tn_tile(const float* __restrict__ D, const float
       atomicAdd(base + (size_t)nn * ld + (k - (ks ? k_split : 0)), x);
     }
   }
+  return false;
+}
+
+typedef const TnGroup __attribute__((address_space(4))) * TnGroupPtr;
+// The last part of tn_tile for a tile with NaNs among its sums, which are taken again in fp32 over the chunk's rows (one that is
+// NaN in fp32 as well ends at its first NaN term); TD, TA: the tile's widths in units of 16; h: the head.  Kept apart from the
+// tiles' own last loops, and rolled: in them it costs registers and 0.5 to 1 us of a launch of 11 to 23, this 0.1 to 0.3.
+__device__ __forceinline__ void tn_again(TnGroupPtr gp, int pi, int h, int m_lo, int m_hi, int n0, int k0, int TD, int TA, const float* lds, int tid) {
+  const auto& q = gp->p[pi];
+  const auto& o = q.out;
+  const float *D = q.D, *A = q.A;
+  float* p00 = o.p[0][0];
+  int n_lo = 0, N = q.N, K = q.K;
+  if (o.head_k > 0) {
+    const int first = h * o.head_n, a0 = first & ~3;
+    D += a0;
+    A += h * o.head_k;
+    p00 += (size_t)a0 * o.ld[0][0];
+    n_lo = first - a0; N = n_lo + o.head_n;
+    K = o.head_cols;
+  }
+  const int TW = 16 * TA, TILE = 16 * TD * TW;
+#pragma unroll 1
+  for (int e = tid; e < TILE; e += 64 * TN_W) {
+    const int tn = e / TW, tk = e % TW, n = n0 + tn, k = k0 + tk;
+    if (n < n_lo || n >= N || k > K) continue;
+    const int slot = ((tn % TD * TA + tk % TA) * 4 + ((tn / TD) & 3)) * 64 + ((tn / (4 * TD) * 16 + tk / TA + 16 * (tk % TA)) & 63);
+    float x = 0.f;
+#pragma unroll 1
+    for (int b = 0; b < TN_W / 2; ++b) x += lds[b * TILE + slot];
+    if (x != x) {
+      x = 0.f;
+#pragma unroll 1
+      for (int m = m_lo; m < m_hi && x == x; ++m) x += D[(size_t)m * q.ldd + n] * (k == K ? 1.f : A[(size_t)m * q.lda + k]);
+    }
+    const int ns = n >= o.n_split, ks = k < K && k >= o.k_split;
+    float* out = k == K ? (ns ? o.bias[1] : o.bias[0]) : ns || ks ? o.p[ns][ks] : p00;
+    const int nn = n - (ns ? o.n_split : 0);
+    if (k == K) { if (out != nullptr) atomicAdd(out + nn, x); }
+    else atomicAdd(out + (size_t)nn * o.ld[ns][ks] + (k - (ks ? o.k_split : 0)), x);
+  }
 }
 
 static_assert(sizeof(TnGroup) <= 4096, "the group travels as a kernel argument");
@@ -675,8 +726,7 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   // Several independent problems share one launch (all weight gradients of a step): find this workgroup's.
   // The argument block is indexed through the kernel-argument segment itself (scalar loads at a computed
   // offset); indexing the by-value parameter would make the compiler spill the whole block to scratch.
-  typedef const TnGroup __attribute__((address_space(4))) * GroupPtr;
-  const GroupPtr gp = (GroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const TnGroupPtr gp = (TnGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const int xcd = blockIdx.x & 7, pos = blockIdx.x >> 3;
   // (a loop over the problems with its scalar loads one after the other took 5 us before the first row was asked for)
   typedef int int16v __attribute__((ext_vector_type(16)));
@@ -718,8 +768,10 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const float* Ap = q.A;
   float* p00 = q.out.p[0][0];
   int dw = q.ldd, aw = q.lda, n_lo = 0, n_hi = N, n_tiling = N, Kt = K;
+  int h = 0;
   if (q.out.head_k > 0) {
-    const int per_head = tiles / q.heads, h = tile / per_head;
+    const int per_head = tiles / q.heads;
+    h = tile / per_head;
     tile -= h * per_head;
     const int first = h * q.out.head_n, a0 = first & ~3;
     Dp += a0; dw -= a0;
@@ -735,17 +787,17 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   int n0, wn, k0, wk;
   tn_piece(n_tiling, np, n0, wn);
   tn_piece(Kb, kp, k0, wk);
+  bool again = false;
 #define TGNN_TN_CASE(WN, WK)                                                                                          \
-  if (wn == WN && wk == WK) {                                                                                         \
-    tn_tile<WN / 16, WK / 16>(Dp, Ap, q.ldd, q.lda, dw, aw, n_lo, n_hi, Kt, p00, q.out.p[0][1], q.out.p[1][0],          \
+  if (wn == WN && wk == WK)                                                                                           \
+    again = tn_tile<WN / 16, WK / 16>(Dp, Ap, q.ldd, q.lda, dw, aw, n_lo, n_hi, Kt, p00, q.out.p[0][1], q.out.p[1][0],          \
                               q.out.p[1][1], q.out.ld[0][0], q.out.ld[0][1], q.out.ld[1][0], q.out.ld[1][1],            \
-                              q.out.n_split, q.out.k_split, bias0, q.out.bias[1], M, m_lo, m_hi, n0, k0, lds);      \
-    return;                                                                                                           \
-  }
-  TGNN_TN_CASE(64, 64) TGNN_TN_CASE(64, 32) TGNN_TN_CASE(64, 16)
-  TGNN_TN_CASE(32, 64) TGNN_TN_CASE(32, 32) TGNN_TN_CASE(32, 16)
-  TGNN_TN_CASE(16, 64) TGNN_TN_CASE(16, 32) TGNN_TN_CASE(16, 16)
+                              q.out.n_split, q.out.k_split, bias0, q.out.bias[1], M, m_lo, m_hi, n0, k0, lds);
+  TGNN_TN_CASE(64, 64) else TGNN_TN_CASE(64, 32) else TGNN_TN_CASE(64, 16)
+  else TGNN_TN_CASE(32, 64) else TGNN_TN_CASE(32, 32) else TGNN_TN_CASE(32, 16)
+  else TGNN_TN_CASE(16, 64) else TGNN_TN_CASE(16, 32) else TGNN_TN_CASE(16, 16)
 #undef TGNN_TN_CASE
+  if (__builtin_expect(again, 0)) tn_again(gp, pi, h, m_lo, m_hi, n0, k0, wn / 16, wk / 16, lds, threadIdx.x);
 }
 
 void TnBatch::add(const float* D, int ldd, const float* A, int lda, int M, int N, int K, const OutMap& out,

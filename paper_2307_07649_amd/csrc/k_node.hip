@@ -186,9 +186,138 @@ __device__ __forceinline__ void node_gather(const NodeArgs& a, int pitch, bool k
   }
 }
 
+// Sums that came out NaN (see split3.h), taken again in fp32 from the rows and weights in memory.  An operand that the split
+// cannot take makes NaN of everything it meets: one in a row all of the row's results, one in the weights a column of every
+// row.  A lane that has seen one looks at all of its results once more after its workgroup's last unit.  What that needs waits
+// in LDS and is worked out anew: kept in registers through the units, the kernel arguments of code that is hardly ever run
+// cost 1.3 us of an 11 us update and 2 us of a 50 us one (scalar registers spilled in the gather), and as a part of the units
+// scratch in the update and one wavefront per SIMD less in the projections of wide rows.
+typedef const NodeArgs __attribute__((address_space(4))) NodeKernArgs;
+struct NodeKept {
+  unsigned long long args;   // the kernel-argument segment
+  int block, blocks;
+};
+__device__ __forceinline__ void node_keep(NodeKept& kept) {
+  if (threadIdx.x == 0) kept = NodeKept{(unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), (int)blockIdx.x, (int)gridDim.x};
+}
+
+// The four sums of column c of s' of node row `row`: r, z, n from the memory, n from the input (without the biases).
+__device__ __forceinline__ floatx4 node_update_plain(const NodeKernArgs& a, int row, int c, int g, int e) {
+  const int dm = a.dm, c0 = 2 * dm + a.dt;
+  const double delta = a.gid != nullptr ? a.delta[row] : a.mail_ts[row] - a.mem_ts[row];
+  floatx4 s = {0.f, 0.f, 0.f, 0.f};
+  const float *wr = a.wih + (size_t)c * a.d_in, *wz = wr + (size_t)dm * a.d_in, *wn = wz + (size_t)dm * a.d_in;
+#pragma unroll 1
+  for (int k = 0; k < a.d_in && s[1] == s[1]; ++k) {   // (z NaN: so is s', whatever the other sums are)
+    float x;
+    if (k < 2 * dm) x = a.mail[(size_t)g * 2 * dm + k];
+    else if (k < c0) x = time_enc(delta, a.time_w[k - 2 * dm], a.time_b[k - 2 * dm]);
+    else x = a.efeat[(size_t)e * a.de + k - c0];
+    s[0] += x * wr[k]; s[1] += x * wz[k]; s[3] += x * wn[k];
+  }
+  wr = a.whh + (size_t)c * dm; wz = wr + (size_t)dm * dm; wn = wz + (size_t)dm * dm;
+#pragma unroll 1
+  for (int k = 0; k < dm && s[1] == s[1]; ++k) {
+    const float x = a.mem[(size_t)g * dm + k];
+    s[0] += x * wr[k]; s[1] += x * wz[k]; s[2] += x * wn[k];
+  }
+  return s;
+}
+// Columns col .. col + live - 1 (at most four) of node row `row`.  A row without a mail has its memory for s'.
+__device__ __forceinline__ void node_update_columns(const NodeKernArgs& a, int row, int col, int live) {
+  const int g = a.gid != nullptr ? a.gid[row] : row;
+  const int e = a.gid != nullptr ? a.row_eid[row] : a.has_in[row] ? row : -1;
+  if (e < 0) return;
+#pragma unroll 1
+  for (int c = col; c < col + min(live, 4); ++c) {
+    float* out = a.Xrow + (size_t)row * a.ldxr + c;
+    if (*out == *out) continue;
+    const floatx4 s = node_update_plain(a, row, c, g, e);
+    const int dm = a.dm;
+    const float r = sigmoidf_(s[0] + a.bih[c] + a.bhh[c]), z = sigmoidf_(s[1] + a.bih[dm + c] + a.bhh[dm + c]);
+    const float hn = s[2] + a.bhh[2 * dm + c], nn = tanhf_(s[3] + a.bih[2 * dm + c] + r * hn);
+    *out = (1.0f - z) * nn + z * a.mem[(size_t)g * dm + c];
+    if (a.gates != nullptr) {
+      float* q = a.gates + (size_t)row * 4 * a.ldh + c;
+      q[0] = r; q[a.ldh] = z; q[2 * a.ldh] = nn; q[3 * a.ldh] = hn;
+    }
+  }
+}
+// What this thread has stored of its workgroup's units.
+__device__ __forceinline__ void node_update_again(const NodeKept& kept, int tid) {
+  const NodeKernArgs& a = *(const NodeKernArgs*)kept.args;
+  const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
+  const NodeSplit sp = node_update_split(n, a.rb_max, a.cb);
+  const int rb = sp.rb, groups = sp.groups, units = node_tiles(n, rb) * groups;
+  const int lane = tid & 63, wave = tid >> 6;
+  if (wave >= (a.cb + groups - 1) / groups) return;   // (a column block lies with the first k part's wavefront)
+#pragma unroll 1
+  for (int u = kept.block; u < units; u += a.unit_blocks) {
+    const int tile = u / groups, col = (u - tile * groups + wave * groups) * 16 + 4 * (lane >> 4);
+#pragma unroll 1
+    for (int m = 0; m < rb; ++m) {
+      const int row = (tile * rb + m) * 16 + (lane & 15);
+      if (row < n && col < a.dm) node_update_columns(a, row, col, a.dm - col);
+    }
+  }
+}
+// The node row x that row `row` of the projections has; NULL: zeros.
+template <class Args> __device__ __forceinline__ const float* node_x_row(const Args& a, int row) {
+  if (a.x_root == nullptr) return a.Xrow + (size_t)row * a.ldxr;
+  if (row < a.R) return a.x_root + (size_t)row * a.dx;
+  const int sl = row - a.R, r = sl / a.k;
+  return sl - r * a.k < a.cnt[r] ? a.x_nbr + (size_t)sl * a.dx : nullptr;
+}
+__device__ __forceinline__ float node_plain_dot(int dx, const float* x, const float* w, float s) {
+#pragma unroll 1
+  for (int j = 0; j < dx && s == s; ++j) s += (x != nullptr ? x[j] : 0.f) * w[j];
+  return s;
+}
+// column `col` of P (col < ldp) or column col - ldp of U
+__device__ __forceinline__ float node_project_plain(const NodeKernArgs& a, int row, int col) {
+  const float* x = node_x_row(a, row);
+  const int half = a.ldp >> 1;
+  if (col >= a.ldp) {   // U = q W_k^c of its head
+    const int u = col - a.ldp, h = u / a.dcp, c = u - h * a.dcp, dh = a.dO / a.H;
+    float s = 0.f;
+    if (h < a.H && c < a.dc)
+#pragma unroll 1
+      for (int n = h * dh; n < (h + 1) * dh && s == s; ++n)
+        s += node_plain_dot(a.dx, x, a.wq + (size_t)n * a.dq, a.bias_q[n]) * a.wk[(size_t)n * a.dkv + a.dx + c];
+    return s;
+  }
+  const int sec = col >= half, n = col - sec * half, second = n >= a.dO, m = n - second * a.dO;
+  if (n >= 2 * a.dO) return 0.f;   // padding
+  const float* w = sec ? (second ? a.wo + (size_t)m * (a.dO + a.dx) + a.dO : a.wq + (size_t)m * a.dq)
+                       : (second ? a.wv : a.wk) + (size_t)m * a.dkv;
+  return node_plain_dot(a.dx, x, w, a.bias_x[col]);
+}
+__device__ __forceinline__ void node_project_again(const NodeKept& kept, int rb_max, int tid) {
+  const NodeKernArgs& a = *(const NodeKernArgs*)kept.args;
+  const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max, pairs = (a.ldp + a.ldz) / 32;
+  const NodeSplit sp = node_project_split(n, rb_max, (pairs + 1) / 2);
+  const int rb = sp.rb, groups = sp.groups, units = node_tiles(n, rb) * groups;
+  const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll 1
+  for (int u = kept.block; u < units; u += kept.blocks) {
+    const int tile = u / groups;
+#pragma unroll 1
+    for (int i = 0; i < rb * 8; ++i) {   // row blocks, and the lane's eight columns of a pair of column blocks
+      const int row = (tile * rb + (i >> 3)) * 16 + (lane & 15);
+      if (row >= n) break;
+#pragma unroll 1
+      for (int pr = u - tile * groups + wave * groups; pr < pairs; pr += groups * NP_W) {
+        const int col = pr * 32 + ((i >> 2) & 1) * 16 + 4 * (lane >> 4) + (i & 3);
+        float* o = col < a.ldp ? a.P + (size_t)row * a.ldp + col : a.U + (size_t)row * a.ldz + (col - a.ldp);
+        if (*o != *o) *o = node_project_plain(a, row, col);
+      }
+    }
+  }
+}
+
 // One unit of the update: tile rows [row0, row0 + 16 NB), column blocks group, group + groups, ...
 template <int NB>
-__device__ __forceinline__ void node_update_unit(const NodeArgs& a, int n, int row0, int group, int groups, char* lds, int* has_s) {
+__device__ __forceinline__ void node_update_unit(const NodeArgs& a, int n, int row0, int group, int groups, char* lds, int* has_s, float& seen) {
   constexpr int DEPTH = 2;   // weight slabs in flight per wavefront
   static_assert(DEPTH * NB % 2 == 0, "operand buffers alternate");
   const int pitch = node_pitch(a.kx, a.kh);
@@ -327,6 +456,7 @@ __device__ __forceinline__ void node_update_unit(const NodeArgs& a, int n, int r
           *reinterpret_cast<floatx4*>(g + 2 * a.ldh) = nn; *reinterpret_cast<floatx4*>(g + 3 * a.ldh) = hn;
         }
         node_store4(a.Xrow + (size_t)row * a.ldxr + col, out, live, (a.ldxr & 3) == 0);
+        seen += out[0] + out[1] + out[2] + out[3];   // (columns past d_m: no NaN of their own)
       }
     }
   }
@@ -366,15 +496,19 @@ __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const NodeSplit sp = node_update_split(n, a.rb_max, a.cb);
   const int tiles = node_tiles(n, sp.rb), units = tiles * sp.groups;
+  __shared__ NodeKept kept;
+  node_keep(kept);
   bool again = false;
+  float seen = 0.f;
   for (int u = blockIdx.x; u < units; u += a.unit_blocks) {
     const int tile = u / sp.groups, group = u - tile * sp.groups;
     if (again) __syncthreads();   // the unit before is done with the LDS
     again = true;
-    if (sp.rb == 1) node_update_unit<1>(a, n, tile * 16, group, sp.groups, lds, has_s);
-    else if (sp.rb == 2) node_update_unit<2>(a, n, tile * 32, group, sp.groups, lds, has_s);
-    else node_update_unit<3>(a, n, tile * 48, group, sp.groups, lds, has_s);
+    if (sp.rb == 1) node_update_unit<1>(a, n, tile * 16, group, sp.groups, lds, has_s, seen);
+    else if (sp.rb == 2) node_update_unit<2>(a, n, tile * 32, group, sp.groups, lds, has_s, seen);
+    else node_update_unit<3>(a, n, tile * 48, group, sp.groups, lds, has_s, seen);
   }
+  if (__builtin_expect(seen != seen, 0)) node_update_again(kept, threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -387,13 +521,8 @@ __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int ro
   for (int i = threadIdx.x; i < 16 * RB * chunks; i += 64 * NP_W) {
     const int lr = i / chunks, c = (i - lr * chunks) * 4, row = min(row0 + lr, n - 1);
     floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
-    const float* src = a.Xrow + (size_t)row * a.ldxr;
+    const float* src = node_x_row(a, row);
     if (a.x_root != nullptr) {
-      if (row < a.R) src = a.x_root + (size_t)row * a.dx;
-      else {
-        const int sl = row - a.R, r = sl / a.k;
-        src = sl - r * a.k < a.cnt[r] ? a.x_nbr + (size_t)sl * a.dx : nullptr;
-      }
       if (src != nullptr) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -415,7 +544,7 @@ __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int ro
 // most.  A slab's registers are asked for again, for the wavefront's next pair, as soon as its MFMAs are issued: the
 // weights are a whole pair ahead and no load waits for a store.
 template <int RB, int KS>
-__device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int row0, int group, int groups, char* lds) {
+__device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int row0, int group, int groups, char* lds, float& seen) {
   node_split_rows<RB>(a, n, row0, lds, group == 0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int li = lane & 15, lg = lane >> 4;
@@ -475,6 +604,8 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
 #pragma unroll
     for (int m = 0; m < RB; ++m) {
       const int row = row0 + m * 16 + li;
+      const floatx4 t = acc[m][0] + acc[m][1];
+      seen += m == 0 ? t[0] + t[1] + t[2] + t[3] : acc[m][0][0];   // every column once, every row once
       if (row < n) {
         float* o = out + (size_t)row * ld;
         *reinterpret_cast<floatx4*>(o) = acc[m][0];
@@ -492,22 +623,29 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
   if (pr < pairs) pair(pr, false);
 }
 
+// (Told that two wavefronts per SIMD are wanted, the compiler keeps the accumulators in vector registers; left to itself it
+// moves them to and from accumulation registers, 300 to 400 instructions in all, and takes a register too many for two
+// wavefronts with eight slabs.  1,284 rows: 10.2 -> 8.8 us.)
 template <int KS>
-__global__ __launch_bounds__(64 * NP_W) void node_project_kernel(NodeArgs a) {
+__global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2))) void node_project_kernel(NodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);
   const int tiles = node_tiles(n, sp.rb), units = tiles * sp.groups;
+  __shared__ NodeKept kept;
+  node_keep(kept);
   bool again = false;
+  float seen = 0.f;
   for (int u = blockIdx.x; u < units; u += gridDim.x) {
     const int tile = u / sp.groups, group = u - tile * sp.groups;
     if (again) __syncthreads();
     again = true;
-    if (sp.rb == 1) node_project_unit<1, KS>(a, n, tile * 16, group, sp.groups, lds);
-    else if (sp.rb == 2) node_project_unit<2, KS>(a, n, tile * 32, group, sp.groups, lds);
-    else if (KS <= 4) node_project_unit<KS <= 4 ? 4 : 2, KS>(a, n, tile * 64, group, sp.groups, lds);
+    if (sp.rb == 1) node_project_unit<1, KS>(a, n, tile * 16, group, sp.groups, lds, seen);
+    else if (sp.rb == 2) node_project_unit<2, KS>(a, n, tile * 32, group, sp.groups, lds, seen);
+    else if (KS <= 4) node_project_unit<KS <= 4 ? 4 : 2, KS>(a, n, tile * 64, group, sp.groups, lds, seen);
   }
+  if (__builtin_expect(seen != seen, 0)) node_project_again(kept, KS <= 4 ? NP_MAX_RB : 2, threadIdx.x);
 }
 
 NodeArgs node_args(tgnn_ctx* ctx, const tgnn_params* p, int n_max, const int32_t* n_dev) {
@@ -519,6 +657,7 @@ NodeArgs node_args(tgnn_ctx* ctx, const tgnn_params* p, int n_max, const int32_t
   a.tau = w.tau; a.Xrow = w.Xrow; a.P = w.P; a.U = w.Umat;
   a.ldx = d.ldx; a.ldh = d.ldh; a.ldxr = d.ldxr; a.ldp = d.ldp; a.ldz = d.ldz;
   a.Wg = w.Wg_s; a.Wp = w.Wp_s;
+  a.wih = p->gru_wih; a.whh = p->gru_whh; a.wq = p->wq; a.wv = p->wv; a.wo = p->wo; a.dq = d.dq;
   a.bias_u = w.bias_x + d.ldp; a.wk = p->wk; a.bias_q = w.bias_x + d.ldkv; a.dkv = d.dkv; a.dO = d.dO; a.dc = d.de + d.dt; a.dcp = d.dcp;
   a.H = d.H;
   a.dm = d.dm; a.dt = d.dt; a.de = d.de; a.ds = d.ds; a.dx = d.dx; a.d_in = d.d_in;

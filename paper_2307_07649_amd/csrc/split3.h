@@ -8,7 +8,12 @@
 // products of normal numbers): relative error 3.4e-7 this way, 4.1e-7 with v_mfma_f32_16x16x4_f32; taking eight
 // products instead of six changes no digit of that.  A bf16 MFMA does sixteen times the work of an fp32 one per cycle
 // (2,040 against 140 TFLOP/s measured), so six of them are 2.4 times as fast.
-// Magnitudes above 3.38e38 round to infinity and parts below 1e-38 may be flushed.
+// The splitting and the choice of products are those of G. Henry, P. T. P. Tang and A. Heinecke, "Leveraging the bfloat16
+// Artificial Intelligence Datatype For Higher-Precision Computations" (ARITH 2019).
+// Parts below 1e-38 may be flushed.  A number that is infinite, or that rounds to infinity in bf16 (finite magnitudes above
+// 3.38e38), has a part inf - inf: every sum it enters is NaN, where fp32 products give an infinity or even a finite number.
+// So a kernel that uses split operands looks at its finished sums and takes each NaN among them once more, as a plain fp32 sum
+// over the operands as they are (a sum that is NaN in fp32, too, ends at its first NaN term).
 #pragma once
 #include <hip/hip_runtime.h>
 

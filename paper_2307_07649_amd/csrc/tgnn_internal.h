@@ -644,6 +644,8 @@ struct NodeArgs {
   const float *bih, *bhh, *bias_x;   // bias_x [ldp + ldz]: biases of P, then of U, which the update launch forms:
   float* bias_u;                     // bias_u[h dcp + c] = sum_d W_k[h dh + d, d_x + c] bias_q[h dh + d]
   const float *wk, *bias_q;
+  const float *wih, *whh, *wq, *wv, *wo;   // the weights as they are, for sums that the split operands cannot take (split3.h)
+  int dq;
   int dkv, dO, dc, dcp, H;
   int dm, dt, de, ds, dx, d_in;
   int cb, kx, kh, kp;        // column blocks of the memory width; k slabs
