@@ -863,8 +863,12 @@ __global__ __launch_bounds__(256) void fattn_bwd_gen_kernel(FusedAttn a) {
 // together, four sums share their exchanges.  Every sum has the same terms in the same order as in the generic path.
 // 17 neighbours, 3 heads, 83 columns, 999 roots: forward and backward 28 and 32 us, the whole step 268 -> 171 us.  Bound by
 // the vector ALUs (sines and cosines twice per slot) and, with few roots, by the chain of a wavefront.
+// A kernel holds M rounds of 64 columns: with one kernel of five rounds for all widths, up to 64 columns paid for five (151
+// and 189 registers, three and two wavefronts per SIMD) and took longer than the generic path from 700 events on.  4,000
+// events, 11 neighbours, one head, 8 and 128 columns, the whole step: generic 291 and 335 us, five rounds 349 and 362, one and
+// two rounds 267 and 297.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int MA_B = 4, MA_M = 5, MA_H = 4, MA_E = 2;
+constexpr int MA_B = 4, MA_M = 5, MA_H = 4, MA_E = 2;   // (M: rounds of 64 columns that a kernel holds, MA_M at most)
 
 // sums over the wavefront of four values; lane 16 r holds that of value mid_of(r)
 __device__ __forceinline__ float mid_sum4(const float (&v)[MA_B]) {
@@ -900,13 +904,13 @@ __device__ __forceinline__ MidSlots mid_slots(const GenLds& L, int j0, int c) {
   return q;
 }
 // this lane's frequencies and phases: column lane + 64 m of {e | Phi}
-struct MidTime {
-  float w[MA_M], b[MA_M];
+template <int M> struct MidTime {
+  float w[M], b[M];
 };
-__device__ __forceinline__ MidTime mid_time(const FusedAttn& a, int lane) {
-  MidTime t;
+template <int M> __device__ __forceinline__ MidTime<M> mid_time(const FusedAttn& a, int lane) {
+  MidTime<M> t;
 #pragma unroll
-  for (int m = 0; m < MA_M; ++m) {
+  for (int m = 0; m < M; ++m) {
     const int tc = lane + 64 * m - a.de;
     const bool live = tc >= 0 && tc < a.dt;
     const int i = live ? tc : 0;
@@ -917,18 +921,18 @@ __device__ __forceinline__ MidTime mid_time(const FusedAttn& a, int lane) {
   return t;
 }
 // the group's columns (zero past d_e + d_t), and the sines of the time columns (zero on edge-feature columns)
-template <bool BWD>
-__device__ __forceinline__ void mid_cols(const FusedAttn& a, int lane, const MidSlots& q, const MidTime& t, float (&cv)[MA_M][MA_B],
-                                         float (&sv)[MA_M][MA_B]) {
+template <bool BWD, int M>
+__device__ __forceinline__ void mid_cols(const FusedAttn& a, int lane, const MidSlots& q, const MidTime<M>& t, float (&cv)[M][MA_B],
+                                         float (&sv)[M][MA_B]) {
 #pragma unroll
-  for (int m = 0; m < MA_M; ++m)
+  for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int i = 0; i < MA_B; ++i) {
       cv[m][i] = 0.f;
       if (64 * m < a.de) cv[m][i] = a.efeat[(size_t)q.e[i] * a.de + min(lane + 64 * m, a.de - 1)];
     }
 #pragma unroll
-  for (int m = 0; m < MA_M; ++m) {
+  for (int m = 0; m < M; ++m) {
     const int col = lane + 64 * m;
     const bool is_t = col >= a.de && col < a.de + a.dt;
     if (64 * m < a.de + a.dt && 64 * m + 64 > a.de) {   // (uniform) some lane has a time column
@@ -948,12 +952,12 @@ __device__ __forceinline__ void mid_cols(const FusedAttn& a, int lane, const Mid
 }
 // a root's per-head row (U or G), and its query (output gradient): columns lane + 64 m of every head's block, element
 // h d_h + lane + 64 t; zero past the widths
-__device__ __forceinline__ void mid_head_row(const FusedAttn& a, const float* row, int lane, float (&x)[MA_H][MA_M]) {
+template <int M> __device__ __forceinline__ void mid_head_row(const FusedAttn& a, const float* row, int lane, float (&x)[MA_H][M]) {
   const int dc = a.de + a.dt;
 #pragma unroll
   for (int h = 0; h < MA_H; ++h)
 #pragma unroll
-    for (int m = 0; m < MA_M; ++m) {
+    for (int m = 0; m < M; ++m) {
       const int col = lane + 64 * m;
       float v = 0.f;
       if (h < a.H && 64 * m < dc) v = row[h * a.dcp + min(col, dc - 1)];
@@ -971,8 +975,8 @@ __device__ __forceinline__ void mid_head_vec(const FusedAttn& a, const float* v,
     }
 }
 // per slot of the group and head: x . c_j + v . P[row_j][off ..], times scale, to out[h k + j]
-__device__ __forceinline__ void mid_scores(const FusedAttn& a, int lane, int j0, int c, const MidSlots& q, const float (&cv)[MA_M][MA_B],
-                                           const float (&x)[MA_H][MA_M], const float (&v)[MA_H][MA_E], int off, float scale, float* out) {
+template <int M> __device__ __forceinline__ void mid_scores(const FusedAttn& a, int lane, int j0, int c, const MidSlots& q, const float (&cv)[M][MA_B],
+                                           const float (&x)[MA_H][M], const float (&v)[MA_H][MA_E], int off, float scale, float* out) {
   float pn[MA_H][MA_E][MA_B];
 #pragma unroll
   for (int h = 0; h < MA_H; ++h)
@@ -992,7 +996,7 @@ __device__ __forceinline__ void mid_scores(const FusedAttn& a, int lane, int j0,
     for (int i = 0; i < MA_B; ++i) {
       acc[i] = 0.f;
 #pragma unroll
-      for (int m = 0; m < MA_M; ++m) acc[i] += x[h][m] * cv[m][i];
+      for (int m = 0; m < M; ++m) acc[i] += x[h][m] * cv[m][i];
 #pragma unroll
       for (int t = 0; t < MA_E; ++t) acc[i] += v[h][t] * pn[h][t][i];
     }
@@ -1001,7 +1005,7 @@ __device__ __forceinline__ void mid_scores(const FusedAttn& a, int lane, int j0,
   }
 }
 
-__global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
+template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   int block = blockIdx.x;
   if (a.fill.gcnt != nullptr) {
@@ -1029,14 +1033,14 @@ __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
     return;
   }
   wave_lds_sync();
-  float u[MA_H][MA_M], qv[MA_H][MA_E], cv[MA_M][MA_B], unused[MA_M][MA_B];
+  float u[MA_H][M], qv[MA_H][MA_E], cv[M][MA_B], unused[M][MA_B];
   mid_head_row(a, a.U + qrow * a.ldz, lane, u);
   mid_head_vec(a, a.P + qrow * a.ldp + a.off_q, lane, qv);
-  const MidTime tm = mid_time(a, lane);
+  const MidTime<M> tm = mid_time<M>(a, lane);
   const float scale = 1.0f / sqrtf((float)c);
   for (int j0 = 0; j0 < c; j0 += MA_B) {
     const MidSlots q = mid_slots(L, j0, c);
-    mid_cols<false>(a, lane, q, tm, cv, unused);
+    mid_cols<false, M>(a, lane, q, tm, cv, unused);
     mid_scores(a, lane, j0, c, q, cv, u, qv, 0, scale, L.sa);
   }
   wave_lds_sync();
@@ -1045,11 +1049,11 @@ __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
   int he[MA_E];
 #pragma unroll
   for (int t = 0; t < MA_E; ++t) he[t] = min(lane + 64 * t, a.dO - 1) / a.dh;
-  float o[MA_E] = {0.f, 0.f}, z[MA_H][MA_M];
+  float o[MA_E] = {0.f, 0.f}, z[MA_H][M];
 #pragma unroll
   for (int h = 0; h < MA_H; ++h)
 #pragma unroll
-    for (int m = 0; m < MA_M; ++m) z[h][m] = 0.f;
+    for (int m = 0; m < M; ++m) z[h][m] = 0.f;
   for (int j0 = 0; j0 < c; j0 += MA_B) {
     const MidSlots q = mid_slots(L, j0, c);
     float pv[MA_E][MA_B];
@@ -1058,7 +1062,7 @@ __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
 #pragma unroll
       for (int i = 0; i < MA_B; ++i)
         pv[t][i] = 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + a.dO + min(lane + 64 * t, a.dO - 1)] : 0.f;
-    mid_cols<false>(a, lane, q, tm, cv, unused);
+    mid_cols<false, M>(a, lane, q, tm, cv, unused);
 #pragma unroll
     for (int i = 0; i < MA_B; ++i) {
       const int j = min(j0 + i, c - 1);
@@ -1073,7 +1077,7 @@ __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
         if (h >= a.H) break;
         const float w = L.sa[HK + h * a.k + j], p = on ? w : 0.f;
 #pragma unroll
-        for (int m = 0; m < MA_M; ++m) z[h][m] += p * cv[m][i];
+        for (int m = 0; m < M; ++m) z[h][m] += p * cv[m][i];
       }
     }
   }
@@ -1084,11 +1088,11 @@ __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
 #pragma unroll
   for (int h = 0; h < MA_H; ++h)
 #pragma unroll
-    for (int m = 0; m < MA_M; ++m)
+    for (int m = 0; m < M; ++m)
       if (h < a.H && lane + 64 * m < a.dcp) zrow[h * a.dcp + lane + 64 * m] = z[h][m];
 }
 
-__global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
+template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r = blockIdx.x * 4 + wave;
@@ -1105,14 +1109,14 @@ __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   wave_lds_sync();
   const size_t qrow = a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
   const float* qv = a.P + qrow * a.ldp + a.off_q;
-  float u[MA_H][MA_M], g[MA_H][MA_M], dv[MA_H][MA_E], cv[MA_M][MA_B], sv[MA_M][MA_B];
+  float u[MA_H][M], g[MA_H][M], dv[MA_H][MA_E], cv[M][MA_B], sv[M][MA_B];
   mid_head_row(a, a.U + qrow * a.ldz, lane, u);
   mid_head_row(a, a.G + (size_t)r * a.ldz, lane, g);
   mid_head_vec(a, a.dOmat + (size_t)r * a.ldh, lane, dv);
-  const MidTime tm = mid_time(a, lane);
+  const MidTime<M> tm = mid_time<M>(a, lane);
   for (int j0 = 0; j0 < c; j0 += MA_B) {
     const MidSlots q = mid_slots(L, j0, c);
-    mid_cols<false>(a, lane, q, tm, cv, sv);
+    mid_cols<false, M>(a, lane, q, tm, cv, sv);
     mid_scores(a, lane, j0, c, q, cv, g, dv, a.dO, 1.0f, L.sa + HK);
   }
   wave_lds_sync();
@@ -1121,9 +1125,9 @@ __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   int he[MA_E];
 #pragma unroll
   for (int t = 0; t < MA_E; ++t) he[t] = min(lane + 64 * t, a.dO - 1) / a.dh;
-  float dq[MA_E] = {0.f, 0.f}, z[MA_H][MA_M], yw[MA_M], yb[MA_M];
+  float dq[MA_E] = {0.f, 0.f}, z[MA_H][M], yw[M], yb[M];
 #pragma unroll
-  for (int m = 0; m < MA_M; ++m) {
+  for (int m = 0; m < M; ++m) {
     yw[m] = yb[m] = 0.f;
 #pragma unroll
     for (int h = 0; h < MA_H; ++h) z[h][m] = 0.f;
@@ -1136,7 +1140,7 @@ __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
 #pragma unroll
       for (int i = 0; i < MA_B; ++i)
         pk[t][i] = 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + min(lane + 64 * t, a.dO - 1)] : 0.f;
-    mid_cols<true>(a, lane, q, tm, cv, sv);
+    mid_cols<true, M>(a, lane, q, tm, cv, sv);
 #pragma unroll
     for (int i = 0; i < MA_B; ++i) {
       const int j = min(j0 + i, c - 1);
@@ -1146,22 +1150,22 @@ __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
         const float w = L.sa[HK + he[t] * a.k + j];
         dq[t] += (on ? w : 0.f) * pk[t][i];
       }
-      float dphi[MA_M];
+      float dphi[M];
 #pragma unroll
-      for (int m = 0; m < MA_M; ++m) dphi[m] = 0.f;
+      for (int m = 0; m < M; ++m) dphi[m] = 0.f;
 #pragma unroll
       for (int h = 0; h < MA_H; ++h) {
         if (h >= a.H) break;
         const float w = L.sa[HK + h * a.k + j], x = L.sa[h * a.k + j], ds = on ? w : 0.f, p = on ? x : 0.f;
 #pragma unroll
-        for (int m = 0; m < MA_M; ++m) {
+        for (int m = 0; m < M; ++m) {
           z[h][m] += ds * cv[m][i];
           dphi[m] += ds * u[h][m] + p * g[h][m];
         }
       }
       const float dtf = (float)q.dt[i];
 #pragma unroll
-      for (int m = 0; m < MA_M; ++m) {
+      for (int m = 0; m < M; ++m) {
         const float t = -dphi[m] * sv[m][i];
         yb[m] += t;
         yw[m] += t * dtf;
@@ -1178,7 +1182,7 @@ __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   }
   float* zrow = a.Zs + (size_t)r * a.ldz;
 #pragma unroll
-  for (int m = 0; m < MA_M; ++m) {
+  for (int m = 0; m < M; ++m) {
     const int col = lane + 64 * m;
 #pragma unroll
     for (int h = 0; h < MA_H; ++h)
@@ -1207,7 +1211,8 @@ void fattn_fwd(const FusedAttn& a, hipStream_t s) {
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_fwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);
   else if (mid_path(a))
-    hipLaunchKernelGGL(fattn_fwd_mid_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
+    hipLaunchKernelGGL(a.dcp <= 64 ? fattn_fwd_mid_kernel<1> : a.dcp <= 128 ? fattn_fwd_mid_kernel<2> : fattn_fwd_mid_kernel<MA_M>, grid,
+                       dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
   else
     hipLaunchKernelGGL(fattn_fwd_gen_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
 }
@@ -1218,7 +1223,8 @@ void fattn_bwd(const FusedAttn& a, hipStream_t s) {
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_bwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);
   else if (mid_path(a))
-    hipLaunchKernelGGL(fattn_bwd_mid_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
+    hipLaunchKernelGGL(a.dcp <= 64 ? fattn_bwd_mid_kernel<1> : a.dcp <= 128 ? fattn_bwd_mid_kernel<2> : fattn_bwd_mid_kernel<MA_M>, grid,
+                       dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
   else
     hipLaunchKernelGGL(fattn_bwd_gen_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
 }

@@ -1,12 +1,13 @@
 """The attention kernels' middle path (groups of four slots) against the generic path, which it replaces up to four heads,
 d_e + d_t <= 320 and d_o <= 128: the same terms in the same order, so the outputs are equal bit for bit; gradients against
-each other (their sums over roots are split differently from run to run)."""
+each other (their sums over roots are split differently from run to run).  Both against the oracle."""
 import numpy as np
 import pytest
 import torch
 
 import synth
 from gpu_common import rel_err
+from oracle import tgnn_oracle as O
 
 pytestmark = pytest.mark.gpu
 
@@ -16,10 +17,12 @@ def dev(a):
 
 
 # (d_mem, d_time, d_edge, heads, k): k around the groups of four and the largest; columns around the rounds of 64 and the
-# limits, no edge features, a time block inside one round and across two; widths past the limits (generic on both sides)
+# limits of the kernels of one, two and five rounds, no edge features, a time block inside one round and across two; widths past
+# the limits (generic on both sides)
 @pytest.mark.parametrize("shape", [
     (12, 5, 3, 3, 1), (12, 5, 0, 4, 4), (72, 50, 33, 3, 17), (100, 100, 186, 4, 11), (128, 128, 192, 4, 20), (112, 64, 0, 4, 32),
     (66, 63, 65, 1, 13), (64, 64, 64, 2, 12), (33, 1, 256, 3, 5), (130, 20, 10, 2, 12), (40, 129, 192, 4, 6), (40, 9, 4, 5, 7),
+    (32, 8, 0, 1, 11), (39, 33, 32, 3, 5), (24, 100, 29, 1, 12),
 ])
 def test_middle_path_equals_the_generic_path(shape):
     from paper_2307_07649_amd import tgnn
@@ -29,10 +32,12 @@ def test_middle_path_equals_the_generic_path(shape):
     p32 = synth.gen_params(d, seed=3, random_phase=True)
     params = tgnn.Params.from_numpy(p32)
     rng = np.random.default_rng(k)
-    x_root = dev(rng.uniform(-1, 1, (R, dm)).astype(np.float32)); x_nbr = dev(rng.uniform(-1, 1, (R * k, dm)).astype(np.float32))
-    e = dev(rng.standard_normal((R * k, de)).astype(np.float32)); dt = dev(rng.uniform(0, 3e5, R * k))
+    host = dict(x_root=rng.uniform(-1, 1, (R, dm)).astype(np.float32), x_nbr=rng.uniform(-1, 1, (R * k, dm)).astype(np.float32),
+                e=rng.standard_normal((R * k, de)).astype(np.float32), dt=rng.uniform(0, 3e5, R * k))
+    x_root, x_nbr, e, dt = (dev(host[n]) for n in ("x_root", "x_nbr", "e", "dt"))
     cnt = rng.integers(0, k + 1, R).astype(np.int32); cnt[0] = k; cnt[1] = 0
-    dz = dev(rng.standard_normal((R, dm)).astype(np.float32))
+    host["dz"] = rng.standard_normal((R, dm)).astype(np.float32)
+    dz = dev(host["dz"])
     out = []
     for flags in (0, tgnn.FLAG_GENERIC_ATTN):
         ctx = tgnn.Context(d.n_nodes, dm, dt_, de, 0, H, k, R, flags=flags)
@@ -46,3 +51,15 @@ def test_middle_path_equals_the_generic_path(shape):
     assert rel_err(r0, r1) <= 2e-6 and rel_err(n0, n1) <= 2e-6
     for n in ("wv", "bv", "wo", "bo", "wq", "wk", "time_w", "time_b"):
         assert np.abs(g0[n] - g1[n]).max() <= 2e-5 * np.abs(g1[n]).max(), n
+    # the oracle, in 64 bits: sums of at most 340 products per score and 32 slots, as in the projections (1e-5); weight
+    # gradients over 53 roots, with sixteen roundings of the terms that cancel in the softmax's backward pass
+    p = O.to_f64(p32)
+    mask = (np.arange(k)[None] < cnt[:, None])
+    ref, cache = O.attention_fwd(p, host["x_root"].astype(np.float64), host["x_nbr"].reshape(R, k, dm) * mask[..., None],
+                                 host["e"].reshape(R, k, de) * mask[..., None], host["dt"].reshape(R, k) * mask, cnt.astype(np.int64), H)
+    assert rel_err(z0, ref) <= 1e-5
+    g, dxr, dxn = O.attention_bwd(p, cache, host["dz"].astype(np.float64), H)
+    assert rel_err(r0, dxr[:, :dm]) <= 2e-5 and rel_err(n0.reshape(R, k, dm), dxn[:, :, :dm] * mask[..., None]) <= 2e-5
+    for n in ("wv", "bv", "wo", "bo", "wq", "wk", "time_w", "time_b"):
+        floor = 16 * 2.0 ** -24 * float(cache["abs_terms"][n].max()) if n in cache["abs_terms"] else 0.0
+        assert np.abs(g0[n] - g[n]).max() <= 2e-5 * np.abs(g[n]).max() + floor, n
