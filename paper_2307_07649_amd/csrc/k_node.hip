@@ -604,8 +604,6 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
 #pragma unroll
     for (int m = 0; m < RB; ++m) {
       const int row = row0 + m * 16 + li;
-      const floatx4 t = acc[m][0] + acc[m][1];
-      seen += m == 0 ? t[0] + t[1] + t[2] + t[3] : acc[m][0][0];   // every column once, every row once
       if (row < n) {
         float* o = out + (size_t)row * ld;
         *reinterpret_cast<floatx4*>(o) = acc[m][0];
@@ -617,6 +615,12 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
         }
       }
     }
+    // every column once and every row once (after the stores: 45.0 against 46.6 us on 20,000 rows, 43.9 without)
+    const floatx4 t = acc[0][0] + acc[0][1];
+    float u = t[0] + t[1] + t[2] + t[3];
+#pragma unroll
+    for (int m = 1; m < RB; ++m) u += acc[m][0][0];
+    seen += u;
   };
   int pr = first;
   for (; pr + stride < pairs; pr += stride) pair(pr, true);
