@@ -29,7 +29,7 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
     q.src = src; q.dst = dst; q.rows = rows; q.cols = cols; q.ldd = ldd; q.srs = srs; q.scs = scs;
     q.nblk = d.H; q.brd = brd; q.bcd = bcd; q.bsrc = bsrc;
   };
-  const bool backward = what != PACK_FORWARD, chain = what == PACK_CHAIN;
+  const bool backward = what != PACK_FORWARD, fused = what == PACK_CHAIN, chain = fused || what == PACK_CHAIN_APART;
   if (p != nullptr) {
     const int dO = d.dO, dm = d.dm, dx = d.dx, dkv = d.dkv, dmrg = d.dO + d.dx, half = d.ldkv;
     // node part of every projection of x = {s' | static}: output columns {W_k ; W_v} then, from column `half`,
@@ -73,14 +73,14 @@ void prologue_fill(tgnn_ctx* ctx, const tgnn_params* p, const BatchSet* bs, cons
       const int dh = dO / d.H, dc = d.de + d.dt;
       // row h dcp + c, column h dh + dd  <-  W[h dh + dd, d_x + c]
       if (!nd) add_bd(p->wk + dx, w.WkcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
-      if (backward && !chain) add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
-      if (chain) {
+      if (backward && !fused) add_bd(p->wv + dx, w.WvcT, dc, dh, d.ldh, 1, dkv, d.dcp, dh, dh * dkv);
+      if (fused) {
         add_bd(p->wv + dx, w.rc_wg, dc, dh, 0, 1, dkv, d.dcp, dh, dh * dkv);
         pa.d[n - 1].mfma_ks = (dO + 15) / 16;
       }
       // row h dh + dd, column h dcp + c  <-  W[h dh + dd, d_x + c]
       if (backward) add_bd(p->wk + dx, w.Wkc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
-      if (!chain) add_bd(p->wv + dx, w.Wvc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
+      if (!fused) add_bd(p->wv + dx, w.Wvc, dh, dc, d.ldz, dkv, 1, dh, d.dcp, dh * dkv);
       else {
         add_bd(p->wv + dx, w.rc_wv, dh, dc, 0, dkv, 1, dh, d.dcp, dh * dkv);
         pa.d[n - 1].mfma_ks = d.ldz / 16;

@@ -6,13 +6,13 @@
 // blocks, one per role (each contiguous in the root order [src | dst | neg] of a batch), when a step has many
 // events; E = 5, one 16-row block {5 src | 5 dst | 5 neg | pad}, when it has few and more workgroups (compute
 // units) are worth more than full blocks:
-//   h      = O_node + Zp (W_v^c)^T per head                       (the attention output)
+//   h      = O_node + Zp (W_v^c)^T per head                       (the attention output; see root_chain_fuses)
 //   z      = ReLU(h W_oh^T + P_o[row(root)])                      (P_o: node part of the merge layer, bias included)
 //   Pdec   = z W_s^T for sources, z W_d^T for destinations         (only the half a root needs)
 //   pairs  : hidden = ReLU(Pdec_src + Pdec_dst + b1), logit, loss, d/d(logit), d/d(hidden) -> dPdec per root
 //   dz     = gate_z(dPdec W_s) for sources, gate_z(dPdec W_d) for destinations
 //   dOmat  = dz W_oh
-//   G_h    = dO_h (W_v^c)_h per head, what the attention's backward pass dots with the slots' own inputs
+//   G_h    = dO_h (W_v^c)_h per head (root_chain_fuses), what the attention's backward pass dots with the slots' own inputs
 // The weights are read from global memory (L2) as MFMA B operands, from copies laid out in operand order (the
 // prologue writes them): 1 KB of contiguous memory per wavefront, column block and 16-wide k slab.
 // h, z, h1, dPdec ({W_s part | W_d part}, the unused half zero), dz and dOmat go to memory for the weight-gradient
@@ -197,6 +197,7 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
   // would pay one memory latency per pass)
   constexpr int ZC_PER = G::ROWS * (RC_ZC / 4) / (64 * RC_WAVES);
   static_assert(G::ROWS * (RC_ZC / 4) % (64 * RC_WAVES) == 0, "whole rounds");
+  const bool fused = a.Zp != nullptr;
   const int z_slabs = a.ldz / 16, z_chunks = (a.ldz + RC_ZC - 1) / RC_ZC;
   floatx4 zc[ZC_PER];
   auto z_load = [&](int chunk) __attribute__((always_inline)) {
@@ -220,9 +221,11 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
       if (s >= o_lo && s < o_hi) w[i] = *reinterpret_cast<const floatx4*>(p + (size_t)s * 256);
     }
   };
-  z_load(0);
-  __builtin_amdgcn_sched_barrier(0);   // keep this issue order
-  o_load(w0, 0);
+  if (fused) {
+    z_load(0);
+    __builtin_amdgcn_sched_barrier(0);   // keep this issue order
+    o_load(w0, 0);
+  }
   int prow[G::NB][4];
 #pragma unroll
   for (int j = 0; j < G::NB; ++j)
@@ -245,7 +248,7 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
 #pragma unroll
   for (int j = 0; j < G::NB; ++j)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) on[j][v] = a.Onode[(size_t)groot(j * 16 + lg * 4 + v) * ldh + min(cb * 16 + li, dO - 1)];
+    for (int v = 0; v < 4; ++v) on[j][v] = (fused ? a.Onode : a.Omat)[(size_t)groot(j * 16 + lg * 4 + v) * ldh + min(cb * 16 + li, dO - 1)];
   float addv[G::NB][4];
 #pragma unroll
   for (int j = 0; j < G::NB; ++j) {
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
         }
       }
     };
-    for (int ch = 0; ch < z_chunks; ++ch) {
+    for (int ch = 0; ch < (fused ? z_chunks : 0); ++ch) {
       if (ch > 0) __syncthreads();   // the chunk before has been read
 #pragma unroll
       for (int u = 0; u < ZC_PER; ++u) {
@@ -304,7 +307,7 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
           const int lr = j * 16 + lg * 4 + v;
           const float x = col < dO ? oacc[j][v] + on[j][v] : 0.f;
           T0[lr * RC_PL + col] = x;
-          if (col < dO && live(lr)) a.Omat[(size_t)groot(lr) * ldh + col] = x;
+          if (fused && col < dO && live(lr)) a.Omat[(size_t)groot(lr) * ldh + col] = x;
         }
     }
   }
@@ -445,7 +448,7 @@ __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) 
   // the weights of this wavefront's first two column blocks of G come in beside it
   RcHeads gh;
   gh.n = a.H * a.dcp; gh.bn = a.dcp; gh.bk = dO / a.H;
-  const int g_blocks = a.ldz / 16;   // (a multiple of two; blocks past the last head's columns meet zero weights)
+  const int g_blocks = fused ? a.ldz / 16 : 0;   // (a multiple of two; blocks past the last head's columns meet zero weights)
   rc_g_load<KS>(wa.w[0], gh, wave, g_blocks, a.Wg_pk, lane);
   rc_g_load<KS>(wa.w[1], gh, wave + RC_WAVES, g_blocks, a.Wg_pk, lane);
   if (has_cb) {
@@ -486,6 +489,21 @@ bool root_chain_fits(const Dims& d) {
 // Few events (wide == false is then chosen): 5 per workgroup, so that a 600-event step occupies 120 compute units
 // instead of 38; many: 16 per workgroup, full MFMA row blocks.
 constexpr int RC_FEW_EVENTS = 1280;
+
+// Where the attention output and G lie inside the chain.  A workgroup goes through all columns of its roots' weighted sums, and
+// with few events there are few workgroups: long rows are then better off in two launches of their own; with many events
+// these launches cost more.  Three and more heads change over earlier (a block of the output meets few of their columns).
+// Step times in us, inside against apart:
+//   two heads        1,216 columns 343 / 336 (8 events), 363 / 359 (100), 432 / 435 (600), 536 / 549 (1,280)
+//                    2,208         550 / 537 (100), 682 / 679 (600), 849 / 865 (1,280), 1,868 / 1,902 (4,000)
+//                    4,224         1,770 / 1,746 (2,000), 2,947 / 2,982 (3,000), 3,307 / 3,355 (4,000)
+//   four and eight   1,088         175 / 168 (100), 307 / 310 (1,280), 615 / 625 (4,000)
+//                    1,440         641 / 634 (2,000), 972 / 973 (3,000), 1,110 / 1,114 (4,000)
+//                    2,400         486 / 458 (8), 615 / 601 (600), 946 / 922 (2,000), 1,740 / 1,729 (4,000)
+//                    8,800         1,273 / 1,169 (100), 1,897 / 1,819 (600)
+bool root_chain_fuses(const Dims& d, int total) {
+  return total < 600 ? d.ldz <= 1024 : d.H <= 2 ? d.ldz <= 2304 || total >= 3000 : d.ldz <= 1536;
+}
 
 void root_chain(ChainArgs a, const BatchSet& bs_host, bool force_wide, hipStream_t s) {
   int total = 0;

@@ -244,7 +244,8 @@ static FusedAttn fused_args(tgnn_ctx* ctx, int R, const AttnIn& in) {
 // U = q (W_k^c) per head (a second GEMM over the node rows), the output is the kernel's node part plus Zp (W_v^c)^T
 // (a GEMM over the roots).  n_rows_dev (may be NULL): device-side row count.
 static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows, const int* n_rows_dev, const AttnIn& in,
-                         StageTimer* tm, hipStream_t s, bool products, const SortArgs& fill = SortArgs(), bool with_output = true) {
+                         StageTimer* tm, hipStream_t s, bool products, const SortArgs& fill = SortArgs(), bool with_output = true,
+                         bool with_merge = true) {
   const Dims& d = ctx->d; Ws& w = ctx->w;
   if (products) {
     if (tm) tm->begin(9);
@@ -265,7 +266,7 @@ static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows,
   fa.fill = fill;
   fattn_fwd(fa, s);
   if (tm) tm->end(10);
-  if (!with_output) return;   // the caller's next launch (the root chain) holds the attention output and the merge layer
+  if (!with_output) return;   // the caller's next launch (the root chain) holds the attention output
   if (tm) tm->begin(7);
   {   // attention output = node part + Zp (W_v^c)^T
     RowAdd add;
@@ -276,6 +277,7 @@ static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows,
     gemm_nt_group(&o, 1, s);
   }
   if (tm) tm->end(7);
+  if (!with_merge) return;   // (... or just the merge layer)
   if (tm) tm->begin(11);
   RowAdd m_add;
   m_add.src = w.P + d.ldkv + d.dO; m_add.ld = d.ldp; m_add.index = in.slot_row; m_add.row0 = 0;
@@ -297,11 +299,12 @@ static QPhi qphi_args(tgnn_ctx* ctx, const tgnn_params* p, tgnn_params* g) {
 // sums that give the gradients of the time-encoding parameters through the keys; adds the column sums of dq to
 // ws.q_part, which the caller cleared (consumed by qphi_block in a later launch).
 static void attn_backward(tgnn_ctx* ctx, tgnn_params* g, const tgnn_params* p, int R, const AttnIn& in, TnBatch& tn,
-                          Side& side, hipStream_t s, StageTimer* tm, bool have_G = false) {
+                          Side& side, hipStream_t s, StageTimer* tm, bool have_dO = false, bool have_G = false) {
   const Dims& d = ctx->d; Ws& w = ctx->w;
   tn.add(w.dz, d.ldh, w.Omat, d.ldh, R, d.dO, d.dO, single_out(g->wo, d.dO + d.dx, nullptr));
-  if (!have_G) {   // (otherwise the root chain has left both)
+  if (!have_dO)   // (otherwise the root chain has left it, and G as well if it holds that)
     gemm_nt(w.dz, d.ldh, w.WoT_o, d.ldh, nullptr, w.dOmat, d.ldh, R, d.dO, d.ldh, d.ldh, false, s);
+  if (!have_G) {
     if (tm) tm->begin(19);
     // G = dO (W_v^c)_h per head
     const NtProblem gm = nt_blocks(nt_live(nt_problem(w.dOmat, d.ldh, w.WvcT, d.ldh, nullptr, w.Gmat, d.ldz, R, d.H * d.dcp,
@@ -1071,7 +1074,7 @@ static bool step_chain(const tgnn_ctx* ctx, const BatchSet& bs) {
   return root_chain_fits(ctx->d) && bs.nneg == 1 && bs.ncls == 0 && !ctx->eval;
 }
 static int step_packs(const tgnn_ctx* ctx, const BatchSet& bs) {
-  return ctx->eval ? PACK_FORWARD : step_chain(ctx, bs) ? PACK_CHAIN : PACK_ALL;
+  return ctx->eval ? PACK_FORWARD : !step_chain(ctx, bs) ? PACK_ALL : root_chain_fuses(ctx->d, bs.total) ? PACK_CHAIN : PACK_CHAIN_APART;
 }
 
 // Enqueues every launch of one training step on `s` (and the context's side stream).
@@ -1153,15 +1156,15 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     tm.end(6);
   }
   // (the fill pass of the slot sort, needed by the backward pass only, rides in the attention launch)
-  const bool chain = step_chain(ctx, bs);
+  const bool chain = step_chain(ctx, bs), fused = chain && root_chain_fuses(d, bs.total);
   const AttnIn ain{w.slot_row, w.slot_gid, w.uidx, w.cnt, g->efeat, w.neid, nullptr, p};
-  attn_forward(ctx, p, R, U, w.ucount, ain, &tm, s, !nd, sort, !chain);
+  attn_forward(ctx, p, R, U, w.ucount, ain, &tm, s, !nd, sort, !fused, !chain);
 
   tm.begin(12);
   if (chain) {
     ChainArgs ca;
     ca.dO = d.dO; ca.ldh = d.ldh; ca.ldkv = d.ldkv; ca.ldp = d.ldp;
-    ca.Onode = w.Onode; ca.Zp = w.Zp; ca.Wv_pk = w.rc_wv; ca.Omat = w.Omat; ca.P_o = w.P + d.ldkv + d.dO; ca.slot_row = w.slot_row;
+    ca.Onode = w.Onode; ca.Zp = fused ? w.Zp : nullptr; ca.Wv_pk = w.rc_wv; ca.Omat = w.Omat; ca.P_o = w.P + d.ldkv + d.dO; ca.slot_row = w.slot_row;
     {
       const size_t ks = (size_t)(d.dO + 15) / 16, blk = ks * ks * 256;
       ca.Wo_pk = w.rc_pk; ca.Ws_pk = w.rc_pk + blk; ca.Wd_pk = w.rc_pk + 2 * blk; ca.WsT_pk = w.rc_pk + 3 * blk;
@@ -1229,7 +1232,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     gemm_nt(w.dPdec, d.ldkv, w.WdecT, d.ldkv, nullptr, w.dz, d.ldh, R, d.dO, d.ldkv, d.ldh, false, s, nullptr, gate);
     tm.end(13);
   }
-  attn_backward(ctx, grads, p, R, ain, tn, side, s, &tm, chain);
+  attn_backward(ctx, grads, p, R, ain, tn, side, s, &tm, chain, fused);
   tm.begin(15);
   // per-row sum of the slot gradients reaching the per-node projections (the query's Phi(0) gradients ride along)
   seg_reduce(ctx, R, S, qphi_args(ctx, p, grads), s);

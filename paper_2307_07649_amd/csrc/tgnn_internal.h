@@ -422,8 +422,9 @@ struct PackDesc {
 };
 constexpr int MAX_PACK = 30;
 // What a call needs packed: every copy but the root chain's (PACK_ALL), the root chain's instead of the separate merge and
-// decoder products' (PACK_CHAIN), or only what a forward pass reads (PACK_FORWARD).
-enum { PACK_ALL = 0, PACK_CHAIN = 1, PACK_FORWARD = 2 };
+// decoder products' (PACK_CHAIN; PACK_CHAIN_APART: the attention output and G are products of their own), or only what a
+// forward pass reads (PACK_FORWARD).
+enum { PACK_ALL = 0, PACK_CHAIN = 1, PACK_FORWARD = 2, PACK_CHAIN_APART = 3 };
 struct PrologueArgs {
   PackDesc d[MAX_PACK];
   int n_pack;
@@ -720,6 +721,7 @@ struct ChainArgs {
   int nb, n[TGNN_MAX_BATCHES];   // batch sizes (events of batch b follow those of the batches before it); set by root_chain
   int dO, ldh, ldkv, ldp;
   const float *Onode, *Zp;    // [R, ldh], [R, ldz]: node part of the attention output, weighted sums of the slots' own inputs
+                              // (Zp == NULL: the attention output is there, and G is not wanted)
   float* Omat;                // [R, ldh] attention output
   const float* Wv_pk;         // W_v^c, block-diagonal over the heads: d_o columns of the output, k = ldz
   const float* P_o;           // node part of the merge layer (bias included), row pitch ldp
@@ -735,6 +737,7 @@ struct ChainArgs {
   float *loss, *g_w2, *g_b2;
 };
 bool root_chain_fits(const Dims& d);
+bool root_chain_fuses(const Dims& d, int total);   // attention output and G inside the chain for `total` events
 // force_wide: 16 events per workgroup whatever the size of the step (otherwise 5 when there are few events)
 void root_chain(ChainArgs a, const BatchSet& bs_host, bool force_wide, hipStream_t s);
 
