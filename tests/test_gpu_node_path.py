@@ -10,8 +10,8 @@ from oracle import tgnn_oracle as O
 
 pytestmark = pytest.mark.gpu
 
-# A pre-activation is a sum of K <= 850 products whose factors are at most 1/sqrt(K) and a few units: fp32 sums are off by
-# less than K 2^-24 times the largest product, 7e-6 here in the worst case and under 1e-6 in practice; the gates and the
+# A pre-activation is a sum of K <= 1,600 products whose factors are at most 1/sqrt(K) and a few units: fp32 sums are off by
+# less than K 2^-24 times the largest product, 9.5e-6 here in the worst case and under 1e-6 in practice; the gates and the
 # projections that follow do not enlarge that.
 NODE_TOL = 1e-5
 
@@ -31,12 +31,16 @@ def make(d):
     return tgnn, ctx, p32, tgnn.Params.from_numpy(p32)
 
 
-# rows: one tile, a remainder of one row, both sides of every change of row blocks and column groups (252 workgroups)
+# rows: one tile, a remainder of one row, both sides of every change of row blocks and column groups (252 workgroups); inputs
+# of 1,080 columns, whose tiles hold two row blocks, and of 1,242 and 1,500, which hold one: there the workgroups go through
+# several units beyond 8,064 and 4,032 rows, with one column group and (under 4,032) with several
 ROWS = [1, 15, 16, 17, 1008, 1009, 1344, 1345, 2017, 4033, 6049, 8065, 12097, 13200]
 
 
 @pytest.mark.parametrize("widths,n", [((100, 100, 172), n) for n in ROWS]
-                         + [(w, n) for w in ((128, 1, 255), (16, 5, 0), (7, 30, 3)) for n in (1, 17, 1345, 4033, 12097)])
+                         + [(w, n) for w in ((128, 1, 255), (16, 5, 0), (7, 30, 3)) for n in (1, 17, 1345, 4033, 12097)]
+                         + [((100, 100, 780), n) for n in (1009, 2017, 4032, 4033, 8065)]
+                         + [((16, 10, 1200), n) for n in (33, 4100)] + [((100, 100, 1200), n) for n in (1345, 4033, 9000)])
 def test_gru_update_row_counts(widths, n):
     d = dims(*widths)
     tgnn, ctx, p32, params = make(d)
@@ -74,10 +78,13 @@ def test_gru_update_in_place(n, tau_over):
     assert torch.equal(rows["mem"], s) and torch.equal(rows[tau_over], tau)
 
 
-# node rows R (1 + k) of the stand-alone attention call: row blocks of 16, 32, 64, remainders; one and two heads, a head
-# boundary inside a column block, static columns (more k slabs)
-@pytest.mark.parametrize("widths,R", [((100, 100, 172, 0, 2), R) for R in (1, 3, 93, 186, 373, 745, 1200)]
-                         + [(w, R) for w in ((100, 100, 131, 100, 2), (30, 9, 5, 3, 3)) for R in (3, 745)])
+# node rows 11 R of the stand-alone attention call: R lies inside every interval of the split into row blocks of 16, 32 and 64
+# and eight to two column groups (512 workgroups: changes at 1,024, 1,360, 2,048, 2,720, 4,096, 5,440 and 8,192 rows), with
+# remainders; one to three heads, a head boundary inside a column block, static columns (eight k slabs: the same splits, with 32
+# rows at most)
+@pytest.mark.parametrize("widths,R", [((100, 100, 172, 0, 2), R) for R in (1, 3, 93, 110, 186, 220, 300, 373, 600, 745, 1200)]
+                         + [((100, 100, 131, 100, 2), R) for R in (3, 93, 110, 186, 220, 300, 373, 600, 745)]
+                         + [((30, 9, 5, 3, 3), R) for R in (3, 745)])
 def test_projections_row_counts(widths, R):
     d = dims(*widths)
     tgnn, ctx, p32, params = make(d)
