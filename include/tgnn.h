@@ -40,7 +40,7 @@ extern "C" {
 #define TGNN_E_HIP (-8)
 
 #define TGNN_FLAG_OVERWRITE_GRADS 1 /* tgnn_train_step clears `grads` first instead of adding to them */
-#define TGNN_FLAG_NO_GRAPH 4        /* tgnn_train_step enqueues its launches (16 on the main path) one by one; by default it records
+#define TGNN_FLAG_NO_GRAPH 4        /* tgnn_train_step enqueues its launches (11 on the main path) one by one; by default it records
                                        them once per call signature (same pointers, batch sizes, lr, stream) into a
                                        HIP graph and replays that with one launch, updating only the batch
                                        descriptors.  Not used on the NULL (legacy default) stream, while the caller's stream is itself being captured
@@ -340,9 +340,9 @@ int32_t tgnn_zero_params(tgnn_ctx* ctx, tgnn_params* g, void* stream);
  *  10 attention forward: gathers the slots' edge features, time encoding, scores, softmax, weighted sums (with the fill
  *    pass of the slot sort)
  *  12 root chain: attention output = node part + Zp (W_v^c)^T, merge layer, decoder + loss, their backward pass down to
- *    the gradient dO of the attention output, and G = dO W_v^c per root, one launch (d_mem a multiple of 4 and <= 128;
- *    otherwise 7 attention output, 11 merge layer, 12 decoder forward + loss, 13 decoder backward, the attention-output
- *    gradient GEMM, 19 G)
+ *    the gradient dO of the attention output, and G = dO W_v^c per root, one launch (d_mem a multiple of 4 and <= 128; with
+ *    long rows of weighted sums 7 attention output and 19 G by themselves; otherwise 7 attention output, 11 merge layer,
+ *    12 decoder forward + loss, 13 decoder backward, the attention-output gradient GEMM, 19 G)
  *  14 attention backward   5 dq = node part + Zs (W_k^c)^T (MFMA)
  *  15 per-node gradient sums (with the gradients through the query's Phi(0)) + node projections backward with GRU
  *    gates backward

@@ -301,7 +301,8 @@ void class_scores(const Dims& d, const BatchSet* bs, int total, const float* Pde
 // is taken as in dec_pair_kernel (a lane's columns, then the exchange over the wavefront).  600 events with 49 negatives:
 // 67 us in dec_pair_kernel (which also wrote the backward pass's rows) and 14 us for the ranks (a thread per event), now
 // 15 us together.
-constexpr int RK_U = 7;   // 13 pairs of a wavefront (49 negatives) in two rounds
+constexpr int RK_U = 7;   // pairs per round, 28 loads in flight: the 12 or 13 pairs that four wavefronts have each of 49 negatives (the
+                          // usual number) are two rounds; a round that is not full repeats the last pair
 __global__ __launch_bounds__(256) void pair_rank_kernel(const BatchSet* __restrict__ bsp, int dO, const float* __restrict__ Pdec,
                                                         int ldp, const float* __restrict__ b1, const float* __restrict__ w2,
                                                         const float* __restrict__ b2, float* __restrict__ logits,

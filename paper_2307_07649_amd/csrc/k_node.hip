@@ -62,7 +62,9 @@ struct NodeSplit {
 __device__ __forceinline__ int node_tiles(int n, int rb) { return rb == 1 ? (n + 15) / 16 : rb == 2 ? (n + 31) / 32 : rb == 3 ? (n + 47) / 48 : (n + 63) / 64; }
 // Update: the splits from the least time per workgroup to the most; the first whose tiles all run at once is taken (a
 // workgroup streams its part of the weights, 13 us / groups, and has 5 us of MFMAs per row block and group, of which the
-// longer counts, and 3 us of gathering per row block).  Beyond 12,288 rows the tallest tiles run in rounds.
+// longer counts, and 3 us of gathering per row block; figures of d_m = d_t = 100, d_e = 186: wider inputs and memories raise
+// the first two alike, so that the order holds, and narrow ones are bound by the gathering, where the splits hardly differ).
+// Beyond ND_GRID tallest tiles (12,096 rows with three row blocks) these run in rounds.
 // (Spelled out: a table of the splits ends up in memory, at a cold load per entry.)
 #define TGNN_ND_SPLIT(RB, G, GRID) \
   if (RB <= rb_max && G <= g_max && node_tiles(n, RB) * G <= GRID) return NodeSplit{RB, G};

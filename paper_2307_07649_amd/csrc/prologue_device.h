@@ -14,7 +14,10 @@ __device__ __forceinline__ size_t split_place(int n, int k, int ks, int groups, 
 }
 
 // The composite weights of the score vectors (see PrologueArgs::Wu_s), on nbx * PRO_COMP blocks.  A wavefront takes 64
-// consecutive columns c of one head (its loads of W_k are coalesced) and four columns j of x.
+// consecutive columns c of one head (its loads of W_k are coalesced) and four columns j of x.  The head's rows of W_k come
+// in runs of 25, all loads of a run at once: a whole number of runs for the widths in most use (heads of 25, 50 and 100), and few
+// enough registers for the sampler's blocks of the same launch; other widths repeat the head's last row up to the end of a
+// run (heads of 32: 18 idle loads in 50, of 64: 11 in 75).
 constexpr int PRO_COMP = 4;   // grid rows
 __device__ __forceinline__ void prologue_composite(const PrologueArgs& a, int block, int blocks) {
   const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6;

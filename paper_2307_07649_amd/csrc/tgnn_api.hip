@@ -1111,9 +1111,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     NodeArgs na = node_args(ctx, p, U, w.ucount);
     na.gid = w.ulist; na.row_eid = w.row_eid; na.delta = w.delta; na.mem = st->mem; na.mail = st->mail; na.efeat = g->efeat;
     na.stat = st->stat;
-    if (!eval) {
-      na.X = w.X; na.Hm = w.Hm; na.gates = w.gates; na.dP = w.dP;
-    }
+    na.X = w.X; na.Hm = w.Hm; na.gates = w.gates; na.dP = w.dP;
     na.scan = sort;
     na.epoch_bump = w.epoch;   // the first launch worked with epoch + 1; from here on that is the epoch
     tm.begin(3);

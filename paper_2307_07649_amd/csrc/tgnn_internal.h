@@ -652,7 +652,7 @@ struct NodeArgs {
   int cb, kx, kh, kp;        // column blocks of the memory width; k slabs
   int rb_max;                // row blocks per tile at most
   int unit_blocks;           // blocks of the update launch before its passengers (set by node_update)
-  SortArgs scan;             // scan.gcnt != NULL: block 0 runs the scan of the slot sort instead
+  SortArgs scan;             // scan.gcnt != NULL: the update's last passenger block runs the scan of the slot sort
   unsigned long long* epoch_bump;   // may be NULL: *epoch_bump += 1
 };
 void node_dims(Dims& d);     // fills nd_*
