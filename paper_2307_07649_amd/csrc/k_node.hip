@@ -17,11 +17,11 @@
 //          launch waits for another.
 //
 // Measured (MI355X, kernel trace, launch to launch): five launches 37 us for 1,284 rows and 140 us for 11,377 rows
-// (d_m = d_t = 100, d_e = 172 / 186); these two 29 and 84 us.
+// (d_m = d_t = 100, d_e = 172 / 186); these two 27 and 84 us.
 //
-// What bounds them: a compute unit draws at most 30 to 42 bytes per cycle of weights from the L2 (measured; 64 is its
-// port), so one workgroup that streams all GRU weights (1.26 MB split, d_m = d_t = 100, d_e = 186) takes 13 us however
-// few rows it has.  Few rows are therefore spread over all compute units by columns, and many rows are taken in tiles as
+// What bounds them: a workgroup that does nothing else draws 50 bytes per cycle from the L2 when every compute unit does (63
+// with 32 of them; measured on 0.6 and 1.26 MB that all read over and over), this one beside its gathering and MFMAs 40, so
+// one that streams all GRU weights (1.26 MB split, d_m = d_t = 100, d_e = 186) takes 11 to 13 us however few rows it has.  Few rows are therefore spread over all compute units by columns, and many rows are taken in tiles as
 // tall as LDS allows, where the MFMAs (5 us per 16 rows) hide the stream.
 #include <algorithm>
 
@@ -603,9 +603,16 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
     const bool is_u = 2 * pr >= p_blk;
     float* out = is_u ? a.U + (2 * pr - p_blk) * 16 + 4 * lg : a.P + 2 * pr * 16 + 4 * lg;
     const int ld = is_u ? a.ldz : a.ldp;
+    // Every column once and every row once.  (With 64-row tiles after the stores: 45.0 against 46.6 us on 20,000 rows, 43.9 without;
+    // with fewer between them: 8.7 against 9.7 us on 1,284.)
+    auto look = [&](int m) __attribute__((always_inline)) {
+      const floatx4 t = acc[m][0] + acc[m][1];
+      seen += m == 0 ? t[0] + t[1] + t[2] + t[3] : acc[m][0][0];
+    };
 #pragma unroll
     for (int m = 0; m < RB; ++m) {
       const int row = row0 + m * 16 + li;
+      if (RB < 4) look(m);
       if (row < n) {
         float* o = out + (size_t)row * ld;
         *reinterpret_cast<floatx4*>(o) = acc[m][0];
@@ -617,12 +624,9 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
         }
       }
     }
-    // every column once and every row once (after the stores: 45.0 against 46.6 us on 20,000 rows, 43.9 without)
-    const floatx4 t = acc[0][0] + acc[0][1];
-    float u = t[0] + t[1] + t[2] + t[3];
+    if (RB == 4)
 #pragma unroll
-    for (int m = 1; m < RB; ++m) u += acc[m][0][0];
-    seen += u;
+      for (int m = 0; m < RB; ++m) look(m);
   };
   int pr = first;
   for (; pr + stride < pairs; pr += stride) pair(pr, true);
