@@ -861,7 +861,7 @@ __global__ __launch_bounds__(256) void fattn_bwd_gen_kernel(FusedAttn a) {
 // of four: their columns are formed once for all heads (the generic path forms them per slot and head, one load and one
 // exchange over the wavefront at a time) and once more for the weighted sums, loads and sums of a group are in flight
 // together, four sums share their exchanges.  Every sum has the same terms in the same order as in the generic path.
-// 17 neighbours, 3 heads, 83 columns, 999 roots: forward and backward 28 and 32 us, the whole step 268 -> 171 us.  Bound by
+// 17 neighbours, 3 heads, 83 columns, 999 roots: forward and backward 25 and 28 us, the whole step 268 -> 157 us.  Bound by
 // the vector ALUs (sines and cosines twice per slot) and, with few roots, by the chain of a wavefront.
 // A kernel holds M rounds of 64 columns: with one kernel of five rounds for all widths, up to 64 columns paid for five (151
 // and 189 registers, three and two wavefronts per SIMD) and took longer than the generic path from 700 events on.  4,000
