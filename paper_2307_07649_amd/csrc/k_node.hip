@@ -203,6 +203,16 @@ __device__ __forceinline__ void node_keep(NodeKept& kept) {
   if (threadIdx.x == 0) kept = NodeKept{(unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), (int)blockIdx.x, (int)gridDim.x};
 }
 
+// Is one of n numbers NaN?  (Then all that comes of them is, in fp32, too.)
+__device__ __forceinline__ bool node_has_nan(const float* x, int n) {
+  for (int i = 0; i < n; i += 8) {   // (eight loads at a time)
+    bool nan = false;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) nan |= x[min(i + u, n - 1)] != x[min(i + u, n - 1)];
+    if (nan) return true;
+  }
+  return false;
+}
 // The four sums of column c of s' of node row `row`: r, z, n from the memory, n from the input (without the biases).
 __device__ __forceinline__ floatx4 node_update_plain(const NodeKernArgs& a, int row, int c, int g, int e) {
   const int dm = a.dm, c0 = 2 * dm + a.dt;
@@ -229,7 +239,9 @@ __device__ __forceinline__ floatx4 node_update_plain(const NodeKernArgs& a, int 
 __device__ __forceinline__ void node_update_columns(const NodeKernArgs& a, int row, int col, int live) {
   const int g = a.gid != nullptr ? a.gid[row] : row;
   const int e = a.gid != nullptr ? a.row_eid[row] : a.has_in[row] ? row : -1;
-  if (e < 0) return;
+  if (e < 0 || node_has_nan(a.mem + (size_t)g * a.dm, a.dm) || node_has_nan(a.mail + (size_t)g * 2 * a.dm, 2 * a.dm) ||
+      node_has_nan(a.efeat + (size_t)e * a.de, a.de))
+    return;
 #pragma unroll 1
   for (int c = col; c < col + min(live, 4); ++c) {
     float* out = a.Xrow + (size_t)row * a.ldxr + c;
@@ -307,6 +319,8 @@ __device__ __forceinline__ void node_project_again(const NodeKept& kept, int rb_
     for (int i = 0; i < rb * 8; ++i) {   // row blocks, and the lane's eight columns of a pair of column blocks
       const int row = (tile * rb + (i >> 3)) * 16 + (lane & 15);
       if (row >= n) break;
+      const float* x = node_x_row(a, row);
+      if (x != nullptr && node_has_nan(x, a.dx)) continue;
 #pragma unroll 1
       for (int pr = u - tile * groups + wave * groups; pr < pairs; pr += groups * NP_W) {
         const int col = pr * 32 + ((i >> 2) & 1) * 16 + 4 * (lane >> 4) + (i & 3);
