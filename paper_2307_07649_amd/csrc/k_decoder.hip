@@ -191,7 +191,11 @@ __global__ __launch_bounds__(256) void dec_class_kernel(const BatchSet* __restri
       const floatx4 a4 = *reinterpret_cast<const floatx4*>(&H[li * DC_HP + 16 * s + 4 * lg]);
       float w[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) w[c] = wr[min(16 * s + 4 * lg + c, dO - 1)];   // (columns past d_o meet zeros of H)
+      for (int c = 0; c < 4; ++c) {   // (columns past d_o: zeros on both sides, so that an infinite weight stays where it is)
+        const int k = 16 * s + 4 * lg + c;
+        const float x = wr[min(k, dO - 1)];
+        w[c] = k < dO ? x : 0.f;
+      }
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[c], w[c], acc, 0, 0, 0);
     }
@@ -226,7 +230,11 @@ __global__ __launch_bounds__(256) void dec_class_kernel(const BatchSet* __restri
       const floatx4 a4 = *reinterpret_cast<const floatx4*>(&L[li * DC_LP + 16 * s + 4 * lg]);
       float w[4];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) w[c] = w2[(size_t)min(16 * s + 4 * lg + c, C - 1) * dO + colc];   // (classes past C meet zeros)
+      for (int c = 0; c < 4; ++c) {   // (classes past C likewise)
+        const int k = 16 * s + 4 * lg + c;
+        const float x = w2[(size_t)min(k, C - 1) * dO + colc];
+        w[c] = k < C ? x : 0.f;
+      }
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[c], w[c], acc, 0, 0, 0);
     }

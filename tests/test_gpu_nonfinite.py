@@ -1,4 +1,4 @@
-"""Infinite, NaN and very large operands in the products on split bf16 operands.  In fp32 an infinite pre-activation takes its
+"""Infinite, NaN and very large operands in the products on split bf16 operands, and infinite weights in padded ones.  In fp32 an infinite pre-activation takes its
 gate to the limit and a product with an infinite factor is infinite; a number above 3.38e38 is finite, though it rounds to
 infinity in bf16.  The kernels give what fp32 arithmetic gives, in these rows and in the ones beside them."""
 import numpy as np
@@ -137,3 +137,25 @@ def test_training_step_with_an_infinite_mail():
         if n == "gru_wih":
             a, r = np.delete(a, (5, 50), axis=1), np.delete(r, (5, 50), axis=1)
         same(a, r, 1e-4)
+
+
+# the classification head pads its products to 64 columns and classes: the last column's and the last class's weights infinite
+@pytest.mark.parametrize("d_mem,classes", [(20, 5), (64, 56), (100, 64)])
+def test_infinite_output_weights_of_the_classification_head(d_mem, classes):
+    P = synth.custom_problem(n_nodes=40, E=120, d_mem=d_mem, d_time=8, d_edge=4, d_static=0, n_heads=2, k=3, batch=40,
+                             n_classes=classes, n_true=1, seed=classes)
+    P["params"]["dec_w2"] = P["params"]["dec_w2"].copy()
+    P["params"]["dec_w2"][classes - 1, d_mem - 1] = INF
+    P["params"]["dec_b1"] = P["params"]["dec_b1"].copy()
+    P["params"]["dec_b1"][-1] = 5.0                      # (the unit that meets the infinite weight is on)
+    G = GpuSide(P)
+    g = G.step([batch_np(P, 0, 40)], lr=0.0)
+    h = g["h1"].astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = h @ np.where(np.isinf(P["params"]["dec_w2"]), 0, P["params"]["dec_w2"]).astype(np.float64).T + P["params"]["dec_b2"]
+        ref[:, -1] += h[:, -1] * INF
+    assert (h[:, -1] > 0).all()
+    same(g["logits"], ref, 1e-5)
+    # d loss / d hidden: a sum over the classes with one infinite term, in the last hidden unit only
+    gb = g["grads"]["dec_b1"]
+    assert np.isfinite(gb[:-1]).all() and not np.isfinite(gb[-1])
