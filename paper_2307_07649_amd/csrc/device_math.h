@@ -36,6 +36,11 @@ __device__ __forceinline__ float time_enc(double delta, float w, float b) {
   return c;
 }
 
+// x plus what the DPP control `CTRL` brings in from another lane of the row of 16
+template <int CTRL> __device__ __forceinline__ float dpp_add(float x) {
+  return x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+
 // One wavefront copies n floats (dst, src aligned to VEC floats, n % VEC == 0) and appends nz zeros.
 template <int VEC>
 __device__ __forceinline__ void wave_copy(float* __restrict__ dst, const float* __restrict__ src, int n, int nz,

@@ -199,9 +199,6 @@ __device__ __forceinline__ void zero_head_rows(const FusedAttn& a, float* row, i
 // n = KR hh + j: register n % 5 of the result, lanes 16 (n / 5) ..
 static_assert(FA_KR == 10 && FA_HM == 2, "laid out for twenty sums");
 constexpr int FA_SR = 5;
-template <int CTRL> __device__ __forceinline__ float dpp_add(float x) {
-  return x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));
-}
 __device__ __forceinline__ void sum_scores(const float (&part)[FA_KR][FA_HM], float (&sum)[FA_SR]) {
   float half[2 * FA_SR];
 #pragma unroll

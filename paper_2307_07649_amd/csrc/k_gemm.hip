@@ -389,6 +389,273 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (TN <= 5
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// NT for few rows, the same sums in the same order.  With a few thousand rows the kernel above is a chain of latencies: it
+// waits for two stages of 32 columns at a time, 0.4 us each whatever the tile, thirteen of them for the widest product of a
+// 600-event step.  Here a wavefront's rows of A are its own: it asks for a chunk of four stages at once and for the next one as
+// it goes, and changes their order to the MFMAs' in 2 KB of LDS that no other wavefront touches (the LDS takes a
+// wavefront's accesses in order), so that the only barrier is one per chunk, for the rows of B, which the four wavefronts
+// share.  B is the first MFMA operand: a lane ends up with four consecutive columns of one row (column n0 + 4 lg, row m0 + 16
+// wave + li), and what its epilogue needs is asked for before the last chunk, 16 bytes at a time.
+// Launches of a 600-event step: 8.2, 10.3 and 8.9 -> 7.0 to 7.9 us.  Tried: operands from memory in the MFMAs' order without LDS
+// (four neighbouring lanes ask for pieces of four rows, the L1 takes four times as long: 10.9 us); every wavefront its own rows of
+// B (8.0); four parts of the k range on sixteen wavefronts (9.0: four times the loads of B).  On many rows the kernel above is
+// faster, with 30,600 by 15 %: this one's registers leave three wavefronts per SIMD on tiles of 32 columns.
+// ------------------------------------------------------------------------------------------------
+constexpr int NT_CHUNK = 4;   // stages of 32 columns per chunk
+
+__device__ __forceinline__ bool aligned4(const void* p, int ld) { return ((reinterpret_cast<size_t>(p) & 15) | (ld & 3)) == 0; }
+// four consecutive floats of which `live` exist (the others read as zero)
+__device__ __forceinline__ floatx4 load4(const float* p, int live, bool vec) {
+  floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+  if (live >= 4 && vec) v = *reinterpret_cast<const floatx4*>(p);
+  else
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < live) v[e] = p[e];
+  return v;
+}
+__device__ __forceinline__ void store4(float* p, const floatx4& v, int live, bool vec) {
+  if (live >= 4 && vec) *reinterpret_cast<floatx4*>(p) = v;
+  else
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (e < live) p[e] = v[e];
+}
+// the sum over the 16 lanes of a row, in all of them
+__device__ __forceinline__ float row_sum(float x) {
+  x = dpp_add<0x128>(x);   // row_ror:8, 4, 2, 1
+  x = dpp_add<0x124>(x);
+  x = dpp_add<0x122>(x);
+  return dpp_add<0x121>(x);
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_few_kernel(NtGroup grp) {
+  constexpr int D = NT_CHUNK, KC = 32 * NT_CHUNK;
+  if ((int)blockIdx.x >= grp.gemm_wgs) {   // passengers, as above
+    wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
+    return;
+  }
+  typedef const NtGroup __attribute__((address_space(4))) * GroupPtr;
+  const GroupPtr gp = (GroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
+  const auto& q = gp->p[pi];
+  const int N = q.N, n_store = q.n_store, col_tiles = q.col_tiles;
+  int M = q.M;
+  const int* m_dev = q.m_dev;
+  const float* __restrict__ A = q.A;
+  const float* __restrict__ B = q.B;
+  const int block = (int)blockIdx.x - q.wg_begin, xcd = block & 7, slot = block >> 3;
+  const int row_tile = (slot / col_tiles) * 8 + xcd, col_tile = slot % col_tiles;
+  if (m_dev != nullptr) M = min(M, load_count(m_dev));
+  if (row_tile * NT_BM >= M) return;   // uniform for the workgroup, before any barrier
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lg = lane >> 4;
+  const int n0 = col_tile * 16, col = n0 + 4 * lg;   // this lane's columns col .. col + 3 ...
+  const int row = row_tile * NT_BM + wave * 16 + li, rowc = min(row, M - 1);   // ... of this row; clamped: what comes of it is dropped
+  const bool row_live = row < M;
+
+  // the stages of 32 columns of this column tile: all of them, or with a block-diagonal B those its blocks reach into
+  int k_lo = 0, k_end = q.k_live > 0 ? q.k_live : q.Kp;
+  if (q.bd_n > 0) {
+    const int h_lo = min(n0, N - 1) / q.bd_n, h_hi = (min(n0 + 16, N) - 1) / q.bd_n;
+    k_lo = (h_lo * q.bd_k) & ~31;
+    k_end = min(k_end, (h_hi + 1) * q.bd_k);
+    if (k_end <= k_lo) k_lo = max(k_end - 1, 0) & ~31;   // (live columns end before the tile's blocks begin: one stage of zeros)
+  }
+  const int slabs = max((k_end - k_lo + 15) >> 4, 1), stages = (slabs + 1) >> 1;   // (an odd last slab: the stage's second one is left out)
+  // A: eight lanes load a row's 128 bytes, a cache line; piece c of row r lies at place c ^ (r >> 1) in LDS: sixteen lanes that
+  // read one piece of sixteen rows, or eight pieces of two, cover all banks
+  const int lr = lane >> 3, lc = lane & 7;
+  const float* pa[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) pa[h] = A + (size_t)min(row_tile * NT_BM + wave * 16 + 8 * h + lr, M - 1) * q.lda + k_lo + 4 * lc;
+  // B: 32 lanes load a row's 512 bytes; piece c of row r lies at place c ^ (r mod 16)
+  const int br = tid >> 5, bc = tid & 31;
+  const float* pb[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) pb[u] = B + (size_t)min(n0 + 8 * u + br, N - 1) * q.ldb;
+  __shared__ __attribute__((aligned(16))) float turn[4][512], Bs[2][16 * KC];
+  float* const mine = turn[wave];
+
+  floatx4 ra[D][2], rb[2], acc = floatx4{0.f, 0.f, 0.f, 0.f};
+  struct Ops {
+    floatx4 a, b;
+  } ops[2];
+  // (The loads are waited for by count, a chunk after they are issued: no branches around them and one order of issue
+  // before and in the loop.  Past the last stage they bring it in again, unused.)
+  auto load_a = [&](int d, int s) __attribute__((always_inline)) {
+    const int off = 32 * min(s, stages - 1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) ra[d][h] = *reinterpret_cast<const floatx4*>(pa[h] + off);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto load_b = [&](int s) __attribute__((always_inline)) {   // the chunk that begins with stage s
+    const int k = min(k_lo + 32 * s + 4 * bc, q.Kp - 4);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) rb[u] = *reinterpret_cast<const floatx4*>(pb[u] + k);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto put_b = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = 8 * u + br;
+      *reinterpret_cast<floatx4*>(&Bs[buf][r * KC + 4 * (bc ^ r)]) = rb[u];
+    }
+  };
+  auto put = [&](int d) __attribute__((always_inline)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int r = 8 * h + lr;
+      *reinterpret_cast<floatx4*>(mine + r * 32 + 4 * (lc ^ (r >> 1))) = ra[d][h];
+    }
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto get = [&](Ops& o, int buf, int d, int h) __attribute__((always_inline)) {   // slab h of stage d, whose rows of A are in LDS
+    o.a = *reinterpret_cast<const floatx4*>(mine + li * 32 + 4 * ((4 * h + lg) ^ (li >> 1)));
+    o.b = *reinterpret_cast<const floatx4*>(&Bs[buf][li * KC + 4 * ((8 * d + 4 * h + lg) ^ li)]);
+    __builtin_amdgcn_sched_barrier(0);   // (the products of the slab before follow: they cover the way through LDS)
+  };
+  auto mma = [&](const Ops& o) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(o.b[c], o.a[c], acc, 0, 0, 0);
+  };
+  load_b(0);
+#pragma unroll
+  for (int d = 0; d < D; ++d) load_a(d, d);
+  // What the epilogue's own loads depend on.  (Asked for whether it is needed or not, from any readable address then: a
+  // branch here, or a comparison, would wait for everything above.)
+  const float* const add_src = q.add.src;
+  const int* const add_index = q.add.index;
+  const int* const gru_has = q.gb.has;
+  const double* const tg_delta = q.tg.delta;
+  const bool gru = q.gb.dgi != nullptr, tgrad = q.tg.g_w != nullptr;
+  const int index_raw = (add_index != nullptr ? add_index : reinterpret_cast<const int*>(A))[add_index != nullptr ? rowc : 0];
+  const int has_raw = (gru ? gru_has : reinterpret_cast<const int*>(A))[gru ? rowc : 0];
+  const double delta = (tgrad ? tg_delta : reinterpret_cast<const double*>(A))[tgrad ? rowc : 0];
+  put_b(0);
+  put(0);
+  __syncthreads();
+  int s0 = 0, buf = 0;
+  for (; s0 + D < stages; s0 += D) {
+    load_b(s0 + D);
+    get(ops[0], buf, 0, 0);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {   // stage s0 + d; the next slab, or stage, changes its order beside each slab's products
+      load_a(d, s0 + d + D);
+      get(ops[1], buf, d, 1);
+      mma(ops[0]);
+      put((d + 1) % D);
+      if (d + 1 < D) get(ops[0], buf, d + 1, 0);
+      else put_b(buf ^ 1);
+      mma(ops[1]);
+    }
+    buf ^= 1;
+    __syncthreads();   // (the buffer that is written next was read before the barrier before)
+  }
+  // what the epilogue needs, on its way beside the last chunk
+  const int arow = add_src == nullptr ? -1 : add_index != nullptr ? index_raw : rowc + q.add.row0, live = N - col;
+  const float* const gate = q.add.gate;
+  floatx4 e0 = floatx4{0.f, 0.f, 0.f, 0.f}, e1 = e0, e2 = e0, e3 = e0, e4 = e0;
+  if (gru) {   // r, z, n, W_hn h + b_hn, h (rows of 16-byte aligned pitch, padded to 32 columns)
+    const int ldh = q.gb.ldh, c = min(col, ldh - 4);
+    const float* g = q.gb.gates + (size_t)rowc * 4 * ldh + c;
+    e0 = *reinterpret_cast<const floatx4*>(g); e1 = *reinterpret_cast<const floatx4*>(g + ldh);
+    e2 = *reinterpret_cast<const floatx4*>(g + 2 * ldh); e3 = *reinterpret_cast<const floatx4*>(g + 3 * ldh);
+    e4 = *reinterpret_cast<const floatx4*>(q.gb.Hm + (size_t)rowc * ldh + c);
+  } else if (!tgrad) {
+    if (q.bias != nullptr) e0 = load4(q.bias + col, live, aligned4(q.bias, 0));
+    if (arow >= 0) e1 = load4(add_src + (size_t)arow * q.add.ld + col, live, aligned4(add_src, q.add.ld));
+    if (gate != nullptr) e2 = load4(gate + (size_t)rowc * q.add.ld_gate + col, live, aligned4(gate, q.add.ld_gate));
+  }
+  get(ops[0], buf, 0, 0);
+#pragma unroll
+  for (int d = 0; d < D; ++d)
+    if (s0 + d < stages) {
+      get(ops[1], buf, d, 1);
+      mma(ops[0]);
+      if (d + 1 < D) {
+        put(d + 1);
+        get(ops[0], buf, d + 1, 0);
+      }
+      if (2 * (s0 + d) + 1 < slabs) mma(ops[1]);
+    }
+
+  if (tgrad) {
+    // Time-encoding gradient epilogue: the tile is not stored.  Each lane multiplies its row's columns by
+    // -sin(w_col delta + b_col) (the argument formed exactly as in the forward kernels); sums over the 16 rows of a
+    // wavefront (row rotations) and the four wavefronts (LDS).
+    __syncthreads();   // all wavefronts have read their last rows of A
+    float (*const red)[4][16] = reinterpret_cast<float (*)[4][16]>(&turn[0][0]);
+    floatx4 sw = floatx4{0.f, 0.f, 0.f, 0.f}, sb = sw;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (v < live && row_live) {
+        float sn, cs;
+        sincos_reduced(fma((double)q.tg.w[col + v], delta, (double)q.tg.b[col + v]), sn, cs);
+        sb[v] = -acc[v] * sn;
+        sw[v] = sb[v] * (float)delta;
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) { sw[v] = row_sum(sw[v]); sb[v] = row_sum(sb[v]); }
+    if (li == 0) {
+      *reinterpret_cast<floatx4*>(&red[0][wave][4 * lg]) = sw;
+      *reinterpret_cast<floatx4*>(&red[1][wave][4 * lg]) = sb;
+    }
+    __syncthreads();
+    if (tid < 32) {
+      const int which = tid >> 4, c = tid & 15;
+      if (n0 + c < N)
+        atomicAdd((which ? q.tg.g_b : q.tg.g_w) + n0 + c, red[which][0][c] + red[which][1][c] + red[which][2][c] + red[which][3][c]);
+    }
+    return;
+  }
+  if (gru) {   // GRU gates backward epilogue: acc is the gradient reaching s' = (1 - z) n + z h
+    if (!row_live) return;
+    const int dm = q.gb.dm;
+    const bool vec = (dm & 3) == 0, has = has_raw != 0;
+    float* const gi = q.gb.dgi + (size_t)row * q.gb.ld3 + col;
+    float* const gh = q.gb.dgh + (size_t)row * q.gb.ld3 + col;
+    floatx4 drp, dzp, dnp, dnr;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float ds = acc[v], r = e0[v], z = e1[v], nn = e2[v], hn = e3[v], h = e4[v];
+      const float dn = ds * (1.0f - z);
+      const float dz = ds * (h - nn);
+      const float dp = dn * (1.0f - nn * nn);
+      const float dr = dp * hn;
+      dnp[v] = has ? dp : 0.f;
+      dzp[v] = has ? dz * z * (1.0f - z) : 0.f;
+      drp[v] = has ? dr * r * (1.0f - r) : 0.f;
+      dnr[v] = has ? dp * r : 0.f;
+    }
+    store4(gi, drp, live, vec); store4(gi + dm, dzp, live, vec); store4(gi + 2 * dm, dnp, live, vec);
+    store4(gh, drp, live, vec); store4(gh + dm, dzp, live, vec); store4(gh + 2 * dm, dnr, live, vec);
+    return;
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const float x = acc[v] + e0[v] + e1[v];
+    const bool on = v < live && row_live && (gate == nullptr || e2[v] > 0.f);
+    acc[v] = on ? (q.relu ? fmaxf(x, 0.f) : x) : 0.f;
+  }
+  if (q.colsum != nullptr) {   // column sums of the tile: the wavefront's 16 rows, then one atomic per wavefront and column
+    float* cs = q.colsum + (size_t)((row_tile * 4 + wave) & (q.colsum_rows - 1)) * N;
+    float sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float t = row_sum(acc[v]);
+      sum = li == v ? t : sum;
+    }
+    if (li < 4 && li < live) atomicAdd(cs + col + li, sum);
+  }
+  if (row_live) store4(q.C + (size_t)row * q.ldc + col, acc, n_store - col, aligned4(q.C, q.ldc));
+}
+
 // Column-tile width in 16-wide MFMA blocks, from sweeps on MI355X: problems of a few thousand rows want the
 // narrowest tiles (many short workgroups, all resident at once), tens of thousands of rows want 2 blocks,
 // and only beyond that do wider tiles (less re-reading of A) pay off.
@@ -424,14 +691,13 @@ void gemm_nt_group(const NtProblem* probs, int n, hipStream_t s, const WbArgs* t
     NtProblem p = probs[i];
     if (p.M <= 0 || p.N <= 0) continue;
     if (p.n_store < p.N) p.n_store = p.N;
-    if (tn == 0) tn = nt_tile_blocks(p.M, p.n_store);   // the first problem decides the tile width
+    if (tn == 0) tn = nt_tile_blocks(p.rows_est > 0 ? std::min(p.rows_est, p.M) : p.M, p.n_store);   // the first problem decides the tile width
     p.col_tiles = (p.n_store + 16 * tn - 1) / (16 * tn);
     p.wg_begin = total;
     total += p.col_tiles * (((p.M + NT_BM - 1) / NT_BM + 7) & ~7);
     g.p[g.n++] = p;
   }
   if (g.n == 0 && tail_blocks == 0) return;
-  if (tn == 0) tn = 1;
   g.gemm_wgs = total;
   total += tail_blocks;
 #define TGNN_NT_CASE(TNV) \
@@ -441,16 +707,14 @@ void gemm_nt_group(const NtProblem* probs, int n, hipStream_t s, const WbArgs* t
     TGNN_NT_CASE(5)
     TGNN_NT_CASE(4)
     TGNN_NT_CASE(2)
-    default:
-    TGNN_NT_CASE(1)
+    default: hipLaunchKernelGGL(gemm_nt_few_kernel, dim3(total), dim3(256), 0, s, g);
   }
 #undef TGNN_NT_CASE
 }
 
 void gemm_nt(const float* A, int lda, const float* B, int ldb, const float* bias, float* C, int ldc, int M, int N,
-             int Kp, int n_store, bool relu, hipStream_t s, const int* m_dev, const RowAdd& add, const TimeGradOut& tg,
-             const GruBwdOut& gb) {
-  const NtProblem p = nt_problem(A, lda, B, ldb, bias, C, ldc, M, N, Kp, n_store, relu, m_dev, add, tg, gb);
+             int Kp, int n_store, bool relu, hipStream_t s, const RowAdd& add) {
+  const NtProblem p = nt_problem(A, lda, B, ldb, bias, C, ldc, M, N, Kp, n_store, relu, nullptr, add);
   gemm_nt_group(&p, 1, s);
 }
 

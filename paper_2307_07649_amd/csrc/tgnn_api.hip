@@ -281,7 +281,7 @@ static void attn_forward(tgnn_ctx* ctx, const tgnn_params* p, int R, int n_rows,
   if (tm) tm->begin(11);
   RowAdd m_add;
   m_add.src = w.P + d.ldkv + d.dO; m_add.ld = d.ldp; m_add.index = in.slot_row; m_add.row0 = 0;
-  gemm_nt(w.Omat, d.ldh, w.Wo_o, d.ldh, nullptr, w.z, d.ldh, R, d.dO, d.ldh, d.ldh, true, s, nullptr, m_add);
+  gemm_nt(w.Omat, d.ldh, w.Wo_o, d.ldh, nullptr, w.z, d.ldh, R, d.dO, d.ldh, d.ldh, true, s, m_add);
   if (tm) tm->end(11);
 }
 
@@ -362,13 +362,14 @@ static void node_proj_backward(tgnn_ctx* ctx, tgnn_params* g, int n_rows, const 
     gb.gates = w.gates; gb.Hm = w.Hm; gb.has = w.has; gb.dgi = w.dgi; gb.dgh = w.dgh;
     gb.dm = d.dm; gb.ldh = d.ldh; gb.ld3 = d.ld3;
   }
-  const NtProblem mine = nt_live(nt_problem(w.dP, d.ldp, w.WxT, d.ldp, nullptr, w.ds_row, d.ldh, n_rows, d.dm, d.ldp, d.ldh,
-                                            false, n_rows_dev, RowAdd(), TimeGradOut(), gb), d.ldkv + 2 * d.dO);
+  const int rows_est = n_rows_dev != nullptr ? tn.dev_rows_est : 0;
+  const NtProblem mine = nt_rows(nt_live(nt_problem(w.dP, d.ldp, w.WxT, d.ldp, nullptr, w.ds_row, d.ldh, n_rows, d.dm, d.ldp, d.ldh,
+                                                    false, n_rows_dev, RowAdd(), TimeGradOut(), gb), d.ldkv + 2 * d.dO), rows_est);
   if (ctx->train_static && through_gru && d.ds > 0) {
     // co-trained static memory (Sec. 3.1): the same product for the static columns of the node rows, stored per row;
     // the rows are scattered to the table by the step's last launch
-    const NtProblem stat = nt_live(nt_problem(w.dP, d.ldp, w.WxT + (size_t)d.dm * d.ldp, d.ldp, nullptr, w.dstat, d.ldst, n_rows,
-                                              d.ds, d.ldp, d.ldst, false, n_rows_dev), d.ldkv + 2 * d.dO);
+    const NtProblem stat = nt_rows(nt_live(nt_problem(w.dP, d.ldp, w.WxT + (size_t)d.dm * d.ldp, d.ldp, nullptr, w.dstat, d.ldst, n_rows,
+                                                      d.ds, d.ldp, d.ldst, false, n_rows_dev), d.ldkv + 2 * d.dO), rows_est);
     const NtProblem pr[2] = {mine, stat};
     gemm_nt_group(pr, 2, s);
   } else {
@@ -1141,10 +1142,10 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
     tm.begin(4);
     {  // W_ih x and W_hh h are independent: one launch
       const NtProblem pr[2] = {
-          nt_live(nt_problem(w.X, d.ldx, w.Wih_p, d.ldx, p->gru_bih, w.gi, d.ld3, U, 3 * d.dm, d.ldx, d.ld3, false, w.ucount),
-                  d.d_in),
-          nt_live(nt_problem(w.Hm, d.ldh, w.Whh_p, d.ldh, p->gru_bhh, w.gh, d.ld3, U, 3 * d.dm, d.ldh, d.ld3, false, w.ucount),
-                  d.dm)};
+          nt_rows(nt_live(nt_problem(w.X, d.ldx, w.Wih_p, d.ldx, p->gru_bih, w.gi, d.ld3, U, 3 * d.dm, d.ldx, d.ld3, false, w.ucount),
+                          d.d_in), U_est),
+          nt_rows(nt_live(nt_problem(w.Hm, d.ldh, w.Whh_p, d.ldh, p->gru_bhh, w.gh, d.ld3, U, 3 * d.dm, d.ldh, d.ld3, false, w.ucount),
+                          d.dm), U_est)};
       gemm_nt_group(pr, 2, s);
     }
     tm.end(4);
@@ -1227,7 +1228,7 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
   if (!chain) {  // dz, gated by the ReLU of the merge layer
     RowAdd gate;
     gate.gate = w.z; gate.ld_gate = d.ldh;
-    gemm_nt(w.dPdec, d.ldkv, w.WdecT, d.ldkv, nullptr, w.dz, d.ldh, R, d.dO, d.ldkv, d.ldh, false, s, nullptr, gate);
+    gemm_nt(w.dPdec, d.ldkv, w.WdecT, d.ldkv, nullptr, w.dz, d.ldh, R, d.dO, d.ldkv, d.ldh, false, s, gate);
     tm.end(13);
   }
   attn_backward(ctx, grads, p, R, ain, tn, side, s, &tm, chain, fused);
@@ -1252,8 +1253,8 @@ static int enqueue_step(tgnn_ctx* ctx, const tgnn_graph* g, tgnn_state* st, cons
      // mails and the SGD update.
     TimeGradOut tg;
     tg.delta = w.delta; tg.w = p->time_w; tg.b = p->time_b; tg.g_w = grads->time_w; tg.g_b = grads->time_b;
-    const NtProblem pr = nt_live(nt_problem(w.dgi, d.ld3, w.WihT_phi, d.ld3, nullptr, nullptr, d.ldt, U, d.dt, d.ld3, d.ldt,
-                                            false, w.ucount, RowAdd(), tg), 3 * d.dm);
+    const NtProblem pr = nt_rows(nt_live(nt_problem(w.dgi, d.ld3, w.WihT_phi, d.ld3, nullptr, nullptr, d.ldt, U, d.dt, d.ld3, d.ldt,
+                                                    false, w.ucount, RowAdd(), tg), 3 * d.dm), U_est);
     WbArgs wb = writeback_args(d, w.bs_dev, bs.total, st, w.winkey, w.epoch, w.Xrow, d.ldxr, w.tau, w.slot_row, nullptr,
                                nullptr, nullptr, nullptr, out_winner, lr != 0.0f ? w.sgd_dev : nullptr, sgd_set.cnt, lr);
     if (ctx->adam && lr != 0.0f) wb.adam = w.adam_dev;

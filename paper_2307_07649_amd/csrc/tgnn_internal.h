@@ -302,9 +302,7 @@ struct GruBwdOut {
   int dm = 0, ldh = 0, ld3 = 0;
 };
 void gemm_nt(const float* A, int lda, const float* B, int ldb, const float* bias, float* C, int ldc, int M,
-             int N, int Kp, int n_store, bool relu, hipStream_t s, const int* m_dev = nullptr,
-             const RowAdd& add = RowAdd(), const TimeGradOut& tg = TimeGradOut(),
-             const GruBwdOut& gb = GruBwdOut());
+             int N, int Kp, int n_store, bool relu, hipStream_t s, const RowAdd& add = RowAdd());
 // The same product as a record, so that two independent ones can share a launch (gemm_nt_group: the tile
 // width is chosen for the first problem; col_tiles and wg_begin are filled in by the launcher).
 struct NtProblem {
@@ -316,6 +314,7 @@ struct NtProblem {
   // [h bd_k, (h + 1) bd_k): a column tile then runs only the k stages its blocks reach into
   int bd_n, bd_k;
   const int* m_dev;
+  int rows_est;   // rows to expect where M is only a bound (0: M)
   int col_tiles, wg_begin;
   RowAdd add;
   TimeGradOut tg;
@@ -337,12 +336,14 @@ inline NtProblem nt_problem(const float* A, int lda, const float* B, int ldb, co
                             const GruBwdOut& gb = GruBwdOut()) {
   NtProblem p;
   p.A = A; p.B = B; p.bias = bias; p.C = C; p.lda = lda; p.ldb = ldb; p.ldc = ldc; p.M = M; p.N = N; p.Kp = Kp;
-  p.n_store = n_store; p.relu = relu ? 1 : 0; p.k_live = 0; p.m_dev = m_dev; p.col_tiles = 0; p.wg_begin = 0;
+  p.n_store = n_store; p.relu = relu ? 1 : 0; p.k_live = 0; p.m_dev = m_dev; p.rows_est = 0; p.col_tiles = 0; p.wg_begin = 0;
   p.add = add; p.tg = tg; p.gb = gb; p.colsum = nullptr; p.colsum_rows = 1; p.bd_n = 0; p.bd_k = 0;
   return p;
 }
 // the same problem with its live column count stated
 inline NtProblem nt_live(NtProblem p, int k_live) { p.k_live = k_live; return p; }
+// the same problem with the row count to expect
+inline NtProblem nt_rows(NtProblem p, int rows_est) { p.rows_est = rows_est; return p; }
 // the same problem with B stated to be block-diagonal (see NtProblem::bd_n)
 inline NtProblem nt_blocks(NtProblem p, int bd_n, int bd_k) { p.bd_n = bd_n; p.bd_k = bd_k; return p; }
 void gemm_nt_group(const NtProblem* probs, int n, hipStream_t s, const WbArgs* tail = nullptr);
