@@ -533,26 +533,48 @@ __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
 template <int RB>
 __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int row0, char* lds, bool keep) {
   const int xpb = node_xpb(a.kp), part = 16 * RB * xpb;
-  const int chunks = 8 * a.kp;   // runs of four columns per row
-  for (int i = threadIdx.x; i < 16 * RB * chunks; i += 64 * NP_W) {
-    const int lr = i / chunks, c = (i - lr * chunks) * 4, row = min(row0 + lr, n - 1);
-    floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
-    const float* src = node_x_row(a, row);
-    if (a.x_root != nullptr) {
-      if (src != nullptr) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (c + e < a.dx) v[e] = src[c + e];
-      }
-      if (keep && row0 + lr < n && c < a.ldxr) *reinterpret_cast<floatx4*>(a.Xrow + (size_t)row * a.ldxr + c) = v;
-    } else if (c < a.ldxr) {   // (pad columns of the node rows are zero)
-      v = *reinterpret_cast<const floatx4*>(src + c);
-    }
+  const int chunks = 8 * a.kp, total = 16 * RB * chunks;   // runs of four columns per row (at most 64) and per tile (at most 4,096)
+  const unsigned magic = ((1u << 22) + chunks - 1) / chunks;   // i / chunks = i magic >> 22 for all i < 4,096
+  auto put = [&](const floatx4& v, int lr, int c) __attribute__((always_inline)) {
     unsigned q[2][3];
     split_pair(v[0], v[1], q[0][0], q[0][1], q[0][2]);
     split_pair(v[2], v[3], q[1][0], q[1][1], q[1][2]);
 #pragma unroll
     for (int t = 0; t < 3; ++t) *reinterpret_cast<uint2*>(lds + t * part + lr * xpb + 2 * c) = make_uint2(q[0][t], q[1][t]);
+  };
+  if (a.x_root != nullptr) {
+    for (int i = threadIdx.x; i < total; i += 64 * NP_W) {
+      const int lr = (int)((unsigned)i * magic >> 22), c = (i - lr * chunks) * 4, row = min(row0 + lr, n - 1);
+      floatx4 v = floatx4{0.f, 0.f, 0.f, 0.f};
+      const float* src = node_x_row(a, row);
+      if (src != nullptr) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c + e < a.dx) v[e] = src[c + e];
+      }
+      if (keep && row0 + lr < n) *reinterpret_cast<floatx4*>(a.Xrow + (size_t)row * a.ldxr + c) = v;
+      put(v, lr, c);
+    }
+    return;
+  }
+  // Four runs at a time, asked for before the first of them is split: one by one, a tile of 32 rows of 200 columns was seven
+  // dependent round trips.  (Pad columns of the node rows are zero.)
+  const float* const x = a.Xrow + (size_t)row0 * a.ldxr;
+  const int last = n - 1 - row0;
+#pragma unroll 1
+  for (int i0 = threadIdx.x; i0 < total; i0 += 4 * 64 * NP_W) {
+    floatx4 v[4];
+    int lr[4], c[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + u * 64 * NP_W, total - 1);   // (past the tile: its last run once more)
+      lr[u] = (int)((unsigned)i * magic >> 22);
+      c[u] = (i - lr[u] * chunks) * 4;
+      v[u] = *reinterpret_cast<const floatx4*>(x + min(lr[u], last) * a.ldxr + c[u]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) put(v[u], lr[u], c[u]);
   }
 }
 
