@@ -37,6 +37,7 @@ constexpr int ND_W = 8;             // wavefronts per workgroup, update
 constexpr int ND_MAX_RB = 3;        // row blocks of 16 per tile, update
 constexpr int ND_LDS = 156 * 1024;  // LDS a tile may take (of 160 KB; the scan and the row flags use the rest)
 constexpr int ND_GRID = 252;        // workgroups of the update at a time: one per compute unit, and room for the passengers
+constexpr int ND_MAX_GROUPS = 4;    // column groups of a tile of the update, at most (its rows come in once per group)
 constexpr int NP_W = 4;             // wavefronts per workgroup, projections
 constexpr int NP_MAX_RB = 4;        // row blocks of 16 per tile, projections
 constexpr int NP_MAX_KS = 8;        // k slabs of a node row
@@ -55,10 +56,32 @@ void node_dims(Dims& d) {
   d.nd_rb = d.nd_cb <= ND_W && d.nd_kp <= NP_MAX_KS ? std::min(rb, ND_MAX_RB) : 0;
 }
 
-// Row blocks per tile and column groups for n rows (known on the device only).
+// Row blocks per tile and column groups for n rows (known on the device only).  Where the tiles do not all run at once, those
+// left over after the whole rounds are spread over all workgroups by as many column groups (groups2) as there is room for.
 struct NodeSplit {
   int rb, groups;
 };
+struct NodeUnits {
+  int groups, whole, groups2, units;   // `whole`: units of whole rounds
+};
+__device__ __forceinline__ NodeUnits node_units(const NodeSplit& sp, int tiles, int grid, int g_max) {
+  NodeUnits k{sp.groups, tiles * sp.groups, sp.groups, tiles * sp.groups};
+  if (k.units > grid) {
+    const int full = k.units / grid * grid / sp.groups, left = tiles - full;   // tiles
+    k.whole = full * sp.groups;
+    if (left > 0) k.groups2 = max(sp.groups, min(g_max, grid / left));
+    k.units = k.whole + left * k.groups2;
+  }
+  return k;
+}
+struct NodeUnit {
+  int tile, group, groups;
+};
+__device__ __forceinline__ NodeUnit node_unit(const NodeUnits& k, int u) {
+  const bool last = u >= k.whole;
+  const int groups = last ? k.groups2 : k.groups, first = last ? k.whole / k.groups : 0, v = last ? u - k.whole : u, t = v / groups;
+  return NodeUnit{first + t, v - t * groups, groups};
+}
 __device__ __forceinline__ int node_tiles(int n, int rb) { return rb == 1 ? (n + 15) / 16 : rb == 2 ? (n + 31) / 32 : rb == 3 ? (n + 47) / 48 : (n + 63) / 64; }
 // Update: the splits from the least time per workgroup to the most; the first whose tiles all run at once is taken (a
 // workgroup streams its part of the weights, 13 us / groups, and has 5 us of MFMAs per row block and group, of which the
@@ -262,15 +285,17 @@ __device__ __forceinline__ void node_update_again(const NodeKept& kept, int tid)
   const NodeKernArgs& a = *(const NodeKernArgs*)kept.args;
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const NodeSplit sp = node_update_split(n, a.rb_max, a.cb);
-  const int rb = sp.rb, groups = sp.groups, units = node_tiles(n, rb) * groups;
+  const int rb = sp.rb;
+  const NodeUnits units = node_units(sp, node_tiles(n, rb), a.unit_blocks, min(a.cb, ND_MAX_GROUPS));
   const int lane = tid & 63, wave = tid >> 6;
-  if (wave >= (a.cb + groups - 1) / groups) return;   // (a column block lies with the first k part's wavefront)
 #pragma unroll 1
-  for (int u = kept.block; u < units; u += a.unit_blocks) {
-    const int tile = u / groups, col = (u - tile * groups + wave * groups) * 16 + 4 * (lane >> 4);
+  for (int u = kept.block; u < units.units; u += a.unit_blocks) {
+    const NodeUnit t = node_unit(units, u);
+    if (wave >= (a.cb + t.groups - 1) / t.groups) continue;   // (a column block lies with the first k part's wavefront)
+    const int col = (t.group + wave * t.groups) * 16 + 4 * (lane >> 4);
 #pragma unroll 1
     for (int m = 0; m < rb; ++m) {
-      const int row = (tile * rb + m) * 16 + (lane & 15);
+      const int row = (t.tile * rb + m) * 16 + (lane & 15);
       if (row < n && col < a.dm) node_update_columns(a, row, col, a.dm - col);
     }
   }
@@ -310,19 +335,20 @@ __device__ __forceinline__ void node_project_again(const NodeKept& kept, int rb_
   const NodeKernArgs& a = *(const NodeKernArgs*)kept.args;
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max, pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, rb_max, (pairs + 1) / 2);
-  const int rb = sp.rb, groups = sp.groups, units = node_tiles(n, rb) * groups;
+  const int rb = sp.rb;
+  const NodeUnits units = node_units(sp, node_tiles(n, rb), kept.blocks, (pairs + 1) / 2);
   const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll 1
-  for (int u = kept.block; u < units; u += kept.blocks) {
-    const int tile = u / groups;
+  for (int u = kept.block; u < units.units; u += kept.blocks) {
+    const NodeUnit t = node_unit(units, u);
 #pragma unroll 1
     for (int i = 0; i < rb * 8; ++i) {   // row blocks, and the lane's eight columns of a pair of column blocks
-      const int row = (tile * rb + (i >> 3)) * 16 + (lane & 15);
+      const int row = (t.tile * rb + (i >> 3)) * 16 + (lane & 15);
       if (row >= n) break;
       const float* x = node_x_row(a, row);
       if (x != nullptr && node_has_nan(x, a.dx)) continue;
 #pragma unroll 1
-      for (int pr = u - tile * groups + wave * groups; pr < pairs; pr += groups * NP_W) {
+      for (int pr = t.group + wave * t.groups; pr < pairs; pr += t.groups * NP_W) {
         const int col = pr * 32 + ((i >> 2) & 1) * 16 + 4 * (lane >> 4) + (i & 3);
         float* o = col < a.ldp ? a.P + (size_t)row * a.ldp + col : a.U + (size_t)row * a.ldz + (col - a.ldp);
         if (*o != *o) *o = node_project_plain(a, row, col);
@@ -511,18 +537,18 @@ __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
   }
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const NodeSplit sp = node_update_split(n, a.rb_max, a.cb);
-  const int tiles = node_tiles(n, sp.rb), units = tiles * sp.groups;
+  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), a.unit_blocks, min(a.cb, ND_MAX_GROUPS));
   __shared__ NodeKept kept;
   node_keep(kept);
   bool again = false;
   float seen = 0.f;
-  for (int u = blockIdx.x; u < units; u += a.unit_blocks) {
-    const int tile = u / sp.groups, group = u - tile * sp.groups;
+  for (int u = blockIdx.x; u < units.units; u += a.unit_blocks) {
+    const NodeUnit t = node_unit(units, u);
     if (again) __syncthreads();   // the unit before is done with the LDS
     again = true;
-    if (sp.rb == 1) node_update_unit<1>(a, n, tile * 16, group, sp.groups, lds, has_s, seen);
-    else if (sp.rb == 2) node_update_unit<2>(a, n, tile * 32, group, sp.groups, lds, has_s, seen);
-    else node_update_unit<3>(a, n, tile * 48, group, sp.groups, lds, has_s, seen);
+    if (sp.rb == 1) node_update_unit<1>(a, n, t.tile * 16, t.group, t.groups, lds, has_s, seen);
+    else if (sp.rb == 2) node_update_unit<2>(a, n, t.tile * 32, t.group, t.groups, lds, has_s, seen);
+    else node_update_unit<3>(a, n, t.tile * 48, t.group, t.groups, lds, has_s, seen);
   }
   if (__builtin_expect(seen != seen, 0)) node_update_again(kept, threadIdx.x);
 }
@@ -678,18 +704,18 @@ __global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);
-  const int tiles = node_tiles(n, sp.rb), units = tiles * sp.groups;
+  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), gridDim.x, (pairs + 1) / 2);
   __shared__ NodeKept kept;
   node_keep(kept);
   bool again = false;
   float seen = 0.f;
-  for (int u = blockIdx.x; u < units; u += gridDim.x) {
-    const int tile = u / sp.groups, group = u - tile * sp.groups;
+  for (int u = blockIdx.x; u < units.units; u += gridDim.x) {
+    const NodeUnit t = node_unit(units, u);
     if (again) __syncthreads();
     again = true;
-    if (sp.rb == 1) node_project_unit<1, KS>(a, n, tile * 16, group, sp.groups, lds, seen);
-    else if (sp.rb == 2) node_project_unit<2, KS>(a, n, tile * 32, group, sp.groups, lds, seen);
-    else if (KS <= 4) node_project_unit<KS <= 4 ? 4 : 2, KS>(a, n, tile * 64, group, sp.groups, lds, seen);
+    if (sp.rb == 1) node_project_unit<1, KS>(a, n, t.tile * 16, t.group, t.groups, lds, seen);
+    else if (sp.rb == 2) node_project_unit<2, KS>(a, n, t.tile * 32, t.group, t.groups, lds, seen);
+    else if (KS <= 4) node_project_unit<KS <= 4 ? 4 : 2, KS>(a, n, t.tile * 64, t.group, t.groups, lds, seen);
   }
   if (__builtin_expect(seen != seen, 0)) node_project_again(kept, KS <= 4 ? NP_MAX_RB : 2, threadIdx.x);
 }

@@ -101,6 +101,19 @@ def test_projections_row_counts(widths, R):
     assert rel_err(z.cpu().numpy(), ref) <= NODE_TOL
 
 
+# more tiles than run at once: the ones left over after the whole rounds in one to four (update) or to nine (projections) column
+# groups, 64-row tiles and 32-row ones
+@pytest.mark.parametrize("n", [12145, 14000, 16200, 20000])
+def test_gru_update_last_round(n):
+    test_gru_update_row_counts((100, 100, 172, 0, 1, 10, 700), n)
+
+
+@pytest.mark.parametrize("widths,R", [((100, 100, 172, 0, 2, 10, 700), 1495), ((100, 100, 172, 0, 2, 10, 700), 1700), ((100, 100, 131, 100, 2), 760),
+                                      ((100, 100, 131, 100, 2), 1100)])
+def test_projections_last_round(widths, R):
+    test_projections_row_counts(widths, R)
+
+
 # where the node path does not fit: a memory wider than eight column blocks, a GRU input wider than the LDS tile, node rows
 # of more than eight k slabs; and one just inside (a single row block per tile)
 @pytest.mark.parametrize("shape", [
