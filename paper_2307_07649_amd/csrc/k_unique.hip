@@ -38,6 +38,7 @@ __device__ __forceinline__ float slot_grad(const SlotGrads& g, int sl, int c) {
 #define TGNN_SEG_CHUNK 16
 #endif
 constexpr int SEG_CHUNK = TGNN_SEG_CHUNK;
+constexpr int SEG_WAVES = 4;   // wavefronts per workgroup
 // What bounds it: a wavefront's two dependent round trips (slot ids, then rows), so what counts is how many wavefronts a
 // SIMD holds.  With up to two heads (TWO) the score gradients and softmax weights of a whole chunk are one gather, a lane
 // per (slot, head, which of the two), handed out by readlane and chosen per column, instead of four loads and registers
@@ -46,8 +47,14 @@ constexpr int SEG_CHUNK = TGNN_SEG_CHUNK;
 // Against four loads per slot and column and atomics throughout: 51.7 -> 49.1 us on 132,000 slots of 11,000 rows (102 instead
 // of 150 registers); with the atomics gone from most rows, 8 replicas 698 -> 682 us a step, 4,000 events 505 -> 490.
 // (Two or four chunks per wavefront, so that a popular row costs fewer atomic updates: slower on 600 and on 4,000 events.)
+// On power-law graphs one row holds a good part of the list, and atomics on one address complete one at a time: the
+// launch ended 5 us after its last wavefront (600 events).  A run that goes on from one wavefront of the workgroup into the next
+// is therefore put together in LDS first, by the wavefront in whose chunk it begins: one atomic update of the row per
+// workgroup.  Runs between a chunk's first and last one are stored from one copy of the code.  Launches: 4,000 events 48.5 -> 32.8 us,
+// eight replicas 42.7 -> 34, 600 events 12.6 -> 9.5.  (Eight wavefronts per workgroup: the same on these, 8.4 instead of 7.3 us on
+// 200 events; sixteen: 13.4, 40 and 42.)
 template <bool TWO>
-__global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, const int32_t* __restrict__ sort_total,
+__global__ __launch_bounds__(64 * SEG_WAVES) void seg_reduce_kernel(int R, int S, int dO, const int32_t* __restrict__ sort_total,
                                                          const int32_t* __restrict__ sorted,
                                                          const int32_t* __restrict__ sorted_row,
                                                          SlotGrads sg, int ldkv, float* __restrict__ dP, int ldp,
@@ -62,7 +69,11 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
     block -= nq;
   }
   const int lane = threadIdx.x & 63;
-  const int p0 = (block * 4 + (threadIdx.x >> 6)) * SEG_CHUNK;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), p0 = (block * SEG_WAVES + wave) * SEG_CHUNK;
+  // what a wavefront's first run leaves to the wavefront before: which halves of the row it has, 4 more if it fills the chunk
+  // and goes on (-1: nothing); and its sums
+  __shared__ int left_state[SEG_WAVES];
+  __shared__ float left[SEG_WAVES][8][64];
   // lanes fetch the chunk's slot ids and rows in parallel, and the rows of the entries after and before it (lanes
   // SEG_CHUNK, SEG_CHUNK + 1), without waiting for the length of the list (entries past it are dropped below); they are
   // broadcast afterwards
@@ -73,7 +84,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
     my_row = sorted_row[at];
   }
   const int total = *sort_total;
-  if (p0 >= total) return;
+  if (block * SEG_WAVES * SEG_CHUNK >= total) return;   // (uniform for the workgroup)
   if (at >= total) my_slot = my_row = -1;
   const int next_row = __builtin_amdgcn_readlane(my_row, SEG_CHUNK), prev_row = __builtin_amdgcn_readlane(my_row, SEG_CHUNK + 1);
   // a neighbour slot's root and position among the root's neighbours: one division per slot, done by the lane that
@@ -104,24 +115,34 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
       ck[u] = live[u] ? c : 0;
       head[u] = ck[u] / sg.dh;
     }
-    float aK[2] = {0.f, 0.f}, aV[2] = {0.f, 0.f}, aQ[2] = {0.f, 0.f}, aM[2] = {0.f, 0.f};
-    bool any_kv = false, any_qm = false;
-    int cur = -1;
-    auto flush = [&](bool whole) __attribute__((always_inline)) {
-      if (cur < 0) return;
-      float* row = dP + (size_t)cur * ldp;
+    // a run's sums {K, V, Q, M} and which halves of the row it has (1: {K | V}, 2: {Q | M})
+    struct Run {
+      float k[2], v[2], q[2], m[2];
+      int row, has;
+    };
+    Run cur, first;   // the run at hand; the chunk's first one, once it has ended
+    auto clear = [&](Run& r, int row) __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) r.k[u] = r.v[u] = r.q[u] = r.m[u] = 0.f;
+      r.row = row; r.has = 0;
+    };
+    clear(cur, -1);
+    clear(first, -1);
+    if (cb > 0) __syncthreads();   // the pass before has been read
+    auto store = [&](const Run& r) __attribute__((always_inline)) {   // a run that no other wavefront has a part of
+      float* row = dP + (size_t)r.row * ldp;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        if (live[u]) {
-          if (any_kv) {
-            if (whole) { row[ck[u]] = aK[u]; row[dO + ck[u]] = aV[u]; }
-            else { atomicAdd(row + ck[u], aK[u]); atomicAdd(row + dO + ck[u], aV[u]); }
-          }
-          if (any_qm) {
-            if (whole) { row[ldkv + ck[u]] = aQ[u]; row[ldkv + dO + ck[u]] = aM[u]; }
-            else { atomicAdd(row + ldkv + ck[u], aQ[u]); atomicAdd(row + ldkv + dO + ck[u], aM[u]); }
-          }
-        }
+        if (live[u] && (r.has & 1)) { row[ck[u]] = r.k[u]; row[dO + ck[u]] = r.v[u]; }
+        if (live[u] && (r.has & 2)) { row[ldkv + ck[u]] = r.q[u]; row[ldkv + dO + ck[u]] = r.m[u]; }
+      }
+    };
+    auto add = [&](const Run& r) __attribute__((always_inline)) {
+      float* row = dP + (size_t)r.row * ldp;
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (live[u] && (r.has & 1)) { atomicAdd(row + ck[u], r.k[u]); atomicAdd(row + dO + ck[u], r.v[u]); }
+        if (live[u] && (r.has & 2)) { atomicAdd(row + ldkv + ck[u], r.q[u]); atomicAdd(row + ldkv + dO + ck[u], r.m[u]); }
       }
     };
     int slots[SEG_CHUNK], rows[SEG_CHUNK];
@@ -155,24 +176,21 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
         }
       }
     }
-    bool from_start = true;   // the run began with the chunk's first entry
 #pragma unroll
     for (int i = 0; i < SEG_CHUNK; ++i) {
-      if (rows[i] != cur) {
-        flush(!(from_start && prev_row == cur));
-        if (i > 0) from_start = false;
-#pragma unroll
-        for (int u = 0; u < 2; ++u) aK[u] = aV[u] = aQ[u] = aM[u] = 0.f;
-        any_kv = any_qm = false;
-        cur = rows[i];
+      if (i > 0 && rows[i] != rows[i - 1]) {   // (uniform.  An entry past the list has row -1: nothing is stored for it)
+        if (cur.row == rows[0] && first.row < 0) first = cur;
+        else if (cur.row >= 0) store(cur);
+        clear(cur, -1);
       }
+      cur.row = rows[i];
       if (rows[i] >= 0) {
         if (slots[i] < R) {
-          any_qm = true;
+          cur.has |= 2;
 #pragma unroll
-          for (int u = 0; u < 2; ++u) { aQ[u] += xa[i][u]; aM[u] += xb[i][u]; }
+          for (int u = 0; u < 2; ++u) { cur.q[u] += xa[i][u]; cur.m[u] += xb[i][u]; }
         } else {
-          any_kv = true;
+          cur.has |= 1;
           float w[4];
           if (TWO) {
 #pragma unroll
@@ -181,13 +199,45 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(int R, int S, int dO, c
           }
 #pragma unroll
           for (int u = 0; u < 2; ++u) {
-            aK[u] += xa[i][u] * (TWO ? (head[u] > 0 ? w[2] : w[0]) : wa[TWO ? 0 : i][u]);
-            aV[u] += xb[i][u] * (TWO ? (head[u] > 0 ? w[3] : w[1]) : wb[TWO ? 0 : i][u]);
+            cur.k[u] += xa[i][u] * (TWO ? (head[u] > 0 ? w[2] : w[0]) : wa[TWO ? 0 : i][u]);
+            cur.v[u] += xb[i][u] * (TWO ? (head[u] > 0 ? w[3] : w[1]) : wb[TWO ? 0 : i][u]);
           }
         }
       }
     }
-    flush(!(from_start && prev_row == cur) && next_row != cur);
+    const bool goes_on = cur.row >= 0 && next_row == cur.row;   // the last run, in the next chunk
+    const bool one = cur.row == rows[0];                        // the chunk is one run
+    if (one) first = cur;
+    const bool began = first.row >= 0 && prev_row == first.row;   // the first run, in the chunk before
+    int left_here = -1;
+    if (began && wave > 0) {   // ... by the wavefront before, which puts the run together
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        left[wave][u][lane] = first.k[u]; left[wave][2 + u][lane] = first.v[u];
+        left[wave][4 + u][lane] = first.q[u]; left[wave][6 + u][lane] = first.m[u];
+      }
+      left_here = first.has + (one && goes_on ? 4 : 0);
+    } else if (!one && first.row >= 0) {
+      if (began) add(first);
+      else store(first);
+    }
+    if (lane == 0) left_state[wave] = left_here;
+    __syncthreads();
+    if (cur.row >= 0 && !(one && began && wave > 0)) {
+      bool ends = !goes_on;
+#pragma unroll 1
+      for (int w = wave + 1; w < SEG_WAVES && !ends; ++w) {
+        const int state = left_state[w];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          cur.k[u] += left[w][u][lane]; cur.v[u] += left[w][2 + u][lane]; cur.q[u] += left[w][4 + u][lane]; cur.m[u] += left[w][6 + u][lane];
+        }
+        cur.has |= state & 3;
+        ends = (state & 4) == 0;
+      }
+      if (ends && !(one && began)) store(cur);
+      else add(cur);
+    }
   }
 }
 
@@ -204,9 +254,9 @@ void seg_reduce(tgnn_ctx* ctx, int R, int S, const QPhi& qphi, hipStream_t s) {
   const Dims& d = ctx->d;
   Ws& w = ctx->w;
   const int waves = (S + SEG_CHUNK - 1) / SEG_CHUNK;
-  const dim3 grid((waves + 3) / 4 + qphi_blocks(qphi));
+  const dim3 grid((waves + SEG_WAVES - 1) / SEG_WAVES + qphi_blocks(qphi));
 #define TGNN_SEG_CASE(TWO)                                                                                             \
-  hipLaunchKernelGGL(seg_reduce_kernel<TWO>, grid, dim3(256), 0, s, R, S, d.dO, w.sort_total, w.sorted, w.sorted_row,  \
+  hipLaunchKernelGGL(seg_reduce_kernel<TWO>, grid, dim3(64 * SEG_WAVES), 0, s, R, S, d.dO, w.sort_total, w.sorted, w.sorted_row,  \
                      slot_grads(ctx, R), d.ldkv, w.dP, d.ldp, qphi)
   if (d.H <= 2) TGNN_SEG_CASE(true);
   else TGNN_SEG_CASE(false);
