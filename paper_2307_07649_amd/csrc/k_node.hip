@@ -62,13 +62,14 @@ struct NodeSplit {
   int rb, groups;
 };
 struct NodeUnits {
-  int groups, whole, groups2, units;   // `whole`: units of whole rounds
+  int groups, whole, groups2, units, full;   // `whole`: units of whole rounds, `full`: their tiles
 };
 __device__ __forceinline__ NodeUnits node_units(const NodeSplit& sp, int tiles, int grid, int g_max) {
-  NodeUnits k{sp.groups, tiles * sp.groups, sp.groups, tiles * sp.groups};
+  NodeUnits k{sp.groups, tiles * sp.groups, sp.groups, tiles * sp.groups, 0};
   if (k.units > grid) {
-    const int full = k.units / grid * grid / sp.groups, left = tiles - full;   // tiles
-    k.whole = full * sp.groups;
+    k.full = k.units / grid * grid / sp.groups;
+    k.whole = k.full * sp.groups;
+    const int left = tiles - k.full;
     if (left > 0) k.groups2 = max(sp.groups, min(g_max, grid / left));
     k.units = k.whole + left * k.groups2;
   }
@@ -79,8 +80,8 @@ struct NodeUnit {
 };
 __device__ __forceinline__ NodeUnit node_unit(const NodeUnits& k, int u) {
   const bool last = u >= k.whole;
-  const int groups = last ? k.groups2 : k.groups, first = last ? k.whole / k.groups : 0, v = last ? u - k.whole : u, t = v / groups;
-  return NodeUnit{first + t, v - t * groups, groups};
+  const int groups = last ? k.groups2 : k.groups, v = last ? u - k.whole : u, t = v / groups;
+  return NodeUnit{(last ? k.full : 0) + t, v - t * groups, groups};
 }
 __device__ __forceinline__ int node_tiles(int n, int rb) { return rb == 1 ? (n + 15) / 16 : rb == 2 ? (n + 31) / 32 : rb == 3 ? (n + 47) / 48 : (n + 63) / 64; }
 // Update: the splits from the least time per workgroup to the most; the first whose tiles all run at once is taken (a
@@ -339,7 +340,7 @@ __device__ __forceinline__ void node_project_again(const NodeKept& kept, int rb_
   const NodeUnits units = node_units(sp, node_tiles(n, rb), kept.blocks, (pairs + 1) / 2);
   const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll 1
-  for (int u = kept.block; u < units.units; u += kept.blocks) {
+  for (int u = kept.block; u < units.units; u += a.unit_blocks) {
     const NodeUnit t = node_unit(units, u);
 #pragma unroll 1
     for (int i = 0; i < rb * 8; ++i) {   // row blocks, and the lane's eight columns of a pair of column blocks
@@ -556,7 +557,7 @@ __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
 // ---------------------------------------------------------------------------------------------------------
 // Rows row0 .. of x -> three bf16 parts in LDS, zero beyond d_x; from ws.Xrow, or (tgnn_temporal_attn_fwd) from the
 // caller's rows, which are then also left in ws.Xrow.
-template <int RB>
+template <int RB, int KS>
 __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int row0, char* lds, bool keep) {
   const int xpb = node_xpb(a.kp), part = 16 * RB * xpb;
   const int chunks = 8 * a.kp, total = 16 * RB * chunks;   // runs of four columns per row (at most 64) and per tile (at most 4,096)
@@ -583,16 +584,17 @@ __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int ro
     }
     return;
   }
-  // Four runs at a time, asked for before the first of them is split: one by one, a tile of 32 rows of 200 columns was seven
-  // dependent round trips.  (Pad columns of the node rows are zero.)
+  // Up to four runs at a time (as many as a thread has), asked for before the first of them is split: one by one, a tile of 32
+  // rows of 200 columns was seven dependent round trips.  (Pad columns of the node rows are zero.)
+  constexpr int U = RB * KS / 2 < 4 ? RB * KS / 2 : 4;
   const float* const x = a.Xrow + (size_t)row0 * a.ldxr;
   const int last = n - 1 - row0;
 #pragma unroll 1
-  for (int i0 = threadIdx.x; i0 < total; i0 += 4 * 64 * NP_W) {
-    floatx4 v[4];
-    int lr[4], c[4];
+  for (int i0 = threadIdx.x; i0 < total; i0 += U * 64 * NP_W) {
+    floatx4 v[U];
+    int lr[U], c[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       const int i = min(i0 + u * 64 * NP_W, total - 1);   // (past the tile: its last run once more)
       lr[u] = (int)((unsigned)i * magic >> 22);
       c[u] = (i - lr[u] * chunks) * 4;
@@ -600,7 +602,7 @@ __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int ro
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) put(v[u], lr[u], c[u]);
+    for (int u = 0; u < U; ++u) put(v[u], lr[u], c[u]);
   }
 }
 
@@ -609,7 +611,7 @@ __device__ __forceinline__ void node_split_rows(const NodeArgs& a, int n, int ro
 // weights are a whole pair ahead and no load waits for a store.
 template <int RB, int KS>
 __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int row0, int group, int groups, char* lds, float& seen) {
-  node_split_rows<RB>(a, n, row0, lds, group == 0);
+  node_split_rows<RB, KS>(a, n, row0, lds, group == 0);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int li = lane & 15, lg = lane >> 4;
   const int xpb = node_xpb(a.kp), part = 16 * RB * xpb;
@@ -704,12 +706,13 @@ __global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);
-  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), gridDim.x, (pairs + 1) / 2);
+  // (the number of workgroups, either way: with eight slabs the argument costs 22 registers, with four gridDim is 0.4 us late)
+  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), KS <= 4 ? a.unit_blocks : (int)gridDim.x, (pairs + 1) / 2);
   __shared__ NodeKept kept;
   node_keep(kept);
   bool again = false;
   float seen = 0.f;
-  for (int u = blockIdx.x; u < units.units; u += gridDim.x) {
+  for (int u = blockIdx.x; u < units.units; u += (KS <= 4 ? a.unit_blocks : (int)gridDim.x)) {
     const NodeUnit t = node_unit(units, u);
     if (again) __syncthreads();
     again = true;
@@ -754,11 +757,13 @@ void node_bias(const NodeArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(node_bias_kernel, dim3(node_bias_blocks(a)), dim3(64 * ND_W), 0, s, a);
 }
 
-void node_project(const NodeArgs& a, hipStream_t s) {
+void node_project(const NodeArgs& args, hipStream_t s) {
+  NodeArgs a = args;
   if (a.n_max <= 0) return;
   const int lds = 3 * 16 * (a.kp <= 4 ? NP_MAX_RB : 2) * node_xpb(a.kp);
   const int units = 8 * ((a.n_max + 15) / 16);
-  const dim3 grid(std::min(units, NP_GRID));
+  a.unit_blocks = std::min(units, NP_GRID);
+  const dim3 grid(a.unit_blocks);
   if (a.kp <= 4) hipLaunchKernelGGL(node_project_kernel<4>, grid, dim3(64 * NP_W), lds, s, a);
   else hipLaunchKernelGGL(node_project_kernel<NP_MAX_KS>, grid, dim3(64 * NP_W), lds, s, a);
 }
