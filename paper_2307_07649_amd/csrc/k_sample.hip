@@ -126,7 +126,11 @@ __device__ __forceinline__ void sample_block(const SampleArgs& a, const BatchSet
   }
   if (FUSED) {
     // The block's slots are gathered by node in an LDS table first, so that a node costs one look at its claim word and
-    // one count per block however many slots refer to it.  Row numbers for the nodes claimed first by this block:
+    // one count per block however many slots refer to it.  The blocks all arrive here at once, and one claim word per node
+    // for the whole chip went from L2 to L2 for each of them: of a launch of 32 us (4,000 events) the claims were 11, of 42 us
+    // (600 events with 49 negatives) 26; the launches now take 26 and 16 us.  So the blocks of an XCD (every eighth block) settle it among themselves first, on a
+    // claim word in their own L2, and one of them asks for the node's; which XCD a block really runs on does not matter to
+    // the result, since whoever is turned away there was turned away by one who asked.  Row numbers for the nodes claimed first by this block:
     // winners are counted per wave (ballot), per block (LDS) and only then on the device-wide row counter, whose
     // atomics serialise in the L2.
     if (claim >= 0) atomicAdd(&tab.val[uniq_table_slot(tab, claim)], 1);
@@ -146,7 +150,8 @@ __device__ __forceinline__ void sample_block(const SampleArgs& a, const BatchSet
         eid[u] = uq.mail_eid[key[u]];
         mem_ts[u] = uq.mem_ts[key[u]];
         mail_ts[u] = uq.mail_ts[key[u]];
-        won[u] = __atomic_load_n(uq.utag + key[u], __ATOMIC_RELAXED) < ep;   // popular nodes: look first
+        if (uq.xtag != nullptr) won[u] = atomicMax(uq.xtag + (size_t)(block & 7) * uq.n_tags + key[u], (unsigned)ep) < (unsigned)ep;
+        else won[u] = __atomic_load_n(uq.utag + key[u], __ATOMIC_RELAXED) < ep;   // look first
       }
     }
 #pragma unroll
@@ -216,7 +221,8 @@ void head_fill(tgnn_ctx* ctx, const tgnn_graph* g, const tgnn_state* st, int n_r
   h.sa.out_nbr = w.nbr; h.sa.out_eid = w.neid; h.sa.out_ts = w.nts; h.sa.out_cnt = w.cnt;
   h.sa.root_node = w.root_node; h.sa.root_t = w.root_t; h.sa.slot_gid = w.slot_gid; h.sa.slot_node = w.slot_node;
   h.sa.winkey = w.winkey; h.sa.bad_ids = w.bad_ids;
-  h.sa.uq = UniqPtrs{w.utag, w.epoch, w.uidx, w.ucount, w.ulist, w.row_eid, w.has, w.delta, w.tau, st->mail_eid, st->mem_ts, st->mail_ts, count ? w.gcnt : nullptr};
+  h.sa.uq = UniqPtrs{w.utag, w.epoch, w.uidx, w.ucount, w.ulist, w.row_eid, w.has, w.delta, w.tau, st->mail_eid, st->mem_ts, st->mail_ts, count ? w.gcnt : nullptr,
+                     w.xtag, d.nrep * d.N};
   const int per_block = SAMPLE_WAVES * (d.k < 16 ? 4 : 1);   // four roots per wavefront when a lane group of 16 holds k + 1 claims
   h.sample_blocks = (n_roots + per_block - 1) / per_block;
   h.pro_bx = 12 * 16 / SAMPLE_WAVES;   // blocks of 1024 threads per grid row of the prologue (C1: 12 measured best of 2 .. 48; 24: +1.6 us per step)

@@ -82,6 +82,10 @@ struct Bump {
   }
 };
 
+// Nodes (of all replicas) up to which the XCDs have claim words of their own (32 bytes per node): with more, a step's blocks
+// hardly meet on one of them.
+constexpr size_t XTAG_NODES = size_t(1) << 22;
+
 static void layout(const Dims& d, Ws& w, Bump& b) {
   const size_t R = d.maxR, RK = d.maxRK, S = d.maxS, B2 = (1 + (size_t)d.maxNeg) * d.maxEv;
   w.root_node = b.take<int32_t>(R);
@@ -93,6 +97,7 @@ static void layout(const Dims& d, Ws& w, Bump& b) {
   w.epoch = b.take<unsigned long long>(1);
   w.bad_ids = b.take<int32_t>(1);
   const size_t NG = (size_t)d.nrep * d.N, U = d.maxU;
+  w.xtag = NG <= XTAG_NODES ? b.take<unsigned>(8 * NG) : nullptr;
   w.utag = b.take<unsigned long long>(NG); w.uidx = b.take<int32_t>(NG); w.ucount_pair = b.take<int32_t>(2); w.ucount = w.ucount_pair;
   w.ulist = b.take<int32_t>(U + 4); w.slot_row = b.take<int32_t>(S); w.gcnt = b.take<int32_t>(NG); w.row_eid = b.take<int32_t>(U);
   w.rowptr = b.take<int32_t>(U + 1); w.cursor = b.take<int32_t>(U); w.sorted = b.take<int32_t>(S);

@@ -74,6 +74,7 @@ struct Ws {
   int32_t* bad_ids;                            // [1] batch node ids outside [0, N) seen by the steps so far
   // distinct (replica, node) rows of the step
   unsigned long long* utag;                    // [nrep*N] epoch of the last step that claimed the node
+  unsigned* xtag;                              // [8, nrep*N] the same among the blocks of an XCD (NULL: too many nodes)
   int32_t *uidx, *ucount, *ulist;              // [nrep*N] row of a claimed node; [1] number of rows; [maxU] row -> gid
   int32_t* ucount_pair;                        // [2] ucount points at one of them: training steps alternate, and
                                                // each clears the counter of the next one
@@ -481,6 +482,8 @@ struct UniqPtrs {
   const int32_t* mail_eid;
   const double *mem_ts, *mail_ts;
   int32_t* gcnt;   // slots per (replica, node); NULL in a forward-only pass
+  unsigned* xtag;  // claim words of the XCDs, n_tags each; NULL: none
+  int n_tags;
 };
 // The first launch of a training step: roots of every batch (node, time, slot ids), write-back arbitration marks,
 // neighbour sampling and row claims (blocks 0 .. sample_blocks - 1, a lane group of 16 or 64 per root, 64 * SAMPLE_WAVES threads per
