@@ -36,6 +36,39 @@ __device__ __forceinline__ float time_enc(double delta, float w, float b) {
   return c;
 }
 
+// Brings the first LINES x 64 bytes of the kernel's argument block into the scalar cache, all lines at once (as many as the
+// block has; the values are not used, and have come in when the asm block ends).  The block is cold, and wherever the
+// compiler first needs a field of it is a miss of its own: with several hundred bytes of arguments a chain of them.
+template <int LINES> __device__ __forceinline__ void warm_kernargs() {
+#ifdef __HIP_DEVICE_COMPILE__
+  const auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  unsigned d[LINES];
+  if constexpr (LINES == 3)
+    asm volatile("s_load_dword %0, %3, 0x0\n\t" "s_load_dword %1, %3, 0x40\n\t" "s_load_dword %2, %3, 0x80\n\t" "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]) : "s"(p));
+  if constexpr (LINES == 5)
+    asm volatile("s_load_dword %0, %5, 0x0\n\t" "s_load_dword %1, %5, 0x40\n\t" "s_load_dword %2, %5, 0x80\n\t" "s_load_dword %3, %5, 0xc0\n\t"
+                 "s_load_dword %4, %5, 0x100\n\t" "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]) : "s"(p));
+  if constexpr (LINES == 6)
+    asm volatile("s_load_dword %0, %6, 0x0\n\t" "s_load_dword %1, %6, 0x40\n\t" "s_load_dword %2, %6, 0x80\n\t" "s_load_dword %3, %6, 0xc0\n\t"
+                 "s_load_dword %4, %6, 0x100\n\t" "s_load_dword %5, %6, 0x140\n\t" "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]) : "s"(p));
+  if constexpr (LINES == 10)
+    asm volatile("s_load_dword %0, %10, 0x0\n\t" "s_load_dword %1, %10, 0x40\n\t" "s_load_dword %2, %10, 0x80\n\t" "s_load_dword %3, %10, 0xc0\n\t"
+                 "s_load_dword %4, %10, 0x100\n\t" "s_load_dword %5, %10, 0x140\n\t" "s_load_dword %6, %10, 0x180\n\t" "s_load_dword %7, %10, 0x1c0\n\t"
+                 "s_load_dword %8, %10, 0x200\n\t" "s_load_dword %9, %10, 0x240\n\t" "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]), "=&s"(d[6]), "=&s"(d[7]), "=&s"(d[8]), "=&s"(d[9]) : "s"(p));
+  if constexpr (LINES == 12)
+    asm volatile("s_load_dword %0, %12, 0x0\n\t" "s_load_dword %1, %12, 0x40\n\t" "s_load_dword %2, %12, 0x80\n\t" "s_load_dword %3, %12, 0xc0\n\t"
+                 "s_load_dword %4, %12, 0x100\n\t" "s_load_dword %5, %12, 0x140\n\t" "s_load_dword %6, %12, 0x180\n\t" "s_load_dword %7, %12, 0x1c0\n\t"
+                 "s_load_dword %8, %12, 0x200\n\t" "s_load_dword %9, %12, 0x240\n\t" "s_load_dword %10, %12, 0x280\n\t" "s_load_dword %11, %12, 0x2c0\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]), "=&s"(d[6]), "=&s"(d[7]), "=&s"(d[8]), "=&s"(d[9]), "=&s"(d[10]), "=&s"(d[11]) : "s"(p));
+  static_assert(LINES == 3 || LINES == 5 || LINES == 6 || LINES == 10 || LINES == 12, "spelled out above");
+#endif
+}
+
 // x plus what the DPP control `CTRL` brings in from another lane of the row of 16
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x) {
   return x + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, true));

@@ -274,6 +274,7 @@ __device__ __forceinline__ void softmax_fast(float* sa, int HK, int k, int c, in
 #define TGNN_FATTN_FWD_WAVES 4
 #endif
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_FWD_WAVES, TGNN_FATTN_FWD_WAVES))) void fattn_fwd_fast_kernel(FusedAttn a) {
+  warm_kernargs<10>();
   extern __shared__ float lds[];
   int block = blockIdx.x;
   if (a.fill.gcnt != nullptr) {   // the first blocks are passengers: the fill pass of the slot sort
@@ -427,6 +428,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_
 #else
 __global__ __launch_bounds__(256) void fattn_bwd_fast_kernel(FusedAttn a) {
 #endif
+  warm_kernargs<6>();
   extern __shared__ float lds[];
   // (wave index and neighbour count are the same for all lanes: saying so keeps them, and every test on them, scalar)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1004,6 +1006,7 @@ template <int M> __device__ __forceinline__ void mid_scores(const FusedAttn& a, 
 
 template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  warm_kernargs<10>();
   int block = blockIdx.x;
   if (a.fill.gcnt != nullptr) {
     const int fill_blocks = uniq_blocks(a.fill.S);
@@ -1091,6 +1094,7 @@ template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(Fus
 
 template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+  warm_kernargs<6>();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r = blockIdx.x * 4 + wave;
   if (r >= a.R) return;

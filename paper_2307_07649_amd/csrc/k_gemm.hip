@@ -42,6 +42,7 @@ __device__ __forceinline__ int nt_swz(int row, int chunk) { return row * NT_P + 
 template <int TN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (TN <= 5 ? 4 : 2)))) void gemm_nt_kernel(NtGroup grp) {
   constexpr int BM = NT_BM, BN = 16 * TN;
+  warm_kernargs<12>();
   if ((int)blockIdx.x >= grp.gemm_wgs) {   // passengers after the products' workgroups: write-back scatter + SGD
     wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
     return;
@@ -432,6 +433,7 @@ __device__ __forceinline__ float row_sum(float x) {
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_few_kernel(NtGroup grp) {
   constexpr int D = NT_CHUNK, KC = 32 * NT_CHUNK;
+  warm_kernargs<12>();
   if ((int)blockIdx.x >= grp.gemm_wgs) {   // passengers, as above
     wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
     return;
@@ -1009,6 +1011,14 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int pi = (word >> (8 * (slot & 3))) & 255u;
   const int local = pos - begin;
   const auto& q = gp->p[pi];
+#ifdef __HIP_DEVICE_COMPILE__
+  {   // (the problem's cache lines at once, see warm_kernargs)
+    static_assert(sizeof(TnProblem) > 128 && sizeof(TnProblem) <= 192, "three or four lines");
+    unsigned d0, d1, d2, d3;
+    asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\ts_load_dword %3, %4, %5\n\t"
+                 "s_waitcnt lgkmcnt(0)" : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3) : "s"(&gp->p[pi]), "i"(sizeof(TnProblem) - 4));
+  }
+#endif
   const int v = (xcd + q.rot) & 7;
   const int tiles = q.tiles, chunks = q.chunks, N = q.N, K = q.K;
   int M = q.M, m_chunk = q.m_chunk;

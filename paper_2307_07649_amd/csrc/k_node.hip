@@ -526,6 +526,7 @@ __global__ __launch_bounds__(64 * ND_W) void node_bias_kernel(NodeArgs a) { node
 
 __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  warm_kernargs<12>();
   __shared__ int has_s[16 * ND_MAX_RB];
   if (a.epoch_bump != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.epoch_bump += 1ull;   // nothing here reads it
   // The last blocks are passengers: the scan of the slot sort and the biases of U.  (Behind the units, in the code too: a
@@ -703,6 +704,7 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
 template <int KS>
 __global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2))) void node_project_kernel(NodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
+  warm_kernargs<12>();
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);

@@ -194,6 +194,15 @@ __global__ __launch_bounds__(256) void sample_kernel(SampleArgs a, BatchSet none
 
 // The first launch of a training step: sampling blocks, then the prologue's blocks (see HeadArgs).
 __global__ __launch_bounds__(64 * SAMPLE_WAVES) void step_head_kernel(HeadArgs h) {
+#ifdef __HIP_DEVICE_COMPILE__
+  {   // (what the sampling blocks need, at once, see warm_kernargs: the sampler's arguments, the first batch, the batch counts)
+    unsigned d0, d1, d2, d3, d4, d5, d6;
+    asm volatile("s_load_dword %0, %7, 0x0\n\ts_load_dword %1, %7, 0x40\n\ts_load_dword %2, %7, 0x80\n\ts_load_dword %3, %7, 0xc0\n\t"
+                 "s_load_dword %4, %7, 0x100\n\ts_load_dword %5, %7, %8\n\ts_load_dword %6, %7, %9\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3), "=&s"(d4), "=&s"(d5), "=&s"(d6)
+                 : "s"(__builtin_amdgcn_kernarg_segment_ptr()), "i"(offsetof(HeadArgs, pa.bs)), "i"(offsetof(HeadArgs, pa.bs.nb)));
+  }
+#endif
   if ((int)blockIdx.x < h.sample_blocks) {
     // the epoch counter still holds the previous step's value: nothing writes it during this launch
     if (h.sa.k < 16) sample_block<true, 16>(h.sa, h.pa.bs, *h.sa.uq.epoch + 1ull, blockIdx.x);
