@@ -648,8 +648,12 @@ __device__ __forceinline__ GenLds gen_lds(char* base, int wave, int k, int H) {
   return g;
 }
 
+// the node row of the root itself
+__device__ __forceinline__ size_t gen_qrow(const FusedAttn& a, int r) {
+  return a.slot_gid != nullptr ? (size_t)a.uidx[a.slot_gid[r]] : a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
+}
 // the slots' ids, node rows and time differences to LDS (and, in a step's forward pass, the rows for the launches after)
-__device__ __forceinline__ void gen_load_slots(const FusedAttn& a, int r, int c, int lane, const GenLds& L, size_t& qrow) {
+__device__ __forceinline__ void gen_load_slots(const FusedAttn& a, int r, int c, int lane, const GenLds& L, size_t qrow) {
   for (int j = lane; j < a.k; j += 64) {
     int e, row;
     double dt;
@@ -658,7 +662,6 @@ __device__ __forceinline__ void gen_load_slots(const FusedAttn& a, int r, int c,
     a.dtk[(size_t)r * a.k + j] = dt;
     if (a.slot_gid != nullptr) a.slot_row[a.R + r * a.k + j] = j < c ? row : -1;
   }
-  qrow = a.slot_gid != nullptr ? (size_t)a.uidx[a.slot_gid[r]] : a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
   if (a.slot_gid != nullptr && lane == 0) a.slot_row[r] = (int)qrow;
 }
 __device__ __forceinline__ void gen_bwd_empty(const FusedAttn& a, int r, int lane, int HK, float* yrow) {   // no neighbours
@@ -723,7 +726,7 @@ __global__ __launch_bounds__(256) void fattn_fwd_gen_kernel(FusedAttn a) {
   const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
   float* pr = a.prob + (size_t)r * HK;
   float* out = a.Onode + (size_t)r * a.ldh;
-  size_t qrow;
+  const size_t qrow = gen_qrow(a, r);
   gen_load_slots(a, r, c, lane, L, qrow);
   if (c == 0) {
     for (int p = lane; p < HK; p += 64) pr[p] = 0.f;
@@ -860,12 +863,15 @@ __global__ __launch_bounds__(256) void fattn_bwd_gen_kernel(FusedAttn a) {
 // of four: their columns are formed once for all heads (the generic path forms them per slot and head, one load and one
 // exchange over the wavefront at a time) and once more for the weighted sums, loads and sums of a group are in flight
 // together, four sums share their exchanges.  Every sum has the same terms in the same order as in the generic path.
-// 17 neighbours, 3 heads, 83 columns, 999 roots: forward and backward 25 and 28 us, the whole step 268 -> 157 us.  Bound by
+// 17 neighbours, 3 heads, 83 columns, 999 roots: the whole step 268 -> 157 us.  Bound by
 // the vector ALUs (sines and cosines twice per slot) and, with few roots, by the chain of a wavefront.
 // A kernel holds M rounds of 64 columns: with one kernel of five rounds for all widths, up to 64 columns paid for five (151
 // and 189 registers, three and two wavefronts per SIMD) and took longer than the generic path from 700 events on.  4,000
 // events, 11 neighbours, one head, 8 and 128 columns, the whole step: generic 291 and 335 us, five rounds 349 and 362, one and
 // two rounds 267 and 297.
+// A root with few others beside it is a chain of its own latencies: with W = 4 a workgroup's wavefronts share one root, the scores
+// by groups of slots and the weighted sums by rounds of columns, so that every sum still has the same terms in the same
+// order.  999 roots, 17 neighbours: forward and backward 25 and 28 -> 21 and 24 us.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int MA_B = 4, MA_M = 5, MA_H = 4, MA_E = 2;   // (M: rounds of 64 columns that a kernel holds, MA_M at most)
 
@@ -922,19 +928,19 @@ template <int M> __device__ __forceinline__ MidTime<M> mid_time(const FusedAttn&
 // the group's columns (zero past d_e + d_t), and the sines of the time columns (zero on edge-feature columns)
 template <bool BWD, int M>
 __device__ __forceinline__ void mid_cols(const FusedAttn& a, int lane, const MidSlots& q, const MidTime<M>& t, float (&cv)[M][MA_B],
-                                         float (&sv)[M][MA_B]) {
+                                         float (&sv)[M][MA_B], unsigned rounds = ~0u) {   // rounds: a bit for each that is wanted
 #pragma unroll
   for (int m = 0; m < M; ++m)
 #pragma unroll
     for (int i = 0; i < MA_B; ++i) {
       cv[m][i] = 0.f;
-      if (64 * m < a.de) cv[m][i] = a.efeat[(size_t)q.e[i] * a.de + min(lane + 64 * m, a.de - 1)];
+      if (64 * m < a.de && (rounds >> m & 1u)) cv[m][i] = a.efeat[(size_t)q.e[i] * a.de + min(lane + 64 * m, a.de - 1)];
     }
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     const int col = lane + 64 * m;
     const bool is_t = col >= a.de && col < a.de + a.dt;
-    if (64 * m < a.de + a.dt && 64 * m + 64 > a.de) {   // (uniform) some lane has a time column
+    if (64 * m < a.de + a.dt && 64 * m + 64 > a.de && (rounds >> m & 1u)) {   // (uniform) some lane has a time column
 #pragma unroll
       for (int i = 0; i < MA_B; ++i) {
         float sn, cs;
@@ -1004,7 +1010,16 @@ template <int M> __device__ __forceinline__ void mid_scores(const FusedAttn& a, 
   }
 }
 
-template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
+// wavefronts of one root meet: a barrier, or within the wavefront
+template <int W> __device__ __forceinline__ void mid_sync() {
+  if (W > 1) __syncthreads();
+  else wave_lds_sync();
+}
+// the rounds of columns that a wavefront sums up; and does it sum up the node rows' part?
+template <int M, int W> __device__ __forceinline__ unsigned mid_rounds(int wave) { return W == 1 ? ~0u : 0x11111111u << wave; }
+template <int M, int W> __device__ __forceinline__ bool mid_nodes(int wave) { return W == 1 || wave == M % W; }
+
+template <int M, int W> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   warm_kernargs<10>();
   int block = blockIdx.x;
@@ -1017,35 +1032,39 @@ template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(Fus
     block -= fill_blocks;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int r = block * 4 + wave;
+  static_assert(W == 1 || W == 4, "a root per wavefront or per workgroup");
+  const int r = W == 1 ? block * 4 + wave : block;
   if (r >= a.R) return;
-  const int HK = a.H * a.k;
-  GenLds L = gen_lds(lds_raw, wave, a.k, a.H);
+  const int HK = a.H * a.k, part = W == 1 ? 0 : wave;
+  GenLds L = gen_lds(lds_raw, W == 1 ? wave : 0, a.k, a.H);
   const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
   float* pr = a.prob + (size_t)r * HK;
   float* out = a.Onode + (size_t)r * a.ldh;
-  size_t qrow;
-  gen_load_slots(a, r, c, lane, L, qrow);
+  size_t qrow = gen_qrow(a, r);
+  if (part == 0) gen_load_slots(a, r, c, lane, L, qrow);
   if (c == 0) {
+    if (part > 0) return;
     for (int p = lane; p < HK; p += 64) pr[p] = 0.f;
     for (int e = lane; e < a.dO; e += 64) out[e] = 0.f;
     zero_head_rows(a, a.Zp + (size_t)r * a.ldz, lane);
     return;
   }
-  wave_lds_sync();
   float u[MA_H][M], qv[MA_H][MA_E], cv[M][MA_B], unused[M][MA_B];
   mid_head_row(a, a.U + qrow * a.ldz, lane, u);
   mid_head_vec(a, a.P + qrow * a.ldp + a.off_q, lane, qv);
   const MidTime<M> tm = mid_time<M>(a, lane);
   const float scale = 1.0f / sqrtf((float)c);
-  for (int j0 = 0; j0 < c; j0 += MA_B) {
+  mid_sync<W>();
+  for (int j0 = part * MA_B; j0 < c; j0 += W * MA_B) {
     const MidSlots q = mid_slots(L, j0, c);
     mid_cols<false, M>(a, lane, q, tm, cv, unused);
     mid_scores(a, lane, j0, c, q, cv, u, qv, 0, scale, L.sa);
   }
-  wave_lds_sync();
-  softmax_heads(L.sa, HK, a.k, c, lane, pr);
-  wave_lds_sync();
+  mid_sync<W>();
+  if (part == 0) softmax_heads(L.sa, HK, a.k, c, lane, pr);
+  mid_sync<W>();
+  const unsigned rounds = mid_rounds<M, W>(part);
+  const bool nodes = mid_nodes<M, W>(part);
   int he[MA_E];
 #pragma unroll
   for (int t = 0; t < MA_E; ++t) he[t] = min(lane + 64 * t, a.dO - 1) / a.dh;
@@ -1061,8 +1080,8 @@ template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(Fus
     for (int t = 0; t < MA_E; ++t)
 #pragma unroll
       for (int i = 0; i < MA_B; ++i)
-        pv[t][i] = 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + a.dO + min(lane + 64 * t, a.dO - 1)] : 0.f;
-    mid_cols<false, M>(a, lane, q, tm, cv, unused);
+        pv[t][i] = nodes && 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + a.dO + min(lane + 64 * t, a.dO - 1)] : 0.f;
+    mid_cols<false, M>(a, lane, q, tm, cv, unused, rounds);
 #pragma unroll
     for (int i = 0; i < MA_B; ++i) {
       const int j = min(j0 + i, c - 1);
@@ -1077,37 +1096,37 @@ template <int M> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(Fus
         if (h >= a.H) break;
         const float w = L.sa[HK + h * a.k + j], p = on ? w : 0.f;
 #pragma unroll
-        for (int m = 0; m < M; ++m) z[h][m] += p * cv[m][i];
+        for (int m = 0; m < M; ++m)
+          if (rounds >> m & 1u) z[h][m] += p * cv[m][i];
       }
     }
   }
 #pragma unroll
   for (int t = 0; t < MA_E; ++t)
-    if (lane + 64 * t < a.dO) out[lane + 64 * t] = o[t];
+    if (nodes && lane + 64 * t < a.dO) out[lane + 64 * t] = o[t];
   float* zrow = a.Zp + (size_t)r * a.ldz;
 #pragma unroll
   for (int h = 0; h < MA_H; ++h)
 #pragma unroll
     for (int m = 0; m < M; ++m)
-      if (h < a.H && lane + 64 * m < a.dcp) zrow[h * a.dcp + lane + 64 * m] = z[h][m];
+      if ((rounds >> m & 1u) && h < a.H && lane + 64 * m < a.dcp) zrow[h * a.dcp + lane + 64 * m] = z[h][m];
 }
 
-template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
+template <int M, int W> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
   warm_kernargs<6>();
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int r = blockIdx.x * 4 + wave;
+  const int r = W == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
   if (r >= a.R) return;
-  const int HK = a.H * a.k, dc = a.de + a.dt;
-  GenLds L = gen_lds(lds_raw, wave, a.k, a.H);
+  const int HK = a.H * a.k, dc = a.de + a.dt, part = W == 1 ? 0 : wave;
+  GenLds L = gen_lds(lds_raw, W == 1 ? wave : 0, a.k, a.H);
   const int c = __builtin_amdgcn_readfirstlane(a.cnt[r]);
   float* yrow = a.Y + (size_t)r * a.ldy;
   if (c == 0) {
-    gen_bwd_empty(a, r, lane, HK, yrow);
+    if (part == 0) gen_bwd_empty(a, r, lane, HK, yrow);
     return;
   }
-  gen_bwd_load(a, r, c, lane, HK, L);
-  wave_lds_sync();
+  if (part == 0) gen_bwd_load(a, r, c, lane, HK, L);
   const size_t qrow = a.slot_row != nullptr ? (size_t)a.slot_row[r] : (size_t)r;
   const float* qv = a.P + qrow * a.ldp + a.off_q;
   float u[MA_H][M], g[MA_H][M], dv[MA_H][MA_E], cv[M][MA_B], sv[M][MA_B];
@@ -1115,14 +1134,17 @@ template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(Fus
   mid_head_row(a, a.G + (size_t)r * a.ldz, lane, g);
   mid_head_vec(a, a.dOmat + (size_t)r * a.ldh, lane, dv);
   const MidTime<M> tm = mid_time<M>(a, lane);
-  for (int j0 = 0; j0 < c; j0 += MA_B) {
+  mid_sync<W>();
+  for (int j0 = part * MA_B; j0 < c; j0 += W * MA_B) {
     const MidSlots q = mid_slots(L, j0, c);
     mid_cols<false, M>(a, lane, q, tm, cv, sv);
     mid_scores(a, lane, j0, c, q, cv, g, dv, a.dO, 1.0f, L.sa + HK);
   }
-  wave_lds_sync();
-  gen_softmax_bwd(a, r, c, lane, HK, L);
-  wave_lds_sync();
+  mid_sync<W>();
+  if (part == 0) gen_softmax_bwd(a, r, c, lane, HK, L);
+  mid_sync<W>();
+  const unsigned rounds = mid_rounds<M, W>(part);
+  const bool nodes = mid_nodes<M, W>(part);
   int he[MA_E];
 #pragma unroll
   for (int t = 0; t < MA_E; ++t) he[t] = min(lane + 64 * t, a.dO - 1) / a.dh;
@@ -1140,8 +1162,8 @@ template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(Fus
     for (int t = 0; t < MA_E; ++t)
 #pragma unroll
       for (int i = 0; i < MA_B; ++i)
-        pk[t][i] = 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + min(lane + 64 * t, a.dO - 1)] : 0.f;
-    mid_cols<true, M>(a, lane, q, tm, cv, sv);
+        pk[t][i] = nodes && 64 * t < a.dO ? a.P[(size_t)q.row[i] * a.ldp + min(lane + 64 * t, a.dO - 1)] : 0.f;
+    mid_cols<true, M>(a, lane, q, tm, cv, sv, rounds);
 #pragma unroll
     for (int i = 0; i < MA_B; ++i) {
       const int j = min(j0 + i, c - 1);
@@ -1159,24 +1181,26 @@ template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(Fus
         if (h >= a.H) break;
         const float w = L.sa[HK + h * a.k + j], x = L.sa[h * a.k + j], ds = on ? w : 0.f, p = on ? x : 0.f;
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-          z[h][m] += ds * cv[m][i];
-          dphi[m] += ds * u[h][m] + p * g[h][m];
-        }
+        for (int m = 0; m < M; ++m)
+          if (rounds >> m & 1u) {
+            z[h][m] += ds * cv[m][i];
+            dphi[m] += ds * u[h][m] + p * g[h][m];
+          }
       }
       const float dtf = (float)q.dt[i];
 #pragma unroll
-      for (int m = 0; m < M; ++m) {
-        const float t = -dphi[m] * sv[m][i];
-        yb[m] += t;
-        yw[m] += t * dtf;
-      }
+      for (int m = 0; m < M; ++m)
+        if (rounds >> m & 1u) {
+          const float t = -dphi[m] * sv[m][i];
+          yb[m] += t;
+          yw[m] += t * dtf;
+        }
     }
   }
 #pragma unroll
   for (int t = 0; t < MA_E; ++t) {
     const int e = lane + 64 * t;
-    if (e < a.dO) {
+    if (nodes && e < a.dO) {
       a.dqn[(size_t)r * a.ldh + e] = dq[t];
       a.Qroot[(size_t)r * a.ldh + e] = qv[e];
     }
@@ -1185,6 +1209,7 @@ template <int M> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(Fus
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     const int col = lane + 64 * m;
+    if (!(rounds >> m & 1u)) continue;
 #pragma unroll
     for (int h = 0; h < MA_H; ++h)
       if (h < a.H && col < a.dcp) zrow[h * a.dcp + col] = z[h][m];
@@ -1200,6 +1225,13 @@ static bool mid_path(const FusedAttn& a) {
   return !a.force_generic && a.H <= MA_H && a.dcp <= 64 * MA_M && a.dO <= 64 * MA_E;
 }
 
+// A workgroup per root (see above) or a wavefront per root.  The four wavefronts ask for the root's own rows four times over, the
+// more columns the dearer, and a compute unit holds four roots at a time instead of sixteen.  Step times in us, workgroup / wavefront:
+//   one round of columns   (1 head, 20 neighbours)    106 / 119 (192 roots), 131 / 139 (999), 165 / 154 (2,100)
+//   two                    (3 heads, 17)              124 / 140,             147 / 156,       202 / 183
+//   five                   (4 heads, 11)              149 / 161,             207 / 183,       293 / 238
+static bool mid_few(const FusedAttn& a) { return a.R <= (a.dcp <= 64 ? 1500 : a.dcp <= 128 ? 1200 : 400); }
+
 static bool fast_path(const FusedAttn& a) {
   return !a.force_generic && a.k <= FA_KR && a.de <= 64 * FA_NE && a.dt <= 64 * FA_NT && a.dO <= 64 * FA_E &&
          a.H <= FA_HM && a.H * a.k <= 64;
@@ -1212,8 +1244,9 @@ void fattn_fwd(const FusedAttn& a, hipStream_t s) {
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_fwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);
   else if (mid_path(a))
-    hipLaunchKernelGGL(a.dcp <= 64 ? fattn_fwd_mid_kernel<1> : a.dcp <= 128 ? fattn_fwd_mid_kernel<2> : fattn_fwd_mid_kernel<MA_M>, grid,
-                       dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
+    hipLaunchKernelGGL(mid_few(a) ? (a.dcp <= 64 ? fattn_fwd_mid_kernel<1, 4> : a.dcp <= 128 ? fattn_fwd_mid_kernel<2, 4> : fattn_fwd_mid_kernel<MA_M, 4>)
+                                  : (a.dcp <= 64 ? fattn_fwd_mid_kernel<1, 1> : a.dcp <= 128 ? fattn_fwd_mid_kernel<2, 1> : fattn_fwd_mid_kernel<MA_M, 1>),
+                       mid_few(a) ? dim3(a.R + fill_blocks) : grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
   else
     hipLaunchKernelGGL(fattn_fwd_gen_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
 }
@@ -1224,8 +1257,9 @@ void fattn_bwd(const FusedAttn& a, hipStream_t s) {
   if (fast_path(a))
     hipLaunchKernelGGL(fattn_bwd_fast_kernel, grid, dim3(256), 4 * sizeof(float) * fattn_lds_floats(a.k, a.H), s, a);
   else if (mid_path(a))
-    hipLaunchKernelGGL(a.dcp <= 64 ? fattn_bwd_mid_kernel<1> : a.dcp <= 128 ? fattn_bwd_mid_kernel<2> : fattn_bwd_mid_kernel<MA_M>, grid,
-                       dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
+    hipLaunchKernelGGL(mid_few(a) ? (a.dcp <= 64 ? fattn_bwd_mid_kernel<1, 4> : a.dcp <= 128 ? fattn_bwd_mid_kernel<2, 4> : fattn_bwd_mid_kernel<MA_M, 4>)
+                                  : (a.dcp <= 64 ? fattn_bwd_mid_kernel<1, 1> : a.dcp <= 128 ? fattn_bwd_mid_kernel<2, 1> : fattn_bwd_mid_kernel<MA_M, 1>),
+                       mid_few(a) ? dim3(a.R) : grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
   else
     hipLaunchKernelGGL(fattn_bwd_gen_kernel, grid, dim3(256), 4 * gattn_lds_bytes(a.k, a.H), s, a);
 }

@@ -63,3 +63,27 @@ def test_middle_path_equals_the_generic_path(shape):
     for n in ("wv", "bv", "wo", "bo", "wq", "wk", "time_w", "time_b"):
         floor = 16 * 2.0 ** -24 * float(cache["abs_terms"][n].max()) if n in cache["abs_terms"] else 0.0
         assert np.abs(g0[n] - g[n]).max() <= 2e-5 * np.abs(g[n]).max() + floor, n
+
+
+# roots on both sides of where a workgroup per root gives way to a wavefront per root, in the kernels of one, two and five rounds
+@pytest.mark.parametrize("shape,R", [((32, 8, 0, 1, 11), 1500), ((32, 8, 0, 1, 11), 1501), ((36, 50, 33, 3, 17), 1200),
+                                     ((36, 50, 33, 3, 17), 1201), ((40, 100, 186, 4, 11), 400), ((40, 100, 186, 4, 11), 401)])
+def test_middle_path_row_counts(shape, R):
+    from paper_2307_07649_amd import tgnn
+    dm, dt_, de, H, k = shape
+    d = synth.ModelDims(n_nodes=50, d_mem=dm, d_time=dt_, d_edge=de, d_static=0, n_heads=H, k=k, batch=R)
+    params = tgnn.Params.from_numpy(synth.gen_params(d, seed=3, random_phase=True))
+    rng = np.random.default_rng(R)
+    x_root, x_nbr = (dev(rng.uniform(-1, 1, (n, dm)).astype(np.float32)) for n in (R, R * k))
+    e, dt = dev(rng.standard_normal((R * k, de)).astype(np.float32)), dev(rng.uniform(0, 3e5, R * k))
+    cnt = dev(rng.integers(0, k + 1, R).astype(np.int32))
+    dz = dev(rng.standard_normal((R, dm)).astype(np.float32))
+    out = []
+    for flags in (0, tgnn.FLAG_GENERIC_ATTN):
+        ctx = tgnn.Context(d.n_nodes, dm, dt_, de, 0, H, k, R, flags=flags)
+        z = ctx.tgnn_temporal_attn_fwd(params, x_root, x_nbr, e, dt, cnt).cpu().numpy()
+        dr, dn = ctx.tgnn_temporal_attn_bwd(params, dz, tgnn.Params.zeros_like(params))
+        out.append((z, dr.cpu().numpy(), dn.cpu().numpy()))
+    (z0, r0, n0), (z1, r1, n1) = out
+    assert np.array_equal(z0, z1)
+    assert rel_err(r0, r1) <= 2e-6 and rel_err(n0, n1) <= 2e-6   # (as above)
