@@ -1013,20 +1013,24 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const auto& q = gp->p[pi];
 #ifdef __HIP_DEVICE_COMPILE__
   {   // (the problem's cache lines at once, see warm_kernargs)
-    static_assert(sizeof(TnProblem) > 128 && sizeof(TnProblem) <= 192, "three or four lines");
-    unsigned d0, d1, d2, d3;
-    asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\ts_load_dword %3, %4, %5\n\t"
-                 "s_waitcnt lgkmcnt(0)" : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3) : "s"(&gp->p[pi]), "i"(sizeof(TnProblem) - 4));
+    static_assert(sizeof(TnProblem) > 192 && sizeof(TnProblem) <= 256, "four or five lines");
+    unsigned d0, d1, d2, d3, d4;
+    asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
+                 "s_load_dword %4, %5, %6\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3), "=&s"(d4) : "s"(&gp->p[pi]), "i"(sizeof(TnProblem) - 4));
   }
 #endif
-  const int v = (xcd + q.rot) & 7;
   const int tiles = q.tiles, chunks = q.chunks, N = q.N, K = q.K;
   int M = q.M, m_chunk = q.m_chunk;
   const int* m_dev = q.m_dev;
   float* const bias0 = q.out.bias[0];
   const bool with_bias = bias0 != nullptr || q.out.bias[1] != nullptr;
-  const int chunk = (local / tiles) * 8 + v;
-  int tile = local % tiles;
+  unsigned long long mine = q.mine[xcd];
+  const int nth = local / tiles;
+  for (int i = 0; i < nth; ++i) mine &= mine - 1ull;
+  if (mine == 0ull) return;   // (never: the queue ends with the last chunk's tiles)
+  const int chunk = __builtin_ctzll(mine);
+  int tile = local - nth * tiles;
   if (m_dev != nullptr) {  // row count known only on the device: split it evenly over the launched chunks
     M = min(M, load_count(m_dev));
     m_chunk = ((M + chunks - 1) / chunks + TN_ROWS - 1) / TN_ROWS * TN_ROWS;
@@ -1099,55 +1103,49 @@ void TnBatch::add(const float* D, int ldd, const float* A, int lda, int M, int N
 // Chunking and placement.  A workgroup's life is a first wait for data, its share of the rows at the pace at which its
 // compute unit's loads come in, and a reduction with one float atomic per tile element.  An XCD holds 64 workgroups at
 // once (two per compute unit) and takes the rest of its queue as these end, so what a chunk length costs is decided by
-// rounds: on a 600-event step queues of 66 workgroups take 18 us, of 84 29 us; on the classification head's 4,000 events
-// queues of 77 long ones 74 us, of 96 shorter ones 59 us.  The rule is the shortest chunks with which no queue exceeds
-// TN_QUEUE workgroups (chunks of TN_BASE_ROWS if that cannot be), unless a walk of the most loaded XCD's queue
+// rounds.  The rule is the shortest chunks with which no queue exceeds TN_QUEUE workgroups, a round (chunks of TN_BASE_ROWS if
+// that cannot be), unless a walk of the most loaded XCD's queue
 // (tn_makespan) finds another length more than 15 % faster: the walk's constants are fitted to 18 launches of five shapes
 // and its error is up to 20 %, so smaller differences mean nothing (taken for them, 80 -> 86 us on 4,000 events, 18.6 ->
-// 21.9 on 600).  All problems of a launch use the same chunk length.  With the walk: classification 77 -> 60 us, stand-alone
-// backward call 49 -> 36 us, a 333-event step of odd widths 21 -> 15 us.
+// 21.9 on 600).  All problems of a launch use the same chunk length.  Queues of at most 60 / 64 / 80, launches in us: 4,000 events
+// 69.8 / 69.8 / 70.0, edge classes 50.1 / 50.5 / 54.7, no edge features 19.8 / 20.8 / 19.8, four negative sets 26.9 / 27.2 /
+// 27.2, stand-alone backward call 34.0 / 35.2 / 35.4, 600 events 20.2 all, eight replicas 110 all.
 // What in-kernel timestamps say about such a launch: a workgroup sees its first rows 3 to 5 us after it starts
 // (argument block, device-side row count, then the rows: three dependent round trips); the reduction and the atomics
 // take 2 to 3 us.  Four wavefronts per workgroup, two workgroups per compute unit: one's reduction runs beside the
 // other's products (eight: 108 against 90 us on a 4,000-event step, 21.7 against 18.3 us on a 600-event one, both with
 // chunks of 1,024 rows at most).
 constexpr int TN_SLOTS = 64;            // workgroups an XCD holds at once
-constexpr int TN_QUEUE = 80, TN_BASE_ROWS = 2048;
+constexpr int TN_QUEUE = 60, TN_BASE_ROWS = 2048;
 constexpr float TN_PLAN_GAIN = 0.85f;
 constexpr float TN_COST_WG = 8.0f;      // us: start, reduction, atomics
 constexpr float TN_COST_ROW = 0.020f;   // us per row of a 64 x 64 tile
 constexpr float TN_COST_LOADS = 0.3f;   // share of that which follows the columns loaded, the rest follows the products
 
-// Chunks of `rows_per_chunk` rows for every problem, then the placement on the eight XCDs: problems in order
-// of decreasing size, each rotated so that the XCDs which receive one chunk more than the others are the least
-// loaded ones so far.  Returns the length of the longest XCD queue.
+// Chunks of `rows_per_chunk` rows for every problem, then the placement on the eight XCDs: chunks in order of decreasing
+// size (tiles), each to the least loaded XCD so far.  (Dealt out in turn, chunk c to XCD (c + rotation) % 8, the longest queue
+// was up to a fifth longer than the mean: 79 instead of 70 us on 4,000 events, 116 instead of 110 on eight replicas.)  Returns
+// the length of the longest XCD queue.
+constexpr int TN_MAX_CHUNKS = 64;   // a bit each
 static int tn_place(TnGroup& g, const int* rows, int rows_per_chunk) {
   for (int i = 0; i < g.n; ++i) {
     TnProblem& p = g.p[i];
-    int chunks = (rows[i] + rows_per_chunk - 1) / rows_per_chunk;
+    int chunks = std::min((rows[i] + rows_per_chunk - 1) / rows_per_chunk, TN_MAX_CHUNKS);
     p.m_chunk = ((p.M + chunks - 1) / chunks + TN_ROWS - 1) / TN_ROWS * TN_ROWS;
     if (p.m_dev == nullptr) chunks = (p.M + p.m_chunk - 1) / p.m_chunk;
     p.chunks = chunks;
   }
   int order[TN_MAX_GROUP], load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   for (int i = 0; i < g.n; ++i) order[i] = i;
-  std::sort(order, order + g.n, [&](int a, int b) { return g.p[a].tiles * g.p[a].chunks > g.p[b].tiles * g.p[b].chunks; });
+  std::sort(order, order + g.n, [&](int a, int b) { return g.p[a].tiles != g.p[b].tiles ? g.p[a].tiles > g.p[b].tiles : a < b; });
   for (int oi = 0; oi < g.n; ++oi) {
     TnProblem& p = g.p[order[oi]];
-    int cnt[8];
-    for (int v = 0; v < 8; ++v) cnt[v] = p.chunks > v ? p.tiles * ((p.chunks - v + 7) / 8) : 0;
-    int best_rot = 0, best_max = 1 << 30;
-    for (int r = 0; r < 8; ++r) {
-      int mx = 0;
-      for (int x = 0; x < 8; ++x) mx = std::max(mx, load[x] + cnt[(x + r) & 7]);
-      if (mx < best_max) { best_max = mx; best_rot = r; }
-    }
-    p.rot = best_rot;
     g.qprob[oi] = (unsigned char)order[oi];
-    for (int x = 0; x < 8; ++x) {
-      p.lane_begin[x] = load[x];
-      g.qbegin[x][oi] = load[x];
-      load[x] += cnt[(x + best_rot) & 7];
+    for (int x = 0; x < 8; ++x) { p.mine[x] = 0; g.qbegin[x][oi] = load[x]; }
+    for (int c = 0; c < p.chunks; ++c) {
+      const int x = (int)(std::min_element(load, load + 8) - load);
+      p.mine[x] |= 1ull << c;
+      load[x] += p.tiles;
     }
   }
   for (int x = 0; x < 8; ++x) {
@@ -1221,7 +1219,7 @@ static int tn_plan(TnGroup& g, const int* rows) {
   }
   for (const Plan& k : kept)
     if (memcmp(k.key, q.key, sizeof(q.key)) == 0) return k.units;
-  // the shortest chunks with which no queue exceeds TN_QUEUE (a round, and the narrow tiles' early ends)
+  // the shortest chunks with which no queue exceeds TN_QUEUE (a round)
   int lo = TN_MIN_UNITS, hi = TN_BASE_ROWS / TN_ROWS;   // hi: taken if nothing smaller fits
   if (tn_place(g, rows, hi * TN_ROWS) <= TN_QUEUE)
     while (lo < hi) {

@@ -370,10 +370,9 @@ struct TnProblem {
   int m_chunk, tiles, chunks;   // tiles: workgroups per chunk of rows
   int heads;                    // out.head_k > 0: number of per-head blocks (N / head_n), else 1
   // Placement of the workgroups (one per chunk and tile).  Workgroup b of the launch runs on XCD b % 8; the
-  // workgroups of XCD x form a queue of their own (position b / 8), in which this problem's start at
-  // lane_begin[x].  XCD x works on the chunks v, v + 8, ... with v = (x + rot) % 8, all tiles of a chunk in a
-  // row, so that the rows of a chunk are fetched into one L2 only.
-  int rot, lane_begin[8];
+  // workgroups of XCD x form a queue of their own (position b / 8).  XCD x works on the chunks in mine[x] (a bit each),
+  // all tiles of a chunk in a row, so that the rows of a chunk are fetched into one L2 only.
+  unsigned long long mine[8];
   OutMap out;
 };
 constexpr int TN_MAX_GROUP = 10;
