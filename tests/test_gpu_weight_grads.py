@@ -51,3 +51,9 @@ def test_weight_gradients(widths, R):
         floor = 16 * 2.0 ** -24 * float(cache["abs_terms"][n].max()) if n in cache["abs_terms"] else 0.0
         err = float(np.abs(gg[n] - g[n]).max())
         assert err <= GRAD_TOL * float(np.abs(g[n]).max()) + floor, (n, err, float(np.abs(g[n]).max()))
+
+
+# narrow tiles over so many rows that the shortest chunks would be more than the 64 a problem may have
+@pytest.mark.parametrize("widths,R", [((8, 2, 1, 1), 2400), ((4, 1, 0, 2), 1700)])
+def test_weight_gradients_many_chunks(widths, R):
+    test_weight_gradients(widths, R)
