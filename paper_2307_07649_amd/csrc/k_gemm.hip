@@ -39,28 +39,21 @@ constexpr int NT_P = 32;
 // operand reads), or the eight chunks of two consecutive rows (stage stores), then cover all 64 banks once.
 __device__ __forceinline__ int nt_swz(int row, int chunk) { return row * NT_P + ((chunk ^ ((row >> 1) & 7)) << 2); }
 
-template <int TN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (TN <= 5 ? 4 : 2)))) void gemm_nt_kernel(NtGroup grp) {
+// The argument block is read through the kernel-argument segment (scalar loads at a computed offset).
+typedef const NtGroup __attribute__((address_space(4))) * NtGroupPtr;
+// Floats of LDS that a tile of TN column blocks takes: two stage buffers of A and of B; the finished tile is staged in the same
+// memory for its row-wise stores.
+template <int TN> constexpr int nt_lds() { return 2 * (NT_BM + 16 * TN) * NT_P; }
+
+// One tile of problem pi: workgroup `block` of the ones that the problem has, `col_tiles` tiles of columns, M rows.
+template <int TN> __device__ __forceinline__ void nt_tile(const NtGroupPtr gp, int pi, int block, int col_tiles, int M, float* smem) {
   constexpr int BM = NT_BM, BN = 16 * TN;
-  warm_kernargs<12>();
-  if ((int)blockIdx.x >= grp.gemm_wgs) {   // passengers after the products' workgroups: write-back scatter + SGD
-    wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
-    return;
-  }
-  // Up to two independent problems share a launch; the second one's workgroups follow the first one's.
-  // The argument block is read through the kernel-argument segment (scalar loads at a computed offset).
-  typedef const NtGroup __attribute__((address_space(4))) * GroupPtr;
-  const GroupPtr gp = (GroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
   const auto& q = gp->p[pi];
   const float* __restrict__ A = q.A;
   const float* __restrict__ B = q.B;
   const float* __restrict__ bias = q.bias;
   float* __restrict__ C = q.C;
   const int lda = q.lda, ldb = q.ldb, ldc = q.ldc, N = q.N, Kp = q.Kp, n_store = q.n_store, relu = q.relu;
-  const int col_tiles = q.col_tiles;
-  int M = q.M;
-  const int* m_dev = q.m_dev;
   RowAdd add;
   add.src = q.add.src; add.index = q.add.index; add.ld = q.add.ld; add.row0 = q.add.row0;
   add.gate = q.add.gate; add.ld_gate = q.add.ld_gate;
@@ -71,15 +64,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (TN <= 5
   gb.dm = q.gb.dm; gb.ldh = q.gb.ldh; gb.ld3 = q.gb.ld3;
   // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  The column tiles of one row tile
   // read the same rows of A, so they are given consecutive slots of one XCD.
-  const int block = (int)blockIdx.x - q.wg_begin;   // wg_begin is a multiple of 8
   const int xcd = block & 7, slot = block >> 3;
   const int row_tile = (slot / col_tiles) * 8 + xcd, col_tile = slot % col_tiles;
-  if (m_dev != nullptr) M = min(M, load_count(m_dev));
   if (row_tile * BM >= M) return;   // uniform for the workgroup, before any barrier
   constexpr int A_PER = BM * 8 / 256, B_F4 = BN * 8;  // float4 loads per stage and thread
   constexpr int B_PER = (B_F4 + 255) / 256;
-  // two stage buffers of A and of B; the finished tile is staged in the same memory for its row-wise stores
-  __shared__ __attribute__((aligned(16))) float smem[2 * (BM + BN) * NT_P];
   float (*As)[BM * NT_P] = reinterpret_cast<float (*)[BM * NT_P]>(smem);
   float (*Bs)[BN * NT_P] = reinterpret_cast<float (*)[BN * NT_P]>(smem + 2 * BM * NT_P);
 
@@ -391,7 +380,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (TN <= 5
 }
 
 // ------------------------------------------------------------------------------------------------
-// NT for few rows, the same sums in the same order.  With a few thousand rows the kernel above is a chain of latencies: it
+// NT for few rows, the same sums in the same order.  With a tile per compute unit or less the kernel above is a chain of latencies: it
 // waits for two stages of 32 columns at a time, 0.4 us each whatever the tile, thirteen of them for the widest product of a
 // 600-event step.  Here a wavefront's rows of A are its own: it asks for a chunk of four stages at once and for the next one as
 // it goes, and changes their order to the MFMAs' in 2 KB of LDS that no other wavefront touches (the LDS takes a
@@ -400,10 +389,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, (TN <= 5
 // wave + li), and what its epilogue needs is asked for before the last chunk, 16 bytes at a time.
 // Launches of a 600-event step: 8.2, 10.3 and 8.9 -> 7.0 to 7.9 us.  Tried: operands from memory in the MFMAs' order without LDS
 // (four neighbouring lanes ask for pieces of four rows, the L1 takes four times as long: 10.9 us); every wavefront its own rows of
-// B (8.0); four parts of the k range on sixteen wavefronts (9.0: four times the loads of B).  On many rows the kernel above is
-// faster, with 30,600 by 15 %: this one's registers leave three wavefronts per SIMD on tiles of 32 columns.
+// B (8.0); four parts of the k range on sixteen wavefronts (9.0: four times the loads of B).  With more tiles the kernel above is
+// faster (see nt_tile_blocks): this one's registers leave three wavefronts per SIMD on tiles of 32 columns.
 // ------------------------------------------------------------------------------------------------
 constexpr int NT_CHUNK = 4;   // stages of 32 columns per chunk
+constexpr int NT_FEW_TURN = 4 * 512, NT_FEW_LDS = NT_FEW_TURN + 2 * 16 * 32 * NT_CHUNK;   // floats of LDS: rows of A, two chunks of B
 
 __device__ __forceinline__ bool aligned4(const void* p, int ld) { return ((reinterpret_cast<size_t>(p) & 15) | (ld & 3)) == 0; }
 // four consecutive floats of which `live` exist (the others read as zero)
@@ -431,25 +421,15 @@ __device__ __forceinline__ float row_sum(float x) {
   return dpp_add<0x121>(x);
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_few_kernel(NtGroup grp) {
+// (arguments as in nt_tile)
+__device__ __forceinline__ void nt_few_tile(const NtGroupPtr gp, int pi, int block, int col_tiles, int M, float* smem) {
   constexpr int D = NT_CHUNK, KC = 32 * NT_CHUNK;
-  warm_kernargs<12>();
-  if ((int)blockIdx.x >= grp.gemm_wgs) {   // passengers, as above
-    wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
-    return;
-  }
-  typedef const NtGroup __attribute__((address_space(4))) * GroupPtr;
-  const GroupPtr gp = (GroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
   const auto& q = gp->p[pi];
-  const int N = q.N, n_store = q.n_store, col_tiles = q.col_tiles;
-  int M = q.M;
-  const int* m_dev = q.m_dev;
+  const int N = q.N, n_store = q.n_store;
   const float* __restrict__ A = q.A;
   const float* __restrict__ B = q.B;
-  const int block = (int)blockIdx.x - q.wg_begin, xcd = block & 7, slot = block >> 3;
+  const int xcd = block & 7, slot = block >> 3;
   const int row_tile = (slot / col_tiles) * 8 + xcd, col_tile = slot % col_tiles;
-  if (m_dev != nullptr) M = min(M, load_count(m_dev));
   if (row_tile * NT_BM >= M) return;   // uniform for the workgroup, before any barrier
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -478,8 +458,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   const float* pb[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) pb[u] = B + (size_t)min(n0 + 8 * u + br, N - 1) * q.ldb;
-  __shared__ __attribute__((aligned(16))) float turn[4][512], Bs[2][16 * KC];
-  float* const mine = turn[wave];
+  float (*const Bs)[16 * KC] = reinterpret_cast<float (*)[16 * KC]>(smem + NT_FEW_TURN);
+  float* const mine = smem + 512 * wave;
 
   floatx4 ra[D][2], rb[2], acc = floatx4{0.f, 0.f, 0.f, 0.f};
   struct Ops {
@@ -591,7 +571,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     // -sin(w_col delta + b_col) (the argument formed exactly as in the forward kernels); sums over the 16 rows of a
     // wavefront (row rotations) and the four wavefronts (LDS).
     __syncthreads();   // all wavefronts have read their last rows of A
-    float (*const red)[4][16] = reinterpret_cast<float (*)[4][16]>(&turn[0][0]);
+    float (*const red)[4][16] = reinterpret_cast<float (*)[4][16]>(smem);
     floatx4 sw = floatx4{0.f, 0.f, 0.f, 0.f}, sb = sw;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -658,26 +638,93 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
   if (row_live) store4(q.C + (size_t)row * q.ldc + col, acc, n_store - col, aligned4(q.C, q.ldc));
 }
 
-// Column-tile width in 16-wide MFMA blocks, from sweeps on MI355X: problems of a few thousand rows want the
-// narrowest tiles (many short workgroups, all resident at once), tens of thousands of rows want 2 blocks,
-// and only beyond that do wider tiles (less re-reading of A) pay off.
-static int nt_tile_blocks(int M, int n_store) {
-  const int nb = (n_store + 15) / 16;
-  int best = 1;
-  if (M > 4096 && M <= 65536) {
-#ifndef TGNN_NT_MID_TILE
-#define TGNN_NT_MID_TILE 2
-#endif
-    best = TGNN_NT_MID_TILE;
-  } else if (M > 65536) {
+// ------------------------------------------------------------------------------------------------
+// The launches.  Up to two independent problems share one; the second one's workgroups follow the first one's, and after both
+// come passengers: write-back scatter + SGD.
+// ------------------------------------------------------------------------------------------------
+__device__ __forceinline__ int nt_rows_of(const NtGroupPtr gp, int pi) {
+  const int* m_dev = gp->p[pi].m_dev;
+  return m_dev != nullptr ? min(gp->p[pi].M, load_count(m_dev)) : gp->p[pi].M;
+}
+__host__ __device__ inline int nt_cols16(int n_store) { return (n_store + 15) >> 4; }
+__host__ __device__ inline int nt_row_tiles(int M) { return (M + NT_BM - 1) >> 6; }
+static_assert(NT_BM == 64, "the shift above");
+__host__ __device__ inline int nt_wgs(int M, int col_tiles) { return col_tiles * ((nt_row_tiles(M) + 7) & ~7); }   // (whole rows of XCDs)
+
+template <int TN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((TN == 5 ? 3 : 1), (TN <= 5 ? 4 : 2)))) void gemm_nt_kernel(NtGroup grp) {
+  __shared__ __attribute__((aligned(16))) float smem[nt_lds<TN>()];
+  warm_kernargs<12>();
+  if ((int)blockIdx.x >= grp.gemm_wgs) return wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
+  const NtGroupPtr gp = (NtGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
+  nt_tile<TN>(gp, pi, (int)blockIdx.x - gp->p[pi].wg_begin, gp->p[pi].col_tiles, nt_rows_of(gp, pi), smem);
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_few_kernel(NtGroup grp) {
+  __shared__ __attribute__((aligned(16))) float smem[NT_FEW_LDS];
+  warm_kernargs<12>();
+  if ((int)blockIdx.x >= grp.gemm_wgs) return wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
+  const NtGroupPtr gp = (NtGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
+  nt_few_tile(gp, pi, (int)blockIdx.x - gp->p[pi].wg_begin, gp->p[pi].col_tiles, nt_rows_of(gp, pi), smem);
+}
+
+// Rows that are known on the device only (the problems' m_dev is the same): the kernel for few rows up to NT_FEW_COUNTED tiles,
+// tiles of 32 columns beyond, laid out for these.
+constexpr int NT_FEW_COUNTED = 512;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_counted_kernel(NtGroup grp) {
+  __shared__ __attribute__((aligned(16))) float smem[NT_FEW_LDS > nt_lds<2>() ? NT_FEW_LDS : nt_lds<2>()];
+  warm_kernargs<12>();
+  if ((int)blockIdx.x >= grp.gemm_wgs) return wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
+  const NtGroupPtr gp = (NtGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
+  // (no branches: they cost up to 0.4 us.  A problem that is not there has no columns, and begins behind all workgroups)
+  const int M = min(gp->p[0].M, load_count(gp->p[0].m_dev)), c0 = nt_cols16(gp->p[0].n_store), c1 = nt_cols16(gp->p[1].n_store);
+  const bool few = nt_row_tiles(M) * (c0 + c1) <= NT_FEW_COUNTED;
+  const int begin = few ? nt_wgs(M, c0) : gp->p[1].wg_begin, pi = (int)blockIdx.x >= begin ? 1 : 0;   // `begin` of the second problem
+  if (few && (int)blockIdx.x >= nt_wgs(M, c0 + c1)) return;
+  const int block = (int)blockIdx.x - (pi ? begin : 0);
+  if (few) nt_few_tile(gp, pi, block, pi ? c1 : c0, M, smem);
+  else nt_tile<2>(gp, pi, block, gp->p[pi].col_tiles, M, smem);
+}
+
+// Which kernel, as column blocks of 16 per tile; 0: the one for few rows, NT_COUNTED: on the device.
+// Rows known here: by the workgroups of 64 x 16 tiles, in whole rows of XCDs (kernels for few rows / one block / two blocks, us):
+//   up to one per compute unit, few rows    roots' output, 544 columns in, 256: 7.4 / 8.3 / 10.9; fewer columns in, up to 0.4 apart
+//   up to five, one block                   the same, 384: 10.3 / 9.6 / 11.2; GRU of d_m 200, 608: 14.3 / 13.6 / 13.8, 1,216: 20.3 / 17.7 / 19.7
+//   beyond, two blocks                      GRU of d_m 200, 1,824: 26.1 / 23.6 / 22.0, 4,864: 58.4 / 51.3 / 46.6
+// With more than 4,096 rows two blocks in any case, and with more than 65,536 wider ones still (less re-reading of A).
+// Rows counted on the device, in tiles of 64 x 16 (kernel for few rows / two blocks): GRU of d_m 144, 540: 12.6 / 12.3, 3,500 and
+// more: 36 / 28; memory gradient of d_m 200, 273: 15.2 / 16.7, 845: 25.9 / 23.4.  How many there are cannot be told from the
+// shapes: a step's 19,800 slots refer to 1,300 nodes on the power-law graphs and to 18,000 on a uniform one.  With up to eight
+// column blocks the memory gradient, whose GRU epilogue the kernel for few rows reads and writes 16 bytes at a time, takes that
+// one at any count (d_m 100: 7.0 / 11.9 on 600 rows, 34.7 / 37.3 on 19,000), and so does the time-encoding gradient as long as
+// there cannot be many rows (d_t 100: 6.2 / 8.4 on 600 rows, 16.6 / 16.0 on 9,500, 34.4 / 32.0 on 28,000; to choose on the device costs
+// it 0.7).
+constexpr int NT_COUNTED = -1, NT_FEW = 256, NT_ONE = 1280, NT_FEW_TG = 2048;
+static int nt_tile_blocks(const NtProblem* p, int n) {
+  const int M = p[0].M, rows = p[0].rows_est > 0 ? std::min(p[0].rows_est, M) : M, nb = nt_cols16(p[0].n_store);
+  const bool counted = p[0].m_dev != nullptr && (n == 1 || (p[1].m_dev == p[0].m_dev && p[1].M == M));
+  if (rows > 65536) {
+    int best = 1;
     float best_cost = 1e30f;
     static const int cand[] = {5, 4, 7, 2};
     for (int c : cand) {
       const float cost = (float)(((nb + c - 1) / c) * c) / nb;   // padded / useful columns
       if (cost < best_cost - 1e-6f) { best_cost = cost; best = c; }
     }
+    return best;
   }
-  return best;
+  int64_t tiles = 0, wgs = 0;
+  for (int i = 0; i < n; ++i) {
+    tiles += (int64_t)nt_row_tiles(p[i].M) * nt_cols16(p[i].n_store);
+    wgs += nt_wgs(p[i].M, nt_cols16(p[i].n_store));
+  }
+  if (counted) {
+    const bool narrow = n == 1 && nb <= 8 && (p[0].gb.dgi != nullptr || (p[0].tg.g_w != nullptr && tiles <= NT_FEW_TG));
+    return narrow || tiles <= NT_FEW_COUNTED ? 0 : NT_COUNTED;
+  }
+  return wgs <= NT_FEW ? 0 : M > 4096 || wgs > NT_ONE ? 2 : 1;
 }
 
 void gemm_nt_group(const NtProblem* probs, int n, hipStream_t s, const WbArgs* tail) {
@@ -688,27 +735,36 @@ void gemm_nt_group(const NtProblem* probs, int n, hipStream_t s, const WbArgs* t
     g.tail = *tail;
     tail_blocks = wb_total_blocks(*tail);
   }
-  int tn = 0, total = 0;
   for (int i = 0; i < n && g.n < 2; ++i) {
     NtProblem p = probs[i];
     if (p.M <= 0 || p.N <= 0) continue;
     if (p.n_store < p.N) p.n_store = p.N;
-    if (tn == 0) tn = nt_tile_blocks(p.rows_est > 0 ? std::min(p.rows_est, p.M) : p.M, p.n_store);   // the first problem decides the tile width
-    p.col_tiles = (p.n_store + 16 * tn - 1) / (16 * tn);
-    p.wg_begin = total;
-    total += p.col_tiles * (((p.M + NT_BM - 1) / NT_BM + 7) & ~7);
     g.p[g.n++] = p;
   }
   if (g.n == 0 && tail_blocks == 0) return;
+  const int tn = g.n > 0 ? nt_tile_blocks(g.p, g.n) : 0, width = tn == NT_COUNTED ? 2 : std::max(tn, 1);
+  int total = 0, cols = 0;
+  for (int i = 0; i < g.n; ++i) {
+    NtProblem& p = g.p[i];
+    p.col_tiles = (p.n_store + 16 * width - 1) / (16 * width);
+    p.wg_begin = total;
+    total += nt_wgs(p.M, p.col_tiles);
+    cols += nt_cols16(p.n_store);
+  }
+  if (tn == NT_COUNTED)   // (with few rows: the workgroups of NT_FEW_COUNTED tiles, in whole rows of XCDs)
+    total = std::max(total, cols * ((NT_FEW_COUNTED / cols + 7) & ~7));
   g.gemm_wgs = total;
+  if (g.n == 1) g.p[1].wg_begin = total;
   total += tail_blocks;
 #define TGNN_NT_CASE(TNV) \
-  case TNV: hipLaunchKernelGGL((gemm_nt_kernel<TNV>), dim3(total), dim3(256), 0, s, g); break;
+  case TNV: hipLaunchKernelGGL(gemm_nt_kernel<TNV>, dim3(total), dim3(256), 0, s, g); break
   switch (tn) {
-    TGNN_NT_CASE(7)
-    TGNN_NT_CASE(5)
-    TGNN_NT_CASE(4)
-    TGNN_NT_CASE(2)
+    TGNN_NT_CASE(7);
+    TGNN_NT_CASE(5);
+    TGNN_NT_CASE(4);
+    TGNN_NT_CASE(2);
+    TGNN_NT_CASE(1);
+    case NT_COUNTED: hipLaunchKernelGGL(gemm_nt_counted_kernel, dim3(total), dim3(256), 0, s, g); break;
     default: hipLaunchKernelGGL(gemm_nt_few_kernel, dim3(total), dim3(256), 0, s, g);
   }
 #undef TGNN_NT_CASE

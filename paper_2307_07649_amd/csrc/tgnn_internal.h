@@ -304,8 +304,8 @@ struct GruBwdOut {
 };
 void gemm_nt(const float* A, int lda, const float* B, int ldb, const float* bias, float* C, int ldc, int M,
              int N, int Kp, int n_store, bool relu, hipStream_t s, const RowAdd& add = RowAdd());
-// The same product as a record, so that two independent ones can share a launch (gemm_nt_group: the tile
-// width is chosen for the first problem; col_tiles and wg_begin are filled in by the launcher).
+// The same product as a record, so that two independent ones can share a launch (gemm_nt_group: one kernel
+// and tile width for both; col_tiles and wg_begin are filled in by the launcher).
 struct NtProblem {
   const float *A, *B, *bias;
   float* C;

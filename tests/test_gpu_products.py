@@ -1,12 +1,13 @@
-"""The fp32 products A B^T of the separate launches (gemm_nt_few_kernel up to 4,096 rows, gemm_nt_kernel beyond), through a
-memory update whose nodes are too wide for the node path: 32-column stages, chunks of four and an odd last 16 columns of the
-inner dimension, and both sides of every row count where tiles or kernels change."""
+"""The fp32 products A B^T of the separate launches, through a memory update whose nodes are too wide for the node path: 32-column
+stages, chunks of four and an odd last 16 columns of the inner dimension, and both sides of every row count where tiles or
+kernels change (gemm_nt_few_kernel, gemm_nt_kernel with tiles of 16 and of 32 columns; gemm_nt_counted_kernel, which chooses by a
+row count that only the device knows)."""
 import numpy as np
 import pytest
 import torch
 
 import synth
-from gpu_common import rel_err
+from gpu_common import GpuSide, OracleSide, batch_np, compare_state, compare_step, custom_problem, rel_err
 from oracle import tgnn_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -23,7 +24,7 @@ def dev(a):
 # inner dimension 2 * 130 + 1 + d_edge: 272 (17 slabs of 16), 273, 288 (nine whole stages), 289, 384 (three whole chunks), 385,
 # 1,029 (nine chunks, the last of one stage)
 @pytest.mark.parametrize("d_edge", [11, 12, 27, 28, 123, 124, 768])
-@pytest.mark.parametrize("n", [1, 16, 63, 64, 65, 4096, 4097])
+@pytest.mark.parametrize("n", [1, 16, 63, 64, 65, 1536, 1537, 4096, 4097])   # (52 tiles of 16 columns per 64 rows: one block up to 1,536)
 def test_wide_memory_update(d_edge, n):
     from paper_2307_07649_amd import tgnn
     d = synth.ModelDims(n_nodes=50, d_mem=130, d_time=1, d_edge=d_edge, d_static=0, n_heads=1, k=10, batch=130)
@@ -40,3 +41,26 @@ def test_wide_memory_update(d_edge, n):
     x = np.concatenate([mail, O.time_encode(mail_ts - mem_ts, p["time_w"], p["time_b"]), ef], axis=1).astype(np.float64)
     ref = O.gru_cell(x, mem.astype(np.float64), p["gru_wih"], p["gru_whh"], p["gru_bih"], p["gru_bhh"])
     assert rel_err(s.cpu().numpy(), np.where(has[:, None] > 0, ref, mem)) <= TOL
+
+
+# Steps whose distinct nodes are few or many beside the same bound on their number (kernel for few rows, tiles of 32 columns):
+# memory wider than the node path holds, where the GRU products are counted ones (52 tiles per 64 rows, the limit between 576 and
+# 577 rows), with the inner dimensions of above for the kernel for few rows; and a time encoding of ten column tiles, whose
+# gradient is one (limit between 3,264 and 3,265 rows).  Uniform graphs late in the stream: nearly every slot its own node.
+@pytest.mark.parametrize("d_mem,d_time,d_edge,n_nodes,batch,rows", [(130, 1, e, 577, 80, (513, 576)) for e in (11, 12, 27, 28, 123, 124, 768)]
+                         + [(130, 1, 3, 640, 120, (577, 640)), (130, 1, 3, 5000, 60, (1000, 1980)), (32, 130, 3, 4000, 160, (2000, 3264)),
+                            (32, 130, 3, 12000, 200, (3265, 6600))])
+def test_counted_rows(d_mem, d_time, d_edge, n_nodes, batch, rows):
+    first = 14 * n_nodes
+    P = custom_problem(n_nodes=n_nodes, E=first + 3 * batch, d_mem=d_mem, d_time=d_time, d_edge=d_edge, d_static=0, n_heads=2, k=10,
+                       batch=batch, seed=5)
+    G = GpuSide(P); Or = OracleSide(P)
+    seen = []
+    for s in range(3):
+        b = batch_np(P, first + s * batch, first + (s + 1) * batch)
+        g = G.step([b], lr=0.01)
+        o = Or.step([b], lr=0.01, gpu=g)
+        compare_step(g, o, label=f"counted rows {d_mem} {d_edge} {n_nodes} step {s}")
+        seen.append(len(np.unique(np.concatenate([b["src"], b["dst"], b["neg"], g["nbr"][g["nbr"] >= 0]]))))
+    assert rows[0] <= min(seen) and max(seen) <= rows[1], seen
+    compare_state(G.state_np(), Or.states[0])
