@@ -795,22 +795,12 @@ void gemm_nt(const float* A, int lda, const float* B, int ldb, const float* bias
 // and W_o (fp32 MFMA: 1.6e-7 to 2.5e-7).
 // The bias gradient rides along as column K of A, which the loader replaces by ones.
 // ------------------------------------------------------------------------------------------------
-constexpr int TT = 64;        // bulk tile edge
 #ifndef TGNN_TN_WAVES
 #define TGNN_TN_WAVES 4
 #endif
 constexpr int TN_W = TGNN_TN_WAVES;   // wavefronts per workgroup
 constexpr int TN_STEP = 32;   // rows per step of a wavefront: the depth of one MFMA
-constexpr int TN_ROWS = 32;   // row chunks are multiples of this
-constexpr int TN_MAX_ROWS = 4096, TN_MIN_UNITS = 4;   // longest chunk that the plan looks at, and the shortest (a step per wavefront)
 
-// A length is cut into 64-wide pieces plus one narrower one (16, 32 or again 64 wide) for the remainder.  (A remainder of
-// 33 .. 48 as a 32- and a 16-wide piece instead of a padded 64-wide one: fewer MFMAs, one more tile; measured on MI355X the
-// extra tile costs more than the padding, 83 against 77 us on 4,000 events.)
-__host__ __device__ inline int tn_pieces(int len) {
-  const int r = len % TT;
-  return len / TT + (r == 0 ? 0 : 1);
-}
 __device__ __forceinline__ void tn_piece(int len, int idx, int& off, int& width) {
   const int full = len / TT;
   if (idx < full) { off = idx * TT; width = TT; return; }
@@ -1053,8 +1043,8 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   // (a loop over the problems with its scalar loads one after the other took 5 us before the first row was asked for)
   typedef int int16v __attribute__((ext_vector_type(16)));
   typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-  const int16v qb = *reinterpret_cast<const int16v __attribute__((address_space(4)))*>(&gp->qbegin[xcd][0]);
-  const uint4v qp = *reinterpret_cast<const uint4v __attribute__((address_space(4)))*>(&gp->qprob[0]);
+  const int16v qb = *reinterpret_cast<const int16v __attribute__((address_space(4)))*>(&gp->plan.qbegin[xcd][0]);
+  const uint4v qp = *reinterpret_cast<const uint4v __attribute__((address_space(4)))*>(&gp->plan.qprob[0]);
   int slot = -1, begin = 0, end = 0;
 #pragma unroll
   for (int t = 0; t < TN_MAX_GROUP; ++t)
@@ -1067,30 +1057,30 @@ __global__ __launch_bounds__(64 * TN_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int pi = (word >> (8 * (slot & 3))) & 255u;
   const int local = pos - begin;
   const auto& q = gp->p[pi];
+  unsigned long long mine = 0;
+  int chunk_word = 0;
 #ifdef __HIP_DEVICE_COMPILE__
-  {   // (the problem's cache lines at once, see warm_kernargs)
-    static_assert(sizeof(TnProblem) > 192 && sizeof(TnProblem) <= 256, "four or five lines");
-    unsigned d0, d1, d2, d3, d4;
-    asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
-                 "s_load_dword %4, %5, %6\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3), "=&s"(d4) : "s"(&gp->p[pi]), "i"(sizeof(TnProblem) - 4));
+  {   // (with the problem's cache lines at once, see warm_kernargs)
+    static_assert(sizeof(TnProblem) > 128 && sizeof(TnProblem) <= 192, "three or four lines");
+    unsigned d0, d1, d2, d3;
+    asm volatile("s_load_dword %0, %6, 0x0\n\ts_load_dword %1, %6, 0x40\n\ts_load_dword %2, %6, 0x80\n\ts_load_dword %3, %6, %7\n\t"
+                 "s_load_dwordx2 %4, %8, 0x0\n\ts_load_dword %5, %9, 0x0\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(d0), "=&s"(d1), "=&s"(d2), "=&s"(d3), "=&s"(mine), "=&s"(chunk_word)
+                 : "s"(&gp->p[pi]), "i"(sizeof(TnProblem) - 4), "s"(&gp->plan.mine[xcd][pi]), "s"(&gp->plan.chunks[pi]));
   }
 #endif
-  const int tiles = q.tiles, chunks = q.chunks, N = q.N, K = q.K;
-  int M = q.M, m_chunk = q.m_chunk;
+  const int tiles = q.tiles, chunks = tn_chunks(chunk_word), shift = tn_shift(chunk_word), N = q.N, K = q.K;
+  int M = q.M;
   const int* m_dev = q.m_dev;
   float* const bias0 = q.out.bias[0];
   const bool with_bias = bias0 != nullptr || q.out.bias[1] != nullptr;
-  unsigned long long mine = q.mine[xcd];
   const int nth = local / tiles;
-  for (int i = 0; i < nth; ++i) mine &= mine - 1ull;
+  for (int i = 0; i < nth >> shift; ++i) mine &= mine - 1ull;
   if (mine == 0ull) return;   // (never: the queue ends with the last chunk's tiles)
-  const int chunk = __builtin_ctzll(mine);
+  const int chunk = (__builtin_ctzll(mine) << shift) + (nth & ((1 << shift) - 1));
   int tile = local - nth * tiles;
-  if (m_dev != nullptr) {  // row count known only on the device: split it evenly over the launched chunks
-    M = min(M, load_count(m_dev));
-    m_chunk = ((M + chunks - 1) / chunks + TN_ROWS - 1) / TN_ROWS * TN_ROWS;
-  }
+  if (m_dev != nullptr) M = min(M, load_count(m_dev));   // (the rows there are, split evenly over the launched chunks)
+  const int m_chunk = tn_chunk_rows(M, chunks);
   if (chunk * m_chunk >= M) return;   // uniform for the workgroup, before any barrier
   __shared__ __attribute__((aligned(16))) float lds[(TN_W / 2) * TT * TT + 4];   // reduction buffers + step counter
   int m_lo = chunk * m_chunk;
@@ -1156,162 +1146,22 @@ void TnBatch::add(const float* D, int ldd, const float* A, int lda, int M, int N
   g.n++;
 }
 
-// Chunking and placement.  A workgroup's life is a first wait for data, its share of the rows at the pace at which its
-// compute unit's loads come in, and a reduction with one float atomic per tile element.  An XCD holds 64 workgroups at
-// once (two per compute unit) and takes the rest of its queue as these end, so what a chunk length costs is decided by
-// rounds.  The rule is the shortest chunks with which no queue exceeds TN_QUEUE workgroups, a round (chunks of TN_BASE_ROWS if
-// that cannot be), unless a walk of the most loaded XCD's queue
-// (tn_makespan) finds another length more than 15 % faster: the walk's constants are fitted to 18 launches of five shapes
-// and its error is up to 20 %, so smaller differences mean nothing (taken for them, 80 -> 86 us on 4,000 events, 18.6 ->
-// 21.9 on 600).  All problems of a launch use the same chunk length.  Queues of at most 60 / 64 / 80, launches in us: 4,000 events
-// 69.8 / 69.8 / 70.0, edge classes 50.1 / 50.5 / 54.7, no edge features 19.8 / 20.8 / 19.8, four negative sets 26.9 / 27.2 /
-// 27.2, stand-alone backward call 34.0 / 35.2 / 35.4, 600 events 20.2 all, eight replicas 110 all.
-// What in-kernel timestamps say about such a launch: a workgroup sees its first rows 3 to 5 us after it starts
-// (argument block, device-side row count, then the rows: three dependent round trips); the reduction and the atomics
-// take 2 to 3 us.  Four wavefronts per workgroup, two workgroups per compute unit: one's reduction runs beside the
-// other's products (eight: 108 against 90 us on a 4,000-event step, 21.7 against 18.3 us on a 600-event one, both with
-// chunks of 1,024 rows at most).
-constexpr int TN_SLOTS = 64;            // workgroups an XCD holds at once
-constexpr int TN_QUEUE = 60, TN_BASE_ROWS = 2048;
-constexpr float TN_PLAN_GAIN = 0.85f;
-constexpr float TN_COST_WG = 8.0f;      // us: start, reduction, atomics
-constexpr float TN_COST_ROW = 0.020f;   // us per row of a 64 x 64 tile
-constexpr float TN_COST_LOADS = 0.3f;   // share of that which follows the columns loaded, the rest follows the products
-
-// Chunks of `rows_per_chunk` rows for every problem, then the placement on the eight XCDs: chunks in order of decreasing
-// size (tiles), each to the least loaded XCD so far.  (Dealt out in turn, chunk c to XCD (c + rotation) % 8, the longest queue
-// was up to a fifth longer than the mean: 79 instead of 70 us on 4,000 events, 116 instead of 110 on eight replicas.)  Returns
-// the length of the longest XCD queue.
-constexpr int TN_MAX_CHUNKS = 64;   // a bit each
-static int tn_place(TnGroup& g, const int* rows, int rows_per_chunk) {
-  for (int i = 0; i < g.n; ++i) {
-    TnProblem& p = g.p[i];
-    int chunks = std::min((rows[i] + rows_per_chunk - 1) / rows_per_chunk, TN_MAX_CHUNKS);
-    p.m_chunk = ((p.M + chunks - 1) / chunks + TN_ROWS - 1) / TN_ROWS * TN_ROWS;
-    if (p.m_dev == nullptr) chunks = (p.M + p.m_chunk - 1) / p.m_chunk;
-    p.chunks = chunks;
-  }
-  int order[TN_MAX_GROUP], load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int i = 0; i < g.n; ++i) order[i] = i;
-  std::sort(order, order + g.n, [&](int a, int b) { return g.p[a].tiles != g.p[b].tiles ? g.p[a].tiles > g.p[b].tiles : a < b; });
-  for (int oi = 0; oi < g.n; ++oi) {
-    TnProblem& p = g.p[order[oi]];
-    g.qprob[oi] = (unsigned char)order[oi];
-    for (int x = 0; x < 8; ++x) { p.mine[x] = 0; g.qbegin[x][oi] = load[x]; }
-    for (int c = 0; c < p.chunks; ++c) {
-      const int x = (int)(std::min_element(load, load + 8) - load);
-      p.mine[x] |= 1ull << c;
-      load[x] += p.tiles;
-    }
-  }
-  for (int x = 0; x < 8; ++x) {
-    g.qbegin[x][g.n] = load[x];
-    for (int t = g.n + 1; t < 16; ++t) g.qbegin[x][t] = 0x7fffffff;
-  }
-  return *std::max_element(load, load + 8);
-}
-
-// What the launch would take, after tn_place: the most loaded XCD's queue on TN_SLOTS slots, each taking the next workgroup
-// as it gets free.
-static float tn_makespan(const TnGroup& g, const int* rows) {
-  float cost[TN_MAX_GROUP][4][4], load[8];   // of a workgroup, by the widths of its tile in units of 16
-  int chunks_of[8][TN_MAX_GROUP];
-  for (int i = 0; i < g.n; ++i) {
-    const int r = (rows[i] + g.p[i].chunks - 1) / g.p[i].chunks;
-    for (int a = 0; a < 4; ++a)
-      for (int b = 0; b < 4; ++b)
-        cost[i][a][b] = TN_COST_WG + TN_COST_ROW * r * (TN_COST_LOADS * (a + b + 2) / 8.0f + (1.0f - TN_COST_LOADS) * (a + 1) * (b + 1) / 16.0f);
-  }
-  auto widths = [](int len, int idx) { const int r = len - idx * TT; return r > 32 ? 3 : r > 16 ? 1 : 0; };   // of piece idx, in 16s less one
-  auto each_tile = [&](int i, auto&& f) {
-    const TnProblem& p = g.p[i];
-    const bool heads = p.out.head_k > 0;
-    const int n = heads ? tn_head_width(p.out.head_n) : p.N;
-    const int k = (heads ? p.out.head_cols : p.K) + (p.out.bias[0] != nullptr || p.out.bias[1] != nullptr ? 1 : 0);
-    for (int h = 0; h < p.heads; ++h)
-      for (int a = 0; a < tn_pieces(n); ++a)
-        for (int b = 0; b < tn_pieces(k); ++b) f(cost[i][widths(n, a)][widths(k, b)]);
-  };
-  int worst = 0;
-  for (int x = 0; x < 8; ++x) {
-    load[x] = 0.f;
-    for (int o = 0; o < g.n; ++o) {
-      const int i = g.qprob[o];
-      chunks_of[x][o] = (g.qbegin[x][o + 1] - g.qbegin[x][o]) / g.p[i].tiles;
-      float sum = 0.f;
-      each_tile(i, [&](float c) { sum += c; });
-      load[x] += sum * chunks_of[x][o];
-    }
-    if (load[x] > load[worst]) worst = x;
-  }
-  float heap[TN_SLOTS] = {}, end = 0.f;   // when each slot gets free, smallest at the front
-  for (int o = 0; o < g.n; ++o)
-    for (int c = 0; c < chunks_of[worst][o]; ++c)
-      each_tile(g.qprob[o], [&](float t) {
-        std::pop_heap(heap, heap + TN_SLOTS, std::greater<float>());
-        heap[TN_SLOTS - 1] += t;
-        end = std::max(end, heap[TN_SLOTS - 1]);
-        std::push_heap(heap, heap + TN_SLOTS, std::greater<float>());
-      });
-  return end;
-}
-
-// The chunk length (in units of TN_ROWS) for a launch.  Depends on the problems' shapes only; the last few are remembered, per
-// thread, so that a program that calls an operator again does not walk the queues again.
-static int tn_plan(TnGroup& g, const int* rows) {
-  struct Plan {
-    int key[1 + 4 * TN_MAX_GROUP], units;
-  };
-  constexpr int KEEP = 8;
-  static thread_local Plan kept[KEEP] = {};
-  static thread_local int next = 0;
-  Plan q = {};
-  q.key[0] = g.n;
-  for (int i = 0; i < g.n; ++i) {
-    const TnProblem& p = g.p[i];
-    const bool bias = p.out.bias[0] != nullptr || p.out.bias[1] != nullptr;
-    q.key[1 + 4 * i] = rows[i]; q.key[2 + 4 * i] = p.N; q.key[3 + 4 * i] = 2 * p.K + (bias ? 1 : 0);
-    q.key[4 + 4 * i] = p.heads * 65536 + p.tiles;
-  }
-  for (const Plan& k : kept)
-    if (memcmp(k.key, q.key, sizeof(q.key)) == 0) return k.units;
-  // the shortest chunks with which no queue exceeds TN_QUEUE (a round)
-  int lo = TN_MIN_UNITS, hi = TN_BASE_ROWS / TN_ROWS;   // hi: taken if nothing smaller fits
-  if (tn_place(g, rows, hi * TN_ROWS) <= TN_QUEUE)
-    while (lo < hi) {
-      const int mid = (lo + hi) / 2;
-      if (tn_place(g, rows, mid * TN_ROWS) <= TN_QUEUE) hi = mid; else lo = mid + 1;
-    }
-  q.units = hi;
-  tn_place(g, rows, hi * TN_ROWS);
-  float best = TN_PLAN_GAIN * tn_makespan(g, rows);
-  // lengths whose chunk counts differ for the longest problem
-  const int most = *std::max_element(rows, rows + g.n);
-  int last = 0;
-  for (int chunks = std::max(1, (most + TN_MAX_ROWS - 1) / TN_MAX_ROWS); chunks <= 64; chunks += 1 + chunks / 6) {
-    const int units = std::max(TN_MIN_UNITS, ((most + chunks - 1) / chunks + TN_ROWS - 1) / TN_ROWS);
-    if (units == last) { if (units == TN_MIN_UNITS) break; continue; }
-    last = units;
-    tn_place(g, rows, units * TN_ROWS);
-    const float t = tn_makespan(g, rows);
-    if (t < best) { best = t; q.units = units; }
-  }
-  kept[next] = q;
-  next = (next + 1) % KEEP;
-  return q.units;
-}
-
 void TnBatch::launch(hipStream_t s) {
   if (g.n == 0) return;
-  int rows[TN_MAX_GROUP];
-  // a row count that lives on the device (distinct nodes of a step) is usually a small part of its bound
-  for (int i = 0; i < g.n; ++i)
-    rows[i] = g.p[i].m_dev == nullptr ? g.p[i].M
-              : dev_rows_est > 0      ? std::min(g.p[i].M, dev_rows_est)
-                                      : (g.p[i].M + 7) / 8;
-  const int longest = tn_place(g, rows, tn_plan(g, rows) * TN_ROWS);
-  const int total_wgs = 8 * longest;
-  hipLaunchKernelGGL(gemm_tn_kernel, dim3(total_wgs), dim3(64 * TN_W), 0, s, g);
+  TnShape shape[TN_MAX_GROUP];
+  for (int i = 0; i < g.n; ++i) {
+    const TnProblem& p = g.p[i];
+    const bool heads = p.out.head_k > 0, counted = p.m_dev != nullptr;
+    // a row count that lives on the device (distinct nodes of a step) is usually a small part of its bound
+    shape[i].rows = !counted ? p.M : dev_rows_est > 0 ? std::min(p.M, dev_rows_est) : (p.M + 7) / 8;
+    shape[i].counted = counted;
+    shape[i].n = heads ? tn_head_width(p.out.head_n) : p.N;
+    shape[i].k = (heads ? p.out.head_cols : p.K) + (p.out.bias[0] != nullptr || p.out.bias[1] != nullptr ? 1 : 0);
+    shape[i].heads = p.heads;
+    shape[i].tiles = p.tiles;
+  }
+  const int longest = tn_place(g.plan, shape, g.n, tn_chunk_units(shape, g.n) * TN_ROWS);
+  hipLaunchKernelGGL(gemm_tn_kernel, dim3(8 * longest), dim3(64 * TN_W), 0, s, g);
   g.n = 0;
 }
 
