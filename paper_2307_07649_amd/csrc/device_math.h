@@ -36,38 +36,53 @@ __device__ __forceinline__ float time_enc(double delta, float w, float b) {
   return c;
 }
 
-// Brings the first LINES x 64 bytes of the kernel's argument block into the scalar cache, all lines at once (as many as the
-// block has; the values are not used, and have come in when the asm block ends).  The block is cold, and wherever the
-// compiler first needs a field of it is a miss of its own: with several hundred bytes of arguments a chain of them.
-template <int LINES> __device__ __forceinline__ void warm_kernargs() {
+// Brings the kernel's explicit arguments into the scalar cache, all lines of them at once; `args`: the kernel's own parameters,
+// all of them, in their order.  (The values are not used, and have come in when the asm block ends.)  The argument block is
+// cold, and wherever the compiler first needs a field of it is a miss of its own: with several hundred bytes of arguments a
+// chain of them.  What lies behind the explicit arguments (block and grid sizes) is there only in kernels that use it; GRID asks for
+// its first word through the pointer that makes it be there.
+template <class... Args> constexpr int kernarg_bytes() {   // (each argument at its alignment)
+  size_t at = 0;
+  ((at = (at + alignof(Args) - 1) / alignof(Args) * alignof(Args) + sizeof(Args)), ...);
+  return (int)at;
+}
+// lines 0 .. 2 and so on, and the word behind the arguments, as one block
+#define TGNN_WARM_3 "s_load_dword %0, %16, 0x0\n\ts_load_dword %1, %16, 0x40\n\ts_load_dword %2, %16, 0x80\n\t"
+#define TGNN_WARM_5 TGNN_WARM_3 "s_load_dword %3, %16, 0xc0\n\ts_load_dword %4, %16, 0x100\n\t"
+#define TGNN_WARM_6 TGNN_WARM_5 "s_load_dword %5, %16, 0x140\n\t"
+#define TGNN_WARM_8 TGNN_WARM_6 "s_load_dword %6, %16, 0x180\n\ts_load_dword %7, %16, 0x1c0\n\t"
+#define TGNN_WARM_13 TGNN_WARM_8 "s_load_dword %8, %16, 0x200\n\ts_load_dword %9, %16, 0x240\n\ts_load_dword %10, %16, 0x280\n\t" \
+                     "s_load_dword %11, %16, 0x2c0\n\ts_load_dword %12, %16, 0x300\n\t"
+#define TGNN_WARM(LOADS)                                                                                                        \
+  asm volatile(LOADS "s_waitcnt lgkmcnt(0)"                                                                                     \
+               : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]), "=&s"(d[6]), "=&s"(d[7]), "=&s"(d[8]), \
+                 "=&s"(d[9]), "=&s"(d[10]), "=&s"(d[11]), "=&s"(d[12]), "=&s"(d[13]), "=&s"(d[14]), "=&s"(d[15])                \
+               : "s"(p), "s"(behind))
+template <bool GRID, class... Args> __device__ __forceinline__ void warm_kernarg_lines() {
 #ifdef __HIP_DEVICE_COMPILE__
+  constexpr int LINES = (kernarg_bytes<Args...>() + 63) / 64;
+  static_assert(LINES == 3 || LINES == 5 || LINES == 6 || LINES == 8 || LINES == 13, "spelled out above");
+  static_assert(!GRID || LINES == 8, "spelled out below");
   const auto p = __builtin_amdgcn_kernarg_segment_ptr();
-  unsigned d[LINES];
-  if constexpr (LINES == 3)
-    asm volatile("s_load_dword %0, %3, 0x0\n\t" "s_load_dword %1, %3, 0x40\n\t" "s_load_dword %2, %3, 0x80\n\t" "s_waitcnt lgkmcnt(0)"
-                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]) : "s"(p));
-  if constexpr (LINES == 5)
-    asm volatile("s_load_dword %0, %5, 0x0\n\t" "s_load_dword %1, %5, 0x40\n\t" "s_load_dword %2, %5, 0x80\n\t" "s_load_dword %3, %5, 0xc0\n\t"
-                 "s_load_dword %4, %5, 0x100\n\t" "s_waitcnt lgkmcnt(0)"
-                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]) : "s"(p));
-  if constexpr (LINES == 6)
-    asm volatile("s_load_dword %0, %6, 0x0\n\t" "s_load_dword %1, %6, 0x40\n\t" "s_load_dword %2, %6, 0x80\n\t" "s_load_dword %3, %6, 0xc0\n\t"
-                 "s_load_dword %4, %6, 0x100\n\t" "s_load_dword %5, %6, 0x140\n\t" "s_waitcnt lgkmcnt(0)"
-                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]) : "s"(p));
-  if constexpr (LINES == 10)
-    asm volatile("s_load_dword %0, %10, 0x0\n\t" "s_load_dword %1, %10, 0x40\n\t" "s_load_dword %2, %10, 0x80\n\t" "s_load_dword %3, %10, 0xc0\n\t"
-                 "s_load_dword %4, %10, 0x100\n\t" "s_load_dword %5, %10, 0x140\n\t" "s_load_dword %6, %10, 0x180\n\t" "s_load_dword %7, %10, 0x1c0\n\t"
-                 "s_load_dword %8, %10, 0x200\n\t" "s_load_dword %9, %10, 0x240\n\t" "s_waitcnt lgkmcnt(0)"
-                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]), "=&s"(d[6]), "=&s"(d[7]), "=&s"(d[8]), "=&s"(d[9]) : "s"(p));
-  if constexpr (LINES == 12)
-    asm volatile("s_load_dword %0, %12, 0x0\n\t" "s_load_dword %1, %12, 0x40\n\t" "s_load_dword %2, %12, 0x80\n\t" "s_load_dword %3, %12, 0xc0\n\t"
-                 "s_load_dword %4, %12, 0x100\n\t" "s_load_dword %5, %12, 0x140\n\t" "s_load_dword %6, %12, 0x180\n\t" "s_load_dword %7, %12, 0x1c0\n\t"
-                 "s_load_dword %8, %12, 0x200\n\t" "s_load_dword %9, %12, 0x240\n\t" "s_load_dword %10, %12, 0x280\n\t" "s_load_dword %11, %12, 0x2c0\n\t"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]), "=&s"(d[6]), "=&s"(d[7]), "=&s"(d[8]), "=&s"(d[9]), "=&s"(d[10]), "=&s"(d[11]) : "s"(p));
-  static_assert(LINES == 3 || LINES == 5 || LINES == 6 || LINES == 10 || LINES == 12, "spelled out above");
+  auto behind = p;
+  if constexpr (GRID) behind = __builtin_amdgcn_implicitarg_ptr();
+  unsigned d[16];
+  if constexpr (LINES == 3) TGNN_WARM(TGNN_WARM_3);
+  if constexpr (LINES == 5) TGNN_WARM(TGNN_WARM_5);
+  if constexpr (LINES == 6) TGNN_WARM(TGNN_WARM_6);
+  if constexpr (LINES == 8 && !GRID) TGNN_WARM(TGNN_WARM_8);
+  if constexpr (LINES == 8 && GRID) TGNN_WARM(TGNN_WARM_8 "s_load_dword %8, %17, 0x0\n\t");
+  if constexpr (LINES == 13) TGNN_WARM(TGNN_WARM_13);
 #endif
 }
+#undef TGNN_WARM
+#undef TGNN_WARM_3
+#undef TGNN_WARM_5
+#undef TGNN_WARM_6
+#undef TGNN_WARM_8
+#undef TGNN_WARM_13
+template <class... Args> __device__ __forceinline__ void warm_kernargs(const Args&...) { warm_kernarg_lines<false, Args...>(); }
+template <class... Args> __device__ __forceinline__ void warm_kernargs_and_grid(const Args&...) { warm_kernarg_lines<true, Args...>(); }
 
 // x plus what the DPP control `CTRL` brings in from another lane of the row of 16
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x) {

@@ -274,7 +274,7 @@ __device__ __forceinline__ void softmax_fast(float* sa, int HK, int k, int c, in
 #define TGNN_FATTN_FWD_WAVES 4
 #endif
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_FWD_WAVES, TGNN_FATTN_FWD_WAVES))) void fattn_fwd_fast_kernel(FusedAttn a) {
-  warm_kernargs<10>();
+  warm_kernargs(a);
   extern __shared__ float lds[];
   int block = blockIdx.x;
   if (a.fill.gcnt != nullptr) {   // the first blocks are passengers: the fill pass of the slot sort
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TGNN_FATTN_
 #else
 __global__ __launch_bounds__(256) void fattn_bwd_fast_kernel(FusedAttn a) {
 #endif
-  warm_kernargs<6>();
+  warm_kernargs(a);
   extern __shared__ float lds[];
   // (wave index and neighbour count are the same for all lanes: saying so keeps them, and every test on them, scalar)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1021,7 +1021,7 @@ template <int M, int W> __device__ __forceinline__ bool mid_nodes(int wave) { re
 
 template <int M, int W> __global__ __launch_bounds__(256) void fattn_fwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  warm_kernargs<10>();
+  warm_kernargs(a);
   int block = blockIdx.x;
   if (a.fill.gcnt != nullptr) {
     const int fill_blocks = uniq_blocks(a.fill.S);
@@ -1114,7 +1114,7 @@ template <int M, int W> __global__ __launch_bounds__(256) void fattn_fwd_mid_ker
 
 template <int M, int W> __global__ __launch_bounds__(256) void fattn_bwd_mid_kernel(FusedAttn a) {
   extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-  warm_kernargs<6>();
+  warm_kernargs(a);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int r = W == 1 ? blockIdx.x * 4 + wave : blockIdx.x;
   if (r >= a.R) return;

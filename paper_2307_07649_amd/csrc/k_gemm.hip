@@ -654,7 +654,7 @@ __host__ __device__ inline int nt_wgs(int M, int col_tiles) { return col_tiles *
 template <int TN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((TN == 5 ? 3 : 1), (TN <= 5 ? 4 : 2)))) void gemm_nt_kernel(NtGroup grp) {
   __shared__ __attribute__((aligned(16))) float smem[nt_lds<TN>()];
-  warm_kernargs<12>();
+  warm_kernargs(grp);
   if ((int)blockIdx.x >= grp.gemm_wgs) return wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
   const NtGroupPtr gp = (NtGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((TN == 5 ? 
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_few_kernel(NtGroup grp) {
   __shared__ __attribute__((aligned(16))) float smem[NT_FEW_LDS];
-  warm_kernargs<12>();
+  warm_kernargs(grp);
   if ((int)blockIdx.x >= grp.gemm_wgs) return wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
   const NtGroupPtr gp = (NtGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const int pi = (gp->n > 1 && (int)blockIdx.x >= gp->p[1].wg_begin) ? 1 : 0;
@@ -675,7 +675,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 constexpr int NT_FEW_COUNTED = 512;
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nt_counted_kernel(NtGroup grp) {
   __shared__ __attribute__((aligned(16))) float smem[NT_FEW_LDS > nt_lds<2>() ? NT_FEW_LDS : nt_lds<2>()];
-  warm_kernargs<12>();
+  warm_kernargs(grp);
   if ((int)blockIdx.x >= grp.gemm_wgs) return wb_sgd_block(grp.tail, blockIdx.x - grp.gemm_wgs);
   const NtGroupPtr gp = (NtGroupPtr)__builtin_amdgcn_kernarg_segment_ptr();
   // (no branches: they cost up to 0.4 us.  A problem that is not there has no columns, and begins behind all workgroups)

@@ -221,10 +221,10 @@ __device__ __forceinline__ void node_gather(const NodeArgs& a, int pitch, bool k
 typedef const NodeArgs __attribute__((address_space(4))) NodeKernArgs;
 struct NodeKept {
   unsigned long long args;   // the kernel-argument segment
-  int block, blocks;
+  int block, blocks;         // this workgroup's number, and how many take units
 };
-__device__ __forceinline__ void node_keep(NodeKept& kept) {
-  if (threadIdx.x == 0) kept = NodeKept{(unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), (int)blockIdx.x, (int)gridDim.x};
+template <class Blocks> __device__ __forceinline__ void node_keep(NodeKept& kept, Blocks blocks) {
+  if (threadIdx.x == 0) kept = NodeKept{(unsigned long long)__builtin_amdgcn_kernarg_segment_ptr(), (int)blockIdx.x, blocks()};
 }
 
 // Is one of n numbers NaN?  (Then all that comes of them is, in fp32, too.)
@@ -526,7 +526,7 @@ __global__ __launch_bounds__(64 * ND_W) void node_bias_kernel(NodeArgs a) { node
 
 __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  warm_kernargs<12>();
+  warm_kernargs_and_grid(a);
   __shared__ int has_s[16 * ND_MAX_RB];
   if (a.epoch_bump != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.epoch_bump += 1ull;   // nothing here reads it
   // The last blocks are passengers: the scan of the slot sort and the biases of U.  (Behind the units, in the code too: a
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(64 * ND_W) void node_update_kernel(NodeArgs a) {
   const NodeSplit sp = node_update_split(n, a.rb_max, a.cb);
   const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), a.unit_blocks, min(a.cb, ND_MAX_GROUPS));
   __shared__ NodeKept kept;
-  node_keep(kept);
+  node_keep(kept, [&] { return a.unit_blocks; });
   bool again = false;
   float seen = 0.f;
   for (int u = blockIdx.x; u < units.units; u += a.unit_blocks) {
@@ -704,14 +704,14 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
 template <int KS>
 __global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2))) void node_project_kernel(NodeArgs a) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  warm_kernargs<12>();
+  warm_kernargs_and_grid(a);
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);
   // (the number of workgroups, either way: with eight slabs the argument costs 22 registers, with four gridDim is 0.4 us late)
   const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), KS <= 4 ? a.unit_blocks : (int)gridDim.x, (pairs + 1) / 2);
   __shared__ NodeKept kept;
-  node_keep(kept);
+  node_keep(kept, [] { return (int)gridDim.x; });
   bool again = false;
   float seen = 0.f;
   for (int u = blockIdx.x; u < units.units; u += (KS <= 4 ? a.unit_blocks : (int)gridDim.x)) {

@@ -159,7 +159,7 @@ __device__ __forceinline__ void rc_g_block(const floatx4 (&w)[KS], const RcHeads
 
 template <int KS, int E>
 __global__ __launch_bounds__(64 * RC_WAVES) void root_chain_kernel(ChainArgs a) {
-  warm_kernargs<5>();
+  warm_kernargs(a);
   typedef RcGeom<E> G;
   __shared__ __attribute__((aligned(16))) float T[2 * G::ROWS * RC_PL];
   float* const T0 = T;                       // h -> Pdec -> dPdec -> dO

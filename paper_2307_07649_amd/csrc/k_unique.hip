@@ -60,7 +60,7 @@ __global__ __launch_bounds__(64 * SEG_WAVES) void seg_reduce_kernel(int R, int S
                                                          SlotGrads sg, int ldkv, float* __restrict__ dP, int ldp,
                                                          QPhi qphi) {
   int block = blockIdx.x;
-  warm_kernargs<3>();
+  warm_kernargs(R, S, dO, sort_total, sorted, sorted_row, sg, ldkv, dP, ldp, qphi);
   if (qphi.part != nullptr) {   // the first blocks are passengers: gradients through the query's Phi(0)
     const int nq = qphi_blocks(qphi);
     if (block < nq) {
