@@ -287,10 +287,10 @@ __device__ __forceinline__ void node_update_again(const NodeKept& kept, int tid)
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const NodeSplit sp = node_update_split(n, a.rb_max, a.cb);
   const int rb = sp.rb;
-  const NodeUnits units = node_units(sp, node_tiles(n, rb), a.unit_blocks, min(a.cb, ND_MAX_GROUPS));
+  const NodeUnits units = node_units(sp, node_tiles(n, rb), kept.blocks, min(a.cb, ND_MAX_GROUPS));
   const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll 1
-  for (int u = kept.block; u < units.units; u += a.unit_blocks) {
+  for (int u = kept.block; u < units.units; u += kept.blocks) {
     const NodeUnit t = node_unit(units, u);
     if (wave >= (a.cb + t.groups - 1) / t.groups) continue;   // (a column block lies with the first k part's wavefront)
     const int col = (t.group + wave * t.groups) * 16 + 4 * (lane >> 4);
@@ -340,7 +340,7 @@ __device__ __forceinline__ void node_project_again(const NodeKept& kept, int rb_
   const NodeUnits units = node_units(sp, node_tiles(n, rb), kept.blocks, (pairs + 1) / 2);
   const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll 1
-  for (int u = kept.block; u < units.units; u += a.unit_blocks) {
+  for (int u = kept.block; u < units.units; u += kept.blocks) {
     const NodeUnit t = node_unit(units, u);
 #pragma unroll 1
     for (int i = 0; i < rb * 8; ++i) {   // row blocks, and the lane's eight columns of a pair of column blocks
@@ -708,13 +708,14 @@ __global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);
-  // (the number of workgroups, either way: with eight slabs the argument costs 22 registers, with four gridDim is 0.4 us late)
-  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), KS <= 4 ? a.unit_blocks : (int)gridDim.x, (pairs + 1) / 2);
+  // (the number of workgroups from gridDim, for any number of slabs: as an argument it costs the kernel of eight slabs 21 vector
+  // registers, spilled to memory)
+  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), (int)gridDim.x, (pairs + 1) / 2);
   __shared__ NodeKept kept;
   node_keep(kept, [] { return (int)gridDim.x; });
   bool again = false;
   float seen = 0.f;
-  for (int u = blockIdx.x; u < units.units; u += (KS <= 4 ? a.unit_blocks : (int)gridDim.x)) {
+  for (int u = blockIdx.x; u < units.units; u += (int)gridDim.x) {
     const NodeUnit t = node_unit(units, u);
     if (again) __syncthreads();
     again = true;
@@ -759,13 +760,11 @@ void node_bias(const NodeArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(node_bias_kernel, dim3(node_bias_blocks(a)), dim3(64 * ND_W), 0, s, a);
 }
 
-void node_project(const NodeArgs& args, hipStream_t s) {
-  NodeArgs a = args;
+void node_project(const NodeArgs& a, hipStream_t s) {
   if (a.n_max <= 0) return;
   const int lds = 3 * 16 * (a.kp <= 4 ? NP_MAX_RB : 2) * node_xpb(a.kp);
   const int units = 8 * ((a.n_max + 15) / 16);
-  a.unit_blocks = std::min(units, NP_GRID);
-  const dim3 grid(a.unit_blocks);
+  const dim3 grid(std::min(units, NP_GRID));   // all of them take units: the kernel and node_project_again go by gridDim
   if (a.kp <= 4) hipLaunchKernelGGL(node_project_kernel<4>, grid, dim3(64 * NP_W), lds, s, a);
   else hipLaunchKernelGGL(node_project_kernel<NP_MAX_KS>, grid, dim3(64 * NP_W), lds, s, a);
 }

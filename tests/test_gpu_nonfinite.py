@@ -114,6 +114,35 @@ def test_projections_and_their_weight_gradients(widths, R):
     same(gg["bv"], g["bv"], 2e-5)
 
 
+# More tiles than workgroups (512 at a time, two column groups): the rows that a workgroup looks at once more are in its second
+# tile, 32 rows high with eight k slabs and 64 with four.  Weights of column j are so small that a huge entry there leaves
+# projections of ordinary size; the split operands cannot take the entry.
+@pytest.mark.parametrize("widths,R", [((100, 20, 31, 100, 2), 800), ((100, 20, 0, 0, 2), 1600)])
+def test_projections_in_rounds(widths, R):
+    from paper_2307_07649_amd import tgnn
+    dm, dt_, de, ds, H = widths
+    k, j = 10, 3
+    d = synth.ModelDims(n_nodes=50, d_mem=dm, d_time=dt_, d_edge=de, d_static=ds, n_heads=H, k=k, batch=600)
+    p32 = synth.gen_params(d, seed=3, random_phase=True)
+    for n, c in (("wk", j), ("wv", j), ("wq", j), ("wo", dm + j)):
+        p32[n][:, c] *= np.float32(2.0 ** -122)
+    ctx = tgnn.Context(d.n_nodes, dm, dt_, de, ds, H, k, 600)
+    params = tgnn.Params.from_numpy(p32)
+    rng = np.random.default_rng(R)
+    x_root = rng.uniform(-1, 1, (R, d.d_x)).astype(np.float32); x_nbr = rng.uniform(-1, 1, (R, k, d.d_x)).astype(np.float32)
+    e = rng.standard_normal((R, k, de)).astype(np.float32); dt = rng.uniform(0, 3e5, (R, k))
+    cnt = np.full(R, k, np.int32)
+    for r in (0, 1, R - 40, R - 39, R - 1):      # a slot of the first rows and of the last ones
+        x_nbr[r, r % k, j] = HUGE if r % 2 else -HUGE
+    x_root[2, j] = HUGE
+    z = ctx.tgnn_temporal_attn_fwd(params, dev(x_root), dev(x_nbr.reshape(R * k, -1)), dev(e.reshape(R * k, -1)) if de else None,
+                                   dev(dt.reshape(-1)), dev(cnt)).cpu().numpy()
+    p = O.to_f64(p32)
+    ref, _ = O.attention_fwd(p, x_root.astype(np.float64), x_nbr.astype(np.float64), e.astype(np.float64), dt, cnt.astype(np.int64), H)
+    assert np.isfinite(ref).all()
+    same(z, ref, 1e-5)
+
+
 def test_training_step_with_an_infinite_mail():
     """A node whose cached mail has an infinite and a huge entry: the memory that the step writes is finite, and so are the
     gradients outside of the two columns of W_ih that these entries meet."""
