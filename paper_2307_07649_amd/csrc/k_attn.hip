@@ -1226,11 +1226,26 @@ static bool mid_path(const FusedAttn& a) {
 }
 
 // A workgroup per root (see above) or a wavefront per root.  The four wavefronts ask for the root's own rows four times over, the
-// more columns the dearer, and a compute unit holds four roots at a time instead of sixteen.  Step times in us, workgroup / wavefront:
-//   one round of columns   (1 head, 20 neighbours)    106 / 119 (192 roots), 131 / 139 (999), 165 / 154 (2,100)
-//   two                    (3 heads, 17)              124 / 140,             147 / 156,       202 / 183
-//   five                   (4 heads, 11)              149 / 161,             207 / 183,       293 / 238
-static bool mid_few(const FusedAttn& a) { return a.R <= (a.dcp <= 64 ? 1500 : a.dcp <= 128 ? 1200 : 400); }
+// more columns the dearer, and a compute unit holds four or five roots at a time (two with five rounds of columns) instead of
+// sixteen and more: a second round of workgroups costs more than the shorter chains give, the sooner the fewer slots there are
+// to share.  With up to four neighbours the scores are one group of slots, of which one wavefront has all.  Step times in us,
+// workgroup / wavefront:
+//   one round of columns    4 heads, 10 neighbours   121 / 130 (600 roots), 130 / 136 (1,128), 135 / 137 (1,275), 145 / 137 (1,500)
+//                           1, 20                    125 / 136,             134 / 140,         140 / 145,         158 / 152
+//                           3, 5                     113 / 115,             120 / 122,         125 / 122,         134 / 123
+//                           4, 3                     106 / 107 (384),       110 / 110 (600),   115 / 114 (1,128), 129 / 116 (1,500)
+//   two                     4, 10                    129 / 136 (600),       135 / 140 (900),   141 / 141 (1,023), 154 / 142 (1,200)
+//                           1, 20                    125 / 134,             131 / 137,         136 / 138,         150 / 141
+//                           3, 5                     119 / 123,             123 / 125,         129 / 126,         140 / 127
+//                           4, 3                     114 / 115 (384),       118 / 118 (600),   122 / 121 (900),   137 / 123 (1,200)
+//   five                    4, 10                    143 / 152 (240),       149 / 156 (399),   167 / 159 (600)
+//                           3, 5                     128 / 132,             134 / 137,         150 / 140
+//                           4, 3                     124 / 125 (96),        132 / 132 (240),   138 / 137 (399),   151 / 140 (600)
+static bool mid_few(const FusedAttn& a) {
+  const bool short_lists = a.k <= 2 * MA_B;
+  const int most = a.dcp <= 64 ? (short_lists ? 1180 : 1350) : a.dcp <= 128 ? (short_lists ? 900 : 1024) : 400;
+  return a.R <= (a.k <= MA_B ? most / 2 : most);
+}
 
 static bool fast_path(const FusedAttn& a) {
   return !a.force_generic && a.k <= FA_KR && a.de <= 64 * FA_NE && a.dt <= 64 * FA_NT && a.dO <= 64 * FA_E &&

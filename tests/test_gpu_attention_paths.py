@@ -24,10 +24,9 @@ def dev(a):
     (66, 63, 65, 1, 13), (64, 64, 64, 2, 12), (33, 1, 256, 3, 5), (130, 20, 10, 2, 12), (40, 129, 192, 4, 6), (40, 9, 4, 5, 7),
     (32, 8, 0, 1, 11), (39, 33, 32, 3, 5), (24, 100, 29, 1, 12),
 ])
-def test_middle_path_equals_the_generic_path(shape):
+def test_middle_path_equals_the_generic_path(shape, R=53):
     from paper_2307_07649_amd import tgnn
     dm, dt_, de, H, k = shape
-    R = 53
     d = synth.ModelDims(n_nodes=50, d_mem=dm, d_time=dt_, d_edge=de, d_static=0, n_heads=H, k=k, batch=R)
     p32 = synth.gen_params(d, seed=3, random_phase=True)
     params = tgnn.Params.from_numpy(p32)
@@ -65,7 +64,7 @@ def test_middle_path_equals_the_generic_path(shape):
         assert np.abs(g0[n] - g[n]).max() <= 2e-5 * np.abs(g[n]).max() + floor, n
 
 
-# roots on both sides of where a workgroup per root gives way to a wavefront per root, in the kernels of one, two and five rounds
+# many roots: a wavefront per root in the kernels of one, two and five rounds of columns (and a workgroup per root up to 400 of five)
 @pytest.mark.parametrize("shape,R", [((32, 8, 0, 1, 11), 1500), ((32, 8, 0, 1, 11), 1501), ((36, 50, 33, 3, 17), 1200),
                                      ((36, 50, 33, 3, 17), 1201), ((40, 100, 186, 4, 11), 400), ((40, 100, 186, 4, 11), 401)])
 def test_middle_path_row_counts(shape, R):
@@ -87,3 +86,12 @@ def test_middle_path_row_counts(shape, R):
     (z0, r0, n0), (z1, r1, n1) = out
     assert np.array_equal(z0, z1)
     assert rel_err(r0, r1) <= 2e-6 and rel_err(n0, n1) <= 2e-6   # (as above)
+
+
+# a root more than the workgroup per root takes: the wavefront-per-root kernels of one, two and five rounds of columns, and of few
+# neighbours; every gradient, against the generic path and the oracle (tolerances of above: sums over up to 17,425 rows)
+@pytest.mark.parametrize("shape,R", [((32, 8, 0, 1, 11), 1350), ((32, 8, 0, 1, 11), 1351), ((33, 8, 20, 3, 8), 1181), ((36, 50, 33, 3, 17), 1024),
+                                     ((36, 50, 33, 3, 17), 1025), ((36, 40, 60, 3, 5), 901), ((40, 100, 186, 4, 11), 401), ((36, 8, 0, 3, 4), 590),
+                                     ((36, 8, 0, 3, 4), 591), ((36, 40, 60, 3, 3), 451), ((40, 100, 100, 4, 4), 201)])
+def test_middle_path_gradients_around_the_row_counts(shape, R):
+    test_middle_path_equals_the_generic_path(shape, R)
