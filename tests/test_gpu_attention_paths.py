@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import synth
-from gpu_common import rel_err
+from gpu_common import GpuSide, OracleSide, batch_np, compare_state, compare_step, custom_problem, rel_err
 from oracle import tgnn_oracle as O
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +95,17 @@ def test_middle_path_row_counts(shape, R):
                                      ((36, 8, 0, 3, 4), 591), ((36, 40, 60, 3, 3), 451), ((40, 100, 100, 4, 4), 201)])
 def test_middle_path_gradients_around_the_row_counts(shape, R):
     test_middle_path_equals_the_generic_path(shape, R)
+
+
+# the same kernels in a training step: rows looked up by node, the slot sort's fill pass beside them
+@pytest.mark.parametrize("dm,dt_,de,H,k,batch", [(32, 8, 0, 1, 11, 450), (32, 8, 0, 1, 11, 451), (36, 50, 33, 3, 17, 341), (36, 50, 33, 3, 17, 342),
+                                                 (36, 8, 0, 3, 4, 196), (36, 8, 0, 3, 4, 197), (40, 100, 186, 4, 11, 134)])
+def test_middle_path_steps(dm, dt_, de, H, k, batch):
+    P = custom_problem(n_nodes=500, E=8 * batch, d_mem=dm, d_time=dt_, d_edge=de, d_static=0, n_heads=H, k=k, batch=batch, seed=6)
+    G = GpuSide(P); Or = OracleSide(P)
+    for s in range(4, 7):
+        b = batch_np(P, s * batch, (s + 1) * batch)
+        g = G.step([b], lr=0.01)
+        o = Or.step([b], lr=0.01, gpu=g)
+        compare_step(g, o, label=f"middle path {dm} {k} {batch} step {s}")
+    compare_state(G.state_np(), Or.states[0])
