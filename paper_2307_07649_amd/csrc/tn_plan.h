@@ -56,13 +56,15 @@ constexpr int tn_chunk_rows(int rows, int chunks) { return ((rows + chunks - 1) 
 // other's products (eight: 108 against 90 us on a 4,000-event step, 21.7 against 18.3 us on a 600-event one, both with
 // chunks of 1,024 rows at most).
 constexpr int TN_SLOTS = 64;            // workgroups an XCD holds at once
-constexpr int TN_QUEUE = 60, TN_BASE_ROWS = 2048;
+constexpr int TN_QUEUE = 60, TN_BASE_ROWS = 2048, TN_MAX_CHUNKS = 64;
 constexpr float TN_PLAN_GAIN = 0.85f;
 constexpr float TN_COST_WG = 8.0f;      // us: start, reduction, atomics
 constexpr float TN_COST_ROW = 0.020f;   // us per row of a 64 x 64 tile
 constexpr float TN_COST_LOADS = 0.3f;   // share of that which follows the columns loaded, the rest follows the products
 
-// Chunks of `rows_per_chunk` rows for every problem, then the placement on the eight XCDs: chunks in order of decreasing
+// Chunks of `rows_per_chunk` rows for every problem, of a long one no more than TN_MAX_CHUNKS as long as TN_BASE_ROWS rows each are
+// enough for that: the workgroups of a tile all add to the same few lines of memory, one after the other, at 0.4 us per chunk
+// (stand-alone backward call of d_m = 34, 19,404 rows: 64 chunks 31 us, 87 chunks 40).  Then the placement on the eight XCDs: chunks in order of decreasing
 // size (tiles), each to the least loaded XCD so far.  (Dealt out in turn, chunk c to XCD (c + rotation) % 8, the longest queue
 // was up to a fifth longer than the mean: 79 instead of 70 us on 4,000 events, 116 instead of 110 on eight replicas.)  Returns
 // the length of the longest XCD queue.
@@ -73,6 +75,7 @@ inline int tn_place(TnPlan& plan, const TnShape* p, int n, int rows_per_chunk) {
   for (int oi = 0; oi < n; ++oi) {
     const int i = order[oi], rows = p[i].rows;
     int chunks = (rows + rows_per_chunk - 1) / rows_per_chunk, shift = 0;
+    chunks = std::min(chunks, std::max(TN_MAX_CHUNKS, (rows + TN_BASE_ROWS - 1) / TN_BASE_ROWS));
     if (!p[i].counted) chunks = (rows + tn_chunk_rows(rows, chunks) - 1) / tn_chunk_rows(rows, chunks);
     while ((chunks - 1) >> shift >= 64) ++shift;
     plan.chunks[i] = chunks | shift << 24;

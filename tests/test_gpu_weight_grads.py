@@ -54,7 +54,8 @@ def test_weight_gradients(widths, R):
         assert err <= GRAD_TOL * float(np.abs(g[n]).max()) + floor, (n, err, float(np.abs(g[n]).max()))
 
 
-# narrow tiles over so many rows that they are more than 64 chunks: a bit of the masks stands for several
+# narrow tiles over so many rows that the shortest chunks would be more than the 64 that add to one tile; and, with 133,100 rows,
+# over more than 64 of the longest: a bit of the masks stands for several
 @pytest.mark.parametrize("widths,R", [((8, 2, 1, 1), 2400), ((4, 1, 0, 2), 1700), ((4, 1, 0, 2), 12100)])
 def test_weight_gradients_many_chunks(widths, R):
     test_weight_gradients(widths, R)

@@ -96,3 +96,16 @@ def test_long_problems(lib, rows):
         shapes = [problem(rows // 11, dm, dm), problem(rows, 2 * dm, dm + 1), problem(rows, 2 * dm, k + 1)]
         _, per_chunk = check(lib, shapes)
         assert max(per_chunk) <= lib.max_rows(), per_chunk
+
+
+# no more than 64 chunks add to a tile as long as their length does not exceed 2,048 rows (narrow problems, whose queues would
+# take more)
+@pytest.mark.parametrize("rows", [8192, 8193, 19404, 60000, 131071, 131072, 131073, 200000])
+@pytest.mark.parametrize("dm,dt,de,H", [(34, 53, 71, 2), (4, 1, 0, 2), (16, 16, 8, 1)])
+def test_chunks_of_a_tile(lib, rows, dm, dt, de, H):
+    R = rows // 11
+    shapes = [problem(R, dm, dm), problem(R, dm // H + 3, de + dt, heads=H), problem(R, 2 * dt, 1), problem(rows, 2 * dm, dm + 1),
+              problem(rows, 2 * dm, dm + 1)]
+    _, per_chunk = check(lib, shapes)
+    for s, rows_per in zip(shapes, per_chunk):
+        assert -(-s[0] // rows_per) <= max(64, -(-s[0] // 2048)), (s, rows_per)
