@@ -698,6 +698,11 @@ __device__ __forceinline__ void node_project_unit(const NodeArgs& a, int n, int 
   if (pr < pairs) pair(pr, false);
 }
 
+// Workgroups of the launch, for the units, the step between them and the second look.  With four slabs from the arguments: gridDim
+// takes the compiler to 177 registers instead of 211 and 32.2 instead of 31.2 us on 4,000 events.  With eight slabs from gridDim:
+// the argument takes it to 256, with 21 more in memory.
+template <int KS> __device__ __forceinline__ int node_project_blocks(const NodeArgs& a) { return KS <= 4 ? a.unit_blocks : (int)gridDim.x; }
+
 // (Told that two wavefronts per SIMD are wanted, the compiler keeps the accumulators in vector registers; left to itself it
 // moves them to and from accumulation registers, 300 to 400 instructions in all, and takes a register too many for two
 // wavefronts with eight slabs.  1,284 rows: 10.2 -> 8.8 us.)
@@ -708,14 +713,13 @@ __global__ __launch_bounds__(64 * NP_W) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int n = a.n_dev != nullptr ? min(a.n_max, *a.n_dev) : a.n_max;
   const int pairs = (a.ldp + a.ldz) / 32;
   const NodeSplit sp = node_project_split(n, KS <= 4 ? NP_MAX_RB : 2, (pairs + 1) / 2);
-  // (the number of workgroups from gridDim, for any number of slabs: as an argument it costs the kernel of eight slabs 21 vector
-  // registers, spilled to memory)
-  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), (int)gridDim.x, (pairs + 1) / 2);
+  const auto blocks = [&] { return node_project_blocks<KS>(a); };
+  const NodeUnits units = node_units(sp, node_tiles(n, sp.rb), blocks(), (pairs + 1) / 2);
   __shared__ NodeKept kept;
-  node_keep(kept, [] { return (int)gridDim.x; });
+  node_keep(kept, blocks);
   bool again = false;
   float seen = 0.f;
-  for (int u = blockIdx.x; u < units.units; u += (int)gridDim.x) {
+  for (int u = blockIdx.x; u < units.units; u += blocks()) {
     const NodeUnit t = node_unit(units, u);
     if (again) __syncthreads();
     again = true;
@@ -760,11 +764,13 @@ void node_bias(const NodeArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(node_bias_kernel, dim3(node_bias_blocks(a)), dim3(64 * ND_W), 0, s, a);
 }
 
-void node_project(const NodeArgs& a, hipStream_t s) {
+void node_project(const NodeArgs& args, hipStream_t s) {
+  NodeArgs a = args;
   if (a.n_max <= 0) return;
   const int lds = 3 * 16 * (a.kp <= 4 ? NP_MAX_RB : 2) * node_xpb(a.kp);
   const int units = 8 * ((a.n_max + 15) / 16);
-  const dim3 grid(std::min(units, NP_GRID));   // all of them take units: the kernel and node_project_again go by gridDim
+  a.unit_blocks = std::min(units, NP_GRID);   // the whole grid
+  const dim3 grid(a.unit_blocks);
   if (a.kp <= 4) hipLaunchKernelGGL(node_project_kernel<4>, grid, dim3(64 * NP_W), lds, s, a);
   else hipLaunchKernelGGL(node_project_kernel<NP_MAX_KS>, grid, dim3(64 * NP_W), lds, s, a);
 }
