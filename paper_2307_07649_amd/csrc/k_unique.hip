@@ -24,8 +24,9 @@ SortArgs sort_args(tgnn_ctx* ctx, int S) {
 //   neighbour slot (r, j) : dP[row, 0 .. 2 d_o)          += {ds[r, h, j] q[r] | p[r, h, j] dO[r]}   (per head h: the
 //                           gradients of the slot's key and value rows, formed here instead of being stored)
 //   root slot r           : dP[row, half .. half + 2 d_o) += {dq[r] | dz[r]}          (half = the pitch of {K | V})
-// One wavefront owns SEG_CHUNK consecutive entries of the row-sorted slot list; runs of one row are summed
-// in registers and leave as one atomic row update per half.
+// One wavefront owns SEG_CHUNK consecutive entries of the row-sorted slot list and sums runs of one row in registers.  A run
+// that lies within a workgroup's entries is stored; one that goes on in another workgroup's leaves as atomic updates, one per
+// workgroup and half of the row.
 // element c < 2 d_o of the gradient of neighbour slot `sl` (= r k + j)
 __device__ __forceinline__ float slot_grad(const SlotGrads& g, int sl, int c) {
   const int r = sl / g.k, j = sl - r * g.k;

@@ -71,11 +71,12 @@ struct Ws {
   double *tau, *delta;                         // [S]
   double* dtk;                                 // [R*k] time difference in the keys (Eq. 5-6), kept for the backward pass
   unsigned long long* winkey;                  // [nrep*N] write-back arbitration: (epoch << 33) | occurrence key
-  unsigned long long* epoch;                   // [1] bumped once per step, makes stale winkey entries lose
+  unsigned long long* epoch;                   // [1] bumped once per step, makes stale winkey entries lose.  A workspace
+                                               // is good for 2^31 steps: winkey has 31 bits of it, xtag 32
   int32_t* bad_ids;                            // [1] batch node ids outside [0, N) seen by the steps so far
   // distinct (replica, node) rows of the step
   unsigned long long* utag;                    // [nrep*N] epoch of the last step that claimed the node
-  unsigned* xtag;                              // [8, nrep*N] the same among the blocks of an XCD (NULL: too many nodes)
+  unsigned* xtag;                              // [8, nrep*N] the same among the blocks of an XCD, low 32 bits (NULL: too many nodes)
   int32_t *uidx, *ucount, *ulist;              // [nrep*N] row of a claimed node; [1] number of rows; [maxU] row -> gid
   int32_t* ucount_pair;                        // [2] ucount points at one of them: training steps alternate, and
                                                // each clears the counter of the next one
@@ -646,7 +647,8 @@ struct NodeArgs {
   int dm, dt, de, ds, dx, d_in;
   int cb, kx, kh, kp;        // column blocks of the memory width; k slabs
   int rb_max;                // row blocks per tile at most
-  int unit_blocks;           // blocks of the update launch before its passengers (set by node_update)
+  int unit_blocks;           // blocks that take units: of the update launch those before its passengers, of the projections the
+                             // whole grid (set by node_update and node_project)
   SortArgs scan;             // scan.gcnt != NULL: the update's last passenger block runs the scan of the slot sort
   unsigned long long* epoch_bump;   // may be NULL: *epoch_bump += 1
 };
