@@ -17,7 +17,7 @@
 //          launch waits for another.
 //
 // Measured (MI355X, kernel trace, launch to launch): five launches 37 us for 1,284 rows and 140 us for 11,377 rows
-// (d_m = d_t = 100, d_e = 172 / 186); these two 27 and 84 us.
+// (d_m = d_t = 100, d_e = 172 / 186); these two 25 and 77 us.
 //
 // What bounds them: a workgroup that does nothing else draws 50 bytes per cycle from the L2 when every compute unit does (63
 // with 32 of them; measured on 0.6 and 1.26 MB that all read over and over), this one beside its gathering and MFMAs 40, so
